@@ -66,37 +66,28 @@ __device__ __forceinline__ void amsgrad_update4(float4 &th, float4 &m, float4 &v
 }
 
 typedef float v4f __attribute__((ext_vector_type(4)));
-typedef float v2f __attribute__((ext_vector_type(2)));
 
-// Streaming (read-once) loads: the gradient is never read again by the same step.
+// Vector types of a lower alignment: gfx950 takes a global load of 8 or 16 bytes at any address, so a row that
+// starts between two 16-byte boundaries is still read with one wide load per lane.  A wavefront's 1 KB then
+// touches nine 128-byte lines instead of eight, where 4- and 8-byte loads of the same data took two to four times
+// the load instructions.
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t v2u_any __attribute__((ext_vector_type(2), aligned(2)));
+
+// Streaming (read-once) loads: the gradient is never read again by the same step.  p: 4-byte aligned.
 __device__ __forceinline__ float4 stream_load4(const float *p)
 {
-    const v4f t = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(p));
+    const v4f t = __builtin_nontemporal_load(reinterpret_cast<const v4f_any *>(p));
     return make_float4(t.x, t.y, t.z, t.w);
-}
-__device__ __forceinline__ float2 stream_load2(const float *p)
-{
-    const v2f t = __builtin_nontemporal_load(reinterpret_cast<const v2f *>(p));
-    return make_float2(t.x, t.y);
 }
 
 // Four consecutive gradient coordinates row[j..j+3], j a multiple of 4.  The row is caller
 // memory of length d whose start may be 16-, 8- or 4-byte aligned (row i of a dense [n][d]
-// array starts at i*d floats); coordinates at or beyond d read as zero.  The alignment test is
-// uniform across a wavefront.
+// array starts at i*d floats); coordinates at or beyond d read as zero.
 __device__ __forceinline__ float4 load_grad4(const float *__restrict__ row, int64_t j, int64_t d)
 {
     const float *p = row + j;
-    if (j + 4 <= d) {
-        const uintptr_t a = reinterpret_cast<uintptr_t>(p) & 15u;
-        if (a == 0) return stream_load4(p);
-        if (a == 8) {
-            const float2 lo = stream_load2(p);
-            const float2 hi = stream_load2(p + 2);
-            return make_float4(lo.x, lo.y, hi.x, hi.y);
-        }
-        return make_float4(p[0], p[1], p[2], p[3]);
-    }
+    if (j + 4 <= d) return stream_load4(p);
     float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
     if (j < d) r.x = p[0];
     if (j + 1 < d) r.y = p[1];
@@ -107,8 +98,13 @@ __device__ __forceinline__ float4 load_grad4(const float *__restrict__ row, int6
 
 // Gradients handed over as bfloat16 (the upper 16 bits of the fp32 value): widened exactly, so every
 // formula downstream sees the same fp32 numbers as with an fp32 copy of them.  Rows start at any 2-byte
-// alignment; 8-/4-/2-byte aligned groups of four take a 64-/32-/16-bit load path.
+// alignment.
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ v2u stream_load_u2(const uint16_t *p)
+{
+    return __builtin_nontemporal_load(reinterpret_cast<const v2u_any *>(p));
+}
 
 __device__ __forceinline__ float bf16_to_float(uint32_t h) { return __uint_as_float(h << 16); }
 
@@ -116,19 +112,9 @@ __device__ __forceinline__ float4 load_grad4(const uint16_t *__restrict__ row, i
 {
     const uint16_t *p = row + j;
     if (j + 4 <= d) {
-        const uintptr_t a = reinterpret_cast<uintptr_t>(p) & 7u;
-        if (a == 0) {
-            const v2u t = __builtin_nontemporal_load(reinterpret_cast<const v2u *>(p));
-            return make_float4(__uint_as_float(t.x << 16), __uint_as_float(t.x & 0xffff0000u),
-                               __uint_as_float(t.y << 16), __uint_as_float(t.y & 0xffff0000u));
-        }
-        if (a == 4) {
-            const uint32_t lo = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p));
-            const uint32_t hi = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p + 2));
-            return make_float4(__uint_as_float(lo << 16), __uint_as_float(lo & 0xffff0000u),
-                               __uint_as_float(hi << 16), __uint_as_float(hi & 0xffff0000u));
-        }
-        return make_float4(bf16_to_float(p[0]), bf16_to_float(p[1]), bf16_to_float(p[2]), bf16_to_float(p[3]));
+        const v2u t = stream_load_u2(p);
+        return make_float4(__uint_as_float(t.x << 16), __uint_as_float(t.x & 0xffff0000u),
+                           __uint_as_float(t.y << 16), __uint_as_float(t.y & 0xffff0000u));
     }
     float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
     if (j < d) r.x = bf16_to_float(p[0]);
@@ -138,7 +124,7 @@ __device__ __forceinline__ float4 load_grad4(const uint16_t *__restrict__ row, i
     return r;
 }
 
-// Gradients handed over as IEEE half precision: same layout and load paths as bfloat16, widened exactly
+// Gradients handed over as IEEE half precision: same layout and loads as bfloat16, widened exactly
 // by the hardware conversion.  The wrapper type only tells the two 16-bit formats apart.
 struct f16bits {
     uint16_t v;
@@ -151,21 +137,9 @@ __device__ __forceinline__ float4 load_grad4(const f16bits *__restrict__ row, in
 {
     const uint16_t *p = reinterpret_cast<const uint16_t *>(row) + j;
     if (j + 4 <= d) {
-        const uintptr_t a = reinterpret_cast<uintptr_t>(p) & 7u;
-        uint32_t lo, hi;
-        if (a == 0) {
-            const v2u t = __builtin_nontemporal_load(reinterpret_cast<const v2u *>(p));
-            lo = t.x;
-            hi = t.y;
-        } else if (a == 4) {
-            lo = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p));
-            hi = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p + 2));
-        } else {
-            lo = (uint32_t)p[0] | ((uint32_t)p[1] << 16);
-            hi = (uint32_t)p[2] | ((uint32_t)p[3] << 16);
-        }
-        return make_float4(f16_to_float(lo & 0xffffu), f16_to_float(lo >> 16), f16_to_float(hi & 0xffffu),
-                           f16_to_float(hi >> 16));
+        const v2u t = stream_load_u2(p);
+        return make_float4(f16_to_float(t.x & 0xffffu), f16_to_float(t.x >> 16), f16_to_float(t.y & 0xffffu),
+                           f16_to_float(t.y >> 16));
     }
     float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
     if (j < d) r.x = f16_to_float(p[0]);
