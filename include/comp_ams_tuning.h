@@ -34,8 +34,8 @@ int comp_ams_set_streaming(comp_ams_t *h, int32_t rows, int32_t state);
  * stored rows exceed 1 GiB in total and the method keeps them - error feedback, CD-Adam - except for
  * CD-Adam's Top-k / Rand-k steps on 16-bit gradients; else 0; Top-k / Rand-k under error feedback: 0 while
  * the rows stay in the caches, else 8, or 16 for rows of 64 Mi coordinates or more; the update without
- * compression, which takes its tiles the same way: 16 with at least 16 workers whose gradients exceed 1 GiB
- * in total).  chunk <= 65536.  May be called between steps.
+ * compression, which takes its tiles the same way: 16 from 128 tiles on).  chunk <= 65536.  May be called
+ * between steps.
  */
 int comp_ams_set_tile_order(comp_ams_t *h, int32_t chunk);
 

@@ -775,17 +775,15 @@ int step_topk_naive(comp_ams *h, const G *g, hipStream_t st)
 template <typename G>
 int step_plain(comp_ams *h, const G *g, hipStream_t st)
 {
-    // Tile order: with many gradient rows far beyond the caches each XCD working through 16 consecutive tiles of
-    // every row measured 9 % faster (n = 32, d = 25.6 M: 797 -> 726 us); n = 16, d = 11.2 M does not respond, and
-    // with n = 8, d = 110 M chunks of 16 to 256 tiles gave -3 to +5 % without a pattern, so few rows keep the plain
-    // order.
-    const int n_tiles = (int)(h->ld / kTile);
-    const bool many_long_rows = h->n >= 16 && (size_t)h->n * (size_t)h->d * sizeof(G) > ((size_t)1 << 30);
-    const int chunk = h->chunk_choice >= 0 ? h->chunk_choice : many_long_rows ? 16 : 0;
+    // Tile order: each XCD working through 16 consecutive tiles (64 quarters) of a row at a time is as fast as the plain
+    // order or faster at every size measured (d = 3 M to 110 M, n = 1 to 64: 0-6 %), as long as there are tiles enough to
+    // reach all XCDs: a vector of 65 536 coordinates, one chunk, would run on one of them.
+    const int n_quarters = (int)(h->ld / kPlainCoords);
+    const int chunk = 4 * (h->chunk_choice >= 0 ? h->chunk_choice : n_quarters >= 8 * 64 ? 16 : 0);
     launch_timed(h, P_PLAIN_UPDATE, st, [&] {
         by_flag(h->params.stream_state, [&](auto ss) {
-            KLAUNCH((plain_update<G, decltype(ss)::value>), grid_blocks(n_tiles, chunk), kThreads, st, g, h->d, h->n,
-                    h->theta, h->m, h->v, h->vhat, h->params, chunk, n_tiles);
+            KLAUNCH((plain_update<G, decltype(ss)::value>), grid_blocks(n_quarters, chunk), kThreads, st, g, h->d, h->n,
+                    h->theta, h->m, h->v, h->vhat, h->params, chunk, n_quarters);
         });
     });
     return COMP_AMS_OK;
