@@ -239,18 +239,57 @@ __global__ __launch_bounds__(kThreads) void bs_pass(const G *__restrict__ g, flo
                scales + (int64_t)i * tb.n_blocks);
 }
 
-// One wavefront per (listed block, worker): see BsTable::scale_list.
-__global__ __launch_bounds__(kWave) void bs_scale(const double *__restrict__ partial, BsTable tb,
-                                                  float *__restrict__ scales)
+// One workgroup per (listed block, worker): see BsTable::scale_list.  One wavefront adds the block's pieces, lane l
+// those at l, l + 64, ..., and a fixed butterfly follows: the order does not depend on the launch shape.
+// Bound by latency.  A block of at most kDirectPieces pieces is added straight from memory.  A longer one (the
+// whole-vector sign of 11.2 M coordinates has 2728 pieces, of 110 M 26 856) is staged in LDS by a workgroup of
+// kThreads, kScaleStage pieces at a time with the next ones in flight: one wavefront alone waits for memory once in
+// 64 pieces.
+constexpr int kDirectPieces = 256;
+constexpr int kScaleStage = 2048;
+constexpr int kStagePer = kScaleStage / kThreads;
+__global__ __launch_bounds__(kThreads) void bs_scale(const double *__restrict__ partial, BsTable tb,
+                                                     float *__restrict__ scales)
 {
+    // dynamic LDS: kScaleStage doubles when some block is long (launched with kThreads), else none
+    extern __shared__ __align__(16) unsigned char scale_lds[];
+    double *stage = reinterpret_cast<double *>(scale_lds);
     const int b = tb.scale_list[blockIdx.x];
     const int i = blockIdx.y;
+    const int tid = threadIdx.x;
     const int q0 = tb.block_piece0[b], q1 = tb.block_piece0[b + 1];
     const double *row = partial + (int64_t)i * tb.n_pieces;
     double acc = 0.0;
-    for (int q = q0 + (int)threadIdx.x; q < q1; q += kWave) acc += row[q];
+    if (q1 - q0 <= kDirectPieces || blockDim.x < kThreads) {
+        if (tid >= kWave) return;
+        for (int q = q0 + tid; q < q1; q += kWave) acc += row[q];
+    } else {
+        double next[kStagePer];
+#pragma unroll
+        for (int u = 0; u < kStagePer; ++u) {
+            const int q = q0 + u * kThreads + tid;
+            next[u] = q < q1 ? row[q] : 0.0;
+        }
+        for (int base = q0; base < q1; base += kScaleStage) {
+            __syncthreads();                                   // the stage has been added up
+#pragma unroll
+            for (int u = 0; u < kStagePer; ++u) stage[u * kThreads + tid] = next[u];
+#pragma unroll
+            for (int u = 0; u < kStagePer; ++u) {
+                const int q = base + kScaleStage + u * kThreads + tid;
+                next[u] = q < q1 ? row[q] : 0.0;
+            }
+            __syncthreads();
+            if (tid < kWave) {
+                const int cnt = min(kScaleStage, q1 - base);
+#pragma unroll 8
+                for (int q = tid; q < cnt; q += kWave) acc += stage[q];
+            }
+        }
+        if (tid >= kWave) return;
+    }
     const double S = wave_sum(acc);
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         const double len = (double)(tb.offsets[b + 1] - tb.offsets[b]);
         scales[(int64_t)i * tb.n_blocks + b] = (float)(S / len);
     }

@@ -47,6 +47,7 @@ struct comp_ams {
     unsigned pass_lds = 0, pass_lds16 = 0;         // dynamic LDS of bs_pass for gradients of 32 / 16 bits (see pass_lds_bytes)
     bool has_split_tiles = false;                  // some tile holds several pieces
     bool mostly_split_tiles = false;               // more than one tile in eight does
+    bool long_blocks = false;                      // some block has more than kDirectPieces pieces
     uint64_t rand_seed = 0;                    // Rand-k: the generator's seed and the number of the next draw
     uint32_t draw = 0;
     std::string err;
@@ -442,6 +443,8 @@ int build_block_table(comp_ams *h, const std::vector<int64_t> &off, int64_t unif
     int64_t split = 0;
     for (int64_t t = 0; t < n_tiles; ++t) split += tile_piece0[t + 1] - tile_piece0[t] > 1;
     h->mostly_split_tiles = split * 8 > n_tiles;
+    h->long_blocks = false;
+    for (int b = 0; b < nb; ++b) h->long_blocks |= block_piece0[b + 1] - block_piece0[b] > kDirectPieces;
     h->tb.n_blocks = nb;
     h->tb.n_pieces = (int32_t)piece_hi.size();
     h->tb.uniform_tiles = (uniform_len > 0 && uniform_len % kTile == 0) ? (int32_t)(uniform_len / kTile) : 0;
@@ -534,6 +537,10 @@ void launch_bs_update(comp_ams *h, hipStream_t st, const AmsParams &p)
     });
 }
 
+// Workgroup size of bs_scale: the staging wavefronts only where some block is long enough to use them.
+inline unsigned scale_threads(const comp_ams *h) { return h->long_blocks ? kThreads : kWave; }
+inline unsigned scale_lds(const comp_ams *h) { return h->long_blocks ? kScaleStage * sizeof(double) : 0u; }
+
 template <typename G>
 int step_blocksign(comp_ams *h, const G *g, hipStream_t st)
 {
@@ -553,7 +560,7 @@ int step_blocksign(comp_ams *h, const G *g, hipStream_t st)
     });
     if (!h->fused_scale && tb.n_scale_list > 0)
         launch_timed(h, P_BS_SCALE, st, [&] {
-            KLAUNCH((bs_scale), dim3(tb.n_scale_list, h->n), kWave, st, h->partial, tb, h->scales);
+            KLAUNCH_LDS((bs_scale), dim3(tb.n_scale_list, h->n), scale_threads(h), scale_lds(h), st, h->partial, tb, h->scales);
         });
     launch_bs_update(h, st, h->params);
     h->pending = (h->method == COMP_AMS_METHOD_EF);
@@ -627,7 +634,7 @@ int step_blocksign_cd(comp_ams *h, const G *g, hipStream_t st)
     const bool whole = h->fused_scale && tb.n_pieces == tb.n_blocks;
     if (!whole && tb.n_scale_list > 0)
         launch_timed(h, P_BS_SCALE, st, [&] {
-            KLAUNCH((bs_scale), dim3(tb.n_scale_list, h->n), kWave, st, h->partial, tb, h->scales);
+            KLAUNCH_LDS((bs_scale), dim3(tb.n_scale_list, h->n), scale_threads(h), scale_lds(h), st, h->partial, tb, h->scales);
         });
     launch_timed(h, P_BS_SERVER, st, [&] {
         const BsMarkov mk{h->ghat_srv, h->gtil, h->signs_srv, h->partial_srv, h->scales_srv, whole ? 1 : 0};
@@ -645,7 +652,7 @@ int step_blocksign_cd(comp_ams *h, const G *g, hipStream_t st)
     if (!whole) {
         if (tb.n_scale_list > 0)
             launch_timed(h, P_BS_SCALE_SERVER, st, [&] {
-                KLAUNCH((bs_scale), dim3(tb.n_scale_list, 1), kWave, st, h->partial_srv, tb, h->scales_srv);
+                KLAUNCH_LDS((bs_scale), dim3(tb.n_scale_list, 1), scale_threads(h), scale_lds(h), st, h->partial_srv, tb, h->scales_srv);
             });
         launch_timed(h, P_BS_APPLY, st, [&] {
             by_flag(h->params.stream_state, [&](auto ss) {
