@@ -245,10 +245,10 @@ inline uint32_t per_step_word(const comp_ams *h, uint32_t draw) { return host_mi
 
 namespace {
 
-enum ProfSlot { P_BS_PASS, P_BS_SCALE, P_BS_UPDATE, P_TK_PASS1, P_TK_HIST, P_TK_PICK, P_TK_COMPACT,
+enum ProfSlot { P_BS_PASS, P_BS_SCALE, P_BS_UPDATE, P_TK_PASS1, P_TK_HIST, P_TK_COMPACT,
                 P_TK_RESOLVE, P_TK_FINAL, P_BS_SERVER, P_BS_SCALE_SERVER, P_BS_APPLY, P_TK_MERGE, P_TK_PASS1_SERVER,
                 P_TK_SELECT_SERVER, P_TK_APPLY, P_PLAIN_UPDATE, P_BS_PASS_UPDATE, P_SLOTS };
-const char *const kProfNames[P_SLOTS] = {"bs_pass", "bs_scale", "bs_update", "tk_pass1", "tk_hist", "tk_pick",
+const char *const kProfNames[P_SLOTS] = {"bs_pass", "bs_scale", "bs_update", "tk_pass1", "tk_hist",
                                          "tk_compact", "tk_resolve", "tk_final", "bs_server",
                                          "bs_scale_server", "bs_apply", "tk_merge", "tk_pass1_server", "tk_select_server",
                                          "tk_apply", "plain_update", "bs_pass_update"};
@@ -665,41 +665,38 @@ int step_blocksign_cd(comp_ams *h, const G *g, hipStream_t st)
     return COMP_AMS_OK;
 }
 
-// The four selection launches between the listing pass and the kernel that uses Tc: candidate histograms (after
-// a miss: the whole vector's), leading digits (after a miss: and the lists anew), compaction of the threshold bin,
+// The three selection launches between the listing pass and the kernel that uses Tc: candidate histograms (after
+// a miss: the whole vector's), leading digits and compaction of the threshold bin (after a miss: the lists anew),
 // last digits (or, rarest, the selection without lists).  kSrc / a / b say how the compressed vector is formed
 // again where that is needed.  cursor_b: the second set of region cursors, which the lists made anew count in.
 template <int kSrc, typename G>
 void launch_select(comp_ams *h, hipStream_t st, const TkGeom &ge, TkWorker *ws, uint2 *cand, uint32_t *cursor,
                    uint32_t *cursor_b, uint4 *tile_dir, uint32_t *hist1, uint32_t *histf, uint32_t *hist_full,
                    uint32_t *hist2, uint32_t *piece_bits, uint64_t *dense, uint2 *dense_dir, const void *a,
-                   const float *b, const int (&slot)[4])
+                   const float *b, const int (&slot)[3])
 {
-    const dim3 shared(ge.slices * ge.parts, ge.n);
-    // tk_pick: one workgroup per vector does the work in the usual case; the others (needed only to list the
-    // vector again after a miss) are kept to about four per compute unit in total
-    const dim3 pick((unsigned)std::min<int>(ge.relist_wgs, std::max(1, 1024 / ge.n)), ge.n);
+    const int per = ge.slices * ge.parts;
+    // tk_compact: one workgroup per piece in the usual case; more (they leave at once then) where listing the vector
+    // again after a miss wants them, up to about four per compute unit in total
+    const int relist = std::min<int>(ge.relist_wgs, std::max(1, 1024 / ge.n));
     launch_timed(h, slot[0], st, [&] {
-        KLAUNCH((tk_hist<kSrc, G>), shared, kThreads, st, ge, ws, cand, cursor, hist1, histf, hist_full, a, b);
+        KLAUNCH((tk_hist<kSrc, G>), dim3(per, ge.n), kThreads, st, ge, ws, cand, cursor, hist1, histf, hist_full, a, b);
     });
     launch_timed(h, slot[1], st, [&] {
-        KLAUNCH((tk_pick<kSrc, G>), pick, kThreads, st, ge, ws, hist1, histf, cursor, cursor_b, hist_full, a, b, cand,
-                tile_dir);
+        KLAUNCH((tk_compact<kSrc, G>), dim3(std::max(per, relist), ge.n), kThreads, st, ge, ws, hist1, histf, cursor, cursor_b,
+                hist_full, a, b, cand, tile_dir, dense, dense_dir, hist2, piece_bits);
     });
     launch_timed(h, slot[2], st, [&] {
-        KLAUNCH((tk_compact), shared, kThreads, st, ge, ws, cand, cursor, cursor_b, dense, dense_dir, hist2, piece_bits);
-    });
-    launch_timed(h, slot[3], st, [&] {
         // error feedback with magnitude keys counts zeros instead of listing them: tk_resolve may need the rows
         const float *rows = (kSrc == kSrcStored && !ge.rand.on) ? static_cast<const float *>(a) : nullptr;
         const ExactSource es{kSrc, std::is_same<G, float>::value ? 0 : std::is_same<G, uint16_t>::value ? 1 : 2, a, b};
-        KLAUNCH((tk_resolve), ge.n, kResolveThreads, st, ge, ws, dense, dense_dir, cursor, cursor_b, hist_full, hist2,
-                piece_bits, cand, tile_dir, rows, es);
+        KLAUNCH((tk_resolve), ge.n, kResolveThreads, st, ge, ws, dense, dense_dir, cursor, cursor_b, hist1, histf, hist_full,
+                hist2, piece_bits, cand, tile_dir, rows, es);
     });
 }
 
-constexpr int kWorkerSelectSlots[4] = {P_TK_HIST, P_TK_PICK, P_TK_COMPACT, P_TK_RESOLVE};
-constexpr int kServerSelectSlots[4] = {P_TK_SELECT_SERVER, P_TK_SELECT_SERVER, P_TK_SELECT_SERVER, P_TK_SELECT_SERVER};
+constexpr int kWorkerSelectSlots[3] = {P_TK_HIST, P_TK_COMPACT, P_TK_RESOLVE};
+constexpr int kServerSelectSlots[3] = {P_TK_SELECT_SERVER, P_TK_SELECT_SERVER, P_TK_SELECT_SERVER};
 
 void launch_final(comp_ams *h, hipStream_t st)
 {
@@ -796,7 +793,7 @@ int step_plain(comp_ams *h, const G *g, hipStream_t st)
     return COMP_AMS_OK;
 }
 
-// One iteration of Algorithm 1 (CD-Adam) with Top-k in both directions, twelve launches.
+// One iteration of Algorithm 1 (CD-Adam) with Top-k in both directions, ten launches.
 template <typename G>
 int step_topk_cd(comp_ams *h, const G *g, hipStream_t st)
 {

@@ -10,7 +10,7 @@
 // The error memory is kept in deferred form: after a step the library stores x_i = g_i + e_i and
 // the worker's threshold Tc_i; e_i[j] = (comp(x_i[j], j) >= Tc_i) ? +0 : x_i[j] is formed on the fly
 // when the next step (or a getter) reads x_i, so kept coordinates are never zeroed by scattered
-// writes and one step needs a single pass over g and the stored vector.  Six launches per step,
+// writes and one step needs a single pass over g and the stored vector.  Five launches per step,
 // ordered only by kernel boundaries (no fences, no waiting inside a kernel):
 //
 //   tk_pass1    one workgroup per (tile, worker): streams g and the stored x once and writes the new
@@ -20,15 +20,13 @@
 //               and appended densely to one of 64 regions of the worker (one atomic add per tile).
 //               A workgroup per tile (instead of a loop over tiles) matters: on this chip a wave
 //               that loops must wait for its stores before it can use its next loads.
-//   tk_hist     histograms of the candidates: coarse bins (top 11 bits) and the fine bins of the
-//               eight coarse bins from the guess's on; with fewer than k candidates (always on the first
+//   tk_hist     histograms of the candidates: the fine bins of the eight coarse bins from the guess's on,
+//               coarse bins (top 11 bits) beyond; with fewer than k candidates (always on the first
 //               step) the guess was too high: then the workgroups count the whole vector into a
 //               full coarse histogram instead
-//   tk_pick     coarse and fine bin of the k-th largest (one workgroup per worker); after such a
-//               miss: the coarse bin from the full histogram, and the candidates are listed again
-//               from the stored x (many workgroups)
-//   tk_compact  candidates in the threshold bin are copied, as comp values, to dense pieces (one
-//               per wavefront)
+//   tk_compact  coarse and fine bin of the k-th largest (every workgroup for itself); candidates in
+//               that threshold bin are copied, as comp values, to dense pieces (one per wavefront);
+//               after such a miss: the candidates are listed again from the stored x
 //   tk_resolve  one workgroup per worker: the remaining digits of Tc over those pieces, and the
 //               guess for the next step
 //   tk_final    per tile, all workers: candidates with comp >= Tc are the kept coordinates; their
@@ -89,7 +87,7 @@ struct TkWorker {
     uint64_t tc;            // threshold composite of the last finished step (pending selection)
     uint32_t guess;         // pass 1 lists elements with fine bin >= guess
     uint32_t slack;         // fine bins kept between the threshold and the next guess
-    // leading digits of the running step's Tc, written by tk_pick, read by the kernels after it
+    // leading digits of the running step's Tc, written by tk_compact, read by tk_resolve
     uint32_t prefix;        // magnitude bits above pshift
     uint32_t pshift;        // kFineShift or kShift1: how many low magnitude bits are still open
     uint32_t rank;          // 1-based rank (from the top) of the k-th largest among elements with this prefix
@@ -102,7 +100,7 @@ struct TkWorker {
                             // replayed from a HIP graph (which repeats its draw) still reads its predecessor's.
     uint32_t overflow;      // tk_pass1 found a candidate region full: the lists are incomplete, tk_hist counts the
                             // whole vector instead (as after a guess that was too high)
-    uint32_t overflow2;     // listing anew, tk_pick found a region full as well: tk_resolve selects without lists
+    uint32_t overflow2;     // listing anew, tk_compact found a region full as well: tk_resolve selects without lists
                             // (exact_select)
     uint32_t pad_;
 };
@@ -128,7 +126,7 @@ struct TkGeom {
     int32_t slice_tiles;    // tiles that append to one candidate region = ceil(n_tiles / slices)
     uint32_t region_cap;    // entries a candidate region holds (see region_base)
     int32_t parts;          // tk_hist / tk_compact: workgroups per region
-    int32_t relist_wgs;     // workgroups per worker in tk_pick (after a miss each loops over tiles; else all but one leave)
+    int32_t relist_wgs;     // workgroups per worker that tk_compact lists with after a miss (each loops over tiles)
     int32_t stream_rows;    // the stored rows are too large to stay cached between steps: tk_pass1 loads them as a stream
     int32_t xcd_chunk;      // tk_pass1: tile_of_block's chunk
     TkRand rand;
@@ -226,6 +224,40 @@ __device__ __forceinline__ void find_rank_bin(const uint32_t *lh, uint32_t *part
     __syncthreads();
 }
 
+// The same for a histogram of 8 * kThreads bins held in registers by a workgroup of kThreads: thread t owns the bins
+// 8 t .. 8 t + 7.
+__device__ __forceinline__ void find_rank_owned(const uint32_t (&own)[8], uint32_t *part, uint32_t *res, uint32_t rank)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t mine = 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) mine += own[q];
+    uint32_t suffix = mine;                       // sum over lanes >= this one
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t t = __shfl_down(suffix, off, kWave);
+        if (lane + off < kWave) suffix += t;
+    }
+    if (lane == 0) part[wave] = suffix;
+    __syncthreads();
+    uint32_t above = suffix - mine;
+    for (int w = wave + 1; w < kThreads / kWave; ++w) above += part[w];
+    if (above < rank && above + mine >= rank) {
+        bool found = false;
+#pragma unroll
+        for (int q = 7; q >= 0; --q) {
+            if (!found && above + own[q] >= rank) {
+                res[0] = threadIdx.x * 8 + q;
+                res[1] = above;
+                res[2] = own[q];
+                found = true;
+            }
+            above += own[q];
+        }
+    }
+    __syncthreads();
+}
+
 // Appends this wavefront's flagged lanes to a list: returns the slot of the calling lane (valid
 // where flag is set) and advances count (uniform over the wavefront).
 __device__ __forceinline__ uint32_t wave_append(bool flag, uint32_t &count)
@@ -273,7 +305,7 @@ __device__ __forceinline__ void block_prefix(uint32_t v, uint32_t *pre, uint32_t
 // A region holds a bounded number of entries (the host sizes a worker's regions for twice max(4 k, d / 64)
 // candidates in all; 1.2 k are listed in steady state), not every coordinate of its tiles.  A tile that does not
 // fit sets the worker's overflow flag and stores nothing: the worker's lists are then incomplete and the step
-// goes on as after a guess that was too high - tk_hist counts the whole vector and tk_pick lists again with
+// goes on as after a guess that was too high - tk_hist counts the whole vector and tk_compact lists again with
 // the coarse bin of the k-th largest; if that does not fit either (thousands of equal magnitudes: nothing
 // narrower than the whole composite key separates them), tk_resolve selects without lists (exact_select).
 __device__ __forceinline__ int64_t worker_base(const TkGeom &ge, int worker)
@@ -310,13 +342,12 @@ __device__ __forceinline__ uint32_t take_space(const uint32_t (&cnt)[4], uint32_
     return at;
 }
 
-// First half of moving a tile's staged candidates (count per wavefront, in LDS) to its region: the
-// thread `allocator` takes the space.  sh: 9 LDS words.  zeros: the wavefront's count of exact zeros (the
-// tile's sum goes into the directory record).  Ends before the barrier so that the caller can put other
-// work between the atomic and its use.
-__device__ __forceinline__ void flush_begin(uint32_t count, uint32_t zeros, uint32_t *sh, int allocator, const TkGeom &ge,
-                                            int i, int t, uint32_t *__restrict__ cursor, uint4 *__restrict__ tile_dir,
-                                            uint32_t *overflow_flag)
+// The space of one tile for a workgroup of four wavefronts that have counted their candidates (count, and zeros: the
+// wavefront's count of exact zeros; the tile's sum goes into the directory record).  Leaves the four counts in
+// sh[0 .. 3] and the offset (or kNoSpace) in sh[4], with a barrier after them.  sh: 9 LDS words.
+__device__ __forceinline__ void take_tile_space(uint32_t count, uint32_t zeros, uint32_t *sh, const TkGeom &ge, int i,
+                                                int t, uint32_t *__restrict__ cursor, uint4 *__restrict__ tile_dir,
+                                                uint32_t *overflow_flag)
 {
     const int tid = threadIdx.x;
     if ((tid & 63) == 0) {
@@ -324,22 +355,11 @@ __device__ __forceinline__ void flush_begin(uint32_t count, uint32_t zeros, uint
         sh[5 + (tid >> 6)] = zeros;
     }
     __syncthreads();
-    if (tid == allocator) {
+    if (tid == 0) {
         const uint32_t cnt[4] = {sh[0], sh[1], sh[2], sh[3]};
         sh[4] = take_space(cnt, sh[5] + sh[6] + sh[7] + sh[8], ge, i, t, cursor, tile_dir, overflow_flag);
     }
-}
-__device__ __forceinline__ void flush_end(const uint2 *stage, uint32_t count, const uint32_t *sh, const TkGeom &ge,
-                                          int i, uint2 *__restrict__ cand)
-{
     __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t off = sh[4];
-    if (off == kNoSpace) return;
-    for (int w = 0; w < wave; ++w) off += sh[w];
-    uint2 *dst = cand + worker_base(ge, i) + off;
-    // the wavefront reads back its own LDS writes: no barrier needed for those
-    for (uint32_t q = lane; q < count; q += kWave) dst[q] = stage[q];
 }
 
 // A wavefront's staged candidates in tk_pass1: the value and the coordinate's place inside the tile, 6 bytes per
@@ -506,7 +526,7 @@ __global__ __launch_bounds__(kThreads) void tk_pass1(const G *__restrict__ g, fl
 // ---------------------------------------------------------------------------------------------
 // The kept values of a tile, summed over the workers, and the AMSGrad update of the tile (tk_final's work).
 //
-// A coordinate of a tile belongs to one wavefront - the same one in tk_pass1, tk_pick's listing and here -
+// A coordinate of a tile belongs to one wavefront - the same one in tk_pass1, tk_compact's listing and here -
 // and a tile's candidates are stored wavefront by wavefront, so each wavefront can sum the kept values
 // of its own coordinates without looking at the others: no workgroup barrier, and the ascending worker
 // order of the sum is just the order of its own instructions (within one worker the coordinates of
@@ -650,17 +670,17 @@ __global__ __launch_bounds__(kThreads) void tk_final(TkGeom ge, const TkWorker *
 }
 
 // ---------------------------------------------------------------------------------------------
-// How the workgroups of tk_hist and tk_compact share a worker's candidates: blockIdx.x = slice *
+// How the workgroups of tk_hist and tk_compact share a worker's candidates: bx (blockIdx.x) = slice *
 // parts + part, and a part is a contiguous piece of the slice's region.
 struct Piece {
     int slice;
     uint32_t q0, q1;     // entries [q0, q1) of the region
 };
-__device__ __forceinline__ Piece piece_of(const TkGeom &ge, const uint32_t *__restrict__ cursor, int worker)
+__device__ __forceinline__ Piece piece_of(const TkGeom &ge, const uint32_t *__restrict__ cursor, int worker, int bx)
 {
     Piece p;
-    p.slice = blockIdx.x / ge.parts;
-    const uint32_t part = blockIdx.x % ge.parts;
+    p.slice = bx / ge.parts;
+    const uint32_t part = bx % ge.parts;
     const uint32_t count = min(cursor[worker * ge.slices + p.slice], ge.region_cap);
     const uint32_t chunk = (count + ge.parts - 1) / ge.parts;
     p.q0 = min(part * chunk, count);
@@ -705,7 +725,7 @@ __device__ __forceinline__ void load_source_tile(float (&x)[4][4], const void *_
 }
 
 // Which way a worker's selection goes in this step, from what the listing pass left (the same test in tk_hist and
-// tk_pick, which see the same cursors and flags):
+// tk_compact, which see the same cursors and flags):
 //   kCaseListed    every element at or above the guess is listed and there are at least k of them: the k-th largest
 //                  is a candidate, the candidate histograms locate it;
 //   kCaseZeroTail  error feedback with magnitude keys, a guess of 0 (every non-zero element is listed) and fewer
@@ -739,10 +759,12 @@ __device__ __forceinline__ uint32_t candidates_listed(const TkGeom &ge, const ui
 }
 
 // First kernel of the selection.  Grid (slices * parts, n).
-// Usual case (kCaseListed): histograms of the candidates of a worker - coarse bins, and the fine bins of the
-// kWindowCoarse coarse bins that start with the guess's.  Loads are issued four at a time.
+// Usual case (kCaseListed): histograms of the candidates of a worker - the fine bins of the kWindowCoarse coarse bins
+// that start with the guess's, and the coarse bins of the candidates beyond that window (those inside it would
+// draw most LDS atomics to eight words; tk_compact adds them up from the fine bins).  Loads are issued four at a
+// time.
 // After a miss (kCaseMiss) the workgroups of the worker count the whole vector, re-formed from what is stored
-// (a, b: see load_source_tile), into the worker's full coarse histogram instead; tk_pick takes the coarse bin of
+// (a, b: see load_source_tile), into the worker's full coarse histogram instead; tk_compact takes the coarse bin of
 // the k-th largest from it and lists again.  Bin 0 (zeros and the smallest denormals) is not counted there but
 // taken as the remainder: in a sparse vector it would draw most LDS atomics of a tile to one word.
 template <int kSrc, typename G>
@@ -762,7 +784,7 @@ __global__ __launch_bounds__(kThreads) void tk_hist(TkGeom ge, const TkWorker *_
     const uint32_t total = candidates_listed(ge, cursor, i, &total_sh);
     const int which = selection_case<kSrc>(ge, total, guess, ws[i].overflow != 0u);
     if (which == kCaseZeroTail) return;
-    const Piece pc = piece_of(ge, cursor, i);
+    const Piece pc = piece_of(ge, cursor, i, (int)blockIdx.x);
     if (which == kCaseListed && pc.q0 >= pc.q1) return;
     const SelKey sk = sel_key_of(ge.rand, ge.rand.step_now, i);
     for (int q = tid; q < kBins1; q += kThreads) lh[q] = 0;
@@ -805,8 +827,10 @@ __global__ __launch_bounds__(kThreads) void tk_hist(TkGeom ge, const TkWorker *_
         for (int u = 0; u < 4; ++u) {
             if (qb + u * kThreads + tid < pc.q1) {
                 const uint32_t fine = sel_key(sk, __uint_as_float(y[u].y), y[u].x) >> kFineShift;
-                atomicAdd(&lh[fine >> (kShift1 - kFineShift)], 1u);
-                if (fine - wbase < (uint32_t)kFineWindow) atomicAdd(&lf[fine - wbase], 1u);
+                if (fine - wbase < (uint32_t)kFineWindow)
+                    atomicAdd(&lf[fine - wbase], 1u);
+                else
+                    atomicAdd(&lh[fine >> (kShift1 - kFineShift)], 1u);
             }
         }
     }
@@ -819,86 +843,155 @@ __global__ __launch_bounds__(kThreads) void tk_hist(TkGeom ge, const TkWorker *_
         if (lf[q]) atomicAdd(histf + (int64_t)i * kFineWindow + q, lf[q]);
 }
 
-// Second kernel of the selection: the leading digits of Tc.  Grid (ge.relist_wgs, n).
-// Usual case (kCaseListed): workgroup 0 of the worker finds the coarse and (if the window covers it) fine bin of
-// the k-th largest from the candidate histograms, and the other workgroups return at once.
+// Second kernel of the selection: the leading digits of Tc, and the elements they leave.  Grid (at least
+// slices * parts, n).
+// Usual case (kCaseListed): every workgroup finds the coarse and (if the window covers it) fine bin of the k-th
+// largest from the candidate histograms for itself - 10 KB from the caches and one scan, about a microsecond, where a
+// launch of its own took six - and copies the candidates of its piece that carry this prefix, as comp values, to the
+// dense storage.  Each wavefront takes a quarter of the workgroup's piece and writes its hits from the start of that
+// quarter onwards (as many slots as it reads, so it cannot overflow), and records {start, count} relative to the
+// worker's first region; no atomics, tk_resolve walks the records.  While copying, the workgroup counts the next
+// kFirstBits bits of comp below the prefix (hist2: [n][kBinsFirst], added to with atomics, emptied by tk_resolve) and
+// every wavefront notes which of those digits occur in its piece (piece_bits: kPieceWords words per piece, written
+// whole).  Nothing is copied where the threshold needs no further digit.  The histograms are cleared by tk_resolve.
 // After a miss tk_hist has counted the whole vector into the worker's full coarse histogram: every workgroup takes
-// the coarse bin of the k-th largest from it (each works it out for itself; workgroup 0 records it) and lists the
-// elements in that bin or above, tile by tile, into the worker's regions - through the second set of cursors
-// (cursor_b, all zero here), since the first still holds the counts this kernel's workgroups decide by.  The
-// worker is flagged `relisted`: tk_compact then reads cursor_b, and tk_resolve clears both.  A region that fills up
-// there as well sets overflow2: tk_resolve then selects without lists (exact_select).
-// Consumes (and clears) the candidate histograms.
+// the coarse bin of the k-th largest from it and lists the elements in that bin or above, tile by tile, into the
+// worker's regions - through the second set of cursors (cursor_b, all zero here), since the first still holds the
+// counts this kernel's workgroups decide by.  The worker is flagged `relisted`: tk_resolve then takes the elements
+// from these lists (no dense pieces exist) and clears both sets.  A region that fills up there as well sets
+// overflow2: tk_resolve then selects without lists (exact_select).
 template <int kSrc, typename G>
-__global__ __launch_bounds__(kThreads) void tk_pick(TkGeom ge, TkWorker *__restrict__ ws,
-                                                    uint32_t *__restrict__ hist1, uint32_t *__restrict__ histf,
-                                                    const uint32_t *__restrict__ cursor,
-                                                    uint32_t *__restrict__ cursor_b,
-                                                    const uint32_t *__restrict__ hist_full,
-                                                    const void *__restrict__ a, const float *__restrict__ b,
-                                                    uint2 *__restrict__ cand, uint4 *__restrict__ tile_dir)
+__global__ __launch_bounds__(kThreads) void tk_compact(TkGeom ge, TkWorker *__restrict__ ws,
+                                                       const uint32_t *__restrict__ hist1,
+                                                       const uint32_t *__restrict__ histf,
+                                                       const uint32_t *__restrict__ cursor,
+                                                       uint32_t *__restrict__ cursor_b,
+                                                       const uint32_t *__restrict__ hist_full,
+                                                       const void *__restrict__ a, const float *__restrict__ b,
+                                                       uint2 *__restrict__ cand, uint4 *__restrict__ tile_dir,
+                                                       uint64_t *__restrict__ dense, uint2 *__restrict__ dense_dir,
+                                                       uint32_t *__restrict__ hist2, uint32_t *__restrict__ piece_bits)
 {
-    __shared__ uint2 stage[4][kSub];
-    __shared__ uint32_t lh[kBins1];
+    __shared__ uint32_t lf[kFineWindow];
+    __shared__ uint32_t win[kWindowCoarse];
+    __shared__ uint32_t lh2[kBinsFirst];
+    __shared__ uint32_t bits[kThreads / kWave][kPieceWords];
     __shared__ uint32_t part[kThreads / kWave];
-    __shared__ uint32_t res[4];
-    __shared__ uint32_t fres[3];
+    __shared__ uint32_t res[3];
     __shared__ uint32_t sh[9];
     __shared__ uint32_t total_sh;
+    static_assert(kBins1 == 8 * kThreads && kFineWindow == 2 * kThreads, "bins owned per thread");
+    static_assert(kFinePerCoarse == kWave && kWindowCoarse == 2 * (kThreads / kWave), "fine bins of two coarse bins per wavefront");
     const int i = blockIdx.y;
     const int bx = blockIdx.x;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
+    const int per = ge.slices * ge.parts;
+    // What the usual case needs goes out before anything waits: this thread's coarse bins, two fine bins (of the
+    // window's coarse bins `wave` and `wave + 4`), and the size of the workgroup's piece
+    const uint4 own0 = *reinterpret_cast<const uint4 *>(hist1 + (int64_t)i * kBins1 + 8 * tid);
+    const uint4 own1 = *reinterpret_cast<const uint4 *>(hist1 + (int64_t)i * kBins1 + 8 * tid + 4);
+    const uint32_t f0 = histf[(int64_t)i * kFineWindow + tid], f1 = histf[(int64_t)i * kFineWindow + kThreads + tid];
+    const Piece pc = piece_of(ge, cursor, i, min(bx, per - 1));
     const uint32_t guess = ws[i].guess;
-    const uint32_t total = candidates_listed(ge, cursor, i, &total_sh);
-    const int which = selection_case<kSrc>(ge, total, guess, ws[i].overflow != 0u);
-    uint32_t *row = hist1 + (int64_t)i * kBins1;
-    uint32_t *frow = histf + (int64_t)i * kFineWindow;
+    const bool overflow = ws[i].overflow != 0u;
+    {
+        lf[tid] = f0;
+        lf[kThreads + tid] = f1;
+        uint32_t s0 = f0, s1 = f1;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            s0 += __shfl_xor(s0, off, kWave);
+            s1 += __shfl_xor(s1, off, kWave);
+        }
+        if (lane == 0) {
+            win[wave] = s0;
+            win[wave + kThreads / kWave] = s1;
+        }
+        for (int q = tid; q < kBinsFirst; q += kThreads) lh2[q] = 0;
+        if (lane < kPieceWords) bits[wave][lane] = 0;
+    }
+    const uint32_t total = candidates_listed(ge, cursor, i, &total_sh);      // ends with a barrier
+    const int which = selection_case<kSrc>(ge, total, guess, overflow);
+    const SelKey sk = sel_key_of(ge.rand, ge.rand.step_now, i);
 
     if (which == kCaseListed) {
-        if (bx != 0) return;
-        for (int q = tid; q < kBins1; q += kThreads) lh[q] = row[q];
-        __syncthreads();
-        find_rank_bin(lh, part, res, kBins1, ge.k);
+        if (bx >= per) return;                      // workgroups beyond the pieces are there for the lists after a miss
+        const uint32_t wb = guess >> (kShift1 - kFineShift);      // first coarse bin of the fine window
+        uint32_t own[8] = {own0.x, own0.y, own0.z, own0.w, own1.x, own1.y, own1.z, own1.w};
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {               // the window's coarse bins are counted in the fine histogram alone
+            const uint32_t at = 8 * tid + q - wb;
+            if (at < (uint32_t)kWindowCoarse) own[q] += win[at];
+        }
+        find_rank_owned(own, part, res, ge.k);
         uint32_t prefix = res[0];                   // coarse bin of the k-th largest
         uint32_t pshift = kShift1;
         uint32_t rank = ge.k - res[1];
         uint32_t count = res[2];
-        const uint32_t wb = guess >> (kShift1 - kFineShift);      // first coarse bin of the fine window
         if (prefix - wb < (uint32_t)kWindowCoarse) {
-            // the fine histogram covers this coarse bin: pick the fine bin as well (one wavefront)
-            if (wave == 0) {
-                const uint32_t c = frow[(prefix - wb) * kFinePerCoarse + lane];
-                uint32_t suffix = c;                // candidates of this coarse bin in fine bins >= lane
+            // the fine histogram covers this coarse bin: pick the fine bin as well (every wavefront for itself)
+            const uint32_t c = lf[(prefix - wb) * kFinePerCoarse + lane];
+            uint32_t suffix = c;                    // candidates of this coarse bin in fine bins >= lane
 #pragma unroll
-                for (int off = 1; off < kWave; off <<= 1) {
-                    const uint32_t t = __shfl_down(suffix, off, kWave);
-                    if (lane + off < kWave) suffix += t;
-                }
-                const uint64_t reach = __ballot(suffix >= rank);  // lane 0 reaches: suffix(0) = count >= rank
-                const int top = reach ? 63 - __builtin_clzll(reach) : 0;
-                if (lane == top) {
-                    fres[0] = (uint32_t)lane;
-                    fres[1] = suffix - c;
-                    fres[2] = c;
-                }
+            for (int off = 1; off < kWave; off <<= 1) {
+                const uint32_t t = __shfl_down(suffix, off, kWave);
+                if (lane + off < kWave) suffix += t;
             }
-            __syncthreads();
-            prefix = (prefix << (kShift1 - kFineShift)) | fres[0];
+            const uint64_t reach = __ballot(suffix >= rank);      // lane 0 reaches: suffix(0) = count >= rank
+            const int top = reach ? 63 - __builtin_clzll(reach) : 0;
+            count = (uint32_t)__shfl((int)c, top, kWave);
+            rank -= (uint32_t)__shfl((int)suffix, top, kWave) - count;
+            prefix = (prefix << (kShift1 - kFineShift)) | (uint32_t)top;
             pshift = kFineShift;
-            rank -= fres[1];
-            count = fres[2];
         }
-        __syncthreads();   // every thread has read the histograms before they are cleared
-        if (tid == 0) {
+        const bool whole = count == rank;
+        if (bx == 0 && tid == 0) {
             ws[i].prefix = prefix;
             ws[i].pshift = pshift;
             ws[i].rank = rank;
-            ws[i].whole = (count == rank) ? 1u : 0u;
+            ws[i].whole = whole ? 1u : 0u;
             ws[i].relisted = 0u;
         }
-        for (int q = tid; q < kBins1; q += kThreads) row[q] = 0;
-        for (int q = tid; q < kFineWindow; q += kThreads) frow[q] = 0;
+        if (whole) return;
+        // the digit of comp right below the prefix (tk_resolve's first digit)
+        const int s_lo = (int)pshift + ge.idx_bits - kFirstBits;      // pshift >= kFineShift > kFirstBits
+        const uint32_t quarter = (pc.q1 - pc.q0 + 3) / 4;
+        const uint32_t w0 = min(pc.q0 + wave * quarter, pc.q1), w1 = min(w0 + quarter, pc.q1);
+        const int64_t rbase = region_base(ge, i, pc.slice);
+        const uint2 *src = cand + rbase;
+        uint64_t *out = dense + rbase + w0;
+        uint32_t kept = 0;
+        for (uint32_t qb = w0; qb < w1; qb += 4 * kWave) {
+            uint2 c[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t q = qb + u * kWave + lane;
+                c[u] = q < w1 ? src[q] : make_uint2(0u, 0u);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t key = sel_key(sk, __uint_as_float(c[u].y), c[u].x);
+                const bool hit = qb + u * kWave + lane < w1 && (key >> pshift) == prefix;
+                const uint32_t slot = wave_append(hit, kept);
+                if (hit) {
+                    const uint64_t comp = composite(key, c[u].x, ge.idx_bits);
+                    out[slot] = comp;
+                    const uint32_t digit = (uint32_t)(comp >> s_lo) & (uint32_t)(kBinsFirst - 1);
+                    atomicAdd(&lh2[digit], 1u);
+                    atomicOr(&bits[wave][digit >> 5], 1u << (digit & 31u));
+                }
+            }
+        }
+        const int64_t rec = ((int64_t)i * per + bx) * 4 + wave;
+        if (lane == 0) dense_dir[rec] = make_uint2((uint32_t)(rbase - worker_base(ge, i)) + w0, kept);
+        // the piece's bitmap, written whole every step (the wavefront reads back its own LDS atomics)
+        if (lane < kPieceWords) piece_bits[rec * kPieceWords + lane] = bits[wave][lane];
+        __syncthreads();
+        for (int q = tid; q < kBinsFirst; q += kThreads) {
+            const uint32_t c = lh2[q];
+            if (c) atomicAdd(hist2 + (int64_t)i * kBinsFirst + q, c);
+        }
         return;
     }
 
@@ -919,22 +1012,21 @@ __global__ __launch_bounds__(kThreads) void tk_pick(TkGeom ge, TkWorker *__restr
     // after a miss: the coarse bin of the k-th largest from the full histogram, and the lists anew
     const uint32_t d = (uint32_t)ge.d;
     {
+        uint32_t own[8];
         uint32_t counted = 0;
-        for (int q = tid; q < kBins1; q += kThreads) {
-            const uint32_t c = hist_full[(int64_t)i * kBins1 + q];
-            lh[q] = c;
-            counted += c;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            own[q] = hist_full[(int64_t)i * kBins1 + 8 * tid + q];
+            counted += own[q];
         }
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) counted += __shfl_xor(counted, off, kWave);
-        if (lane == 0) part[wave] = counted;
+        if (lane == 0) sh[wave] = counted;
         __syncthreads();
-        if (tid == 0) lh[0] = d - (part[0] + part[1] + part[2] + part[3]);   // bin 0 is the remainder
-        __syncthreads();
-        find_rank_bin(lh, part, res, kBins1, ge.k);        // the histogram holds all d >= k elements
+        if (tid == 0) own[0] = d - (sh[0] + sh[1] + sh[2] + sh[3]);   // bin 0 is the remainder
+        find_rank_owned(own, part, res, ge.k);             // the histogram holds all d >= k elements
     }
     const uint32_t prefix = res[0];
-    const SelKey sk = sel_key_of(ge.rand, ge.rand.step_now, i);
     if (bx == 0 && tid == 0) {
         ws[i].prefix = prefix;
         ws[i].pshift = kShift1;
@@ -947,7 +1039,8 @@ __global__ __launch_bounds__(kThreads) void tk_pick(TkGeom ge, TkWorker *__restr
         const uint32_t base = (uint32_t)t * kTile;
         float x[4][4];
         load_source_tile<kSrc, G>(x, a, i, ge, brow, base, d);
-        uint32_t count = 0, zeros = 0;
+        // count first, then write straight from the registers into the space taken: no staging lists
+        uint32_t count = 0, zeros = 0, hits = 0;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -959,81 +1052,24 @@ __global__ __launch_bounds__(kThreads) void tk_pick(TkGeom ge, TkWorker *__restr
                     zeros += (uint32_t)__popcll(__ballot(zero));
                     hit = hit && !zero;
                 }
-                const uint32_t slot = wave_append(hit, count);
-                if (hit) stage[wave][slot] = make_uint2(j, __float_as_uint(x[r][c]));
+                count += (uint32_t)__popcll(__ballot(hit));
+                hits |= (hit ? 1u : 0u) << (r * 4 + c);
             }
-        flush_begin(count, zeros, sh, 0, ge, i, t, cursor_b, tile_dir, &ws[i].overflow2);
-        flush_end(stage[wave], count, sh, ge, i, cand);
-        __syncthreads();   // sh and stage are reused by the next tile
-    }
-}
-
-// Copies the candidates that carry the prefix, as comp values, to the dense storage.  Each wavefront
-// takes a quarter of the workgroup's piece and writes its hits from the start of that quarter
-// onwards (as many slots as it reads, so it cannot overflow), and records {start, count} relative to
-// the worker's first region; no atomics, tk_resolve walks the records.  While copying, the workgroup counts the
-// next kFirstBits bits of comp below the prefix (hist2: [n][kBinsFirst], added to with atomics, emptied by
-// tk_resolve) and every wavefront notes which of those digits occur in its piece (piece_bits: kPieceWords words
-// per piece, written whole).  Grid (slices * parts, n).  Nothing to do for a worker whose threshold needs no
-// further digit, or whose lists did not fit (tk_resolve then selects without lists).
-__global__ __launch_bounds__(kThreads) void tk_compact(TkGeom ge, const TkWorker *__restrict__ ws,
-                                                       const uint2 *__restrict__ cand,
-                                                       const uint32_t *__restrict__ cursor,
-                                                       const uint32_t *__restrict__ cursor_b,
-                                                       uint64_t *__restrict__ dense, uint2 *__restrict__ dense_dir,
-                                                       uint32_t *__restrict__ hist2, uint32_t *__restrict__ piece_bits)
-{
-    __shared__ uint32_t lh2[kBinsFirst];
-    __shared__ uint32_t bits[kThreads / kWave][kPieceWords];
-    const int per = gridDim.x;
-    const int i = blockIdx.y;
-    const int bx = blockIdx.x;
-    if (ws[i].whole || ws[i].overflow2) return;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const uint32_t prefix = ws[i].prefix, pshift = ws[i].pshift;
-    // the digit of comp right below the prefix (tk_resolve's first digit)
-    const int s_lo = (int)pshift + ge.idx_bits - kFirstBits;      // pshift >= kFineShift > kFirstBits
-    for (int b = tid; b < kBinsFirst; b += kThreads) lh2[b] = 0;
-    if (lane < kPieceWords) bits[wave][lane] = 0;
-    __syncthreads();
-    const SelKey sk = sel_key_of(ge.rand, ge.rand.step_now, i);
-    const Piece pc = piece_of(ge, ws[i].relisted ? cursor_b : cursor, i);   // lists made anew count in cursor_b
-    const uint32_t quarter = (pc.q1 - pc.q0 + 3) / 4;
-    const uint32_t w0 = min(pc.q0 + wave * quarter, pc.q1), w1 = min(w0 + quarter, pc.q1);
-    const int64_t rbase = region_base(ge, i, pc.slice);
-    const uint2 *src = cand + rbase;
-    uint64_t *out = dense + rbase + w0;
-    uint32_t count = 0;
-    for (uint32_t qb = w0; qb < w1; qb += 4 * kWave) {
-        uint2 c[4];
+        take_tile_space(count, zeros, sh, ge, i, t, cursor_b, tile_dir, &ws[i].overflow2);
+        uint32_t at = sh[4];
+        if (at != kNoSpace) {
+            for (int w = 0; w < wave; ++w) at += sh[w];
+            uint2 *dst = cand + worker_base(ge, i);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t q = qb + u * kWave + lane;
-            c[u] = q < w1 ? src[q] : make_uint2(0u, 0u);
-        }
+            for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t key = sel_key(sk, __uint_as_float(c[u].y), c[u].x);
-            const bool hit = qb + u * kWave + lane < w1 && (key >> pshift) == prefix;
-            const uint32_t slot = wave_append(hit, count);
-            if (hit) {
-                const uint64_t comp = composite(key, c[u].x, ge.idx_bits);
-                out[slot] = comp;
-                const uint32_t digit = (uint32_t)(comp >> s_lo) & (uint32_t)(kBinsFirst - 1);
-                atomicAdd(&lh2[digit], 1u);
-                atomicOr(&bits[wave][digit >> 5], 1u << (digit & 31u));
-            }
+                for (int c = 0; c < 4; ++c) {
+                    const bool hit = (hits >> (r * 4 + c)) & 1u;
+                    const uint32_t slot = wave_append(hit, at);
+                    if (hit) dst[slot] = make_uint2(base + 4 * (tid + kThreads * r) + c, __float_as_uint(x[r][c]));
+                }
         }
-    }
-    const int64_t rec = ((int64_t)i * per + bx) * 4 + wave;
-    if (lane == 0) dense_dir[rec] = make_uint2((uint32_t)(rbase - worker_base(ge, i)) + w0, count);
-    // the piece's bitmap, written whole every step (the wavefront reads back its own LDS atomics)
-    if (lane < kPieceWords) piece_bits[rec * kPieceWords + lane] = bits[wave][lane];
-    __syncthreads();
-    for (int b = tid; b < kBinsFirst; b += kThreads) {
-        const uint32_t c = lh2[b];
-        if (c) atomicAdd(hist2 + (int64_t)i * kBinsFirst + b, c);
+        __syncthreads();   // sh is reused by the next tile
     }
 }
 
@@ -1377,6 +1413,8 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
                                                               const uint2 *__restrict__ dense_dir,
                                                               uint32_t *__restrict__ cursor,
                                                               uint32_t *__restrict__ cursor_b,
+                                                              uint32_t *__restrict__ hist1,
+                                                              uint32_t *__restrict__ histf,
                                                               uint32_t *__restrict__ hist_full,
                                                               uint32_t *__restrict__ hist2,
                                                               const uint32_t *__restrict__ piece_bits,
@@ -1399,7 +1437,19 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
     const int i = blockIdx.x;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
+    // what the usual case needs goes out before the record says whether it is the usual case
+    const int pieces = ge.slices * ge.parts * 4;                 // a multiple of 4, at most 2 * kResolveThreads
+    static_assert(kBinsFirst == kResolveThreads, "one bin of the first digit per thread");
+    const uint32_t first_count = hist2[(int64_t)i * kBinsFirst + tid];
+    uint4 two = make_uint4(0u, 0u, 0u, 0u);                      // {start, count} of pieces 2 tid and 2 tid + 1
+    if (2 * tid < pieces) two = *reinterpret_cast<const uint4 *>(dense_dir + (int64_t)i * pieces + 2 * tid);
     const TkWorker w = ws[i];
+    // Emptied for the next step: the cursors and candidate histograms (tk_compact was their last reader; zero already
+    // in a step that did not use them) and the counts of the first digit.  slices <= 1024 threads.
+    if (tid < ge.slices) cursor[i * ge.slices + tid] = 0;
+    for (int q = tid; q < kBins1; q += kResolveThreads) hist1[(int64_t)i * kBins1 + q] = 0;
+    if (tid < kFineWindow) histf[(int64_t)i * kFineWindow + tid] = 0;
+    hist2[(int64_t)i * kBinsFirst + tid] = 0;
     const int s_hi = (int)w.pshift + ge.idx_bits;
     uint64_t tc = (uint64_t)w.prefix << s_hi;
     const uint4 *dir_row = tile_dir + (int64_t)i * ge.n_tiles;
@@ -1408,19 +1458,54 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
         if (tid == 0) ws[i].whole = kExact;          // for the records (comp_ams_get_selection_info)
     } else if (w.whole == kZeroTail) {
         tc = zero_tail_threshold(dir_row, xs + (int64_t)i * ge.ld, ge, w.rank, L);
-    } else if (!w.whole) {
-        // tk_compact counted the first digit below the prefix while it copied: take its counts (and leave the
-        // worker's row of hist2 empty for the next step)
-        for (int b = tid; b < kBinsFirst; b += kResolveThreads) {
-            uint32_t *at = hist2 + (int64_t)i * kBinsFirst + b;
-            L.lh[b] = *at;
-            *at = 0u;
+    } else if (w.relisted && !w.whole) {
+        // lists made anew: the digits over the worker's regions themselves (the elements above the prefix are there
+        // too and do not match it), walked as one run of elements
+        const int regions = ge.slices;
+        uint32_t mine = 0;
+        if (tid < regions) mine = min(cursor_b[i * regions + tid], ge.region_cap);
+        const uint32_t before = resolve_scan(mine, L.part, &L.res[3]);
+        if (tid < regions) rpre[tid] = before;
+        if (tid == regions - 1) rpre[regions] = before + mine;
+        __syncthreads();
+        const uint32_t cnt = rpre[regions];
+        if (xs != nullptr && w.prefix == 0u && cnt < ge.k)
+            // the bin of the smallest keys is listed without its zeros, so the lists hold every non-zero element:
+            // fewer than k, and the k-th largest is a zero
+            tc = zero_tail_threshold(dir_row, xs + (int64_t)i * ge.ld, ge, ge.k - cnt, L);
+        else {
+            const SelKey sk = sel_key_of(ge.rand, ge.rand.step_now, i);
+            const uint2 *list = cand + worker_base(ge, i);
+            int top = 1;
+            while (2 * top < regions) top *= 2;
+            auto fetch = [&](const uint32_t (&q)[kScanUnroll], uint64_t (&comp)[kScanUnroll]) {
+                if (q[0] >= cnt) return;
+                int r[kScanUnroll];
+#pragma unroll
+                for (int u = 0; u < kScanUnroll; ++u) r[u] = 0;
+                for (int bit = top; bit > 0; bit >>= 1) {
+                    uint32_t start[kScanUnroll];
+#pragma unroll
+                    for (int u = 0; u < kScanUnroll; ++u) start[u] = rpre[min(r[u] + bit, regions)];
+#pragma unroll
+                    for (int u = 0; u < kScanUnroll; ++u) r[u] = (start[u] <= q[u] && r[u] + bit < regions) ? r[u] + bit : r[u];
+                }
+                uint2 e[kScanUnroll];
+#pragma unroll
+                for (int u = 0; u < kScanUnroll; ++u)
+                    e[u] = q[u] < cnt ? list[(uint32_t)r[u] * ge.region_cap + (q[u] - rpre[r[u]])] : make_uint2(0u, 0u);
+#pragma unroll
+                for (int u = 0; u < kScanUnroll; ++u)
+                    comp[u] = composite(sel_key(sk, __uint_as_float(e[u].y), e[u].x), e[u].x, ge.idx_bits);
+            };
+            tc = resolve_digits(fetch, cnt, w.prefix, w.rank, s_hi, L);
         }
-        const int pieces = ge.slices * ge.parts * 4;
+    } else if (!w.whole) {
+        // tk_compact counted the first digit below the prefix while it copied: take its counts
+        L.lh[tid] = first_count;
         const uint64_t *wdense = dense + region_base(ge, i, 0);
         // exclusive prefix sum of the piece counts, two pieces per thread
-        const uint2 a = (2 * tid < pieces) ? dense_dir[(int64_t)i * pieces + 2 * tid] : make_uint2(0u, 0u);
-        const uint2 b = (2 * tid + 1 < pieces) ? dense_dir[(int64_t)i * pieces + 2 * tid + 1] : make_uint2(0u, 0u);
+        const uint2 a = make_uint2(two.x, two.y), b = make_uint2(two.z, two.w);
         uint32_t incl = a.y + b.y;
 #pragma unroll
         for (int off = 1; off < kWave; off <<= 1) {
@@ -1522,8 +1607,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
             }
         }
     }
-    if (tid < ge.slices) cursor[i * ge.slices + tid] = 0;      // tk_compact was their last reader (slices <= 1024 threads)
-    if (w.relisted) {                                          // tk_pick was the last reader of the full histogram
+    if (w.relisted) {                                          // tk_compact was the last reader of the full histogram
         if (tid < ge.slices) cursor_b[i * ge.slices + tid] = 0;
         for (int q = tid; q < kBins1; q += kResolveThreads) hist_full[(int64_t)i * kBins1 + q] = 0;
     }
