@@ -654,24 +654,30 @@ __global__ __launch_bounds__(kThreads) void bs_pass_update(const G *__restrict__
     if (tid == 0) partial[(int64_t)i * tb.n_pieces + t] = S;
 }
 
-// Wire form of the sign bits of one vector: output word q holds the coordinates 32 q .. 32 q + 31, bit
-// j % 32 for coordinate j (set = negative), zero past d.  Those 32 coordinates are eight consecutive
-// float4 of one row r of the tile, i.e. the r-th nibble of eight consecutive sign words.
-__global__ __launch_bounds__(kThreads) void bs_pack_signs(const uint16_t *__restrict__ words, int64_t d,
-                                                          uint32_t *__restrict__ out)
+// Wire form of one message: the n_scales scales (none where only the bits are wanted), then the sign bits: output word
+// q holds the coordinates 32 q .. 32 q + 31, bit j % 32 for coordinate j (set = negative), zero past d.  Those 32
+// coordinates are eight consecutive float4 of one row r of the tile, i.e. the r-th nibble of eight consecutive sign
+// words, which one 16-byte load brings in.  A launch of a few microseconds, bound by latency: the scales ride in it, since
+// a copy of their own took as long again.
+__global__ __launch_bounds__(kThreads) void bs_pack_message(const float *__restrict__ scales, int32_t n_scales,
+                                                            const uint16_t *__restrict__ words, int64_t d,
+                                                            float *__restrict__ out_scales, uint32_t *__restrict__ out_bits)
 {
     const int64_t q = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (q < n_scales) out_scales[q] = scales[q];
     if (q * 32 >= d) return;
     const int64_t t = (q * 32) / kTile;
     const int vec0 = (int)((q * 32) % kTile) / 4;            // first of the eight float4
-    const int r = vec0 / kThreads, tid0 = vec0 % kThreads;
+    const int r = vec0 / kThreads, tid0 = vec0 % kThreads;   // tid0: a multiple of 8
+    const uint4 w = *reinterpret_cast<const uint4 *>(words + t * kThreads + tid0);
+    const uint32_t pair[4] = {w.x, w.y, w.z, w.w};
     uint32_t bits = 0;
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-        bits |= (((uint32_t)words[t * kThreads + tid0 + u] >> (r * 4)) & 0xfu) << (4 * u);
+    for (int u = 0; u < 4; ++u)
+        bits |= (((pair[u] >> (r * 4)) & 0xfu) | (((pair[u] >> (16 + r * 4)) & 0xfu) << 4)) << (8 * u);
     const int64_t left = d - q * 32;
     if (left < 32) bits &= (1u << left) - 1u;
-    out[q] = bits;
+    out_bits[q] = bits;
 }
 
 // e_i of one worker in its defined form, from the stored x and the pending scales.  out may be xrow itself
