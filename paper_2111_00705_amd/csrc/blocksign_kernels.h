@@ -56,7 +56,51 @@ struct BsTable {
     const int32_t *scale_list;   // [n_scale_list] the blocks whose scale bs_scale forms from the piece sums: all but
     int32_t n_scale_list;        // those that lie inside one tile next to other pieces (bs_pass writes their scale)
     int32_t xcd_chunk;           // bs_pass: tile_of_block's chunk
+    int32_t small_log2;          // > 0: uniform blocks of 2^small_log2 coordinates, 4 <= 2^small_log2 < kTile (short blocks)
 };
+
+// Short blocks.  With uniform blocks of a power of two below a tile a float4 lies inside one block, whose number is a shift
+// of the coordinate, and a block's float4 sit in consecutive lanes of one row r of the tile (or in consecutive rows):
+// the sum of |x| is a butterfly in registers, up to 256 coordinates inside one wavefront, and the block's scale is
+// complete in the workgroup of its tile.  No table, no staging in LDS, no bs_scale.  Step plus get_theta, n = 16,
+// d = 11.2 M, general way / this one, us: error feedback B = 16 660 / 507, B = 256 483 / 476, B = 2048 540 / 476; CD-Adam
+// B = 16 810 / 510, B = 1024 606 / 540; n = 20, d = 300, B = 16 under CD-Adam 43 / 24.
+constexpr int kSmallMinLog2 = 2, kSmallMaxLog2 = 11;      // 4 .. 2048 coordinates
+
+// Sums of |x| over the block of each row's float4 of this thread, fp64 in a fixed order: S[r] for the block that holds the
+// coordinates 4 (tid + 256 r) .. + 3 of the tile (padding holds 0).  part: 16 doubles of LDS.  All threads of the
+// workgroup call this; contains a barrier for blocks of more than 256 coordinates.
+__device__ __forceinline__ void small_block_sums(const float (&x)[4][4], int log2_len, double (&S)[4], double *part)
+{
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        S[r] = ((double)fabsf(x[r][0]) + (double)fabsf(x[r][1])) + ((double)fabsf(x[r][2]) + (double)fabsf(x[r][3]));
+    const int lanes = 1 << min(log2_len - 2, 6);
+    for (int off = 1; off < lanes; off <<= 1) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) S[r] += __shfl_xor(S[r], off, kWave);
+    }
+    if (log2_len <= 8) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane == 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[r * 4 + wave] = S[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        if (log2_len == 9) {
+            S[r] = part[r * 4 + (wave & 2)] + part[r * 4 + (wave & 2) + 1];
+        } else {
+            const double row = ((part[r * 4] + part[r * 4 + 1]) + part[r * 4 + 2]) + part[r * 4 + 3];
+            S[r] = row;
+        }
+    }
+    if (log2_len == 11) {
+        S[0] = S[1] = S[0] + S[1];
+        S[2] = S[3] = S[2] + S[3];
+    }
+}
 
 // Sign bits: per worker, per tile, one 16-bit word per thread of the workgroup.  Bit r*4 + c of
 // word `tid` is the sign of the coordinate  tile*4096 + 4*(tid + 256*r) + c,  i.e. of the c-th
@@ -156,7 +200,8 @@ __device__ __forceinline__ void piece_sums(const float (&x)[4][4], int64_t base,
 enum { kBsEf = 0, kBsCd = 1, kBsNaive = 2 };
 
 // G: element type of the gradients, float or uint16_t (bfloat16 bits).
-template <bool kPending, int kMode, typename G>
+// kSmall: short blocks (BsTable::small_log2); partial is not used then.
+template <bool kPending, int kMode, bool kSmall, typename G>
 __global__ __launch_bounds__(kThreads) void bs_pass(const G *__restrict__ g, float *__restrict__ xs,
                                                     int64_t d, int64_t ld, BsTable tb,
                                                     float *scales,          // [n][n_blocks]: the previous step's are
@@ -164,7 +209,7 @@ __global__ __launch_bounds__(kThreads) void bs_pass(const G *__restrict__ g, flo
                                                     uint16_t *__restrict__ signs,
                                                     double *__restrict__ partial)
 {
-    __shared__ double scratch[4];
+    __shared__ double scratch[kSmall ? 16 : 4];
     // dynamic LDS, kPassTileLds bytes when the table has tiles of several pieces (only those use it): the staged
     // |x| and the piece ends.  The host may ask for more: the amount also sets how many workgroups share a
     // compute unit, which this kernel is sensitive to (see pass_lds_bytes in the host code).
@@ -179,7 +224,7 @@ __global__ __launch_bounds__(kThreads) void bs_pass(const G *__restrict__ g, flo
     const int64_t base = (int64_t)t * kTile;
     const G *grow = g + (int64_t)i * d;
     float *xrow = xs + (int64_t)i * ld;
-    const bool uni = tb.uniform_tiles > 0;
+    const bool uni = kSmall || tb.uniform_tiles > 0;
     const int p0 = uni ? t : tb.tile_piece0[t], p1 = uni ? t + 1 : tb.tile_piece0[t + 1];
     const float *sp = s_prev + (int64_t)i * tb.n_blocks;
 
@@ -197,7 +242,13 @@ __global__ __launch_bounds__(kThreads) void bs_pass(const G *__restrict__ g, flo
     const bool single = (p1 - p0 == 1);
     const int P = p1 - p0;
     const int b0 = (uni || (single && !kPending)) ? 0 : tb.piece_blk[p0];     // block of the tile's first piece
-    const float s_single = (kPending && single) ? sp[uni ? t / tb.uniform_tiles : b0] : 0.f;
+    float s_single = (!kSmall && kPending && single) ? sp[uni ? t / tb.uniform_tiles : b0] : 0.f;
+    float s_row[4] = {0.f, 0.f, 0.f, 0.f};          // kSmall: the pending scale of each row's float4
+    if (kSmall && kPending) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            s_row[r] = sp[min((int)((base + 4 * (tid + kThreads * r)) >> tb.small_log2), tb.n_blocks - 1)];
+    }
     if (!single) stage_piece_bounds(bound, p0, p1, tb, base);               // uniform over the workgroup
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -206,6 +257,7 @@ __global__ __launch_bounds__(kThreads) void bs_pass(const G *__restrict__ g, flo
         const float gg[4] = {gv[r].x, gv[r].y, gv[r].z, gv[r].w};
         const float xx[4] = {xv[r].x, xv[r].y, xv[r].z, xv[r].w};
         float keep[4];     // what goes back to the stored vector
+        if (kSmall) s_single = s_row[r];
         int q = (kPending && !single) ? piece_index(bound, P, l0) : 0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -234,6 +286,20 @@ __global__ __launch_bounds__(kThreads) void bs_pass(const G *__restrict__ g, flo
         for (int c = 0; c < 4; ++c) sign_bits |= (__float_as_uint(x[r][c]) >> 31) << (r * 4 + c);
     }
     *word = (uint16_t)sign_bits;
+    if constexpr (kSmall) {
+        // a block's scale is rewritten by its first lane, after the block's own lanes have used the old one: they are in
+        // the same wavefront, or the barrier inside lies between
+        double S[4];
+        small_block_sums(x, tb.small_log2, S, scratch);
+        const int64_t len = (int64_t)1 << tb.small_log2;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int64_t j = base + 4 * (tid + kThreads * r);
+            if ((j & (len - 1)) == 0 && j < d)
+                scales[(int64_t)i * tb.n_blocks + (j >> tb.small_log2)] = (float)(S[r] / (double)min(len, d - j));
+        }
+        return;
+    }
     // every thread has read the scales it needs (the loop above) before any is rewritten (after the barrier inside)
     piece_sums(x, base, p0, p1, tb, scratch, absx, bound, partial + (int64_t)i * tb.n_pieces,
                scales + (int64_t)i * tb.n_blocks);
@@ -521,6 +587,104 @@ __global__ __launch_bounds__(kThreads) void bs_update(int64_t d, int64_t ld, int
         st4_state<kStreamState>(v + j, vv[r]);
         st4_state<kStreamState>(vhat + j, vh[r]);
     }
+}
+
+// bs_update for short blocks (BsTable::small_log2): a quarter of a tile per workgroup, one float4 per thread.  Workgroup
+// 4 t + w takes the words of the threads 64 w .. 64 w + 63 of tile t, wavefront r of it their nibble r, so the four
+// wavefronts share the sign words they read, and with one float4 the registers leave room for many wavefronts: the
+// sign words and scales of eight workers are in flight together.  HBM-bound where the vector is long (32 B per
+// coordinate, n/8 B of signs, 4 n / B B of scales), latency-bound below a million coordinates.
+// kMarkov (blocks of at most 256 coordinates, which lie inside a wavefront): CD-Adam's server stage, lines 8-16 of
+// Algorithm 1 in this one launch (no bs_scale, no bs_apply).
+template <bool kEarlyState, bool kMarkov, bool kStreamState>
+__global__ __launch_bounds__(kThreads) void bs_update_small(int64_t d, int64_t ld, int n, BsTable tb,
+                                                            const float *__restrict__ scales,
+                                                            const uint16_t *__restrict__ signs,
+                                                            float *__restrict__ theta, float *__restrict__ m,
+                                                            float *__restrict__ v, float *__restrict__ vhat, AmsParams p,
+                                                            BsMarkov mk)
+{
+    const int t = blockIdx.x >> 2;
+    const int slot = (blockIdx.x & 3) * kWave + (threadIdx.x & 63), r = threadIdx.x >> 6;   // thread of the tile, row
+    const int64_t j = (int64_t)t * kTile + 4 * (slot + kThreads * r);
+    const int blk = min((int)(j >> tb.small_log2), tb.n_blocks - 1);
+    const int64_t sstride = ld / kTile * kThreads;
+    const uint16_t *srow = signs + (int64_t)t * kThreads + slot;
+    const float *sc = scales + blk;
+
+    float4 th, mm, vv, vh;
+    if (kEarlyState) {
+        th = ld4_state<kStreamState>(theta + j);
+        mm = ld4_state<kStreamState>(m + j);
+        vv = ld4_state<kStreamState>(v + j);
+        vh = ld4_state<kStreamState>(vhat + j);
+    }
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int i0 = 0; i0 < n; i0 += kSignBatch) {
+        uint32_t bits[kSignBatch];
+        float s[kSignBatch];
+#pragma unroll
+        for (int u = 0; u < kSignBatch; ++u) {
+            const int i = min(i0 + u, n - 1);            // clamped: the copies past n are not used
+            bits[u] = srow[i * sstride];
+            s[u] = sc[(int64_t)i * tb.n_blocks];
+        }
+#pragma unroll
+        for (int u = 0; u < kSignBatch; ++u) {
+            if (i0 + u < n) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) acc[c] = fadd(acc[c], signed_scale(s[u], bits[u] >> (4 * r), c));
+            }
+        }
+    }
+    // padding coordinates take no gradient
+    float gb[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) gb[c] = j + c < d ? fdiv(acc[c], p.n_workers) : 0.f;
+    if (kMarkov) {
+        const float4 gh4 = ld4(mk.ghat + j), gt4 = ld4(mk.gtil + j);
+        const float gh[4] = {gh4.x, gh4.y, gh4.z, gh4.w}, gt[4] = {gt4.x, gt4.y, gt4.z, gt4.w};
+        float nh[4], w[4];
+        uint32_t neg = 0;
+        double S = 0.0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            nh[c] = (j + c < d) ? fadd(gh[c], gb[c]) : gh[c];          // padding coordinates stay 0
+            w[c] = (j + c < d) ? fsub(nh[c], gt[c]) : 0.f;
+            neg |= (__float_as_uint(w[c]) >> 31) << c;
+        }
+        st4(mk.ghat + j, make_float4(nh[0], nh[1], nh[2], nh[3]));
+        S = ((double)fabsf(w[0]) + (double)fabsf(w[1])) + ((double)fabsf(w[2]) + (double)fabsf(w[3]));
+        const int lanes = 1 << (tb.small_log2 - 2);
+        for (int off = 1; off < lanes; off <<= 1) S += __shfl_xor(S, off, kWave);
+        const int64_t len = (int64_t)1 << tb.small_log2;
+        const int64_t first = j & ~(len - 1);
+        const float s = (float)(S / (double)max((int64_t)1, min(len, d - first)));
+        if (j == first && j < d) mk.scales[blk] = s;
+        // the server's sign words: the four wavefronts hold a nibble each
+        __shared__ uint32_t nib[4][kWave];
+        nib[r][threadIdx.x & 63] = neg;
+        __syncthreads();
+        if (r == 0) {
+            const int lane = threadIdx.x;
+            mk.signs[(int64_t)t * kThreads + slot] =
+                (uint16_t)(nib[0][lane] | (nib[1][lane] << 4) | (nib[2][lane] << 8) | (nib[3][lane] << 12));
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) gb[c] = (j + c < d) ? fadd(gt[c], signed_scale(s, neg, c)) : gt[c];   // gtilde
+        st4(mk.gtil + j, make_float4(gb[0], gb[1], gb[2], gb[3]));
+    }
+    if (!kEarlyState) {
+        th = ld4_state<kStreamState>(theta + j);
+        mm = ld4_state<kStreamState>(m + j);
+        vv = ld4_state<kStreamState>(v + j);
+        vh = ld4_state<kStreamState>(vhat + j);
+    }
+    amsgrad_update4(th, mm, vv, vh, make_float4(gb[0], gb[1], gb[2], gb[3]), p);
+    st4_state<kStreamState>(theta + j, th);
+    st4_state<kStreamState>(m + j, mm);
+    st4_state<kStreamState>(v + j, vv);
+    st4_state<kStreamState>(vhat + j, vh);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -145,9 +145,9 @@ inline bool state_exceeds_caches(const comp_ams *h)
 // 1.32 ms up to 24 KB, 1.54 ms at 32 KB, 1.83 ms at 40 KB), so it never gets more than 16 KB beyond its need.
 inline unsigned pass_lds_bytes(const comp_ams *h, bool grads16)
 {
-    const unsigned need = h->has_split_tiles ? kPassTileLds : 0u;
+    const unsigned need = h->has_split_tiles && !h->tb.small_log2 ? kPassTileLds : 0u;
     if (h->lds_choice >= 0) return std::max(need, (unsigned)h->lds_choice);
-    if (h->mostly_split_tiles) return need;
+    if (h->mostly_split_tiles && !h->tb.small_log2) return need;
     if (grads16) return std::max(need, 16u * 1024u);
     // (with the tile order of xcd_chunk_for the larger amount pays from about half a GiB of rows: n = 16, d = 11.2 M
     // 354 against 358-360 us, n = 8, d = 25.6 M 393-395 against 410 us)
@@ -448,6 +448,9 @@ int build_block_table(comp_ams *h, const std::vector<int64_t> &off, int64_t unif
     h->tb.n_blocks = nb;
     h->tb.n_pieces = (int32_t)piece_hi.size();
     h->tb.uniform_tiles = (uniform_len > 0 && uniform_len % kTile == 0) ? (int32_t)(uniform_len / kTile) : 0;
+    h->tb.small_log2 = 0;
+    for (int lg = kSmallMinLog2; lg <= kSmallMaxLog2; ++lg)
+        if (uniform_len == (int64_t)1 << lg && nb > 1) h->tb.small_log2 = lg;
     apply_streaming(h);
     {
         bool ok = true;
@@ -514,12 +517,27 @@ int copy_in(comp_ams *h, float *dst_dev, const float *src, size_t count, int on_
     return COMP_AMS_OK;
 }
 
+// bs_update_small for the sign words and scales of the most recent step.  Few tiles: nothing hides the state loads, so
+// they are issued first (kEarlyState).
+template <bool kMarkov>
+void launch_update_small(comp_ams *h, hipStream_t st, const AmsParams &p, const BsMarkov &mk)
+{
+    by_flag(h->params.stream_state, [&](auto ss) { by_flag(h->ld / kTile < 2048, [&](auto early) {
+        KLAUNCH((bs_update_small<decltype(early)::value, kMarkov, decltype(ss)::value>), (unsigned)(h->ld / kTile * 4), kThreads, st,
+                h->d, h->ld, h->n, h->tb, h->scales, h->signs, h->theta, h->m, h->v, h->vhat, p, mk);
+    }); });
+}
+
 // bs_update for the sign words, piece sums and scales of the most recent step, with the hyper-parameters p.
 void launch_bs_update(comp_ams *h, hipStream_t st, const AmsParams &p)
 {
     const BsTable &tb = h->tb;
     const unsigned ugrid = (unsigned)(h->ld / kTile);
     launch_timed(h, P_BS_UPDATE, st, [&] {
+        if (tb.small_log2 > 0) {
+            launch_update_small<false>(h, st, p, BsMarkov{});
+            return;
+        }
         // few tiles: nothing hides the state loads, so issue them first; many tiles: load late, run more
         // workgroups per compute unit
         const bool early = h->ld / kTile < 2048;
@@ -547,18 +565,18 @@ int step_blocksign(comp_ams *h, const G *g, hipStream_t st)
     const BsTable &tb = h->tb;
     const dim3 grid(grid_blocks(h->ld / kTile, tb.xcd_chunk), h->n);
     const unsigned lds = sizeof(G) == 2 ? h->pass_lds16 : h->pass_lds;
-    launch_timed(h, P_BS_PASS, st, [&] {
+    launch_timed(h, P_BS_PASS, st, [&] { by_flag(tb.small_log2 > 0, [&](auto sm) {
         if (h->method == COMP_AMS_METHOD_NAIVE)   // C(g_i) itself: the stored rows are not touched
-            KLAUNCH_LDS((bs_pass<false, kBsNaive, G>), grid, kThreads, lds, st, g, h->e, h->d, h->ld, tb, h->scales,
+            KLAUNCH_LDS((bs_pass<false, kBsNaive, decltype(sm)::value, G>), grid, kThreads, lds, st, g, h->e, h->d, h->ld, tb, h->scales,
                     h->signs, h->partial);
         else if (h->pending)
-            KLAUNCH_LDS((bs_pass<true, kBsEf, G>), grid, kThreads, lds, st, g, h->e, h->d, h->ld, tb, h->scales, h->signs,
+            KLAUNCH_LDS((bs_pass<true, kBsEf, decltype(sm)::value, G>), grid, kThreads, lds, st, g, h->e, h->d, h->ld, tb, h->scales, h->signs,
                     h->partial);
         else
-            KLAUNCH_LDS((bs_pass<false, kBsEf, G>), grid, kThreads, lds, st, g, h->e, h->d, h->ld, tb, h->scales, h->signs,
+            KLAUNCH_LDS((bs_pass<false, kBsEf, decltype(sm)::value, G>), grid, kThreads, lds, st, g, h->e, h->d, h->ld, tb, h->scales, h->signs,
                     h->partial);
-    });
-    if (!h->fused_scale && tb.n_scale_list > 0)
+    }); });
+    if (!h->fused_scale && !tb.small_log2 && tb.n_scale_list > 0)
         launch_timed(h, P_BS_SCALE, st, [&] {
             KLAUNCH_LDS((bs_scale), dim3(tb.n_scale_list, h->n), scale_threads(h), scale_lds(h), st, h->partial, tb, h->scales);
         });
@@ -621,18 +639,27 @@ int step_blocksign_cd(comp_ams *h, const G *g, hipStream_t st)
     const dim3 grid(grid_blocks(h->ld / kTile, tb.xcd_chunk), h->n);
     const unsigned ugrid = (unsigned)(h->ld / kTile);
     const unsigned lds = sizeof(G) == 2 ? h->pass_lds16 : h->pass_lds;
-    launch_timed(h, P_BS_PASS, st, [&] {
+    launch_timed(h, P_BS_PASS, st, [&] { by_flag(tb.small_log2 > 0, [&](auto sm) {
         if (h->pending)
-            KLAUNCH_LDS((bs_pass<true, kBsCd, G>), grid, kThreads, lds, st, g, h->e, h->d, h->ld, tb, h->scales, h->signs,
+            KLAUNCH_LDS((bs_pass<true, kBsCd, decltype(sm)::value, G>), grid, kThreads, lds, st, g, h->e, h->d, h->ld, tb, h->scales, h->signs,
                     h->partial);
         else
-            KLAUNCH_LDS((bs_pass<false, kBsCd, G>), grid, kThreads, lds, st, g, h->e, h->d, h->ld, tb, h->scales, h->signs,
+            KLAUNCH_LDS((bs_pass<false, kBsCd, decltype(sm)::value, G>), grid, kThreads, lds, st, g, h->e, h->d, h->ld, tb, h->scales, h->signs,
                     h->partial);
-    });
+    }); });
+    if (tb.small_log2 > 0 && tb.small_log2 <= 8) {
+        // blocks inside a wavefront: lines 8-16 in one launch
+        launch_timed(h, P_BS_SERVER, st, [&] {
+            const BsMarkov mk{h->ghat_srv, h->gtil, h->signs_srv, h->partial_srv, h->scales_srv, 1};
+            launch_update_small<true>(h, st, h->params, mk);
+        });
+        h->pending = true;
+        return COMP_AMS_OK;
+    }
     // every tile exactly one block (uniform blocks of one tile): the worker scales and the server's own
     // scale are formed inside bs_update, which then also applies the server's message - two launches in all
     const bool whole = h->fused_scale && tb.n_pieces == tb.n_blocks;
-    if (!whole && tb.n_scale_list > 0)
+    if (!whole && !tb.small_log2 && tb.n_scale_list > 0)
         launch_timed(h, P_BS_SCALE, st, [&] {
             KLAUNCH_LDS((bs_scale), dim3(tb.n_scale_list, h->n), scale_threads(h), scale_lds(h), st, h->partial, tb, h->scales);
         });

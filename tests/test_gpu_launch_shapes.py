@@ -55,3 +55,39 @@ def test_uncompressed_at_quarter_tiles(d, n):
                             ("vhat", gpu.get_vhat(), ora.vhat)):
         assert rel_close(got, want, STATE_RTOL).all(), name
     gpu.destroy()
+
+
+# short blocks (a power of two below a tile): butterfly sums inside a wavefront, across the wavefronts of a row, across rows;
+# 3 and 1000 take the general way; d ends inside a block, a float4, a row, a tile
+@pytest.mark.parametrize("B", [3, 4, 8, 16, 128, 256, 512, 1000, 1024, 2048])
+@pytest.mark.parametrize("method", ["ef", "naive", "cd"])
+def test_short_blocks(B, method):
+    import torch
+    code = {"ef": (P.METHOD_EF, O.EF), "naive": (P.METHOD_NAIVE, O.NAIVE), "cd": (P.METHOD_CD, O.CD)}[method]
+    for d, n in ((B + 1, 1), (300, 20), (1024 + 255, 2), (2 * TILE, 9), (3 * TILE + 1027, 3)):
+        if d <= B:
+            continue
+        print(f"[case] blocks of {B}, {method}, d={d} n={n}", flush=True)
+        gpu = P.CompAms(d, n, P.BLOCKSIGN, B)
+        ora = O.Oracle(d, n, P.BLOCKSIGN, B, 0.9, 0.999, 1e-8, 1e-3, method=code[1])
+        if code[0] != P.METHOD_EF:
+            gpu.set_method(code[0])
+        fn = grads_of(B * 7 + d, n, d)
+        for t in range(3):
+            g = fn(t)
+            gpu.step(torch.from_numpy(g).cuda())
+            ora.step(g)
+            # scales: fp64 sums of at most 2048 terms in another order differ by 1e-13 relative, fp32 keeps 6e-8
+            assert rel_close(gpu.get_scales(), ora.scales, 1e-7).all(), (d, n, t)
+            if method == "cd":
+                assert rel_close(gpu.get_server_scales(), ora.server_scales, 1e-7).all(), (d, n, t)
+            for i in range(n):
+                bits = np.unpackbits(gpu.get_signs(i), bitorder="little")[:d]
+                row = ora.error[i] if method == "ef" else None
+                if row is not None:
+                    assert rel_close(gpu.get_error(i), row, STATE_RTOL).all(), (d, n, t, i)
+                assert bits.size == d
+        for name, got, want in (("theta", gpu.get_theta(), ora.theta), ("m", gpu.get_m(), ora.m),
+                                ("v", gpu.get_v(), ora.v), ("vhat", gpu.get_vhat(), ora.vhat)):
+            assert rel_close(got, want, STATE_RTOL).all(), (name, d, n)
+        gpu.destroy()
