@@ -28,7 +28,7 @@
 //
 //   bs_pass<.., kBsCd>   ghat_i += pending c_i, u = g - ghat_i, store ghat_i, sign bits and piece sums of u
 //   bs_scale             as above
-//   bs_update<.., kMarkov = true>  mean of the c_i as above, ghat += mean, w = ghat - gtilde, sign bits and piece
+//   bs_server            mean of the c_i as above, ghat += mean, w = ghat - gtilde, sign bits and piece
 //                        sums of w (the server's compression, lines 8-9 of Algorithm 1)
 //   bs_scale             once more, for the single vector w
 //   bs_apply             gtilde += copysign(s, w), then the AMSGrad update with gtilde
@@ -364,16 +364,11 @@ __global__ __launch_bounds__(kThreads) void bs_scale(const double *__restrict__ 
 constexpr int kScaleChunk = 1024;   // workers whose scales are staged in LDS at a time
 constexpr int kSignBatch = 8;       // workers whose sign words are loaded together
 
-// kFusedScale: every tile lies inside one block of at most kMaxFusedPieces pieces; the block's
-// scale is formed here from the partial sums (and stored by the tile at the block's start).
-// kEarlyState: load theta, m, v, vhat at the start (small grids: nothing else would hide that
-// latency); otherwise after the worker loop (large grids: fewer live registers, more workgroups
-// per compute unit).
-// kMarkov: CD-Adam's server stage instead of the AMSGrad update: the mean of the c_i goes into
-// ghat (Algorithm 1, line 8), w = ghat - gtilde is formed, and its sign bits and piece sums are
-// written for the second compression (line 9).  The arrays of the Markov struct are only touched
-// then; theta, m, v, vhat only otherwise.
-// kStreamState: theta, m, v, vhat are loaded and stored as streams (see ld4_state).
+// CD-Adam's server stage (Algorithm 1, lines 8-9): the mean of the c_i goes into ghat, w = ghat - gtilde is formed, and
+// its sign bits and piece sums are written for the second compression.  One workgroup per tile: a piece of w is summed
+// by the workgroup that holds all of it.  kFusedScale: every tile lies inside one block of at most kMaxFusedPieces
+// pieces; the workers' scales are then formed here from the partial sums (and stored by the tile at the block's
+// start).  kStreamState: theta, m, v, vhat (touched only with whole_blocks) are loaded and stored as streams.
 struct BsMarkov {
     float *ghat;            // [ld] the server's aggregate
     float *gtil;            // [ld] gtilde of the step before (rewritten here only when whole_blocks is set)
@@ -384,8 +379,8 @@ struct BsMarkov {
                             // workgroup, so lines 9-16 of Algorithm 1 follow at once (no bs_scale, no bs_apply)
 };
 
-template <bool kFusedScale, bool kEarlyState, bool kMarkov, bool kStreamState>
-__global__ __launch_bounds__(kThreads) void bs_update(int64_t d, int64_t ld, int n, BsTable tb,
+template <bool kFusedScale, bool kStreamState>
+__global__ __launch_bounds__(kThreads) void bs_server(int64_t d, int64_t ld, int n, BsTable tb,
                                                       const double *__restrict__ partial,
                                                       float *__restrict__ scales,
                                                       const uint16_t *__restrict__ signs,
@@ -395,24 +390,13 @@ __global__ __launch_bounds__(kThreads) void bs_update(int64_t d, int64_t ld, int
 {
     __shared__ float s_lds[kScaleChunk];
     __shared__ double scratch[4];
-    __shared__ float absx[kMarkov ? kTile : 1];      // piece_sums of the server's vector
+    __shared__ float absx[kTile];                    // piece_sums of the server's vector
     __shared__ uint16_t bound[kTile];                // piece ends of a tile where several blocks meet
     const int t = blockIdx.x;
     const int tid = threadIdx.x;
     const int64_t base = (int64_t)t * kTile;
     const int n_tiles = (int)(ld / kTile);
 
-    float4 th[4], mm[4], vv[4], vh[4];
-    if (kEarlyState && !kMarkov) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int64_t j = base + 4 * (tid + kThreads * r);
-            th[r] = ld4_state<kStreamState>(theta + j);
-            mm[r] = ld4_state<kStreamState>(m + j);
-            vv[r] = ld4_state<kStreamState>(v + j);
-            vh[r] = ld4_state<kStreamState>(vhat + j);
-        }
-    }
     float acc[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) acc[q] = 0.f;
@@ -509,108 +493,90 @@ __global__ __launch_bounds__(kThreads) void bs_update(int64_t d, int64_t ld, int
             for (int q = 0; q < 16; ++q) acc[q] = fadd(acc[q], signed_scale(sc[blk[q]], w, q));
         }
     }
-    if (kMarkov) {
-        float w[4][4];
-        uint32_t sign_bits = 0;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int64_t j = base + 4 * (tid + kThreads * r);
-            const float4 gh4 = ld4(mk.ghat + j), gt4 = ld4(mk.gtil + j);
-            const float gh[4] = {gh4.x, gh4.y, gh4.z, gh4.w}, gt[4] = {gt4.x, gt4.y, gt4.z, gt4.w};
-            float nh[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                // padding coordinates stay 0
-                nh[c] = (j + c < d) ? fadd(gh[c], fdiv(acc[r * 4 + c], p.n_workers)) : gh[c];
-                w[r][c] = (j + c < d) ? fsub(nh[c], gt[c]) : 0.f;
-                sign_bits |= (__float_as_uint(w[r][c]) >> 31) << (r * 4 + c);
-            }
-            st4(mk.ghat + j, make_float4(nh[0], nh[1], nh[2], nh[3]));
-        }
-        mk.signs[(int64_t)t * kThreads + tid] = (uint16_t)sign_bits;
-        __syncthreads();   // s_lds readers are done before scratch is used (separate arrays; keeps phases apart)
-        if (!mk.whole_blocks) {
-            piece_sums(w, base, p0, p1, tb, scratch, absx, bound, mk.partial, mk.scales);
-            return;
-        }
-        // c = C(w) with the scale of this tile's block, gtilde += c, AMSGrad with gtilde
-        double a64 = 0.0;
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) a64 += (double)fabsf(w[r][c]);
-        const double S = block_sum(a64, scratch);
-        const double blen = (double)min((int64_t)kTile, d - base);
-        const float s = (float)(S / blen);
-        if (tid == 0) mk.scales[b_single] = s;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int64_t j = base + 4 * (tid + kThreads * r);
-            const float4 gt4 = ld4(mk.gtil + j);       // in cache: read a moment ago
-            const float gt[4] = {gt4.x, gt4.y, gt4.z, gt4.w};
-            float nt[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                nt[c] = (j + c < d) ? fadd(gt[c], signed_scale(s, sign_bits, r * 4 + c)) : gt[c];   // padding stays 0
-            const float4 g4 = make_float4(nt[0], nt[1], nt[2], nt[3]);
-            float4 th4 = ld4_state<kStreamState>(theta + j), m4 = ld4_state<kStreamState>(m + j), v4 = ld4_state<kStreamState>(v + j), vh4 = ld4_state<kStreamState>(vhat + j);
-            amsgrad_update4(th4, m4, v4, vh4, g4, p);
-            st4(mk.gtil + j, g4);
-            st4_state<kStreamState>(theta + j, th4);
-            st4_state<kStreamState>(m + j, m4);
-            st4_state<kStreamState>(v + j, v4);
-            st4_state<kStreamState>(vhat + j, vh4);
-        }
-        return;
-    }
-    if (!kEarlyState) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int64_t j = base + 4 * (tid + kThreads * r);
-            th[r] = ld4_state<kStreamState>(theta + j);
-            mm[r] = ld4_state<kStreamState>(m + j);
-            vv[r] = ld4_state<kStreamState>(v + j);
-            vh[r] = ld4_state<kStreamState>(vhat + j);
-        }
-    }
+    float w[4][4];
+    uint32_t sign_bits = 0;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int64_t j = base + 4 * (tid + kThreads * r);
-        // padding coordinates take no gradient
-        const float4 gbar = make_float4(j < d ? fdiv(acc[r * 4], p.n_workers) : 0.f,
-                                        j + 1 < d ? fdiv(acc[r * 4 + 1], p.n_workers) : 0.f,
-                                        j + 2 < d ? fdiv(acc[r * 4 + 2], p.n_workers) : 0.f,
-                                        j + 3 < d ? fdiv(acc[r * 4 + 3], p.n_workers) : 0.f);
-        amsgrad_update4(th[r], mm[r], vv[r], vh[r], gbar, p);
-        st4_state<kStreamState>(theta + j, th[r]);
-        st4_state<kStreamState>(m + j, mm[r]);
-        st4_state<kStreamState>(v + j, vv[r]);
-        st4_state<kStreamState>(vhat + j, vh[r]);
+        const float4 gh4 = ld4(mk.ghat + j), gt4 = ld4(mk.gtil + j);
+        const float gh[4] = {gh4.x, gh4.y, gh4.z, gh4.w}, gt[4] = {gt4.x, gt4.y, gt4.z, gt4.w};
+        float nh[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            // padding coordinates stay 0
+            nh[c] = (j + c < d) ? fadd(gh[c], fdiv(acc[r * 4 + c], p.n_workers)) : gh[c];
+            w[r][c] = (j + c < d) ? fsub(nh[c], gt[c]) : 0.f;
+            sign_bits |= (__float_as_uint(w[r][c]) >> 31) << (r * 4 + c);
+        }
+        st4(mk.ghat + j, make_float4(nh[0], nh[1], nh[2], nh[3]));
+    }
+    mk.signs[(int64_t)t * kThreads + tid] = (uint16_t)sign_bits;
+    __syncthreads();   // s_lds readers are done before scratch is used (separate arrays; keeps phases apart)
+    if (!mk.whole_blocks) {
+        piece_sums(w, base, p0, p1, tb, scratch, absx, bound, mk.partial, mk.scales);
+        return;
+    }
+    // c = C(w) with the scale of this tile's block, gtilde += c, AMSGrad with gtilde
+    double a64 = 0.0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) a64 += (double)fabsf(w[r][c]);
+    const double S = block_sum(a64, scratch);
+    const double blen = (double)min((int64_t)kTile, d - base);
+    const float s = (float)(S / blen);
+    if (tid == 0) mk.scales[b_single] = s;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int64_t j = base + 4 * (tid + kThreads * r);
+        const float4 gt4 = ld4(mk.gtil + j);       // in cache: read a moment ago
+        const float gt[4] = {gt4.x, gt4.y, gt4.z, gt4.w};
+        float nt[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            nt[c] = (j + c < d) ? fadd(gt[c], signed_scale(s, sign_bits, r * 4 + c)) : gt[c];   // padding stays 0
+        const float4 g4 = make_float4(nt[0], nt[1], nt[2], nt[3]);
+        float4 th4 = ld4_state<kStreamState>(theta + j), m4 = ld4_state<kStreamState>(m + j), v4 = ld4_state<kStreamState>(v + j), vh4 = ld4_state<kStreamState>(vhat + j);
+        amsgrad_update4(th4, m4, v4, vh4, g4, p);
+        st4(mk.gtil + j, g4);
+        st4_state<kStreamState>(theta + j, th4);
+        st4_state<kStreamState>(m + j, m4);
+        st4_state<kStreamState>(v + j, v4);
+        st4_state<kStreamState>(vhat + j, vh4);
     }
 }
 
-// bs_update for short blocks (BsTable::small_log2): a quarter of a tile per workgroup, one float4 per thread.  Workgroup
-// 4 t + w takes the words of the threads 64 w .. 64 w + 63 of tile t, wavefront r of it their nibble r, so the four
-// wavefronts share the sign words they read, and with one float4 the registers leave room for many wavefronts: the
-// sign words and scales of eight workers are in flight together.  HBM-bound where the vector is long (32 B per
-// coordinate, n/8 B of signs, 4 n / B B of scales), latency-bound below a million coordinates.
-// kMarkov (blocks of at most 256 coordinates, which lie inside a wavefront): CD-Adam's server stage, lines 8-16 of
-// Algorithm 1 in this one launch (no bs_scale, no bs_apply).
-template <bool kEarlyState, bool kMarkov, bool kStreamState>
-__global__ __launch_bounds__(kThreads) void bs_update_small(int64_t d, int64_t ld, int n, BsTable tb,
-                                                            const float *__restrict__ scales,
-                                                            const uint16_t *__restrict__ signs,
-                                                            float *__restrict__ theta, float *__restrict__ m,
-                                                            float *__restrict__ v, float *__restrict__ vhat, AmsParams p,
-                                                            BsMarkov mk)
+// Server average and AMSGrad update, a quarter of a tile per workgroup, one float4 per thread.  Workgroup 4 t + w takes the
+// words of the threads 64 w .. 64 w + 63 of tile t, wavefront r of it their nibble r, so the four wavefronts share the
+// sign words they read.  With one float4 the registers leave room for many wavefronts, and the sign words (and scales)
+// of eight workers are in flight together.  HBM-bound where the vector is long (32 B per coordinate, n/8 B of signs),
+// latency-bound below a million coordinates.
+// kBlocks: where a float4's scales come from -
+//   kBlocksShort  short blocks (BsTable::small_log2): one scale per float4
+//   kBlocksFused  every tile lies inside one block of at most kMaxFusedPieces pieces: the scale is formed here from the
+//                 piece sums (and stored by the tile at the block's start)
+//   kBlocksTable  any table: one scale where the tile lies inside one block, else one per coordinate
+// kEarlyState: theta, m, v, vhat are loaded first (small grids: nothing else would hide that latency).
+// kMarkov (kBlocksShort with blocks of at most 256 coordinates, which lie inside a wavefront): CD-Adam's server stage,
+// lines 8-16 of Algorithm 1 in this one launch (no bs_scale, no bs_apply).
+enum { kBlocksShort = 0, kBlocksFused = 1, kBlocksTable = 2 };
+template <int kBlocks, bool kEarlyState, bool kMarkov, bool kStreamState>
+__global__ __launch_bounds__(kThreads) void bs_update(int64_t d, int64_t ld, int n, BsTable tb,
+                                                      const double *__restrict__ partial, float *__restrict__ scales,
+                                                      const uint16_t *__restrict__ signs,
+                                                      float *__restrict__ theta, float *__restrict__ m,
+                                                      float *__restrict__ v, float *__restrict__ vhat, AmsParams p,
+                                                      BsMarkov mk)
 {
+    __shared__ float s_lds[kBlocks == kBlocksFused ? kScaleChunk : 1];
     const int t = blockIdx.x >> 2;
-    const int slot = (blockIdx.x & 3) * kWave + (threadIdx.x & 63), r = threadIdx.x >> 6;   // thread of the tile, row
-    const int64_t j = (int64_t)t * kTile + 4 * (slot + kThreads * r);
-    const int blk = min((int)(j >> tb.small_log2), tb.n_blocks - 1);
-    const int64_t sstride = ld / kTile * kThreads;
+    const int lane = threadIdx.x & 63, r = threadIdx.x >> 6;
+    const int slot = (blockIdx.x & 3) * kWave + lane;                       // thread of the tile; r: row
+    const int64_t base = (int64_t)t * kTile;
+    const int64_t j = base + 4 * (slot + kThreads * r);
+    const int n_tiles = (int)(ld / kTile);
+    const int64_t sstride = (int64_t)n_tiles * kThreads;
     const uint16_t *srow = signs + (int64_t)t * kThreads + slot;
-    const float *sc = scales + blk;
 
     float4 th, mm, vv, vh;
     if (kEarlyState) {
@@ -620,20 +586,125 @@ __global__ __launch_bounds__(kThreads) void bs_update_small(int64_t d, int64_t l
         vh = ld4_state<kStreamState>(vhat + j);
     }
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int i0 = 0; i0 < n; i0 += kSignBatch) {
-        uint32_t bits[kSignBatch];
-        float s[kSignBatch];
+    int blk = 0;                                    // the float4's block (kBlocksShort), the tile's (else)
+    if constexpr (kBlocks == kBlocksShort) {
+        blk = min((int)(j >> tb.small_log2), tb.n_blocks - 1);
+        const float *sc = scales + blk;
+        for (int i0 = 0; i0 < n; i0 += kSignBatch) {
+            uint32_t bits[kSignBatch];
+            float s[kSignBatch];
 #pragma unroll
-        for (int u = 0; u < kSignBatch; ++u) {
-            const int i = min(i0 + u, n - 1);            // clamped: the copies past n are not used
-            bits[u] = srow[i * sstride];
-            s[u] = sc[(int64_t)i * tb.n_blocks];
+            for (int u = 0; u < kSignBatch; ++u) {
+                const int i = min(i0 + u, n - 1);            // clamped: the copies past n are not used
+                bits[u] = srow[i * sstride];
+                s[u] = sc[(int64_t)i * tb.n_blocks];
+            }
+#pragma unroll
+            for (int u = 0; u < kSignBatch; ++u) {
+                if (i0 + u < n) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc[c] = fadd(acc[c], signed_scale(s[u], bits[u] >> (4 * r), c));
+                }
+            }
         }
+    } else if constexpr (kBlocks == kBlocksFused) {
+        int q0, q1;
+        double len;
+        if (tb.uniform_tiles > 0) {
+            blk = t / tb.uniform_tiles;
+            q0 = blk * tb.uniform_tiles;
+            q1 = min(q0 + tb.uniform_tiles, n_tiles);
+            len = (double)min((int64_t)tb.uniform_tiles * kTile, d - (int64_t)q0 * kTile);
+        } else {
+            blk = tb.piece_blk[t];                   // one piece per tile
+            q0 = tb.block_piece0[blk];
+            q1 = tb.block_piece0[blk + 1];
+            len = (double)(tb.offsets[blk + 1] - tb.offsets[blk]);
+        }
+        for (int c0 = 0; c0 < n; c0 += kScaleChunk) {
+            const int cn = min(kScaleChunk, n - c0);
+            uint32_t bits[kSignBatch];
 #pragma unroll
-        for (int u = 0; u < kSignBatch; ++u) {
-            if (i0 + u < n) {
+            for (int u = 0; u < kSignBatch; ++u) bits[u] = srow[min(c0 + u, n - 1) * sstride];   // before the barriers
+            if (c0) __syncthreads();
+            for (int u = threadIdx.x; u < cn; u += kThreads) {       // one thread per worker: the scale of this tile's block
+                const double *prow = partial + (int64_t)(c0 + u) * tb.n_pieces;
+                double S = 0.0;
+                for (int q = q0; q < q1; ++q) S += prow[q];
+                const float s = (float)(S / len);
+                if (q0 == t && (blockIdx.x & 3) == 0) scales[(int64_t)(c0 + u) * tb.n_blocks + blk] = s;
+                s_lds[u] = s;
+            }
+            __syncthreads();
+            for (int u0 = 0; u0 < cn; u0 += kSignBatch) {
+                uint32_t next[kSignBatch];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) acc[c] = fadd(acc[c], signed_scale(s[u], bits[u] >> (4 * r), c));
+                for (int u = 0; u < kSignBatch; ++u) next[u] = srow[min(c0 + u0 + kSignBatch + u, n - 1) * sstride];
+#pragma unroll
+                for (int u = 0; u < kSignBatch; ++u) {
+                    if (u0 + u < cn) {
+                        const float s = s_lds[u0 + u];
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) acc[c] = fadd(acc[c], signed_scale(s, bits[u] >> (4 * r), c));
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kSignBatch; ++u) bits[u] = next[u];
+            }
+        }
+    } else {
+        const int p0 = tb.uniform_tiles > 0 ? t : tb.tile_piece0[t], p1 = tb.uniform_tiles > 0 ? t + 1 : tb.tile_piece0[t + 1];
+        blk = tb.uniform_tiles > 0 ? t / tb.uniform_tiles : tb.piece_blk[p0];
+        if (p1 - p0 == 1) {
+            const float *sc = scales + blk;          // uniform over the workgroup
+            for (int i0 = 0; i0 < n; i0 += kSignBatch) {
+                uint32_t bits[kSignBatch];
+                float s[kSignBatch];
+#pragma unroll
+                for (int u = 0; u < kSignBatch; ++u) {
+                    const int i = min(i0 + u, n - 1);
+                    bits[u] = srow[i * sstride];
+                    s[u] = sc[(int64_t)i * tb.n_blocks];
+                }
+#pragma unroll
+                for (int u = 0; u < kSignBatch; ++u) {
+                    if (i0 + u < n) {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) acc[c] = fadd(acc[c], signed_scale(s[u], bits[u] >> (4 * r), c));
+                    }
+                }
+            }
+        } else {
+            // several blocks meet in this tile: the piece of each coordinate by binary search over the tile's piece ends
+            // (consecutive pieces of a tile belong to consecutive blocks); padding past d takes the last one
+            int lo = p0, hi = p1 - 1;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (j < (int64_t)tb.piece_hi[mid]) hi = mid; else lo = mid + 1;
+            }
+            int at[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                while (lo + 1 < p1 && j + c >= (int64_t)tb.piece_hi[lo]) ++lo;
+                at[c] = blk + (lo - p0);
+            }
+            for (int i0 = 0; i0 < n; i0 += 4) {
+                uint32_t bits[4];
+                float s[4][4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int i = min(i0 + u, n - 1);
+                    bits[u] = srow[i * sstride];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) s[u][c] = scales[(int64_t)i * tb.n_blocks + at[c]];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (i0 + u < n) {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) acc[c] = fadd(acc[c], signed_scale(s[u][c], bits[u] >> (4 * r), c));
+                    }
+                }
             }
         }
     }
@@ -663,10 +734,9 @@ __global__ __launch_bounds__(kThreads) void bs_update_small(int64_t d, int64_t l
         if (j == first && j < d) mk.scales[blk] = s;
         // the server's sign words: the four wavefronts hold a nibble each
         __shared__ uint32_t nib[4][kWave];
-        nib[r][threadIdx.x & 63] = neg;
+        nib[r][lane] = neg;
         __syncthreads();
         if (r == 0) {
-            const int lane = threadIdx.x;
             mk.signs[(int64_t)t * kThreads + slot] =
                 (uint16_t)(nib[0][lane] | (nib[1][lane] << 4) | (nib[2][lane] << 8) | (nib[3][lane] << 12));
         }

@@ -517,41 +517,25 @@ int copy_in(comp_ams *h, float *dst_dev, const float *src, size_t count, int on_
     return COMP_AMS_OK;
 }
 
-// bs_update_small for the sign words and scales of the most recent step.  Few tiles: nothing hides the state loads, so
-// they are issued first (kEarlyState).
-template <bool kMarkov>
-void launch_update_small(comp_ams *h, hipStream_t st, const AmsParams &p, const BsMarkov &mk)
+// bs_update for the sign words, piece sums and scales of the most recent step, with the hyper-parameters p.  Few tiles:
+// nothing hides the state loads, so they are issued first (kEarlyState).
+template <int kBlocks, bool kMarkov>
+void launch_update(comp_ams *h, hipStream_t st, const AmsParams &p, const BsMarkov &mk)
 {
     by_flag(h->params.stream_state, [&](auto ss) { by_flag(h->ld / kTile < 2048, [&](auto early) {
-        KLAUNCH((bs_update_small<decltype(early)::value, kMarkov, decltype(ss)::value>), (unsigned)(h->ld / kTile * 4), kThreads, st,
-                h->d, h->ld, h->n, h->tb, h->scales, h->signs, h->theta, h->m, h->v, h->vhat, p, mk);
+        KLAUNCH((bs_update<kBlocks, decltype(early)::value, kMarkov, decltype(ss)::value>), (unsigned)(h->ld / kTile * 4),
+                kThreads, st, h->d, h->ld, h->n, h->tb, h->partial, h->scales, h->signs, h->theta, h->m, h->v, h->vhat, p, mk);
     }); });
 }
-
-// bs_update for the sign words, piece sums and scales of the most recent step, with the hyper-parameters p.
 void launch_bs_update(comp_ams *h, hipStream_t st, const AmsParams &p)
 {
-    const BsTable &tb = h->tb;
-    const unsigned ugrid = (unsigned)(h->ld / kTile);
     launch_timed(h, P_BS_UPDATE, st, [&] {
-        if (tb.small_log2 > 0) {
-            launch_update_small<false>(h, st, p, BsMarkov{});
-            return;
-        }
-        // few tiles: nothing hides the state loads, so issue them first; many tiles: load late, run more
-        // workgroups per compute unit
-        const bool early = h->ld / kTile < 2048;
-#define CAMS_BS_UPDATE(F, E)                                                                                  \
-    by_flag(h->params.stream_state, [&](auto ss) {                                                            \
-        KLAUNCH((bs_update<F, E, false, decltype(ss)::value>), ugrid, kThreads, st, h->d, h->ld, h->n, tb,   \
-                h->partial, h->scales, h->signs, h->theta, h->m, h->v, h->vhat, p, BsMarkov{});               \
-    })
-        if (h->fused_scale) {
-            if (early) CAMS_BS_UPDATE(true, true); else CAMS_BS_UPDATE(true, false);
-        } else {
-            if (early) CAMS_BS_UPDATE(false, true); else CAMS_BS_UPDATE(false, false);
-        }
-#undef CAMS_BS_UPDATE
+        if (h->tb.small_log2 > 0)
+            launch_update<kBlocksShort, false>(h, st, p, BsMarkov{});
+        else if (h->fused_scale)
+            launch_update<kBlocksFused, false>(h, st, p, BsMarkov{});
+        else
+            launch_update<kBlocksTable, false>(h, st, p, BsMarkov{});
     });
 }
 
@@ -651,7 +635,7 @@ int step_blocksign_cd(comp_ams *h, const G *g, hipStream_t st)
         // blocks inside a wavefront: lines 8-16 in one launch
         launch_timed(h, P_BS_SERVER, st, [&] {
             const BsMarkov mk{h->ghat_srv, h->gtil, h->signs_srv, h->partial_srv, h->scales_srv, 1};
-            launch_update_small<true>(h, st, h->params, mk);
+            launch_update<kBlocksShort, true>(h, st, h->params, mk);
         });
         h->pending = true;
         return COMP_AMS_OK;
@@ -667,12 +651,12 @@ int step_blocksign_cd(comp_ams *h, const G *g, hipStream_t st)
         const BsMarkov mk{h->ghat_srv, h->gtil, h->signs_srv, h->partial_srv, h->scales_srv, whole ? 1 : 0};
         if (whole)
             by_flag(h->params.stream_state, [&](auto ss) {
-                KLAUNCH((bs_update<true, false, true, decltype(ss)::value>), ugrid, kThreads, st, h->d, h->ld,
+                KLAUNCH((bs_server<true, decltype(ss)::value>), ugrid, kThreads, st, h->d, h->ld,
                         h->n, tb, h->partial, h->scales, h->signs, h->theta, h->m, h->v, h->vhat, h->params, mk);
             });
         else
             by_flag(h->params.stream_state, [&](auto ss) {
-                KLAUNCH((bs_update<false, false, true, decltype(ss)::value>), ugrid, kThreads, st, h->d, h->ld,
+                KLAUNCH((bs_server<false, decltype(ss)::value>), ugrid, kThreads, st, h->d, h->ld,
                         h->n, tb, h->partial, h->scales, h->signs, h->theta, h->m, h->v, h->vhat, h->params, mk);
             });
     });
