@@ -1084,6 +1084,7 @@ constexpr int kFew = 256;         // at most this many elements are ranked direc
 static_assert(kMaxPieces <= 2 * kResolveThreads, "two pieces per thread in the prefix sum");
 
 constexpr int kScanUnroll = 4;    // independent loads per thread in the scans of the dense set
+constexpr int kStaged = 8192;     // elements under the first digit of Tc that are collected in LDS for the further digits
 
 // LDS of the digit search, shared by tk_resolve and tk_select.
 struct ResolveLds {
@@ -1429,6 +1430,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
             uint32_t rstart[kMaxPieces];
             uint32_t plist[kFew];        // pieces that hold an element with the first digit of Tc
             uint32_t n_plist;
+            uint64_t staged[kStaged];
         } pieces;
         ExactLds exact;
     };
@@ -1602,6 +1604,50 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
                 }
                 __syncthreads();
                 tc = L.tc_sh;
+            } else if (found && left <= (uint32_t)kStaged) {
+                // Many elements under the first digit: exact ties, which 16-bit gradients produce by the thousand (a fine
+                // bin holds two of their values), are told apart only by the index bits at the far end of comp.  The
+                // elements are collected in LDS once, a piece per team of 8 lanes and four pieces of a team in flight,
+                // and the further digits scan LDS; through the piece table every digit was a scan of the whole bin.
+                constexpr int kTeam = 8, kTeams = kResolveThreads / kTeam;
+                const int team = tid / kTeam, tl = tid % kTeam;
+                if (tid == 0) L.n_few = 0;
+                __syncthreads();
+                auto collect = [&](uint64_t comp, bool valid) {
+                    const bool hit = valid && (comp >> s_lo) == prefix1;
+                    const uint64_t hm = __ballot(hit);
+                    if (!hm) return;
+                    uint32_t at = 0;
+                    if (lane == 0) at = atomicAdd(&L.n_few, (uint32_t)__popcll(hm));
+                    at = __builtin_amdgcn_readfirstlane(at) + __popcll(hm & ((1ull << lane) - 1ull));
+                    if (hit && at < (uint32_t)kStaged) U.pieces.staged[at] = comp;
+                };
+                for (int p0 = 0; p0 < pieces; p0 += 4 * kTeams) {              // uniform over the workgroup
+                    uint32_t first[4], count[4], most = 0;
+                    uint64_t comp[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int p = p0 + u * kTeams + team;
+                        first[u] = p < pieces ? rstart[p] : 0u;
+                        count[u] = p < pieces ? rpre[p + 1] - rpre[p] : 0u;
+                        comp[u] = (uint32_t)tl < count[u] ? wdense[first[u] + tl] : 0ull;
+                        most = max(most, count[u]);
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) collect(comp[u], (uint32_t)tl < count[u]);
+                    for (uint32_t e = kTeam; __any(e < most); e += kTeam) {    // uniform over the wavefront
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) comp[u] = e + tl < count[u] ? wdense[first[u] + e + tl] : 0ull;
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) collect(comp[u], e + tl < count[u]);
+                    }
+                }
+                __syncthreads();
+                auto staged = [&](const uint32_t (&q)[kScanUnroll], uint64_t (&comp)[kScanUnroll]) {
+#pragma unroll
+                    for (int u = 0; u < kScanUnroll; ++u) comp[u] = q[u] < left ? U.pieces.staged[q[u]] : 0ull;
+                };
+                tc = resolve_digits(staged, left, prefix1, rank1, s_lo, L);
             } else {
                 tc = resolve_digits(fetch, cnt, w.prefix, w.rank, s_hi, L, true);
             }
