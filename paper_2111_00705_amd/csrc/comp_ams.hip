@@ -89,7 +89,7 @@ struct comp_ams {
     TkGeom ge{};
     TkWorker *ws = nullptr;
     uint2 *cand = nullptr;                     // [n][slices][region_cap] candidate (index, value bits)
-    uint32_t *cursor = nullptr;                // [n][slices] entries in each region (zero between steps)
+    uint32_t *cursor = nullptr;                // [n][slices] entries in each region (zero between steps), kCursorStride words apart
     uint4 *tile_dir = nullptr;                 // [n][n_tiles] {offset in the worker's space, counts per wavefront, zeros}
     uint32_t *hist_full = nullptr;             // [n][2048] coarse-bin counts of the whole vector (only after a miss)
     uint32_t *hist1 = nullptr;                 // [n][2048] coarse-bin counts of the candidates
@@ -876,13 +876,13 @@ int reset_topk_workers(comp_ams *h)
     std::vector<TkWorker> init((size_t)h->n);
     fresh_tk_workers(init);
     HIP_TRY(h, hipMemcpy(h->ws, init.data(), init.size() * sizeof(TkWorker), hipMemcpyHostToDevice));
-    HIP_TRY(h, hipMemset(h->cursor, 0, (size_t)h->n * h->ge.slices * sizeof(uint32_t)));
-    HIP_TRY(h, hipMemset(h->cursor_b, 0, (size_t)h->n * h->ge.slices * sizeof(uint32_t)));
-    HIP_TRY(h, hipMemset(h->small_ctr, 0, (size_t)h->n * sizeof(uint32_t)));
+    HIP_TRY(h, hipMemset(h->cursor, 0, (size_t)h->n * h->ge.slices * kCursorStride * sizeof(uint32_t)));
+    HIP_TRY(h, hipMemset(h->cursor_b, 0, (size_t)h->n * h->ge.slices * kCursorStride * sizeof(uint32_t)));
+    HIP_TRY(h, hipMemset(h->small_ctr, 0, (size_t)h->n * kCursorStride * sizeof(uint32_t)));
     if (h->srv.ws) {
         HIP_TRY(h, hipMemcpy(h->srv.ws, init.data(), sizeof(TkWorker), hipMemcpyHostToDevice));
-        HIP_TRY(h, hipMemset(h->srv.cursor, 0, (size_t)h->srv.ge.slices * sizeof(uint32_t)));
-        HIP_TRY(h, hipMemset(h->cursor_b_s, 0, (size_t)h->srv.ge.slices * sizeof(uint32_t)));
+        HIP_TRY(h, hipMemset(h->srv.cursor, 0, (size_t)h->srv.ge.slices * kCursorStride * sizeof(uint32_t)));
+        HIP_TRY(h, hipMemset(h->cursor_b_s, 0, (size_t)h->srv.ge.slices * kCursorStride * sizeof(uint32_t)));
     }
     return COMP_AMS_OK;
 }
@@ -1072,8 +1072,8 @@ int comp_ams_create(comp_ams_t **out, int64_t d, int32_t n, int32_t compressor, 
         const size_t region_entries = (size_t)n * ge.slices * (size_t)ge.region_cap;
         if ((rc = dev_alloc_t(h, h->allocs, &h->ws, (size_t)n)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->cand, region_entries, false)) ||
-            (rc = dev_alloc_t(h, h->allocs, &h->cursor, (size_t)n * ge.slices)) ||
-            (rc = dev_alloc_t(h, h->allocs, &h->cursor_b, (size_t)n * ge.slices)) ||
+            (rc = dev_alloc_t(h, h->allocs, &h->cursor, (size_t)n * ge.slices * kCursorStride)) ||
+            (rc = dev_alloc_t(h, h->allocs, &h->cursor_b, (size_t)n * ge.slices * kCursorStride)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->tile_dir, segs)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->hist_full, (size_t)n * kBins1)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->hist1, (size_t)n * kBins1)) ||
@@ -1082,7 +1082,7 @@ int comp_ams_create(comp_ams_t **out, int64_t d, int32_t n, int32_t compressor, 
             (rc = dev_alloc_t(h, h->allocs, &h->dense, region_entries, false)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->dense_dir, (size_t)n * ge.slices * ge.parts * 4)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->piece_bits, (size_t)n * ge.slices * ge.parts * 4 * kPieceWords, false)) ||
-            (rc = dev_alloc_t(h, h->allocs, &h->small_ctr, (size_t)n)) ||
+            (rc = dev_alloc_t(h, h->allocs, &h->small_ctr, (size_t)n * kCursorStride)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->sel_count, 1)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->sel_out_idx, (size_t)ge.k)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->sel_out_val, (size_t)ge.k)))
@@ -1616,8 +1616,8 @@ int comp_ams_set_method(comp_ams_t *h, int32_t method)
             const size_t region_entries = (size_t)sv.ge.slices * (size_t)sv.ge.region_cap;
             if ((rc = dev_alloc_t(h, h->allocs, &sv.ws, 1)) ||
                 (rc = dev_alloc_t(h, h->allocs, &sv.cand, region_entries, false)) ||
-                (rc = dev_alloc_t(h, h->allocs, &sv.cursor, (size_t)sv.ge.slices)) ||
-                (rc = dev_alloc_t(h, h->allocs, &h->cursor_b_s, (size_t)sv.ge.slices)) ||
+                (rc = dev_alloc_t(h, h->allocs, &sv.cursor, (size_t)sv.ge.slices * kCursorStride)) ||
+                (rc = dev_alloc_t(h, h->allocs, &h->cursor_b_s, (size_t)sv.ge.slices * kCursorStride)) ||
                 (rc = dev_alloc_t(h, h->allocs, &sv.tile_dir, tiles)) ||
                 (rc = dev_alloc_t(h, h->allocs, &h->hist_full_s, (size_t)kBins1)) ||
                 (rc = dev_alloc_t(h, h->allocs, &h->hist1_s, (size_t)kBins1)) ||
