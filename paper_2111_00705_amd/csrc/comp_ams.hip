@@ -100,7 +100,7 @@ struct comp_ams {
     uint64_t *dense = nullptr;                 // laid out like cand: comp of the candidates in the threshold bin
 
     uint2 *dense_dir = nullptr;                // [n][64 * parts * 4] {start, count} of each wavefront's piece
-    uint32_t *small_ctr = nullptr;             // [n] short vectors (step_topk_small): entries listed
+    uint32_t *small_ctr = nullptr;             // [n + 1] short vectors: entries listed (the last one the server's)
     uint32_t *sel_count = nullptr, *sel_out_idx = nullptr;
     float *sel_out_val = nullptr;
     // CD-Adam with Top-k: the same selection structures once more, for the server's single vector
@@ -734,30 +734,39 @@ inline unsigned tk_pass_lds(const comp_ams *h, size_t grad_bytes)
     return rows_exceed_caches(h) && !tk_long_rows(h) ? 7000u : 9u * 1024u;
 }
 
-// Error feedback on a short vector: listing pass, one selection kernel (tk_small_select), update - three launches.
-template <typename G>
-int step_topk_small(comp_ams *h, const G *g, hipStream_t st)
+// Short vectors: the geometry with one region per vector (all of its space), and the selection in one launch.
+inline bool is_short(const comp_ams *h) { return h->ge.n_tiles <= kSmallTiles; }
+inline TkGeom short_geometry(TkGeom ge)
 {
-    TkGeom sge = h->ge;
-    sge.region_cap = (uint32_t)sge.slices * sge.region_cap;      // one region per worker: all of its space
-    sge.slices = 1;
-    sge.slice_tiles = sge.n_tiles;
-    sge.xcd_chunk = 0;
-    launch_timed(h, P_TK_PASS1, st, [&] {
-        KLAUNCH((tk_pass1<kPassEf, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
-                h->tile_dir);
+    ge.region_cap = (uint32_t)ge.slices * ge.region_cap;
+    ge.slices = 1;
+    ge.slice_tiles = ge.n_tiles;
+    ge.xcd_chunk = 0;
+    return ge;
+}
+template <int kSrc, typename G>
+void launch_short_select(comp_ams *h, hipStream_t st, const TkGeom &sge, TkWorker *ws, uint2 *cand, uint32_t *count,
+                         uint4 *tile_dir, const void *a, const float *b, int slot)
+{
+    launch_timed(h, slot, st, [&] {
+        const ExactSource es{kSrc, std::is_same<G, float>::value ? 0 : std::is_same<G, uint16_t>::value ? 1 : 2, a, b};
+        KLAUNCH((tk_small_select), (unsigned)sge.n, kResolveThreads, st, sge, ws, cand, count, tile_dir, es);
     });
-    launch_timed(h, P_TK_RESOLVE, st, [&] {
-        KLAUNCH((tk_small_select), (unsigned)h->n, kResolveThreads, st, sge, h->ws, h->cand, h->small_ctr, h->tile_dir, h->e);
-    });
-    launch_final(h, st);
-    return COMP_AMS_OK;
 }
 
 template <typename G>
 int step_topk(comp_ams *h, const G *g, hipStream_t st)
 {
-    if (h->ge.n_tiles <= kSmallTiles) return step_topk_small(h, g, st);
+    if (is_short(h)) {
+        const TkGeom sge = short_geometry(h->ge);
+        launch_timed(h, P_TK_PASS1, st, [&] {
+            KLAUNCH((tk_pass1<kPassEf, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
+                    h->tile_dir);
+        });
+        launch_short_select<kSrcStored, float>(h, st, sge, h->ws, h->cand, h->small_ctr, h->tile_dir, h->e, nullptr, P_TK_RESOLVE);
+        launch_final(h, st);
+        return COMP_AMS_OK;
+    }
     const TkGeom &ge = h->ge;
     const TkGeom pge = pass_geometry<G>(h);
     launch_timed(h, P_TK_PASS1, st, [&] {
@@ -774,6 +783,16 @@ int step_topk(comp_ams *h, const G *g, hipStream_t st)
 template <typename G>
 int step_topk_naive(comp_ams *h, const G *g, hipStream_t st)
 {
+    if (is_short(h)) {
+        const TkGeom sge = short_geometry(h->ge);
+        launch_timed(h, P_TK_PASS1, st, [&] {
+            KLAUNCH((tk_pass1<kPassNaive, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
+                    h->tile_dir);
+        });
+        launch_short_select<kSrcGradOnly, G>(h, st, sge, h->ws, h->cand, h->small_ctr, h->tile_dir, g, nullptr, P_TK_RESOLVE);
+        launch_final(h, st);
+        return COMP_AMS_OK;
+    }
     const TkGeom &ge = h->ge;
     const TkGeom pge = pass_geometry<G>(h);
     launch_timed(h, P_TK_PASS1, st, [&] {
@@ -804,30 +823,51 @@ int step_plain(comp_ams *h, const G *g, hipStream_t st)
     return COMP_AMS_OK;
 }
 
-// One iteration of Algorithm 1 (CD-Adam) with Top-k in both directions, ten launches.
+// One iteration of Algorithm 1 (CD-Adam) with Top-k in both directions: ten launches, six on a short vector.
 template <typename G>
 int step_topk_cd(comp_ams *h, const G *g, hipStream_t st)
 {
     const TkGeom &ge = h->ge;
     const TkGeom pge = pass_geometry<G>(h);
     const TkSide &sv = h->srv;
-    launch_timed(h, P_TK_PASS1, st, [&] {
-        KLAUNCH_LDS((tk_pass1<kPassCd, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, tk_pass_lds(h, sizeof(G)), st, g, h->e, pge, h->ws,
-                h->cand, h->cursor, h->tile_dir);
-    });
-    launch_select<kSrcGrad, G>(h, st, ge, h->ws, h->cand, h->cursor, h->cursor_b, h->tile_dir, h->hist1, h->histf,
-                               h->hist_full, h->hist2, h->piece_bits, h->dense, h->dense_dir, g, h->e, kWorkerSelectSlots);
+    const bool brief = is_short(h);
+    if (brief) {
+        const TkGeom sge = short_geometry(ge);
+        launch_timed(h, P_TK_PASS1, st, [&] {
+            KLAUNCH((tk_pass1<kPassCd, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
+                    h->tile_dir);
+        });
+        launch_short_select<kSrcGrad, G>(h, st, sge, h->ws, h->cand, h->small_ctr, h->tile_dir, g, h->e, P_TK_RESOLVE);
+    } else {
+        launch_timed(h, P_TK_PASS1, st, [&] {
+            KLAUNCH_LDS((tk_pass1<kPassCd, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, tk_pass_lds(h, sizeof(G)), st, g, h->e, pge, h->ws,
+                    h->cand, h->cursor, h->tile_dir);
+        });
+        launch_select<kSrcGrad, G>(h, st, ge, h->ws, h->cand, h->cursor, h->cursor_b, h->tile_dir, h->hist1, h->histf,
+                                   h->hist_full, h->hist2, h->piece_bits, h->dense, h->dense_dir, g, h->e, kWorkerSelectSlots);
+    }
     launch_timed(h, P_TK_MERGE, st, [&] {
         KLAUNCH((tk_merge), ge.n_tiles, kThreads, st, ge, h->ws, h->cand, h->tile_dir, h->e, h->ghat_srv,
                                                   h->params.n_workers);
     });
-    launch_timed(h, P_TK_PASS1_SERVER, st, [&] {
-        KLAUNCH((tk_pass1<kPassDiff, float>), dim3(grid_blocks(ge.n_tiles, sv.ge.xcd_chunk), 1), kThreads, st, h->ghat_srv,
-                h->gtil, sv.ge, sv.ws, sv.cand, sv.cursor, sv.tile_dir);
-    });
-    launch_select<kSrcDiff, float>(h, st, sv.ge, sv.ws, sv.cand, sv.cursor, h->cursor_b_s, sv.tile_dir, h->hist1_s, h->histf_s,
-                                   h->hist_full_s, h->hist2_s, h->piece_bits_s, h->dense_s, h->dense_dir_s, h->ghat_srv, h->gtil,
-                                   kServerSelectSlots);
+    if (brief) {
+        const TkGeom sge = short_geometry(sv.ge);
+        uint32_t *count = h->small_ctr + (size_t)h->n * kCursorStride;      // the server's, after the workers'
+        launch_timed(h, P_TK_PASS1_SERVER, st, [&] {
+            KLAUNCH((tk_pass1<kPassDiff, float>), dim3(sge.n_tiles, 1), kThreads, st, h->ghat_srv, h->gtil, sge, sv.ws, sv.cand,
+                    count, sv.tile_dir);
+        });
+        launch_short_select<kSrcDiff, float>(h, st, sge, sv.ws, sv.cand, count, sv.tile_dir, h->ghat_srv, h->gtil,
+                                             P_TK_SELECT_SERVER);
+    } else {
+        launch_timed(h, P_TK_PASS1_SERVER, st, [&] {
+            KLAUNCH((tk_pass1<kPassDiff, float>), dim3(grid_blocks(ge.n_tiles, sv.ge.xcd_chunk), 1), kThreads, st, h->ghat_srv,
+                    h->gtil, sv.ge, sv.ws, sv.cand, sv.cursor, sv.tile_dir);
+        });
+        launch_select<kSrcDiff, float>(h, st, sv.ge, sv.ws, sv.cand, sv.cursor, h->cursor_b_s, sv.tile_dir, h->hist1_s, h->histf_s,
+                                       h->hist_full_s, h->hist2_s, h->piece_bits_s, h->dense_s, h->dense_dir_s, h->ghat_srv, h->gtil,
+                                       kServerSelectSlots);
+    }
     launch_timed(h, P_TK_APPLY, st, [&] {
         by_flag(h->params.stream_state, [&](auto ss) {
             KLAUNCH((tk_apply<decltype(ss)::value>), ge.n_tiles, kThreads, st, sv, h->gtil, h->theta, h->m, h->v,
@@ -878,7 +918,7 @@ int reset_topk_workers(comp_ams *h)
     HIP_TRY(h, hipMemcpy(h->ws, init.data(), init.size() * sizeof(TkWorker), hipMemcpyHostToDevice));
     HIP_TRY(h, hipMemset(h->cursor, 0, (size_t)h->n * h->ge.slices * kCursorStride * sizeof(uint32_t)));
     HIP_TRY(h, hipMemset(h->cursor_b, 0, (size_t)h->n * h->ge.slices * kCursorStride * sizeof(uint32_t)));
-    HIP_TRY(h, hipMemset(h->small_ctr, 0, (size_t)h->n * kCursorStride * sizeof(uint32_t)));
+    HIP_TRY(h, hipMemset(h->small_ctr, 0, ((size_t)h->n + 1) * kCursorStride * sizeof(uint32_t)));
     if (h->srv.ws) {
         HIP_TRY(h, hipMemcpy(h->srv.ws, init.data(), sizeof(TkWorker), hipMemcpyHostToDevice));
         HIP_TRY(h, hipMemset(h->srv.cursor, 0, (size_t)h->srv.ge.slices * kCursorStride * sizeof(uint32_t)));
@@ -1082,7 +1122,7 @@ int comp_ams_create(comp_ams_t **out, int64_t d, int32_t n, int32_t compressor, 
             (rc = dev_alloc_t(h, h->allocs, &h->dense, region_entries, false)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->dense_dir, (size_t)n * ge.slices * ge.parts * 4)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->piece_bits, (size_t)n * ge.slices * ge.parts * 4 * kPieceWords, false)) ||
-            (rc = dev_alloc_t(h, h->allocs, &h->small_ctr, (size_t)n * kCursorStride)) ||
+            (rc = dev_alloc_t(h, h->allocs, &h->small_ctr, ((size_t)n + 1) * kCursorStride)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->sel_count, 1)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->sel_out_idx, (size_t)ge.k)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->sel_out_val, (size_t)ge.k)))

@@ -38,8 +38,8 @@
 //
 // The candidate regions are bounded (see region_base): a region that fills up is detected, and the step then
 // goes the way of a guess that was too high (whole-vector count, lists made anew) and, if the lists still do not
-// fit, selects without lists inside tk_resolve (exact_select).  Vectors of at most 16 tiles take three launches: tk_pass1,
-// tk_small_select, tk_final.
+// fit, selects without lists inside tk_resolve (exact_select).  In vectors of at most 16 tiles one kernel
+// (tk_small_select) takes the place of tk_hist, tk_compact and tk_resolve.
 //
 // Exact zeros under error feedback: when fewer than k coordinates are non-zero the k-th largest is a zero and
 // zeros are selected by lower index.  They are never listed as candidates (millions of equal keys would be);
@@ -1666,51 +1666,63 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
 
 
 // ---------------------------------------------------------------------------------------------
-// Short vectors (at most kSmallTiles tiles) under error feedback: the selection in one launch.
-// On such a vector every kernel of the selection chain is a launch on an idle chip, and five of them cost more
-// than the work.  The listing pass is tk_pass1 itself with a single candidate region per worker (few tiles share
-// its cursor); then one workgroup per worker finds the threshold from the list by itself - the digits of Tc over
+// Short vectors (at most kSmallTiles tiles): the selection in one launch.
+// On such a vector every kernel of the selection chain is a launch on an idle chip, and three of them cost more
+// than the work.  The listing pass is tk_pass1 itself with a single candidate region per vector (few tiles share
+// its cursor); then one workgroup per vector finds the threshold from the list by itself - the digits of Tc over
 // the listed comp values, or, when the list does not hold the k-th largest (first step, a guess that was too high,
-// a full region), by counting over the stored row (exact_select).  The tile directory and the list have the
-// usual form, so tk_final and the getters follow unchanged.  (Finding the threshold inside the listing pass, by
-// the workgroup that finishes a worker's last tile, was built and measured: the device-scope fences it needs on
-// this multi-XCD part cost more than the launch they save - 21.6 us against 6 + 5.)
+// a full region), by counting over the vector itself (exact_select).  The tile directory and the list have the
+// usual form, so the kernels after it and the getters follow unchanged.  (Finding the threshold inside the listing
+// pass, by the workgroup that finishes a worker's last tile, was built and measured: the device-scope fences it needs
+// on this multi-XCD part cost more than the launch they save - 21.6 us against 6 + 5.)
+// Bound by latency: a list of up to kScanUnroll entries per thread (a vector of 65 536 coordinates lists 1.2 k) is read
+// once, into registers, and the digits are found from those.
 constexpr int kSmallTiles = 16;
 
-// sge: the handle's geometry with slices = 1 and region_cap = all of a worker's space.  count: [n] entries listed
-// (cleared here for the next step).
+// sge: the vectors' geometry with slices = 1 and region_cap = all of a vector's space.  count: entries listed per
+// vector, kCursorStride words apart (cleared here for the next step).  es: how a vector is re-formed.
 __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom sge, TkWorker *__restrict__ ws,
                                                                    uint2 *__restrict__ cand, uint32_t *__restrict__ count,
-                                                                   uint4 *__restrict__ tile_dir, const float *__restrict__ xs)
+                                                                   uint4 *__restrict__ tile_dir, ExactSource es)
 {
     __shared__ ResolveLds L;
     __shared__ ExactLds E;
     const int i = blockIdx.x;
     const int tid = threadIdx.x;
+    const uint2 *list = cand + worker_base(sge, i);
+    const uint32_t total = count[i * kCursorStride];
     const TkWorker w = ws[i];
     const SelKey sk = sel_key_of(sge.rand, sge.rand.step_now, i);
-    const uint32_t total = count[i * kCursorStride];
-    const ExactSource es{kSrcStored, 0, xs, nullptr};
+    const bool zeros_listed = es.src != kSrcStored || sk.on;         // see tk_pass1
     uint64_t tc;
     bool missed = false;
     if (!w.overflow && total >= sge.k) {
         // every element at or above the guess is listed and there are at least k: Tc is the k-th largest of the
         // list (the comp value itself: a digit's bin may reach below the guess, where nothing is listed)
-        const uint2 *list = cand + worker_base(sge, i);
-        auto fetch = [&](const uint32_t (&q)[kScanUnroll], uint64_t (&comp)[kScanUnroll]) {
-#pragma unroll
-            for (int u = 0; u < kScanUnroll; ++u) {
-                comp[u] = 0ull;
-                if (q[u] < total) {
-                    const uint2 e = list[q[u]];
-                    comp[u] = composite(sel_key(sk, __uint_as_float(e.y), e.x), e.x, sge.idx_bits);
-                }
-            }
+        auto comp_of = [&](uint32_t q) -> uint64_t {
+            if (q >= total) return 0ull;
+            const uint2 e = list[q];
+            return composite(sel_key(sk, __uint_as_float(e.y), e.x), e.x, sge.idx_bits);
         };
-        tc = resolve_digits<false>(fetch, total, 0ull, sge.k, 31 + sge.idx_bits, L);
-    } else if (!w.overflow && !sk.on && w.guess == 0u) {
-        // magnitude keys, every non-zero element is listed and they are fewer than k: the threshold lies among the
-        // zeros, which the list leaves out - all candidates are kept, and Tc comes from counting over the row
+        if (total <= (uint32_t)(kScanUnroll * kResolveThreads)) {
+            uint64_t held[kScanUnroll];
+#pragma unroll
+            for (int u = 0; u < kScanUnroll; ++u) held[u] = comp_of(u * kResolveThreads + tid);
+            auto fetch = [&](const uint32_t (&)[kScanUnroll], uint64_t (&comp)[kScanUnroll]) {
+#pragma unroll
+                for (int u = 0; u < kScanUnroll; ++u) comp[u] = held[u];       // one batch: q[u] = u * kResolveThreads + tid
+            };
+            tc = resolve_digits<false>(fetch, total, 0ull, sge.k, 31 + sge.idx_bits, L);
+        } else {
+            auto fetch = [&](const uint32_t (&q)[kScanUnroll], uint64_t (&comp)[kScanUnroll]) {
+#pragma unroll
+                for (int u = 0; u < kScanUnroll; ++u) comp[u] = comp_of(q[u]);
+            };
+            tc = resolve_digits<false>(fetch, total, 0ull, sge.k, 31 + sge.idx_bits, L);
+        }
+    } else if (!w.overflow && !zeros_listed && w.guess == 0u) {
+        // every non-zero element is listed and they are fewer than k: the threshold lies among the zeros, which the
+        // list leaves out - all candidates are kept, and Tc comes from counting over the vector
         tc = exact_threshold(es, sge, i, L);
     } else {
         missed = true;
