@@ -713,8 +713,12 @@ void launch_final(comp_ams *h, hipStream_t st)
 {
     launch_timed(h, P_TK_FINAL, st, [&] {
         by_flag(h->params.stream_state, [&](auto ss) {
-            KLAUNCH((tk_final<decltype(ss)::value>), h->ge.n_tiles, kThreads, st, h->ge, h->ws, h->cand, h->tile_dir,
-                    h->theta, h->m, h->v, h->vhat, h->params);
+            if (h->ge.n_tiles <= kShortFinalTiles)
+                KLAUNCH((tk_final_short<decltype(ss)::value>), 4 * h->ge.n_tiles, kThreads, st, h->ge, h->ws, h->cand,
+                        h->tile_dir, h->theta, h->m, h->v, h->vhat, h->params);
+            else
+                KLAUNCH((tk_final<decltype(ss)::value>), h->ge.n_tiles, kThreads, st, h->ge, h->ws, h->cand, h->tile_dir,
+                        h->theta, h->m, h->v, h->vhat, h->params);
         });
     });
 }

@@ -542,13 +542,17 @@ constexpr int kFinBatch = 8;   // workers whose candidates a wavefront has in fl
 // worker order.  ws: the records that hold the selection's thresholds (and, for Rand-k, the draw they were made
 // with).  kScatter (CD-Adam, Algorithm 1, line 6): the kept value u = c_i[j] is also added to
 // ghat_i[j] in `rows` ([n][ld]); the old values are fetched for a whole batch before they are used.
-template <bool kScatter>
+// wave: the wavefront of the listing pass whose list is read.  kRow: only the coordinates of row `row` of its quarter are
+// summed, into acc of 256 floats.
+template <bool kScatter, bool kRow>
 __device__ __forceinline__ void sum_kept_tile(float *acc, const TkGeom &ge, const TkWorker *__restrict__ ws,
                                               const uint2 *__restrict__ cand, const uint4 *__restrict__ tile_dir,
-                                              int t, float *__restrict__ rows)
+                                              int t, float *__restrict__ rows, int wave, int row)
 {
     const uint32_t base = (uint32_t)t * kTile;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
+    auto mine = [&](uint32_t j) { return !kRow || (int)((j - base) >> 10) == row; };
+    auto place = [&](uint32_t j) { return kRow ? ((j - base) & 1023u) - 256u * (uint32_t)wave : j - base; };
     for (int w0 = 0; w0 < ge.n; w0 += kWave) {
         const int nw = min(kWave, ge.n - w0);
         // lane l: where worker w0 + l keeps this wavefront's candidates of the tile, and its threshold
@@ -585,7 +589,7 @@ __device__ __forceinline__ void sum_kept_tile(float *acc, const TkGeom &ge, cons
                 const uint64_t tc = ((uint64_t)tc_hi << 32) | tc_lo;
                 SelKey sk = {0u, 0u, 0u};
                 if (ge.rand.on) sk = {1u, (uint32_t)__shfl((int)my_sk.a, w, kWave), (uint32_t)__shfl((int)my_sk.b, w, kWave)};
-                keep[u] = (uint32_t)lane < cnt[u] &&
+                keep[u] = (uint32_t)lane < cnt[u] && mine(e[u].x) &&
                           composite(sel_key(sk, __uint_as_float(e[u].y), e[u].x), e[u].x, ge.idx_bits) >= tc;
                 old[u] = 0.f;
                 if (kScatter && keep[u]) old[u] = rows[(int64_t)(w0 + w) * ge.ld + e[u].x];
@@ -595,7 +599,7 @@ __device__ __forceinline__ void sum_kept_tile(float *acc, const TkGeom &ge, cons
                 const int w = min(wb + u, nw - 1);
                 if (keep[u]) {
                     const float x = __uint_as_float(e[u].y);
-                    const uint32_t l = e[u].x - base;
+                    const uint32_t l = place(e[u].x);
                     acc[l] = fadd(acc[l], x);
                     if (kScatter) rows[(int64_t)(w0 + w) * ge.ld + e[u].x] = fadd(old[u], x);
                 }
@@ -611,8 +615,8 @@ __device__ __forceinline__ void sum_kept_tile(float *acc, const TkGeom &ge, cons
                     for (uint32_t q = kWave + lane; q < cnt[u]; q += kWave) {
                         const uint2 c = src[q];
                         const float x = __uint_as_float(c.y);
-                        if (composite(sel_key(sk, x, c.x), c.x, ge.idx_bits) >= tc) {
-                            const uint32_t l = c.x - base;
+                        if (mine(c.x) && composite(sel_key(sk, x, c.x), c.x, ge.idx_bits) >= tc) {
+                            const uint32_t l = place(c.x);
                             acc[l] = fadd(acc[l], x);
                             if (kScatter) {
                                 float *gh = rows + (int64_t)(w0 + w) * ge.ld + c.x;
@@ -643,7 +647,7 @@ __global__ __launch_bounds__(kThreads) void tk_final(TkGeom ge, const TkWorker *
 #pragma unroll
     for (int r = 0; r < 4; ++r) st4(acc + 4 * (tid + kThreads * r), make_float4(0.f, 0.f, 0.f, 0.f));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    sum_kept_tile<false>(acc, ge, ws, cand, tile_dir, t, nullptr);
+    sum_kept_tile<false, false>(acc, ge, ws, cand, tile_dir, t, nullptr, tid >> 6, 0);
 
     // the state is loaded only now: fewer live registers above (more workgroups per compute unit),
     // which measured faster than loading it first
@@ -671,6 +675,41 @@ __global__ __launch_bounds__(kThreads) void tk_final(TkGeom ge, const TkWorker *
         // with a sparse average vhat = max(vhat, v) moves at few coordinates (v only decays elsewhere)
         st4_if_changed<kStreamState>(vhat + j, vh[r], vh0);
     }
+}
+
+// The same with a quarter of a tile per workgroup, for vectors of at most kShortFinalTiles tiles, which leave the chip
+// idle otherwise: quarter w holds the coordinates of the listing pass's wavefront w, and wavefront r here takes row r
+// of them (one float4 per lane, the state loaded before anything else).  The four wavefronts each read the quarter's
+// lists, which is what it costs.  Step plus get_theta, n = 8, k = 1 %, a tile per workgroup / a quarter, us:
+// d = 65 000 38.0 / 35.9, 262 144 49.1 / 47.0, 1 M 67.2 / 65.8, 2 M 89.5 / 92.0, 4 M 139.7 / 145.5; d = 110 M 2455 / 2497.
+constexpr int kShortFinalTiles = 320;
+template <bool kStreamState>
+__global__ __launch_bounds__(kThreads) void tk_final_short(TkGeom ge, const TkWorker *__restrict__ ws,
+                                                     const uint2 *__restrict__ cand,
+                                                     const uint4 *__restrict__ tile_dir,
+                                                     float *__restrict__ theta, float *__restrict__ m,
+                                                     float *__restrict__ v, float *__restrict__ vhat, AmsParams p)
+{
+    __shared__ float acc4[4][4 * kWave];
+    const int t = blockIdx.x >> 2, w = blockIdx.x & 3;
+    const int lane = threadIdx.x & 63, r = threadIdx.x >> 6;
+    const int64_t j = (int64_t)t * kTile + 1024 * r + 256 * w + 4 * lane;
+    float *acc = acc4[r];
+    float4 th = ld4_state<kStreamState>(theta + j), mm = ld4_state<kStreamState>(m + j),
+           vv = ld4_state<kStreamState>(v + j), vh = ld4_state<kStreamState>(vhat + j);
+    st4(acc + 4 * lane, make_float4(0.f, 0.f, 0.f, 0.f));
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    sum_kept_tile<false, true>(acc, ge, ws, cand, tile_dir, t, nullptr, w, r);
+    const float4 a = ld4(acc + 4 * lane);
+    const float4 gbar = make_float4(fdiv(a.x, p.n_workers), fdiv(a.y, p.n_workers), fdiv(a.z, p.n_workers),
+                                    fdiv(a.w, p.n_workers));
+    const float4 vh0 = vh;
+    amsgrad_update4(th, mm, vv, vh, gbar, p);
+    st4_state<kStreamState>(theta + j, th);
+    st4_state<kStreamState>(m + j, mm);
+    st4_state<kStreamState>(v + j, vv);
+    // with a sparse average vhat = max(vhat, v) moves at few coordinates (v only decays elsewhere)
+    st4_if_changed<kStreamState>(vhat + j, vh, vh0);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1761,7 +1800,7 @@ __global__ __launch_bounds__(kThreads) void tk_merge(TkGeom ge, const TkWorker *
 #pragma unroll
     for (int r = 0; r < 4; ++r) st4(acc + 4 * (tid + kThreads * r), make_float4(0.f, 0.f, 0.f, 0.f));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    sum_kept_tile<true>(acc, ge, ws, cand, tile_dir, t, ghat_rows);
+    sum_kept_tile<true, false>(acc, ge, ws, cand, tile_dir, t, ghat_rows, tid >> 6, 0);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int l = 4 * (tid + kThreads * r);

@@ -91,3 +91,82 @@ def test_short_blocks(B, method):
                                 ("v", gpu.get_v(), ora.v), ("vhat", gpu.get_vhat(), ora.vhat)):
             assert rel_close(got, want, STATE_RTOL).all(), (name, d, n)
         gpu.destroy()
+
+
+def sparse_pair(d, n, k, method, compressor=P.TOPK):
+    code = {"ef": (P.METHOD_EF, O.EF), "naive": (P.METHOD_NAIVE, O.NAIVE), "cd": (P.METHOD_CD, O.CD)}[method]
+    gpu = P.CompAms(d, n, compressor, k)
+    ora = O.Oracle(d, n, compressor, k, 0.9, 0.999, 1e-8, 1e-3, method=code[1])
+    if code[0] != P.METHOD_EF:
+        gpu.set_method(code[0])
+    return gpu, ora
+
+
+def sparse_steps(gpu, ora, fn, steps, method, tag):
+    import torch
+    for t in range(steps):
+        g = fn(t)
+        gpu.step(torch.from_numpy(g).cuda())
+        ora.step(g)
+        for i in range(gpu.n):
+            assert np.array_equal(gpu.get_selected(i)[0], ora.selected[i]), f"{tag} step {t} worker {i}: kept set"
+            if method == "ef":
+                assert np.array_equal(gpu.get_error(i).view(np.uint32), ora.error[i].view(np.uint32)), f"{tag} {t} {i}: error"
+            if method == "cd":
+                assert np.array_equal(gpu.get_ghat_worker(i).view(np.uint32), ora.ghat_workers[i].view(np.uint32)), f"{tag} {t} {i}"
+        if method == "cd":
+            assert np.array_equal(gpu.get_gtilde().view(np.uint32), ora.gtilde.view(np.uint32)), f"{tag} step {t}: gtilde"
+        for name, got, want in (("theta", gpu.get_theta(), ora.theta), ("m", gpu.get_m(), ora.m), ("v", gpu.get_v(), ora.v),
+                                ("vhat", gpu.get_vhat(), ora.vhat)):
+            assert rel_close(got, want, STATE_RTOL).all(), f"{tag} step {t}: {name}"
+
+
+# vectors of up to 16 tiles: one selection kernel, its list in registers up to 4096 entries; 17 tiles: the chain
+@pytest.mark.parametrize("method", ["ef", "naive", "cd"])
+@pytest.mark.parametrize("d,n,k", [(7, 1, 7), (4097, 9, 40), (16 * TILE, 2, 655), (16 * TILE, 2, 20_000), (16 * TILE + 1, 2, 655)])
+def test_short_vectors(method, d, n, k):
+    print(f"[case] short vectors {method} d={d} n={n} k={k}", flush=True)
+    gpu, ora = sparse_pair(d, n, k, method)
+
+    def fn(t):         # a thousandfold drop at step 3: the guess is far too high, the vector is counted anew
+        return grads_of(d + k, n, d)(t) * f32(1e-3 if t == 3 else 1.0)
+    sparse_steps(gpu, ora, fn, 5, method, f"{method} d={d}")
+    gpu.destroy()
+
+
+# tk_final_short / tk_final at the boundary between them; more than 64 kept values in a wavefront's quarter, more than
+# one batch of eight workers
+@pytest.mark.parametrize("tiles,n,share", [(320, 9, 0.3), (321, 9, 0.3), (320, 1, 0.001)])
+def test_update_of_kept_values(tiles, n, share):
+    d = tiles * TILE - 3
+    print(f"[case] update of kept values, {tiles} tiles n={n} share={share}", flush=True)
+    gpu, ora = sparse_pair(d, n, int(d * share), "ef")
+    sparse_steps(gpu, ora, grads_of(tiles + n, n, d), 2, "ef", f"tiles={tiles}")
+    gpu.destroy()
+
+
+# exact ties in the threshold bin: `values` magnitudes, d / values coordinates each - ranked directly, collected in LDS
+# (up to 8192 under the first digit), or scanned in place
+@pytest.mark.parametrize("method", ["ef", "naive", "cd"])
+@pytest.mark.parametrize("values", [2000, 60, 12])
+def test_ties_in_the_threshold_bin(method, values):
+    d, n = 200_003, 2
+    print(f"[case] ties {method} {values} magnitudes", flush=True)
+    gpu, ora = sparse_pair(d, n, 30_001, method)
+
+    def fn(t):
+        r = np.random.default_rng([values, t])
+        mag = np.exp2(-r.integers(0, values, (n, d)) * (16.0 / values)).astype(f32)
+        return np.ascontiguousarray(np.where(r.random((n, d)) < 0.5, mag, -mag).astype(f32))
+    sparse_steps(gpu, ora, fn, 4, method, f"{method} {values}")
+    gpu.destroy()
+
+
+# CD-Adam on a vector long enough for more than 64 candidate regions on the server, with a drop that makes every
+# selection list anew
+def test_cd_lists_anew_on_a_long_vector():
+    d, n = 2100 * TILE + 5, 1
+    print("[case] CD-Adam lists anew, 2101 tiles", flush=True)
+    gpu, ora = sparse_pair(d, n, 50_000, "cd")
+    sparse_steps(gpu, ora, lambda t: grads_of(3, n, d)(t) * f32(10.0 ** (-2 * t)), 3, "cd", "long")
+    gpu.destroy()
