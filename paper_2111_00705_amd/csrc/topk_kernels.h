@@ -900,8 +900,8 @@ __global__ __launch_bounds__(kThreads) void tk_hist(TkGeom ge, const TkWorker *_
 // After a miss tk_hist has counted the whole vector into the worker's full coarse histogram: every workgroup takes
 // the coarse bin of the k-th largest from it and lists the elements in that bin or above, tile by tile, into the
 // worker's regions - through the second set of cursors (cursor_b, all zero here), since the first still holds the
-// counts this kernel's workgroups decide by.  The worker is flagged `relisted`: tk_resolve then takes the elements
-// from these lists (no dense pieces exist) and clears both sets.  A region that fills up there as well sets
+// counts this kernel's workgroups decide by - and count the first digit in that bin as above.  The worker is flagged
+// `relisted`: tk_resolve then takes the elements from these lists (no dense pieces exist) and clears both sets.  A region that fills up there as well sets
 // overflow2: tk_resolve then selects without lists (exact_select).
 template <int kSrc, typename G>
 __global__ __launch_bounds__(kThreads) void tk_compact(TkGeom ge, TkWorker *__restrict__ ws,
@@ -1089,12 +1089,16 @@ __global__ __launch_bounds__(kThreads) void tk_compact(TkGeom ge, TkWorker *__re
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const uint32_t j = base + 4 * (tid + kThreads * r) + c;
-                bool hit = j < d && (sel_key(sk, x[r][c], j) >> kShift1) >= prefix;
+                const uint32_t key = sel_key(sk, x[r][c], j);
+                bool hit = j < d && (key >> kShift1) >= prefix;
                 if (kSrc == kSrcStored && !sk.on) {          // zeros are counted, not listed (as in tk_pass1)
                     const bool zero = j < d && mag_key(x[r][c]) == 0u;
                     zeros += (uint32_t)__popcll(__ballot(zero));
                     hit = hit && !zero;
                 }
+                // the digit below the prefix, as in the usual case
+                if (hit && (key >> kShift1) == prefix)
+                    atomicAdd(&lh2[(key >> (kShift1 - kFirstBits)) & (uint32_t)(kBinsFirst - 1)], 1u);
                 count += (uint32_t)__popcll(__ballot(hit));
                 hits |= (hit ? 1u : 0u) << (r * 4 + c);
             }
@@ -1113,6 +1117,11 @@ __global__ __launch_bounds__(kThreads) void tk_compact(TkGeom ge, TkWorker *__re
                 }
         }
         __syncthreads();   // sh is reused by the next tile
+    }
+    __syncthreads();
+    for (int q = tid; q < kBinsFirst; q += kThreads) {
+        const uint32_t c = lh2[q];
+        if (c) atomicAdd(hist2 + (int64_t)i * kBinsFirst + q, c);
     }
 }
 
@@ -1504,8 +1513,12 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
     } else if (w.whole == kZeroTail) {
         tc = zero_tail_threshold(dir_row, xs + (int64_t)i * ge.ld, ge, w.rank, L);
     } else if (w.relisted && !w.whole) {
-        // lists made anew: the digits over the worker's regions themselves (the elements above the prefix are there
-        // too and do not match it), walked as one run of elements
+        // Lists made anew: the elements under the prefix stand in the worker's regions among those above it.  The first
+        // digit is known as in the usual case; the elements under it are collected in LDS (one pass over the regions, a
+        // region per wavefront) and searched there, or, where they are too many, found by digits over all regions.
+        // First steps, us: CD-Adam n = 8, d = 11.2 M bf16 797 (1261 with every digit scanned over the regions), error
+        // feedback n = 16, d = 11.2 M 929 (1026).
+        L.lh[tid] = first_count;
         const int regions = ge.slices;
         uint32_t mine = 0;
         if (tid < regions) mine = min(cursor_b[(i * regions + tid) * kCursorStride], ge.region_cap);
@@ -1521,29 +1534,67 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
         else {
             const SelKey sk = sel_key_of(ge.rand, ge.rand.step_now, i);
             const uint2 *list = cand + worker_base(ge, i);
-            int top = 1;
-            while (2 * top < regions) top *= 2;
-            auto fetch = [&](const uint32_t (&q)[kScanUnroll], uint64_t (&comp)[kScanUnroll]) {
-                if (q[0] >= cnt) return;
-                int r[kScanUnroll];
+            find_rank_bin(L.lh, L.part, L.res, kBinsFirst, w.rank);
+            const int s_lo = s_hi - kFirstBits;
+            const uint32_t left = L.res[2], rank1 = w.rank - L.res[1];
+            const bool found = L.res[3] != 0u;
+            const uint64_t prefix1 = ((uint64_t)w.prefix << kFirstBits) | L.res[0];
+            if (found && left == rank1) {
+                tc = prefix1 << s_lo;
+            } else if (found && left <= (uint32_t)kStaged) {
+                if (tid == 0) L.n_few = 0;
+                __syncthreads();
+                for (int reg = wave; reg < regions; reg += kResolveThreads / kWave) {
+                    const uint32_t count = rpre[reg + 1] - rpre[reg];
+                    const uint2 *src = list + (uint32_t)reg * ge.region_cap;
+                    for (uint32_t q0 = 0; q0 < count; q0 += 8 * kWave) {
+                        uint2 e[8];
 #pragma unroll
-                for (int u = 0; u < kScanUnroll; ++u) r[u] = 0;
-                for (int bit = top; bit > 0; bit >>= 1) {
-                    uint32_t start[kScanUnroll];
+                        for (int u = 0; u < 8; ++u) {
+                            const uint32_t q = q0 + u * kWave + lane;
+                            e[u] = q < count ? src[q] : make_uint2(0u, 0u);
+                        }
 #pragma unroll
-                    for (int u = 0; u < kScanUnroll; ++u) start[u] = rpre[min(r[u] + bit, regions)];
-#pragma unroll
-                    for (int u = 0; u < kScanUnroll; ++u) r[u] = (start[u] <= q[u] && r[u] + bit < regions) ? r[u] + bit : r[u];
+                        for (int u = 0; u < 8; ++u) {
+                            const uint64_t comp = composite(sel_key(sk, __uint_as_float(e[u].y), e[u].x), e[u].x, ge.idx_bits);
+                            if (q0 + u * kWave + lane < count && (comp >> s_lo) == prefix1) {
+                                const uint32_t at = atomicAdd(&L.n_few, 1u);
+                                if (at < (uint32_t)kStaged) U.pieces.staged[at] = comp;
+                            }
+                        }
+                    }
                 }
-                uint2 e[kScanUnroll];
+                __syncthreads();
+                auto staged = [&](const uint32_t (&q)[kScanUnroll], uint64_t (&comp)[kScanUnroll]) {
 #pragma unroll
-                for (int u = 0; u < kScanUnroll; ++u)
-                    e[u] = q[u] < cnt ? list[(uint32_t)r[u] * ge.region_cap + (q[u] - rpre[r[u]])] : make_uint2(0u, 0u);
+                    for (int u = 0; u < kScanUnroll; ++u) comp[u] = q[u] < left ? U.pieces.staged[q[u]] : 0ull;
+                };
+                tc = resolve_digits(staged, left, prefix1, rank1, s_lo, L);
+            } else {
+                int top = 1;
+                while (2 * top < regions) top *= 2;
+                auto fetch = [&](const uint32_t (&q)[kScanUnroll], uint64_t (&comp)[kScanUnroll]) {
+                    if (q[0] >= cnt) return;
+                    int r[kScanUnroll];
 #pragma unroll
-                for (int u = 0; u < kScanUnroll; ++u)
-                    comp[u] = composite(sel_key(sk, __uint_as_float(e[u].y), e[u].x), e[u].x, ge.idx_bits);
-            };
-            tc = resolve_digits(fetch, cnt, w.prefix, w.rank, s_hi, L);
+                    for (int u = 0; u < kScanUnroll; ++u) r[u] = 0;
+                    for (int bit = top; bit > 0; bit >>= 1) {
+                        uint32_t start[kScanUnroll];
+#pragma unroll
+                        for (int u = 0; u < kScanUnroll; ++u) start[u] = rpre[min(r[u] + bit, regions)];
+#pragma unroll
+                        for (int u = 0; u < kScanUnroll; ++u) r[u] = (start[u] <= q[u] && r[u] + bit < regions) ? r[u] + bit : r[u];
+                    }
+                    uint2 e[kScanUnroll];
+#pragma unroll
+                    for (int u = 0; u < kScanUnroll; ++u)
+                        e[u] = q[u] < cnt ? list[(uint32_t)r[u] * ge.region_cap + (q[u] - rpre[r[u]])] : make_uint2(0u, 0u);
+#pragma unroll
+                    for (int u = 0; u < kScanUnroll; ++u)
+                        comp[u] = composite(sel_key(sk, __uint_as_float(e[u].y), e[u].x), e[u].x, ge.idx_bits);
+                };
+                tc = resolve_digits(fetch, cnt, w.prefix, w.rank, s_hi, L, true);
+            }
         }
     } else if (!w.whole) {
         // tk_compact counted the first digit below the prefix while it copied: take its counts
