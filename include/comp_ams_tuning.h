@@ -44,9 +44,9 @@ int comp_ams_set_tile_order(comp_ams_t *h, int32_t chunk);
  * amount decides how many workgroups share a compute unit (160 KB each), to which the pass responds by a
  * few per cent.  -1 = chosen from the sizes, the method and the gradient type (the default), else
  * 0 .. 61440.  BLOCKSIGN: the pass always gets at least what its block table needs (24 KB when a tile
- * holds several blocks' pieces).  TOPK / RANDK: the amount is added to the 24 KB of candidate staging
- * lists the pass always holds (default under error feedback with 32-bit gradients: 9 KB, or 7000 bytes
- * for rows under 64 Mi coordinates that do not stay in the caches; else none);
+ * holds several blocks' pieces).  TOPK / RANDK: the amount is added to 24 KB (the size of the candidate
+ * staging lists of a workgroup; default under error feedback with 32-bit gradients: 9 KB, or 7000 bytes
+ * for rows under 64 Mi coordinates that exceed the caches; else nothing beyond what the pass uses itself);
  * no effect on vectors of at most 16 tiles.  May be called between steps.
  */
 int comp_ams_set_pass_lds(comp_ams_t *h, int32_t bytes);

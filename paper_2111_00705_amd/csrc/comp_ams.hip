@@ -723,19 +723,22 @@ void launch_final(comp_ams *h, hipStream_t st)
     });
 }
 
-// Dynamic LDS handed to tk_pass1 beyond its own 24 KB of staging lists: unused by the kernel, it only sets how many
-// workgroups share a compute unit (six without it).  The passes that only read want all six (n = 16, d = 11.2 M,
-// CD-Adam: 245 against 257 us with four; n = 8, d = 110 M: 1.134 against 1.173 ms).  The error-feedback pass, which
-// also writes the row back, is best with four or five on 32-bit gradients (n = 8, d = 110 M: 1.67-1.68 ms, 1.70 with
-// six, 1.74 with eight) and gets 9 KB, which leaves four (five for shorter rows, see tk_ef_chunk_for); on 16-bit
-// gradients it issues more instructions per byte and wants the six as well (same shape, bfloat16: 1.44 against
-// 1.76 ms).  comp_ams_set_pass_lds overrides.
-inline unsigned tk_pass_lds(const comp_ams *h, size_t grad_bytes)
+// Dynamic LDS handed to tk_pass1: unused by the kernel, it only sets how many workgroups share a compute unit, counted
+// on top of the 24 KB of staging lists (which the variants that list from registers reserve here instead).  The passes
+// that only read want as many as fit (staging: n = 16, d = 11.2 M, CD-Adam: 245 us with the six that the lists allow,
+// 257 with four; n = 8, d = 110 M: 1.134 against 1.173 ms).  The error-feedback pass, which also writes the row back,
+// is best with four or five on 32-bit gradients (n = 8, d = 110 M: step plus get_theta 2418 us, 2487 with seven) and
+// gets 9 KB, which leaves four (five for shorter rows, see tk_ef_chunk_for); on 16-bit gradients it issues more
+// instructions per byte and wants the six as well (same shape, bfloat16, the pass alone: 1.44 against 1.76 ms).
+// comp_ams_set_pass_lds overrides.
+template <int kMode, typename G>
+unsigned tk_pass_lds(const comp_ams *h)
 {
-    if (h->lds_choice >= 0) return (unsigned)h->lds_choice;
-    if (h->method != COMP_AMS_METHOD_EF || grad_bytes != 4) return 0u;
+    const unsigned lists = kListDirect<kMode, G> ? kStageBytes : 0u;
+    if (h->lds_choice >= 0) return lists + (unsigned)h->lds_choice;
+    if (kMode != kPassEf || sizeof(G) != 4) return 0u;
     // five workgroups per unit for rows that stream and are not long (see tk_ef_chunk_for), else four
-    return rows_exceed_caches(h) && !tk_long_rows(h) ? 7000u : 9u * 1024u;
+    return lists + (rows_exceed_caches(h) && !tk_long_rows(h) ? 7000u : 9u * 1024u);
 }
 
 // Short vectors: the geometry with one region per vector (all of its space), and the selection in one launch.
@@ -774,7 +777,7 @@ int step_topk(comp_ams *h, const G *g, hipStream_t st)
     const TkGeom &ge = h->ge;
     const TkGeom pge = pass_geometry<G>(h);
     launch_timed(h, P_TK_PASS1, st, [&] {
-        KLAUNCH_LDS((tk_pass1<kPassEf, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, tk_pass_lds(h, sizeof(G)), st, g, h->e, pge, h->ws,
+        KLAUNCH_LDS((tk_pass1<kPassEf, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassEf, G>(h)), st, g, h->e, pge, h->ws,
                 h->cand, h->cursor, h->tile_dir);
     });
     launch_select<kSrcStored, float>(h, st, ge, h->ws, h->cand, h->cursor, h->cursor_b, h->tile_dir, h->hist1, h->histf,
@@ -800,7 +803,7 @@ int step_topk_naive(comp_ams *h, const G *g, hipStream_t st)
     const TkGeom &ge = h->ge;
     const TkGeom pge = pass_geometry<G>(h);
     launch_timed(h, P_TK_PASS1, st, [&] {
-        KLAUNCH_LDS((tk_pass1<kPassNaive, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, tk_pass_lds(h, sizeof(G)), st, g, h->e, pge, h->ws,
+        KLAUNCH_LDS((tk_pass1<kPassNaive, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassNaive, G>(h)), st, g, h->e, pge, h->ws,
                 h->cand, h->cursor, h->tile_dir);
     });
     launch_select<kSrcGradOnly, G>(h, st, ge, h->ws, h->cand, h->cursor, h->cursor_b, h->tile_dir, h->hist1, h->histf,
@@ -844,7 +847,7 @@ int step_topk_cd(comp_ams *h, const G *g, hipStream_t st)
         launch_short_select<kSrcGrad, G>(h, st, sge, h->ws, h->cand, h->small_ctr, h->tile_dir, g, h->e, P_TK_RESOLVE);
     } else {
         launch_timed(h, P_TK_PASS1, st, [&] {
-            KLAUNCH_LDS((tk_pass1<kPassCd, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, tk_pass_lds(h, sizeof(G)), st, g, h->e, pge, h->ws,
+            KLAUNCH_LDS((tk_pass1<kPassCd, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassCd, G>(h)), st, g, h->e, pge, h->ws,
                     h->cand, h->cursor, h->tile_dir);
         });
         launch_select<kSrcGrad, G>(h, st, ge, h->ws, h->cand, h->cursor, h->cursor_b, h->tile_dir, h->hist1, h->histf,

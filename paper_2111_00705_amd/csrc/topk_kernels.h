@@ -71,6 +71,7 @@ constexpr int kFirstBits = 10;    // first digit below the prefix, counted by tk
 constexpr int kBinsFirst = 1 << kFirstBits;
 constexpr int kPieceWords = kBinsFirst / 32;   // words of a dense piece's bitmap: which first digits occur in it
 constexpr int kSub = kTile / 4;   // coordinates of a tile that one wavefront handles = capacity of its staged list
+constexpr unsigned kStageBytes = 4 * kSub * (sizeof(float) + sizeof(uint16_t));   // staging lists of a workgroup of tk_pass1
 constexpr int kMinSlices = 64;    // candidate regions per vector: a power of two in [kMinSlices, kMaxSlices]
                                   // (fewer for a vector of fewer tiles than that)
 constexpr int kMaxSlices = 512;
@@ -493,14 +494,93 @@ __device__ __forceinline__ void finish_tile(const float (*stage_val)[kSub], cons
     }
 }
 
+// Whether tk_pass1 lists straight from its registers: each wavefront counts its candidates, the workgroup takes the
+// tile's space, and each wavefront writes its own - against staging lists in LDS that the last wavefront to finish copies
+// out alone.  A store then carries one or two candidates instead of a run of them, which costs nothing until they are
+// many, and no LDS is held.  Step plus get_theta, staged / direct, us: error feedback fp32 n = 16, d = 11.2 M 488 / 475,
+// n = 8, d = 25 M 628 / 606, d = 110 M 2433 / 2418; naive compression (held at 64 registers: eight workgroups per unit
+// where the lists allowed six) n = 8, d = 3 M bf16 83 / 80, n = 4, d = 60 M bf16 613 / 574, Rand-k n = 16, d = 6 M fp32
+// 173 / 164.  Error feedback on 16-bit gradients loses (Rand-k n = 16, d = 1.2 M f16 92.8 / 94.1, Top-k n = 16, d = 11.2 M
+// bf16 439 / 441), and CD-Adam has no pattern (n = 8: d = 11.2 M bf16 374 / 369, d = 8 M f16 with 5 % kept 384 / 389, d = 25 M
+// fp32 695 / 697): those stage.
+template <int kMode, typename G>
+constexpr bool kListDirect = (kMode == kPassEf && sizeof(G) == 4) || kMode == kPassNaive;
+
+// A tile listed straight from the registers.
+template <bool kFull, int kMode, typename G>
+__device__ __forceinline__ void pass1_direct(const G *__restrict__ grow, float *__restrict__ xrow, uint32_t base, uint32_t d,
+                                             const KeptTest &kt, uint32_t guess, const SelKey &sk, const SelKey &sk_prev,
+                                             int stream_rows, uint32_t *sh, const TkGeom &ge, int i, int t,
+                                             uint2 *__restrict__ cand, uint32_t *__restrict__ cursor,
+                                             uint4 *__restrict__ tile_dir, uint32_t *overflow_flag)
+{
+    const int tid = threadIdx.x, wave = tid >> 6;
+    float4 gv[4], xv[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const uint32_t j = base + 4 * (tid + kThreads * r);
+        if constexpr (kMode == kPassDiff)
+            gv[r] = ld4_row(grow + j, stream_rows);
+        else
+            gv[r] = load_grad4(grow, j, d);
+        xv[r] = kMode == kPassNaive ? make_float4(0.f, 0.f, 0.f, 0.f) : ld4_row(xrow + j, stream_rows);
+    }
+    float x[4][4];
+    uint32_t count = 0, zeros = 0, hits = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const uint32_t j = base + 4 * (tid + kThreads * r);
+        const float gg[4] = {gv[r].x, gv[r].y, gv[r].z, gv[r].w};
+        const float xo[4] = {xv[r].x, xv[r].y, xv[r].z, xv[r].w};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if (kMode == kPassNaive) {
+                x[r][c] = (kFull || j + c < d) ? gg[c] : 0.f;
+            } else if (kMode != kPassEf) {
+                x[r][c] = (kFull || j + c < d) ? fsub(gg[c], xo[c]) : 0.f;
+            } else {
+                const float e = was_kept(kt, sel_key(sk_prev, xo[c], j + c), j + c) ? 0.f : xo[c];
+                x[r][c] = (kFull || j + c < d) ? fadd(gg[c], e) : 0.f;
+            }
+        }
+        if (kMode == kPassEf) st4_stream(xrow + j, make_float4(x[r][0], x[r][1], x[r][2], x[r][3]));
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const bool valid = kFull || j + c < d;
+            bool hit = valid && (sel_key(sk, x[r][c], j + c) >> kFineShift) >= guess;
+            if (kMode == kPassEf && !sk.on) {
+                const bool zero = valid && mag_key(x[r][c]) == 0u;
+                zeros += (uint32_t)__popcll(__ballot(zero));
+                hit = hit && !zero;
+            }
+            count += (uint32_t)__popcll(__ballot(hit));
+            hits |= (hit ? 1u : 0u) << (r * 4 + c);
+        }
+    }
+    take_tile_space(count, zeros, sh, ge, i, t, cursor, tile_dir, overflow_flag);
+    uint32_t at = sh[4];
+    if (at == kNoSpace) return;
+    for (int w = 0; w < wave; ++w) at += sh[w];
+    uint2 *dst = cand + worker_base(ge, i);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const bool hit = (hits >> (r * 4 + c)) & 1u;
+            const uint32_t slot = wave_append(hit, at);
+            if (hit) dst[slot] = make_uint2(base + 4 * (tid + kThreads * r) + c, __float_as_uint(x[r][c]));
+        }
+}
+
 // G: element type of g - float, or uint16_t (bfloat16 bits) for gradients handed over as bfloat16.
 template <int kMode, typename G>
-__global__ __launch_bounds__(kThreads) void tk_pass1(const G *__restrict__ g, float *__restrict__ xs, TkGeom ge,
+__global__ __launch_bounds__(kThreads, kMode == kPassNaive ? 8 : 1) void tk_pass1(const G *__restrict__ g, float *__restrict__ xs, TkGeom ge,
                                                      TkWorker *ws, uint2 *__restrict__ cand,
                                                      uint32_t *__restrict__ cursor, uint4 *__restrict__ tile_dir)
 {
-    __shared__ float stage_val[4][kSub];
-    __shared__ uint16_t stage_at[4][kSub];
+    constexpr bool kDirect = kListDirect<kMode, G>;   // the lists are not used then, and take no LDS
+    __shared__ float stage_val[kDirect ? 1 : 4][kSub];
+    __shared__ uint16_t stage_at[kDirect ? 1 : 4][kSub];
     __shared__ uint32_t sh[9];
     const int t = tile_of_block(blockIdx.x, ge.xcd_chunk);
     if (t >= ge.n_tiles) return;
@@ -513,18 +593,26 @@ __global__ __launch_bounds__(kThreads) void tk_pass1(const G *__restrict__ g, fl
     const SelKey sk_prev = sel_key_of(ge.rand, ws[i].step_word, i);
     const uint32_t d = (uint32_t)ge.d;
     const uint32_t base = (uint32_t)t * kTile;
-    if (tid == 0) sh[4] = 0;
-    __syncthreads();
-    uint32_t count, zeros = 0;
     const G *grow = g + (int64_t)i * (kMode == kPassDiff ? ge.ld : ge.d);
-    const Stage stage{stage_val[wave], stage_at[wave]};
-    if (base + kTile <= d)
-        count = pass1_tile<true, kMode, G>(grow, xs + (int64_t)i * ge.ld, base, d, kt, guess, sk, sk_prev,
-                                           stage, ge.stream_rows, zeros);
-    else
-        count = pass1_tile<false, kMode, G>(grow, xs + (int64_t)i * ge.ld, base, d, kt, guess, sk, sk_prev,
-                                            stage, ge.stream_rows, zeros);
-    finish_tile(stage_val, stage_at, sh, count, zeros, ge, i, t, cand, cursor, tile_dir, &ws[i].overflow);
+    float *xrow = xs + (int64_t)i * ge.ld;
+    if constexpr (kDirect) {
+        if (base + kTile <= d)
+            pass1_direct<true, kMode, G>(grow, xrow, base, d, kt, guess, sk, sk_prev, ge.stream_rows, sh, ge, i, t, cand,
+                                         cursor, tile_dir, &ws[i].overflow);
+        else
+            pass1_direct<false, kMode, G>(grow, xrow, base, d, kt, guess, sk, sk_prev, ge.stream_rows, sh, ge, i, t, cand,
+                                          cursor, tile_dir, &ws[i].overflow);
+    } else {
+        if (tid == 0) sh[4] = 0;
+        __syncthreads();
+        uint32_t count, zeros = 0;
+        const Stage stage{stage_val[wave], stage_at[wave]};
+        if (base + kTile <= d)
+            count = pass1_tile<true, kMode, G>(grow, xrow, base, d, kt, guess, sk, sk_prev, stage, ge.stream_rows, zeros);
+        else
+            count = pass1_tile<false, kMode, G>(grow, xrow, base, d, kt, guess, sk, sk_prev, stage, ge.stream_rows, zeros);
+        finish_tile(stage_val, stage_at, sh, count, zeros, ge, i, t, cand, cursor, tile_dir, &ws[i].overflow);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
