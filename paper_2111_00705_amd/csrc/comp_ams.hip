@@ -116,21 +116,23 @@ struct comp_ams {
 };
 
 // What a step touches once per step - the n stored rows; theta, m, v, vhat - is accessed as a stream
-// (see ld4_row, ld4_state) when it cannot stay in the 256 MB memory-side cache until the next step anyway.
-// Measured with 16 workers from 1.2 M to 25 M coordinates: rows of 183 MB in total are faster cached
-// (110 against 118 us per step), rows of 275 MB faster streamed (176 against 188 us).  The state is faster
-// cached when it fits and the rows stream past it (11.2 M coordinates, 179 MB: tk_final 70 -> 62 us), faster
-// streamed when it does not fit, and also when the rows are cached and it would compete with them (1.2 M
-// coordinates: 52.2 against 52.9 us per step).
-// With CD-Adam the server's ghat and gtilde are read and written next to the state; the six arrays then
-// compete for the cache together (11.2 M coordinates: 268 MB, and streaming the state is 8 % faster).
-constexpr size_t kCacheResidentBytes = (size_t)224 << 20;
-inline bool rows_exceed_caches(const comp_ams *h) { return (size_t)h->n * (size_t)h->ld * sizeof(float) > kCacheResidentBytes; }
-inline bool state_exceeds_caches(const comp_ams *h)
-{
-    const size_t arrays = h->method == COMP_AMS_METHOD_CD ? 6 : 4;
-    return arrays * (size_t)h->ld * sizeof(float) > kCacheResidentBytes;
-}
+// (see ld4_row, ld4_state) when it could not stay in the 256 MB memory-side cache until the next step anyway.
+// Between two steps a training program runs a forward and a backward pass through that cache, so the line is drawn
+// where three handles stepped in turn measured it, not one handle stepped back to back (step plus get_theta, us,
+// cached / streamed, three in turn; one handle).  Rows, n = 16: error feedback Top-k 64 MB 84.4 / 85.3, 96 MB
+// 110.8 / 103.9 (104.0 / 103.5), 192 MB 174.6 / 158.1 (156.0 / 157.4); blocks of 4096 64 MB 57.3 / 59.5, 96 MB 79.2 / 76.9
+// (72.9 / 77.0), 192 MB 146.2 / 133.2 (127.5 / 132.3).  State: error feedback Top-k n = 16 64 MB 200 / 199, 96 MB 277 / 271
+// (266 / 273), 160 MB 438 / 423 (412 / 417); no compression n = 8 bf16 64 MB 52 / 54, 96 MB 75 / 71 (69 / 71), 160 MB
+// 118 / 108 (99 / 107); CD-Adam, whose server vectors are read and written next to the state, Top-k n = 8 64 MB
+// 172 / 169, 96 MB 222 / 212 (201 / 195).  Under error feedback with cached rows the state streams, since it would
+// compete with them.
+constexpr size_t kCacheResidentBytes = (size_t)80 << 20;
+inline size_t row_bytes(const comp_ams *h) { return (size_t)h->n * (size_t)h->ld * sizeof(float); }
+inline bool rows_exceed_caches(const comp_ams *h) { return row_bytes(h) > kCacheResidentBytes; }
+inline bool state_exceeds_caches(const comp_ams *h) { return 4 * (size_t)h->ld * sizeof(float) > kCacheResidentBytes; }
+// What one kernel of a step leaves for the next one of the same step stays cached up to this size, and launch shapes
+// for rows that fill the chip for long start here.
+constexpr size_t kWithinStepBytes = (size_t)224 << 20;
 // Dynamic LDS of bs_pass.  Tiles of several pieces need kPassTileLds.  Beyond that the amount is a knob that sets
 // how many workgroups share a compute unit, and the pass responds to it by a few per cent (one session, same
 // build).  Where most tiles are whole (blocks of a tile, or layers): once the rows are well beyond the caches,
@@ -186,7 +188,7 @@ inline int xcd_chunk_for(const comp_ams *h)
 inline bool tk_long_rows(const comp_ams *h) { return h->d >= ((int64_t)64 << 20); }
 inline int tk_ef_chunk_for(const comp_ams *h)
 {
-    if (!rows_exceed_caches(h)) return 0;
+    if (row_bytes(h) <= kWithinStepBytes) return 0;
     return tk_long_rows(h) ? 16 : 8;
 }
 
@@ -210,8 +212,7 @@ inline void apply_streaming(comp_ams *h)
     if (h->chunk_choice < 0 && h->method == COMP_AMS_METHOD_EF) h->ge.xcd_chunk = tk_ef_chunk_for(h);
     h->srv.ge.xcd_chunk = 0;   // the server's single vector: not measured, left alone
     // the state stays cached if it fits - except under error feedback with cached rows, where it would
-    // compete with them (CD-Adam with cached rows measured the other way: 55.9 against 58.0 us per step with
-    // 1.2 M coordinates; methods without memory do not touch the rows at all)
+    // compete with them (methods without memory do not touch the rows at all)
     const bool rows_cached = rows == 0 && h->method == COMP_AMS_METHOD_EF;
     h->params.stream_state = h->state_choice < 0 ? ((state_exceeds_caches(h) || rows_cached) ? 1 : 0) : h->state_choice;
 }
@@ -737,7 +738,7 @@ unsigned tk_pass_lds(const comp_ams *h)
     const unsigned lists = kListDirect<kMode, G> ? kStageBytes : 0u;
     if (h->lds_choice >= 0) return lists + (unsigned)h->lds_choice;
     if (kMode != kPassEf || sizeof(G) != 4) return 0u;
-    // five workgroups per unit for rows that stream and are not long (see tk_ef_chunk_for), else four
+    // five workgroups per unit for rows that exceed the caches by far and are not long (see tk_ef_chunk_for), else four
     return lists + (rows_exceed_caches(h) && !tk_long_rows(h) ? 7000u : 9u * 1024u);
 }
 
@@ -1653,7 +1654,7 @@ int comp_ams_set_method(comp_ams_t *h, int32_t method)
             sv.ge = h->ge;
             sv.ge.n = 1;
             // ghat and gtilde are reused within the step if they are small enough to stay cached
-            sv.ge.stream_rows = 2 * (size_t)h->ld * sizeof(float) > kCacheResidentBytes ? 1 : 0;
+            sv.ge.stream_rows = 2 * (size_t)h->ld * sizeof(float) > kWithinStepBytes ? 1 : 0;
             sv.ge.relist_wgs = (int32_t)std::min<int64_t>(sv.ge.n_tiles, 2048);
             // one vector, all tiles: enough regions that a cursor sees few tens of atomic adds
             int slices = kMinSlices;
