@@ -557,6 +557,7 @@ __global__ __launch_bounds__(kThreads) void bs_server(int64_t d, int64_t ld, int
 //                 piece sums (and stored by the tile at the block's start)
 //   kBlocksTable  any table: one scale where the tile lies inside one block, else one per coordinate
 // kEarlyState: theta, m, v, vhat are loaded first (small grids: nothing else would hide that latency).
+// theta_out (kBlocksFused; may be null): d floats of the caller's, 4-byte aligned, that receive the new theta as well.
 // kMarkov (kBlocksShort with blocks of at most 256 coordinates, which lie inside a wavefront): CD-Adam's server stage,
 // lines 8-16 of Algorithm 1 in this one launch (no bs_scale, no bs_apply).
 enum { kBlocksShort = 0, kBlocksFused = 1, kBlocksTable = 2 };
@@ -566,7 +567,7 @@ __global__ __launch_bounds__(kThreads) void bs_update(int64_t d, int64_t ld, int
                                                       const uint16_t *__restrict__ signs,
                                                       float *__restrict__ theta, float *__restrict__ m,
                                                       float *__restrict__ v, float *__restrict__ vhat, AmsParams p,
-                                                      BsMarkov mk)
+                                                      BsMarkov mk, float *__restrict__ theta_out)
 {
     __shared__ float s_lds[kBlocks == kBlocksFused ? kScaleChunk : 1];
     const int t = blockIdx.x >> 2;
@@ -752,6 +753,17 @@ __global__ __launch_bounds__(kThreads) void bs_update(int64_t d, int64_t ld, int
     }
     amsgrad_update4(th, mm, vv, vh, make_float4(gb[0], gb[1], gb[2], gb[3]), p);
     st4_state<kStreamState>(theta + j, th);
+    if (kBlocks == kBlocksFused && theta_out) {
+        // a caller who asked for theta while this update was pending gets it from the registers
+        if (j + 4 <= d) {
+            const v4f o = {th.x, th.y, th.z, th.w};
+            *reinterpret_cast<v4f_any *>(theta_out + j) = o;
+        } else {
+            if (j < d) theta_out[j] = th.x;
+            if (j + 1 < d) theta_out[j + 1] = th.y;
+            if (j + 2 < d) theta_out[j + 2] = th.z;
+        }
+    }
     st4_state<kStreamState>(m + j, mm);
     st4_state<kStreamState>(v + j, vv);
     st4_state<kStreamState>(vhat + j, vh);

@@ -170,3 +170,29 @@ def test_cd_lists_anew_on_a_long_vector():
     gpu, ora = sparse_pair(d, n, 50_000, "cd")
     sparse_steps(gpu, ora, lambda t: grads_of(3, n, d)(t) * f32(10.0 ** (-2 * t)), 3, "cd", "long")
     gpu.destroy()
+
+
+# theta asked for while the update of uniform whole-tile blocks is pending: written by the update itself to device memory
+# (any 4-byte alignment, nothing past d), copied to host memory
+@pytest.mark.parametrize("d", [4096, 2 * TILE + 1, 3 * TILE - 2, 5 * TILE - 1])
+def test_theta_of_a_pending_update(d):
+    import torch
+    n = 3
+    print(f"[case] theta of a pending update d={d}", flush=True)
+    gpu, ora = make_pair(d, n, P.BLOCKSIGN, TILE)
+    fn = grads_of(d, n, d)
+    room = torch.full((d + 9,), 7.5, device="cuda")
+    for t in range(4):
+        g = fn(t)
+        gpu.step(torch.from_numpy(g).cuda())
+        ora.step(g)
+        if t == 2:
+            assert rel_close(gpu.get_theta(), ora.theta, STATE_RTOL).all()
+        out = room[1 + t:1 + t + d]
+        out.fill_(7.5)
+        gpu.get_theta(out=out)
+        assert rel_close(out.cpu().numpy(), ora.theta, STATE_RTOL).all(), t
+        assert np.array_equal(out.cpu().numpy(), gpu.get_theta()), t
+        assert bool((room[1 + t + d:] == 7.5).all()) and bool((room[:1 + t] == 7.5).all()), "written past the end"
+        room.fill_(7.5)
+    gpu.destroy()
