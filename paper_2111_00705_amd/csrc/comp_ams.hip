@@ -501,15 +501,6 @@ int flush_pending(comp_ams *h);
     int rc = device_scope__.enter(h); \
     if (!rc) rc = flush_pending(h)
 
-int copy_out(comp_ams *h, float *dst, const float *src_dev, size_t count, int on_device)
-{
-    if (!dst) return fail(h, COMP_AMS_EINVAL, "output pointer is NULL");
-    HIP_TRY(h, hipMemcpyAsync(dst, src_dev, count * sizeof(float),
-                              on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(h, hipStreamSynchronize(h->stream));
-    return COMP_AMS_OK;
-}
-
 // Whether a kernel on the handle's GPU may write to p as floats: ordinary device memory of that GPU.  (A copy also reaches
 // memory of another GPU, or host memory handed over as device memory.)
 bool is_own_device_memory(const comp_ams *h, const void *p)
@@ -521,6 +512,25 @@ bool is_own_device_memory(const comp_ams *h, const void *p)
         return false;
     }
     return at.type == hipMemoryTypeDevice && at.device == h->device;
+}
+
+// From this size on copy_out_floats outruns the runtime's copy (d = 25.6 M: 34 against 42 us); below, they are equal.
+constexpr size_t kOwnCopyBytes = (size_t)64 << 20;
+
+int copy_out(comp_ams *h, float *dst, const float *src_dev, size_t count, int on_device)
+{
+    if (!dst) return fail(h, COMP_AMS_EINVAL, "output pointer is NULL");
+    if (on_device && count * sizeof(float) >= kOwnCopyBytes && is_own_device_memory(h, dst)) {
+        const int64_t pieces = ((int64_t)count + 16 * kThreads - 1) / (16 * kThreads);
+        copy_out_floats<<<grid_blocks(pieces, 16), kThreads, 61440u, h->stream>>>(dst, src_dev, (int64_t)count, 16);
+        HIP_TRY(h, hipGetLastError());
+        HIP_TRY(h, hipStreamSynchronize(h->stream));
+        return COMP_AMS_OK;
+    }
+    HIP_TRY(h, hipMemcpyAsync(dst, src_dev, count * sizeof(float),
+                              on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, h->stream));
+    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    return COMP_AMS_OK;
 }
 
 int copy_in(comp_ams *h, float *dst_dev, const float *src, size_t count, int on_device)

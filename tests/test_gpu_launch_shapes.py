@@ -196,3 +196,22 @@ def test_theta_of_a_pending_update(d):
         assert bool((room[1 + t + d:] == 7.5).all()) and bool((room[:1 + t] == 7.5).all()), "written past the end"
         room.fill_(7.5)
     gpu.destroy()
+
+
+# state of 64 MB and more copied to device memory by the library's own kernel: any 4-byte alignment, nothing past d
+@pytest.mark.parametrize("extra,shift", [(0, 0), (1, 1), (2, 3), (4095, 2)])
+def test_large_state_to_device_memory(extra, shift):
+    import torch
+    d = (16 << 20) + extra
+    print(f"[case] large state to device memory d={d} shift={shift}", flush=True)
+    gpu = P.CompAms(d, 1, P.TOPK, 1)
+    theta = torch.randn(d, device="cuda")
+    gpu.set_theta(theta)
+    room = torch.full((d + 16,), 7.5, device="cuda")
+    out = room[shift:shift + d]
+    gpu.get_theta(out=out)
+    assert torch.equal(out, theta)
+    assert bool((room[:shift] == 7.5).all()) and bool((room[shift + d:] == 7.5).all())
+    gpu.get_v(out=out)
+    assert bool((out == 0).all())
+    gpu.destroy()
