@@ -766,6 +766,18 @@ unsigned tk_pass_lds(const comp_ams *h)
     return lists + (rows_exceed_caches(h) && !tk_long_rows(h) ? 7000u : 9u * 1024u);
 }
 
+// Calls f with what tk_pass1 may take for granted about the keys (see kKeyEither) as a compile-time constant.
+template <typename F>
+void by_key(const comp_ams *h, size_t grad_bytes, F &&f)
+{
+    if (h->method == COMP_AMS_METHOD_EF && grad_bytes == 4 && tk_long_rows(h))
+        f(std::integral_constant<int, kKeyEither>{});
+    else if (h->compressor == COMP_AMS_RANDK)
+        f(std::integral_constant<int, kKeyScore>{});
+    else
+        f(std::integral_constant<int, kKeyMagnitude>{});
+}
+
 // Short vectors: the geometry with one region per vector (all of its space), and the selection in one launch.
 inline bool is_short(const comp_ams *h) { return h->ge.n_tiles <= kSmallTiles; }
 inline TkGeom short_geometry(TkGeom ge)
@@ -791,20 +803,20 @@ int step_topk(comp_ams *h, const G *g, hipStream_t st)
 {
     if (is_short(h)) {
         const TkGeom sge = short_geometry(h->ge);
-        launch_timed(h, P_TK_PASS1, st, [&] {
-            KLAUNCH((tk_pass1<kPassEf, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
+        launch_timed(h, P_TK_PASS1, st, [&] { by_key(h, sizeof(G), [&](auto key) {
+            KLAUNCH((tk_pass1<kPassEf, decltype(key)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
                     h->tile_dir);
-        });
+        }); });
         launch_short_select<kSrcStored, float>(h, st, sge, h->ws, h->cand, h->small_ctr, h->tile_dir, h->e, nullptr, P_TK_RESOLVE);
         launch_final(h, st);
         return COMP_AMS_OK;
     }
     const TkGeom &ge = h->ge;
     const TkGeom pge = pass_geometry<G>(h);
-    launch_timed(h, P_TK_PASS1, st, [&] {
-        KLAUNCH_LDS((tk_pass1<kPassEf, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassEf, G>(h)), st, g, h->e, pge, h->ws,
+    launch_timed(h, P_TK_PASS1, st, [&] { by_key(h, sizeof(G), [&](auto key) {
+        KLAUNCH_LDS((tk_pass1<kPassEf, decltype(key)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassEf, G>(h)), st, g, h->e, pge, h->ws,
                 h->cand, h->cursor, h->tile_dir);
-    });
+    }); });
     launch_select<kSrcStored, float>(h, st, ge, h->ws, h->cand, h->cursor, h->cursor_b, h->tile_dir, h->hist1, h->histf,
                                      h->hist_full, h->hist2, h->piece_bits, h->dense, h->dense_dir, h->e, nullptr, kWorkerSelectSlots);
     launch_final(h, st);
@@ -817,20 +829,20 @@ int step_topk_naive(comp_ams *h, const G *g, hipStream_t st)
 {
     if (is_short(h)) {
         const TkGeom sge = short_geometry(h->ge);
-        launch_timed(h, P_TK_PASS1, st, [&] {
-            KLAUNCH((tk_pass1<kPassNaive, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
+        launch_timed(h, P_TK_PASS1, st, [&] { by_key(h, sizeof(G), [&](auto key) {
+            KLAUNCH((tk_pass1<kPassNaive, decltype(key)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
                     h->tile_dir);
-        });
+        }); });
         launch_short_select<kSrcGradOnly, G>(h, st, sge, h->ws, h->cand, h->small_ctr, h->tile_dir, g, nullptr, P_TK_RESOLVE);
         launch_final(h, st);
         return COMP_AMS_OK;
     }
     const TkGeom &ge = h->ge;
     const TkGeom pge = pass_geometry<G>(h);
-    launch_timed(h, P_TK_PASS1, st, [&] {
-        KLAUNCH_LDS((tk_pass1<kPassNaive, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassNaive, G>(h)), st, g, h->e, pge, h->ws,
+    launch_timed(h, P_TK_PASS1, st, [&] { by_key(h, sizeof(G), [&](auto key) {
+        KLAUNCH_LDS((tk_pass1<kPassNaive, decltype(key)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassNaive, G>(h)), st, g, h->e, pge, h->ws,
                 h->cand, h->cursor, h->tile_dir);
-    });
+    }); });
     launch_select<kSrcGradOnly, G>(h, st, ge, h->ws, h->cand, h->cursor, h->cursor_b, h->tile_dir, h->hist1, h->histf,
                                    h->hist_full, h->hist2, h->piece_bits, h->dense, h->dense_dir, g, nullptr, kWorkerSelectSlots);
     launch_final(h, st);
@@ -865,16 +877,16 @@ int step_topk_cd(comp_ams *h, const G *g, hipStream_t st)
     const bool brief = is_short(h);
     if (brief) {
         const TkGeom sge = short_geometry(ge);
-        launch_timed(h, P_TK_PASS1, st, [&] {
-            KLAUNCH((tk_pass1<kPassCd, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
+        launch_timed(h, P_TK_PASS1, st, [&] { by_key(h, sizeof(G), [&](auto key) {
+            KLAUNCH((tk_pass1<kPassCd, decltype(key)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
                     h->tile_dir);
-        });
+        }); });
         launch_short_select<kSrcGrad, G>(h, st, sge, h->ws, h->cand, h->small_ctr, h->tile_dir, g, h->e, P_TK_RESOLVE);
     } else {
-        launch_timed(h, P_TK_PASS1, st, [&] {
-            KLAUNCH_LDS((tk_pass1<kPassCd, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassCd, G>(h)), st, g, h->e, pge, h->ws,
+        launch_timed(h, P_TK_PASS1, st, [&] { by_key(h, sizeof(G), [&](auto key) {
+            KLAUNCH_LDS((tk_pass1<kPassCd, decltype(key)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassCd, G>(h)), st, g, h->e, pge, h->ws,
                     h->cand, h->cursor, h->tile_dir);
-        });
+        }); });
         launch_select<kSrcGrad, G>(h, st, ge, h->ws, h->cand, h->cursor, h->cursor_b, h->tile_dir, h->hist1, h->histf,
                                    h->hist_full, h->hist2, h->piece_bits, h->dense, h->dense_dir, g, h->e, kWorkerSelectSlots);
     }
@@ -885,17 +897,17 @@ int step_topk_cd(comp_ams *h, const G *g, hipStream_t st)
     if (brief) {
         const TkGeom sge = short_geometry(sv.ge);
         uint32_t *count = h->small_ctr + (size_t)h->n * kCursorStride;      // the server's, after the workers'
-        launch_timed(h, P_TK_PASS1_SERVER, st, [&] {
-            KLAUNCH((tk_pass1<kPassDiff, float>), dim3(sge.n_tiles, 1), kThreads, st, h->ghat_srv, h->gtil, sge, sv.ws, sv.cand,
+        launch_timed(h, P_TK_PASS1_SERVER, st, [&] { by_key(h, sizeof(G), [&](auto key) {
+            KLAUNCH((tk_pass1<kPassDiff, decltype(key)::value, float>), dim3(sge.n_tiles, 1), kThreads, st, h->ghat_srv, h->gtil, sge, sv.ws, sv.cand,
                     count, sv.tile_dir);
-        });
+        }); });
         launch_short_select<kSrcDiff, float>(h, st, sge, sv.ws, sv.cand, count, sv.tile_dir, h->ghat_srv, h->gtil,
                                              P_TK_SELECT_SERVER);
     } else {
-        launch_timed(h, P_TK_PASS1_SERVER, st, [&] {
-            KLAUNCH((tk_pass1<kPassDiff, float>), dim3(grid_blocks(ge.n_tiles, sv.ge.xcd_chunk), 1), kThreads, st, h->ghat_srv,
+        launch_timed(h, P_TK_PASS1_SERVER, st, [&] { by_key(h, sizeof(G), [&](auto key) {
+            KLAUNCH((tk_pass1<kPassDiff, decltype(key)::value, float>), dim3(grid_blocks(ge.n_tiles, sv.ge.xcd_chunk), 1), kThreads, st, h->ghat_srv,
                     h->gtil, sv.ge, sv.ws, sv.cand, sv.cursor, sv.tile_dir);
-        });
+        }); });
         launch_select<kSrcDiff, float>(h, st, sv.ge, sv.ws, sv.cand, sv.cursor, h->cursor_b_s, sv.tile_dir, h->hist1_s, h->histf_s,
                                        h->hist_full_s, h->hist2_s, h->piece_bits_s, h->dense_s, h->dense_dir_s, h->ghat_srv, h->gtil,
                                        kServerSelectSlots);
@@ -1136,7 +1148,7 @@ int comp_ams_create(comp_ams_t **out, int64_t d, int32_t n, int32_t compressor, 
         ge.idx_bits = ib;
         // more regions per worker measured no faster (n workers already spread the cursors); fewer when the
         // vector has fewer tiles than that, so that many workers with a small model do not reserve 64 empty regions each
-        int slices = kMinSlices;
+        int slices = ge.n_tiles >= kLongTiles ? kLongSlices : kMinSlices;
         while (slices > 1 && slices / 2 >= ge.n_tiles) slices /= 2;
         set_slices(ge, slices);
         ge.relist_wgs = (int32_t)std::min<int64_t>(ge.n_tiles, std::max(1, 2048 / n));

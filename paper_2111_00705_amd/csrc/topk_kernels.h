@@ -72,8 +72,12 @@ constexpr int kBinsFirst = 1 << kFirstBits;
 constexpr int kPieceWords = kBinsFirst / 32;   // words of a dense piece's bitmap: which first digits occur in it
 constexpr int kSub = kTile / 4;   // coordinates of a tile that one wavefront handles = capacity of its staged list
 constexpr unsigned kStageBytes = 4 * kSub * (sizeof(float) + sizeof(uint16_t));   // staging lists of a workgroup of tk_pass1
-constexpr int kMinSlices = 64;    // candidate regions per vector: a power of two in [kMinSlices, kMaxSlices]
+constexpr int kMinSlices = 32;    // candidate regions per vector: a power of two in [kMinSlices, kMaxSlices]
                                   // (fewer for a vector of fewer tiles than that)
+constexpr int kLongSlices = 64;   // from kLongTiles tiles on.  Fewer regions are fewer workgroups with histograms to flush, more
+constexpr int kLongTiles = 512;   // are fewer atomic adds in a row on a cursor.  Step plus get_theta, 64 / 32 regions, us: error
+                                  // feedback n = 8, d = 200 000 46.2 / 45.2, Rand-k n = 16, d = 1.2 M f16 93.0 / 91.8, CD-Adam n = 8,
+                                  // d = 1 M 89.1 / 86.5; naive n = 8, d = 3 M bf16 79.7 / 80.4; d = 11 M and more equal
 constexpr int kMaxSlices = 512;
 constexpr int kCursorStride = 32; // words between two region cursors: a 128-byte line each.  The atomic adds of all XCDs on
                                   // one line are served one after the other, also where they go to different words (64
@@ -506,6 +510,12 @@ __device__ __forceinline__ void finish_tile(const float (*stage_val)[kSub], cons
 template <int kMode, typename G>
 constexpr bool kListDirect = (kMode == kPassEf && sizeof(G) == 4) || kMode == kPassNaive;
 
+// What the listing pass knows at compile time about the keys: magnitudes (Top-k), scores (Rand-k), or nothing.  Without
+// a branch per element: step plus get_theta, us, n = 4, d = 65 536 33.5 / 32.7, n = 8, d = 2 M 89.3 / 87.9, n = 16, d = 11.2 M
+// 462 / 459, Rand-k n = 16, d = 1.2 M f16 92.5 / 90.9, naive n = 8, d = 3 M bf16 79.2 / 77.8 - but n = 8, d = 110 M 2345 / 2367:
+// the rows of tk_long_rows keep the branch.
+enum { kKeyMagnitude = 0, kKeyScore = 1, kKeyEither = 2 };
+
 // A tile listed straight from the registers.
 template <bool kFull, int kMode, typename G>
 __device__ __forceinline__ void pass1_direct(const G *__restrict__ grow, float *__restrict__ xrow, uint32_t base, uint32_t d,
@@ -573,7 +583,7 @@ __device__ __forceinline__ void pass1_direct(const G *__restrict__ grow, float *
 }
 
 // G: element type of g - float, or uint16_t (bfloat16 bits) for gradients handed over as bfloat16.
-template <int kMode, typename G>
+template <int kMode, int kKey, typename G>
 __global__ __launch_bounds__(kThreads, kMode == kPassNaive ? 8 : 1) void tk_pass1(const G *__restrict__ g, float *__restrict__ xs, TkGeom ge,
                                                      TkWorker *ws, uint2 *__restrict__ cand,
                                                      uint32_t *__restrict__ cursor, uint4 *__restrict__ tile_dir)
@@ -589,8 +599,9 @@ __global__ __launch_bounds__(kThreads, kMode == kPassNaive ? 8 : 1) void tk_pass
     const int wave = tid >> 6;
     const uint32_t guess = ws[i].guess;
     const KeptTest kt = kept_test(ws[i].tc, ge.idx_bits);
-    const SelKey sk = sel_key_of(ge.rand, ge.rand.step_now, i);
-    const SelKey sk_prev = sel_key_of(ge.rand, ws[i].step_word, i);
+    SelKey sk = sel_key_of(ge.rand, ge.rand.step_now, i);
+    SelKey sk_prev = sel_key_of(ge.rand, ws[i].step_word, i);
+    if constexpr (kKey != kKeyEither) sk.on = sk_prev.on = kKey == kKeyScore ? 1u : 0u;
     const uint32_t d = (uint32_t)ge.d;
     const uint32_t base = (uint32_t)t * kTile;
     const G *grow = g + (int64_t)i * (kMode == kPassDiff ? ge.ld : ge.d);
