@@ -37,9 +37,10 @@ PROFILE_SUFFIX = {"ef": "", "cd": "_cd_adam", "naive": "_naive", "none": "_uncom
 
 # The templated kernel behind each timing slot, by variant: which row of a rocprofv3 summary a slot reads.
 KERNEL_VARIANT = {
-    ("tk_pass1", "ef"): "cams::tk_pass1<0, float>", ("tk_pass1", "cd"): "cams::tk_pass1<1, float>",
-    ("tk_pass1", "naive"): "cams::tk_pass1<3, float>", ("tk_pass1", "randk"): "cams::tk_pass1<0, float>",
-    ("tk_pass1", "bf16"): "cams::tk_pass1<0, unsigned short>",
+    # <mode, key, gradient type>: the mode names the row, a run has one kind of key and one gradient type
+    ("tk_pass1", "ef"): "cams::tk_pass1<0, ", ("tk_pass1", "cd"): "cams::tk_pass1<1, ",
+    ("tk_pass1", "naive"): "cams::tk_pass1<3, ", ("tk_pass1", "randk"): "cams::tk_pass1<0, ",
+    ("tk_pass1", "bf16"): "cams::tk_pass1<0, ",
     ("bs_pass_update", "ef"): "cams::bs_pass_update<true, float",      # the steady-state variant (stored rows pending)
 }
 

@@ -368,7 +368,10 @@ constexpr int kSignBatch = 8;       // workers whose sign words are loaded toget
 // its sign bits and piece sums are written for the second compression.  One workgroup per tile: a piece of w is summed
 // by the workgroup that holds all of it.  kFusedScale: every tile lies inside one block of at most kMaxFusedPieces
 // pieces; the workers' scales are then formed here from the partial sums (and stored by the tile at the block's
-// start).  kStreamState: theta, m, v, vhat (touched only with whole_blocks) are loaded and stored as streams.
+// start).  kStreamState: theta, m, v, vhat (touched only with whole_blocks) and ghat, which nothing else in a step reads, are
+// loaded and stored as streams; gtilde, which bs_apply reads again, is left cached until its own last store.  (Whole-vector
+// sign, step plus get_theta: n = 8, d = 11.2 M 336.5 -> 331.8 us, n = 2, d = 60 M bf16 877 -> 831; blocks of 4096, n = 8,
+// d = 8 M 236 -> 226.)
 struct BsMarkov {
     float *ghat;            // [ld] the server's aggregate
     float *gtil;            // [ld] gtilde of the step before (rewritten here only when whole_blocks is set)
@@ -498,7 +501,7 @@ __global__ __launch_bounds__(kThreads) void bs_server(int64_t d, int64_t ld, int
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int64_t j = base + 4 * (tid + kThreads * r);
-        const float4 gh4 = ld4(mk.ghat + j), gt4 = ld4(mk.gtil + j);
+        const float4 gh4 = ld4_state<kStreamState>(mk.ghat + j), gt4 = ld4(mk.gtil + j);
         const float gh[4] = {gh4.x, gh4.y, gh4.z, gh4.w}, gt[4] = {gt4.x, gt4.y, gt4.z, gt4.w};
         float nh[4];
 #pragma unroll
@@ -508,7 +511,7 @@ __global__ __launch_bounds__(kThreads) void bs_server(int64_t d, int64_t ld, int
             w[r][c] = (j + c < d) ? fsub(nh[c], gt[c]) : 0.f;
             sign_bits |= (__float_as_uint(w[r][c]) >> 31) << (r * 4 + c);
         }
-        st4(mk.ghat + j, make_float4(nh[0], nh[1], nh[2], nh[3]));
+        st4_state<kStreamState>(mk.ghat + j, make_float4(nh[0], nh[1], nh[2], nh[3]));
     }
     mk.signs[(int64_t)t * kThreads + tid] = (uint16_t)sign_bits;
     __syncthreads();   // s_lds readers are done before scratch is used (separate arrays; keeps phases apart)
@@ -538,7 +541,7 @@ __global__ __launch_bounds__(kThreads) void bs_server(int64_t d, int64_t ld, int
         const float4 g4 = make_float4(nt[0], nt[1], nt[2], nt[3]);
         float4 th4 = ld4_state<kStreamState>(theta + j), m4 = ld4_state<kStreamState>(m + j), v4 = ld4_state<kStreamState>(v + j), vh4 = ld4_state<kStreamState>(vhat + j);
         amsgrad_update4(th4, m4, v4, vh4, g4, p);
-        st4(mk.gtil + j, g4);
+        st4_state<kStreamState>(mk.gtil + j, g4);
         st4_state<kStreamState>(theta + j, th4);
         st4_state<kStreamState>(m + j, m4);
         st4_state<kStreamState>(v + j, v4);
@@ -714,7 +717,7 @@ __global__ __launch_bounds__(kThreads) void bs_update(int64_t d, int64_t ld, int
 #pragma unroll
     for (int c = 0; c < 4; ++c) gb[c] = j + c < d ? fdiv(acc[c], p.n_workers) : 0.f;
     if (kMarkov) {
-        const float4 gh4 = ld4(mk.ghat + j), gt4 = ld4(mk.gtil + j);
+        const float4 gh4 = ld4_state<kStreamState>(mk.ghat + j), gt4 = ld4_state<kStreamState>(mk.gtil + j);
         const float gh[4] = {gh4.x, gh4.y, gh4.z, gh4.w}, gt[4] = {gt4.x, gt4.y, gt4.z, gt4.w};
         float nh[4], w[4];
         uint32_t neg = 0;
@@ -725,7 +728,7 @@ __global__ __launch_bounds__(kThreads) void bs_update(int64_t d, int64_t ld, int
             w[c] = (j + c < d) ? fsub(nh[c], gt[c]) : 0.f;
             neg |= (__float_as_uint(w[c]) >> 31) << c;
         }
-        st4(mk.ghat + j, make_float4(nh[0], nh[1], nh[2], nh[3]));
+        st4_state<kStreamState>(mk.ghat + j, make_float4(nh[0], nh[1], nh[2], nh[3]));
         S = ((double)fabsf(w[0]) + (double)fabsf(w[1])) + ((double)fabsf(w[2]) + (double)fabsf(w[3]));
         const int lanes = 1 << (tb.small_log2 - 2);
         for (int off = 1; off < lanes; off <<= 1) S += __shfl_xor(S, off, kWave);
@@ -743,7 +746,7 @@ __global__ __launch_bounds__(kThreads) void bs_update(int64_t d, int64_t ld, int
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) gb[c] = (j + c < d) ? fadd(gt[c], signed_scale(s, neg, c)) : gt[c];   // gtilde
-        st4(mk.gtil + j, make_float4(gb[0], gb[1], gb[2], gb[3]));
+        st4_state<kStreamState>(mk.gtil + j, make_float4(gb[0], gb[1], gb[2], gb[3]));
     }
     if (!kEarlyState) {
         th = ld4_state<kStreamState>(theta + j);
@@ -999,7 +1002,7 @@ __global__ __launch_bounds__(kThreads) void bs_apply(int64_t d, BsTable tb, cons
         }
         const float4 g4 = make_float4(nt[0], nt[1], nt[2], nt[3]);
         amsgrad_update4(th[r], mm[r], vv[r], vh[r], g4, p);
-        st4(gtil + j, g4);
+        st4_state<kStreamState>(gtil + j, g4);
         st4_state<kStreamState>(theta + j, th[r]);
         st4_state<kStreamState>(m + j, mm[r]);
         st4_state<kStreamState>(v + j, vv[r]);

@@ -95,11 +95,11 @@ struct comp_ams {
     uint32_t *hist1 = nullptr;                 // [n][2048] coarse-bin counts of the candidates
     uint32_t *histf = nullptr;                 // [n][512] fine-bin counts from the guess's coarse bin on
     uint32_t *cursor_b = nullptr;              // [n][slices] the cursors that lists made anew after a miss count in
-    uint32_t *piece_bits = nullptr;            // [n][64 * parts * 4][32] which first digits occur in each dense piece
+    uint32_t *piece_bits = nullptr;            // [n][slices * parts * 4][32] which first digits occur in each dense piece
     uint32_t *hist2 = nullptr;                 // [n][1024] threshold bin: counts of the first digit below the prefix
     uint64_t *dense = nullptr;                 // laid out like cand: comp of the candidates in the threshold bin
 
-    uint2 *dense_dir = nullptr;                // [n][64 * parts * 4] {start, count} of each wavefront's piece
+    uint2 *dense_dir = nullptr;                // [n][slices * parts * 4] {start, count} of each wavefront's piece
     uint32_t *small_ctr = nullptr;             // [n + 1] short vectors: entries listed (the last one the server's)
     uint32_t *sel_count = nullptr, *sel_out_idx = nullptr;
     float *sel_out_val = nullptr;
@@ -1146,8 +1146,8 @@ int comp_ams_create(comp_ams_t **out, int64_t d, int32_t n, int32_t compressor, 
         int ib = 1;
         while (((int64_t)1 << ib) < d) ++ib;
         ge.idx_bits = ib;
-        // more regions per worker measured no faster (n workers already spread the cursors); fewer when the
-        // vector has fewer tiles than that, so that many workers with a small model do not reserve 64 empty regions each
+        // see kLongTiles; fewer when the vector has fewer tiles than that, so that many workers with a small model do not
+        // reserve dozens of empty regions each
         int slices = ge.n_tiles >= kLongTiles ? kLongSlices : kMinSlices;
         while (slices > 1 && slices / 2 >= ge.n_tiles) slices /= 2;
         set_slices(ge, slices);

@@ -17,7 +17,7 @@
 //               x; lists "candidates" - elements whose fine magnitude bin (top 17 bits, 0.2 % wide)
 //               is >= the worker's guess, which is the previous step's threshold minus a little
 //               slack - as (index, value) pairs, staged in LDS (value and place in the tile, 6 bytes)
-//               and appended densely to one of 64 regions of the worker (one atomic add per tile).
+//               and appended densely to one of 32 or 64 regions of the worker (one atomic add per tile).
 //               A workgroup per tile (instead of a loop over tiles) matters: on this chip a wave
 //               that loops must wait for its stores before it can use its next loads.
 //   tk_hist     histograms of the candidates: the fine bins of the eight coarse bins from the guess's on,
@@ -2011,7 +2011,7 @@ __global__ __launch_bounds__(kThreads) void tk_apply(TkSide sv, float *__restric
         const float4 g4 = make_float4(fadd(gt[r].x, c4.x), fadd(gt[r].y, c4.y), fadd(gt[r].z, c4.z),
                                       fadd(gt[r].w, c4.w));
         amsgrad_update4(th[r], mm[r], vv[r], vh[r], g4, p);
-        st4_if_changed<false>(gtil + j, g4, gt[r]);      // gtilde moves at the k kept coordinates only
+        st4_if_changed<kStreamState>(gtil + j, g4, gt[r]);      // gtilde moves at the k kept coordinates only
         st4_state<kStreamState>(theta + j, th[r]);
         st4_state<kStreamState>(m + j, mm[r]);
         st4_state<kStreamState>(v + j, vv[r]);
