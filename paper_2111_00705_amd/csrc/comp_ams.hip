@@ -514,15 +514,22 @@ bool is_own_device_memory(const comp_ams *h, const void *p)
     return at.type == hipMemoryTypeDevice && at.device == h->device;
 }
 
-// From this size on copy_out_floats outruns the runtime's copy (d = 25.6 M: 34 against 42 us); below, they are equal.
-constexpr size_t kOwnCopyBytes = (size_t)64 << 20;
+// From this size on copy_out_floats outruns the runtime's copy; below, they are equal.  What a step has just written is
+// partly still in the memory-side cache, so the source is read with ordinary loads while it can be there, and as a
+// stream, in probe_copy's launch shape, beyond.  Step plus get_theta, us, the runtime's copy / this: whole-vector sign
+// under CD-Adam n = 8, d = 11.2 M 332.6 / 322.0 (12 MB read as a stream: naive n = 8, d = 3 M bf16 78.3 / 82.0, with ordinary
+// loads 77.4), no compression n = 4, d = 20 M 201 / 189, Top-k n = 16, d = 11.2 M 464 / 458, n = 8, d = 110 M 2406 / 2369.
+constexpr size_t kOwnCopyBytes = (size_t)4 << 20;
 
 int copy_out(comp_ams *h, float *dst, const float *src_dev, size_t count, int on_device)
 {
     if (!dst) return fail(h, COMP_AMS_EINVAL, "output pointer is NULL");
     if (on_device && count * sizeof(float) >= kOwnCopyBytes && is_own_device_memory(h, dst)) {
         const int64_t pieces = ((int64_t)count + 16 * kThreads - 1) / (16 * kThreads);
-        copy_out_floats<<<grid_blocks(pieces, 16), kThreads, 61440u, h->stream>>>(dst, src_dev, (int64_t)count, 16);
+        if (count * sizeof(float) >= kWithinStepBytes)
+            copy_out_floats<true><<<grid_blocks(pieces, 16), kThreads, 61440u, h->stream>>>(dst, src_dev, (int64_t)count, 16);
+        else
+            copy_out_floats<false><<<(unsigned)pieces, kThreads, 0, h->stream>>>(dst, src_dev, (int64_t)count, 0);
         HIP_TRY(h, hipGetLastError());
         HIP_TRY(h, hipStreamSynchronize(h->stream));
         return COMP_AMS_OK;

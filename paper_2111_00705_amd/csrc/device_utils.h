@@ -236,7 +236,9 @@ __global__ __launch_bounds__(kThreads) void probe_copy(float *__restrict__ dst, 
 }
 
 // State handed to a caller in device memory: probe_copy's shape for any count and a destination of 4-byte alignment (src
-// 16-byte aligned).  d = 110 M: 440 MB read and written in 138 us, where the runtime's copy takes 172.
+// 16-byte aligned).  HBM-bound: d = 110 M, 440 MB read and written in 138 us, where the runtime's copy takes 172.  kStream:
+// src is read as a stream (see the host code).
+template <bool kStream>
 __global__ __launch_bounds__(kThreads) void copy_out_floats(float *__restrict__ dst, const float *__restrict__ src,
                                                             int64_t count, int chunk)
 {
@@ -244,7 +246,7 @@ __global__ __launch_bounds__(kThreads) void copy_out_floats(float *__restrict__ 
     float4 v[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-        if (j0 + 4 * kThreads * r + 4 <= count) v[r] = stream_load4(src + j0 + 4 * kThreads * r);
+        if (j0 + 4 * kThreads * r + 4 <= count) v[r] = ld4_state<kStream>(src + j0 + 4 * kThreads * r);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int64_t j = j0 + 4 * kThreads * r;

@@ -198,11 +198,12 @@ def test_theta_of_a_pending_update(d):
     gpu.destroy()
 
 
-# state of 64 MB and more copied to device memory by the library's own kernel: any 4-byte alignment, nothing past d
-@pytest.mark.parametrize("extra,shift", [(0, 0), (1, 1), (2, 3), (4095, 2)])
-def test_large_state_to_device_memory(extra, shift):
+# state copied to device memory by the library's own kernel (from 4 MB on; as a stream from 224 MB on): any 4-byte
+# alignment, nothing past d
+@pytest.mark.parametrize("d,shift", [(1 << 20, 0), ((1 << 20) + 1, 1), ((16 << 20) + 2, 3), ((16 << 20) + 4095, 2),
+                                     (56 << 20, 0), ((56 << 20) + 3, 1)])
+def test_large_state_to_device_memory(d, shift):
     import torch
-    d = (16 << 20) + extra
     print(f"[case] large state to device memory d={d} shift={shift}", flush=True)
     gpu = P.CompAms(d, 1, P.TOPK, 1)
     theta = torch.randn(d, device="cuda")
