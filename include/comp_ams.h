@@ -121,7 +121,7 @@ int comp_ams_set_rand(comp_ams_t *h, uint64_t seed, uint32_t draw);
  * One optimisation step on grads_dev: n*d floats in device memory, row-major [n][d]
  * (worker i at grads_dev + i*d), read-only, owned by the caller and borrowed until the work
  * enqueued on `hip_stream` (a hipStream_t, NULL = the null stream) has completed.
- * The base pointer must be 4-byte aligned; 16-byte alignment gives the fast path.
+ * The base pointer must be 4-byte aligned; rows need no further alignment.
  * The call only launches kernels (no allocation, no memset, no wait while the stream stays the
  * same), so it may be recorded into a HIP graph; record after at least one ordinary step on the same
  * stream (the first step of a handle launches a different variant of the first kernel than the later
