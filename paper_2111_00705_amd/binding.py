@@ -221,9 +221,7 @@ class CompAms:
         self._check(lib().comp_ams_set_method(self._h, method))
 
     def get_ghat_worker(self, worker, out=None):
-        if out is None:
-            out = np.empty(self.d, dtype=np.float32)
-        p, dev = _ptr(out)
+        out, p, dev = self._room(out)
         self._check(lib().comp_ams_get_ghat_worker(self._h, worker, p, dev))
         return out
 
@@ -305,10 +303,17 @@ class CompAms:
     def step_f16_ptr(self, grads_ptr, stream=0):
         self._check(lib().comp_ams_step_f16(self._h, grads_ptr, stream))
 
-    def _get_vec(self, fn, out):
+    def _room(self, out):
+        """(destination, pointer, on_device) of a getter of d floats: the caller's array or tensor, or a new array."""
         if out is None:
             out = np.empty(self.d, dtype=np.float32)
-        p, dev = _ptr(out)
+        size = out.size if isinstance(out, np.ndarray) else out.numel()
+        if size < self.d:
+            raise ValueError(f"the destination holds {size} floats, {self.d} are written")
+        return (out, *_ptr(out))
+
+    def _get_vec(self, fn, out):
+        out, p, dev = self._room(out)
         self._check(fn(self._h, p, dev))
         return out
 
@@ -325,9 +330,7 @@ class CompAms:
         return self._get_vec(lib().comp_ams_get_vhat, out)
 
     def get_error(self, worker, out=None):
-        if out is None:
-            out = np.empty(self.d, dtype=np.float32)
-        p, dev = _ptr(out)
+        out, p, dev = self._room(out)
         self._check(lib().comp_ams_get_error(self._h, worker, p, dev))
         return out
 

@@ -501,17 +501,22 @@ int flush_pending(comp_ams *h);
     int rc = device_scope__.enter(h); \
     if (!rc) rc = flush_pending(h)
 
-// Whether a kernel on the handle's GPU may write to p as floats: ordinary device memory of that GPU.  (A copy also reaches
-// memory of another GPU, or host memory handed over as device memory.)
-bool is_own_device_memory(const comp_ams *h, const void *p)
+// Whether a kernel on the handle's GPU may write `count` floats at p: ordinary device memory of that GPU, with room for all of
+// them in p's allocation.  (A copy also reaches memory of another GPU, or host memory handed over as device memory, and the
+// runtime refuses one that runs past the end of its destination's allocation; a kernel would write there.)
+bool is_own_device_memory(const comp_ams *h, const void *p, size_t count)
 {
     if (!p || (reinterpret_cast<uintptr_t>(p) & (sizeof(float) - 1))) return false;
     hipPointerAttribute_t at{};
-    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess ||
+        hipMemGetAddressRange(&base, &size, const_cast<void *>(p)) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    return at.type == hipMemoryTypeDevice && at.device == h->device;
+    const size_t before = (size_t)(static_cast<const char *>(p) - static_cast<const char *>(base));
+    return at.type == hipMemoryTypeDevice && at.device == h->device && before <= size && count * sizeof(float) <= size - before;
 }
 
 // From this size on copy_out_floats outruns the runtime's copy; below, they are equal.  What a step has just written is
@@ -524,7 +529,7 @@ constexpr size_t kOwnCopyBytes = (size_t)4 << 20;
 int copy_out(comp_ams *h, float *dst, const float *src_dev, size_t count, int on_device)
 {
     if (!dst) return fail(h, COMP_AMS_EINVAL, "output pointer is NULL");
-    if (on_device && count * sizeof(float) >= kOwnCopyBytes && is_own_device_memory(h, dst)) {
+    if (on_device && count * sizeof(float) >= kOwnCopyBytes && is_own_device_memory(h, dst, count)) {
         const int64_t pieces = ((int64_t)count + 16 * kThreads - 1) / (16 * kThreads);
         if (count * sizeof(float) >= kWithinStepBytes)
             copy_out_floats<true><<<grid_blocks(pieces, 16), kThreads, 61440u, h->stream>>>(dst, src_dev, (int64_t)count, 16);
@@ -1308,7 +1313,7 @@ int comp_ams_get_theta(comp_ams_t *h, float *out, int on_device)
 {
     ENTER_DEVICE(h);
     if (rc) return rc;
-    if (h->final_pending && on_device && is_own_device_memory(h, out)) {
+    if (h->final_pending && on_device && is_own_device_memory(h, out, (size_t)h->d)) {
         // the pending update writes theta to the caller's buffer as well: no copy behind it (uniform blocks of 4096,
         // n = 16, d = 1.2 M: step plus get_theta 65.2 -> 61.7 us).  An update is only left pending where the scales are
         // formed from the piece sums (kBlocksFused).

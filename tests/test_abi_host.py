@@ -75,3 +75,16 @@ def test_valid_create_without_gpu_reports_a_device_error_not_a_crash():
     with pytest.raises(P.CompAmsError) as ei:
         P.CompAms(100, 2, P.TOPK, 10)
     assert ei.value.code == P.EDEVICE
+
+
+def test_getters_refuse_a_destination_without_room_for_the_vector():
+    import torch
+    h = object.__new__(P.CompAms)              # no handle behind it: the check comes before the library is called
+    h._h, h.d, h.n, h.k = None, 10, 2, 1
+    for short in (np.empty(9, np.float32), torch.empty(9), torch.empty(0)):
+        for get in (h.get_theta, h.get_m, h.get_v, h.get_vhat, h.get_ghat_server, h.get_gtilde,
+                    lambda out: h.get_error(0, out=out), lambda out: h.get_ghat_worker(0, out=out)):
+            with pytest.raises(ValueError):
+                get(out=short)
+    with pytest.raises(P.CompAmsError):        # room enough: the library answers (no handle)
+        h.get_theta(out=np.empty(10, np.float32))

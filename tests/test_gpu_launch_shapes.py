@@ -216,3 +216,27 @@ def test_large_state_to_device_memory(d, shift):
     gpu.get_v(out=out)
     assert bool((out == 0).all())
     gpu.destroy()
+
+
+# the same two ways out of the library with a destination whose allocation ends one float early: the copy that refuses it
+# is the one that gets it, an error is reported, and the handle goes on
+@pytest.mark.parametrize("comp,kb,d", [(P.TOPK, 1, (1 << 20) + 3), (P.BLOCKSIGN, TILE, 2 * TILE + 1)])
+def test_state_to_device_memory_that_is_too_small(comp, kb, d):
+    import ctypes as C
+    import torch
+    print(f"[case] device memory one float short, comp={comp} d={d}", flush=True)
+    L = P.lib()
+    gpu = P.CompAms(d, 1, comp, kb)
+    theta = torch.randn(d, device="cuda")
+    gpu.set_theta(theta)
+    gpu.step(torch.zeros((1, d), device="cuda"))
+    p = C.c_void_p()
+    assert L.hipMalloc(C.byref(p), C.c_size_t(4 * (d - 1))) == 0
+    getters = [L.comp_ams_get_theta, L.comp_ams_get_m, L.comp_ams_get_v, L.comp_ams_get_vhat]
+    for get in getters:
+        assert get(gpu._h, p, 1) == P.EDEVICE
+        assert L.comp_ams_last_error(gpu._h)
+    assert L.hipFree(p) == 0
+    out = torch.empty(d, device="cuda")
+    assert torch.equal(gpu.get_theta(out=out), theta)        # gradients of zero leave the model where it was
+    gpu.destroy()
