@@ -100,6 +100,7 @@ struct comp_ams {
     uint64_t *dense = nullptr;                 // laid out like cand: comp of the candidates in the threshold bin
 
     uint2 *dense_dir = nullptr;                // [n][slices * parts * 4] {start, count} of each wavefront's piece
+    bool has_guess = false;                    // a step has run since the selection records were reset
     uint32_t *small_ctr = nullptr;             // [n + 1] short vectors: entries listed (the last one the server's)
     uint32_t *sel_count = nullptr, *sel_out_idx = nullptr;
     float *sel_out_val = nullptr;
@@ -790,8 +791,11 @@ void by_key(const comp_ams *h, size_t grad_bytes, F &&f)
         f(std::integral_constant<int, kKeyMagnitude>{});
 }
 
-// Short vectors: the geometry with one region per vector (all of its space), and the selection in one launch.
-inline bool is_short(const comp_ams *h) { return h->ge.n_tiles <= kSmallTiles; }
+// Short vectors: the geometry with one region per vector (all of its space), and the selection in one launch.  Without a
+// guess (the first step of a handle, or after its error memory was set) every selection of the step is a miss, and beyond
+// kShortBatch tiles the three launches of many workgroups serve that faster.  First step, n = 8, k = 1 %, us, one launch /
+// three: naive d = 5000 37 / 44, d = 20 000 42 / 44, d = 65 536 55 / 48; CD-Adam 62 / 73, 74 / 72, 106 / 86.
+inline bool is_short(const comp_ams *h) { return h->ge.n_tiles <= (h->has_guess ? kSmallTiles : kShortBatch); }
 inline TkGeom short_geometry(TkGeom ge)
 {
     ge.region_cap = (uint32_t)ge.slices * ge.region_cap;
@@ -805,8 +809,7 @@ void launch_short_select(comp_ams *h, hipStream_t st, const TkGeom &sge, TkWorke
                          uint4 *tile_dir, const void *a, const float *b, int slot)
 {
     launch_timed(h, slot, st, [&] {
-        const ExactSource es{kSrc, std::is_same<G, float>::value ? 0 : std::is_same<G, uint16_t>::value ? 1 : 2, a, b};
-        KLAUNCH((tk_small_select), (unsigned)sge.n, kResolveThreads, st, sge, ws, cand, count, tile_dir, es);
+        KLAUNCH((tk_small_select<kSrc, G>), (unsigned)sge.n, kResolveThreads, st, sge, ws, cand, count, tile_dir, a, b);
     });
 }
 
@@ -971,6 +974,7 @@ int reset_topk_workers(comp_ams *h)
 {
     std::vector<TkWorker> init((size_t)h->n);
     fresh_tk_workers(init);
+    h->has_guess = false;
     HIP_TRY(h, hipMemcpy(h->ws, init.data(), init.size() * sizeof(TkWorker), hipMemcpyHostToDevice));
     HIP_TRY(h, hipMemset(h->cursor, 0, (size_t)h->n * h->ge.slices * kCursorStride * sizeof(uint32_t)));
     HIP_TRY(h, hipMemset(h->cursor_b, 0, (size_t)h->n * h->ge.slices * kCursorStride * sizeof(uint32_t)));
@@ -1071,6 +1075,7 @@ int step_any(comp_ams *h, const G *grads_dev, void *hip_stream)
                                                            : step_blocksign(h, grads_dev, st);
     if (rc) return rc;
     HIP_TRY(h, hipGetLastError());
+    h->has_guess = true;
     ++h->steps;
     ++h->draw;
     return COMP_AMS_OK;

@@ -838,31 +838,36 @@ __device__ __forceinline__ Piece piece_of(const TkGeom &ge, const uint32_t *__re
 //   kSrcGradOnly  a = g itself (naive compression)
 enum { kSrcStored = 0, kSrcGrad = 1, kSrcDiff = 2, kSrcGradOnly = 3 };
 
+// The coordinates j .. j + 3 of vector i (j a multiple of 4).  a: for kSrcGrad / kSrcGradOnly the gradients (elements of
+// type G), else padded float rows; brow: row i of b.
+template <int kSrc, typename G>
+__device__ __forceinline__ float4 load_source4(const void *__restrict__ a, int i, const TkGeom &ge,
+                                               const float *__restrict__ brow, uint32_t j, uint32_t d)
+{
+    float4 av;
+    if constexpr (kSrc == kSrcGrad || kSrc == kSrcGradOnly)
+        av = load_grad4(static_cast<const G *>(a) + (int64_t)i * ge.d, j, d);
+    else
+        av = ld4(static_cast<const float *>(a) + (int64_t)i * ge.ld + j);
+    if (kSrc == kSrcGrad || kSrc == kSrcDiff) {
+        const float4 bv = ld4(brow + j);
+        av = make_float4(fsub(av.x, bv.x), fsub(av.y, bv.y), fsub(av.z, bv.z), fsub(av.w, bv.w));
+    }
+    return av;
+}
+
 // The 16 values of this thread in the tile at `base` (coordinates base + 4 (tid + 256 r) + c).
-// a: for kSrcGrad / kSrcGradOnly row i of the gradients (elements of type G), else a padded float row.
 template <int kSrc, typename G>
 __device__ __forceinline__ void load_source_tile(float (&x)[4][4], const void *__restrict__ a, int i, const TkGeom &ge,
                                                  const float *__restrict__ brow, uint32_t base, uint32_t d)
 {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const uint32_t j = base + 4 * (threadIdx.x + kThreads * r);
-        float4 av;
-        if constexpr (kSrc == kSrcGrad || kSrc == kSrcGradOnly)
-            av = load_grad4(static_cast<const G *>(a) + (int64_t)i * ge.d, j, d);
-        else
-            av = ld4(static_cast<const float *>(a) + (int64_t)i * ge.ld + j);
-        x[r][0] = av.x;
-        x[r][1] = av.y;
-        x[r][2] = av.z;
-        x[r][3] = av.w;
-        if (kSrc == kSrcGrad || kSrc == kSrcDiff) {
-            const float4 bv = ld4(brow + j);
-            x[r][0] = fsub(x[r][0], bv.x);
-            x[r][1] = fsub(x[r][1], bv.y);
-            x[r][2] = fsub(x[r][2], bv.z);
-            x[r][3] = fsub(x[r][3], bv.w);
-        }
+        const float4 v = load_source4<kSrc, G>(a, i, ge, brow, base + 4 * (threadIdx.x + kThreads * r), d);
+        x[r][0] = v.x;
+        x[r][1] = v.y;
+        x[r][2] = v.z;
+        x[r][3] = v.w;
     }
 }
 
@@ -1859,8 +1864,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
 // On such a vector every kernel of the selection chain is a launch on an idle chip, and three of them cost more
 // than the work.  The listing pass is tk_pass1 itself with a single candidate region per vector (few tiles share
 // its cursor); then one workgroup per vector finds the threshold from the list by itself - the digits of Tc over
-// the listed comp values, or, when the list does not hold the k-th largest (first step, a guess that was too high,
-// a full region), by counting over the vector itself (exact_select).  The tile directory and the list have the
+// the listed comp values, after listing the vector again when the list does not hold the k-th largest.  The tile directory and the list have the
 // usual form, so the kernels after it and the getters follow unchanged.  (Finding the threshold inside the listing
 // pass, by the workgroup that finishes a worker's last tile, was built and measured: the device-scope fences it needs
 // on this multi-XCD part cost more than the launch they save - 21.6 us against 6 + 5.)
@@ -1868,24 +1872,169 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
 // once, into registers, and the digits are found from those.
 constexpr int kSmallTiles = 16;
 
+// After a miss (a guess that was too high, a full region, the first step of a vector of few tiles) the workgroup lists the
+// vector again by itself: one pass counts the coarse bins, a second lists what lies in the k-th largest's bin or above,
+// kShortBatch tiles in flight.  Bound by one compute unit's loads and LDS atomics.  Counting the whole composite key over
+// the vector at once (exact_select: up to six sweeps of scalar loads, one more to list) made one miss cost what ten steps
+// gain.  Step plus get_theta, n = 8, d = 65 536, k = 1 %, scale a thousandth for 6 steps of 12, us, the three launches of long
+// vectors / exact_select at every miss / this: naive 46.8 / 48.1 / 36.9, CD-Adam 74.4 / 129.0 / 67.8; fresh gradients, n = 32,
+// d = 60 000: naive 55.0 / 59.0 / 45.2, error feedback (which had exact_select before) 69.6 / 65.9 / 52.5.
+constexpr int kShortBatch = 4;
+constexpr int kRankAll = 128;     // a list of at most this many entries is ranked as it is, without digits
+static_assert(kRankAll <= kFew, "held in ResolveLds::few");
+struct ShortLds {
+    uint32_t count[kWave], zeros[kShortBatch];
+};
+// What is known of Tc: the bits of comp above the `open` low ones, and its rank among the elements that carry them.
+struct ShortDigits {
+    uint64_t prefix;
+    uint32_t rank;
+    int open;
+};
+static_assert(kTile == 4 * kResolveThreads, "a float4 of each tile per thread");
+static_assert(kShortBatch * kResolveThreads / kWave == kWave, "a wavefront's count of a tile per lane");
+
+// Lists the vector again, as one run from the start of its space, and writes every tile's record.  Returns the number of
+// entries, or kNoSpace where they do not fit (the list is then of no use).  All kResolveThreads threads call this; ends
+// with a barrier.
+template <int kSrc, typename G>
+__device__ __forceinline__ uint32_t list_short_again(const TkGeom &ge, int i, const void *__restrict__ a,
+                                                     const float *__restrict__ b, const SelKey &sk,
+                                                     uint2 *__restrict__ cand, uint4 *__restrict__ tile_dir, ResolveLds &L,
+                                                     ShortLds &S, ShortDigits &top)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t d = (uint32_t)ge.d;
+    const float *brow = (kSrc == kSrcGrad || kSrc == kSrcDiff) ? b + (int64_t)i * ge.ld : nullptr;
+    const bool skip_zeros = kSrc == kSrcStored && !sk.on;               // zeros are counted, not listed (as in tk_pass1)
+    for (int q = tid; q < kBins1; q += kResolveThreads) L.lh[q] = 0;
+    __syncthreads();
+    for (int t0 = 0; t0 < ge.n_tiles; t0 += kShortBatch) {
+        float4 v[kShortBatch];
+#pragma unroll
+        for (int u = 0; u < kShortBatch; ++u)
+            if (t0 + u < ge.n_tiles) v[u] = load_source4<kSrc, G>(a, i, ge, brow, (uint32_t)(t0 + u) * kTile + 4 * tid, d);
+#pragma unroll
+        for (int u = 0; u < kShortBatch; ++u) {
+            if (t0 + u >= ge.n_tiles) continue;
+            const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t j = (uint32_t)(t0 + u) * kTile + 4 * tid + c;
+                const uint32_t bin = sel_key(sk, x[c], j) >> kShift1;
+                if (bin != 0 && j < d) atomicAdd(&L.lh[bin], 1u);      // bin 0 is the remainder
+            }
+        }
+    }
+    __syncthreads();
+    find_rank_bin(L.lh, L.part, L.res, kBins1, ge.k);
+    const uint32_t prefix = L.res[3] ? L.res[0] : 0u;                   // fewer than k counted: bin 0
+    if (L.res[3]) top = {prefix, ge.k - L.res[1], kShift1 + ge.idx_bits};
+    uint32_t run = 0;
+    for (int t0 = 0; t0 < ge.n_tiles; t0 += kShortBatch) {              // uniform over the workgroup
+        float x[kShortBatch][4];
+        uint32_t hits = 0, count[kShortBatch];
+#pragma unroll
+        for (int u = 0; u < kShortBatch; ++u) {
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (t0 + u < ge.n_tiles) v = load_source4<kSrc, G>(a, i, ge, brow, (uint32_t)(t0 + u) * kTile + 4 * tid, d);
+            x[u][0] = v.x;
+            x[u][1] = v.y;
+            x[u][2] = v.z;
+            x[u][3] = v.w;
+        }
+        if (tid < kShortBatch) S.zeros[tid] = 0;                         // read, in the round before, by these threads' wavefront
+        __syncthreads();                                                // and the counts by all
+#pragma unroll
+        for (int u = 0; u < kShortBatch; ++u) {
+            uint32_t zeros = 0;
+            count[u] = 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t j = (uint32_t)(t0 + u) * kTile + 4 * tid + c;        // at or beyond d in tiles past the last
+                bool hit = j < d && (sel_key(sk, x[u][c], j) >> kShift1) >= prefix;
+                if (skip_zeros) {
+                    const bool zero = j < d && mag_key(x[u][c]) == 0u;
+                    zeros += (uint32_t)__popcll(__ballot(zero));
+                    hit = hit && !zero;
+                }
+                count[u] += (uint32_t)__popcll(__ballot(hit));
+                hits |= (hit ? 1u : 0u) << (u * 4 + c);
+            }
+            if (lane == 0) {
+                // in the order of the list: tile by tile, the listing pass's wavefronts one after the other (wavefront
+                // wave & 3 of it owns what this one holds, its row wave >> 2)
+                S.count[u * 16 + (wave & 3) * 4 + (wave >> 2)] = count[u];
+                if (zeros) atomicAdd(&S.zeros[u], zeros);
+            }
+        }
+        __syncthreads();
+        // every wavefront adds the counts up for itself
+        const uint32_t mine = S.count[lane];
+        uint32_t incl = mine;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const uint32_t up = __shfl_up(incl, off, kWave);
+            if (lane >= off) incl += up;
+        }
+        const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
+        if (total > ge.region_cap - run) return kNoSpace;               // uniform over the workgroup
+        if (wave == 0) {
+            // lane 16 u + 4 w: the first of the four counts of wavefront w of tile t0 + u
+            uint32_t quad = mine + (uint32_t)__shfl_down((int)mine, 1, kWave);
+            quad += (uint32_t)__shfl_down((int)quad, 2, kWave);
+            const uint32_t w1 = (uint32_t)__shfl_down((int)quad, 4, kWave), w2 = (uint32_t)__shfl_down((int)quad, 8, kWave),
+                           w3 = (uint32_t)__shfl_down((int)quad, 12, kWave);
+            if ((lane & 15) == 0 && t0 + (lane >> 4) < ge.n_tiles)
+                tile_dir[(int64_t)i * ge.n_tiles + t0 + (lane >> 4)] =
+                    make_uint4(run + incl - mine, quad | (w1 << 16), w2 | (w3 << 16), S.zeros[lane >> 4]);
+        }
+        uint2 *dst = cand + worker_base(ge, i) + run;
+#pragma unroll
+        for (int u = 0; u < kShortBatch; ++u) {
+            uint32_t at = (uint32_t)__shfl((int)(incl - mine), u * 16 + (wave & 3) * 4 + (wave >> 2), kWave);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const bool hit = (hits >> (u * 4 + c)) & 1u;
+                const uint32_t slot = wave_append(hit, at);
+                if (hit) dst[slot] = make_uint2((uint32_t)(t0 + u) * kTile + 4 * tid + c, __float_as_uint(x[u][c]));
+            }
+        }
+        run += total;
+    }
+    __syncthreads();                                                    // the list is read back by other threads
+    return run;
+}
+
 // sge: the vectors' geometry with slices = 1 and region_cap = all of a vector's space.  count: entries listed per
-// vector, kCursorStride words apart (cleared here for the next step).  es: how a vector is re-formed.
+// vector, kCursorStride words apart (cleared here for the next step).  a, b: how a vector is re-formed (load_source4).
+template <int kSrc, typename G>
 __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom sge, TkWorker *__restrict__ ws,
                                                                    uint2 *__restrict__ cand, uint32_t *__restrict__ count,
-                                                                   uint4 *__restrict__ tile_dir, ExactSource es)
+                                                                   uint4 *__restrict__ tile_dir, const void *__restrict__ a,
+                                                                   const float *__restrict__ b)
 {
     __shared__ ResolveLds L;
-    __shared__ ExactLds E;
+    __shared__ union {
+        ShortLds again;
+        ExactLds exact;
+    } U;
     const int i = blockIdx.x;
     const int tid = threadIdx.x;
     const uint2 *list = cand + worker_base(sge, i);
-    const uint32_t total = count[i * kCursorStride];
+    uint32_t total = count[i * kCursorStride];
     const TkWorker w = ws[i];
     const SelKey sk = sel_key_of(sge.rand, sge.rand.step_now, i);
-    const bool zeros_listed = es.src != kSrcStored || sk.on;         // see tk_pass1
+    const bool zeros_listed = kSrc != kSrcStored || sk.on;           // see tk_pass1
+    const ExactSource es{kSrc, std::is_same<G, float>::value ? 0 : std::is_same<G, uint16_t>::value ? 1 : 2, a, b};
+    // a list of every non-zero element (the guess was 0) needs no other, however short it is
+    const bool missed = w.overflow || (total < sge.k && (zeros_listed || w.guess != 0u));
+    ShortDigits top = {0ull, sge.k, 31 + sge.idx_bits};
+    if (missed) total = list_short_again<kSrc, G>(sge, i, a, b, sk, cand, tile_dir, L, U.again, top);
     uint64_t tc;
-    bool missed = false;
-    if (!w.overflow && total >= sge.k) {
+    if (missed && total == kNoSpace) {
+        tc = exact_select(es, sge, i, cand, tile_dir, L, U.exact);
+    } else if (total >= sge.k) {
         // every element at or above the guess is listed and there are at least k: Tc is the k-th largest of the
         // list (the comp value itself: a digit's bin may reach below the guess, where nothing is listed)
         auto comp_of = [&](uint32_t q) -> uint64_t {
@@ -1893,7 +2042,18 @@ __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom sge, T
             const uint2 e = list[q];
             return composite(sel_key(sk, __uint_as_float(e.y), e.x), e.x, sge.idx_bits);
         };
-        if (total <= (uint32_t)(kScanUnroll * kResolveThreads)) {
+        if (total <= (uint32_t)kRankAll) {
+            if ((uint32_t)tid < total) L.few[tid] = comp_of(tid);
+            __syncthreads();
+            if ((uint32_t)tid < total) {
+                const uint64_t mine = L.few[tid];
+                uint32_t greater = 0;
+                for (uint32_t u = 0; u < total; ++u) greater += L.few[u] > mine ? 1u : 0u;
+                if (greater + 1 == sge.k) L.tc_sh = mine;             // comp values are unique: exactly one thread
+            }
+            __syncthreads();
+            tc = L.tc_sh;
+        } else if (total <= (uint32_t)(kScanUnroll * kResolveThreads)) {
             uint64_t held[kScanUnroll];
 #pragma unroll
             for (int u = 0; u < kScanUnroll; ++u) held[u] = comp_of(u * kResolveThreads + tid);
@@ -1901,25 +2061,22 @@ __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom sge, T
 #pragma unroll
                 for (int u = 0; u < kScanUnroll; ++u) comp[u] = held[u];       // one batch: q[u] = u * kResolveThreads + tid
             };
-            tc = resolve_digits<false>(fetch, total, 0ull, sge.k, 31 + sge.idx_bits, L);
+            tc = resolve_digits<false>(fetch, total, top.prefix, top.rank, top.open, L);
         } else {
             auto fetch = [&](const uint32_t (&q)[kScanUnroll], uint64_t (&comp)[kScanUnroll]) {
 #pragma unroll
                 for (int u = 0; u < kScanUnroll; ++u) comp[u] = comp_of(q[u]);
             };
-            tc = resolve_digits<false>(fetch, total, 0ull, sge.k, 31 + sge.idx_bits, L);
+            tc = resolve_digits<false>(fetch, total, top.prefix, top.rank, top.open, L);
         }
-    } else if (!w.overflow && !zeros_listed && w.guess == 0u) {
+    } else {
         // every non-zero element is listed and they are fewer than k: the threshold lies among the zeros, which the
         // list leaves out - all candidates are kept, and Tc comes from counting over the vector
         tc = exact_threshold(es, sge, i, L);
-    } else {
-        missed = true;
-        tc = exact_select(es, sge, i, cand, tile_dir, L, E);
     }
     if (tid == 0) {
         ws[i].relisted = missed ? 1u : 0u;
-        ws[i].whole = missed ? kExact : 0u;
+        ws[i].whole = missed && total == kNoSpace ? kExact : 0u;
         finish_worker(ws, i, w, tc, sge, missed);
         count[i * kCursorStride] = 0;
     }

@@ -134,6 +134,53 @@ def test_short_vectors(method, d, n, k):
     gpu.destroy()
 
 
+# a short vector whose list does not hold the k-th largest is listed again by its selection kernel, four tiles at a time:
+# the first step of a handle, and every collapse of the scale under naive compression.  Part of a tile, whole tiles and
+# batches of tiles, more entries than the registers hold.
+@pytest.mark.parametrize("dtype", ["fp32", "bf16", "f16"])
+@pytest.mark.parametrize("comp", [P.TOPK, P.RANDK])
+@pytest.mark.parametrize("method", ["ef", "naive", "cd"])
+def test_short_vectors_listed_again(method, comp, dtype):
+    import torch
+    for d, n, k in ((3, 2, 2), (4096, 2, 40), (4 * TILE + 1, 3, 170), (9 * TILE - 2, 1, 9), (16 * TILE, 2, 655), (60_001, 2, 6_001)):
+        print(f"[case] short vectors listed again {method} comp={comp} {dtype} d={d} n={n} k={k}", flush=True)
+        gpu, ora = sparse_pair(d, n, k, method, comp)
+        tt = {"fp32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+        step = {"fp32": gpu.step, "bf16": gpu.step_bf16, "f16": gpu.step_f16}[dtype]
+        for t, factor in enumerate((1.0, 1.0, 2.0 ** -7, 1.0, 2.0 ** -7)):
+            g = torch.from_numpy(grads_of(d, n, d)(t) * f32(100.0 * factor)).to(tt)
+            step(g.cuda())
+            ora.step(g.float().numpy())
+            for i in range(n):
+                assert np.array_equal(gpu.get_selected(i)[0], ora.selected[i]), (d, t, i)
+                info = gpu.get_selection_info(i)
+                if t == 0 or (factor < 1.0 and method == "naive" and comp == P.TOPK):
+                    assert info["relisted"] == 1 and info["whole_bin"] != 3, (d, t, i, info)     # 3: without lists
+            if method == "ef":
+                assert all(np.array_equal(gpu.get_error(i).view(np.uint32), ora.error[i].view(np.uint32)) for i in range(n)), (d, t)
+            if method == "cd":
+                assert np.array_equal(gpu.get_server_selected()[0], ora.server_selected), (d, t)
+                assert np.array_equal(gpu.get_gtilde().view(np.uint32), ora.gtilde.view(np.uint32)), (d, t)
+            assert rel_close(gpu.get_theta(), ora.theta, STATE_RTOL).all(), (d, t)
+        gpu.destroy()
+
+
+# the same with more elements in the k-th largest's bin than the space holds (selected without lists), and with fewer
+# non-zero coordinates than k
+@pytest.mark.parametrize("method", ["ef", "naive", "cd"])
+@pytest.mark.parametrize("share", [1.0, 0.003])
+def test_short_vectors_of_equal_values_or_few_nonzeros(method, share):
+    d, n, k = 60_001, 2, 600
+    print(f"[case] short vectors, {share} of the coordinates equal, the others zero, {method}", flush=True)
+    gpu, ora = sparse_pair(d, n, k, method)
+
+    def fn(t):
+        r = np.random.default_rng([5, t])
+        return np.ascontiguousarray(np.where(r.random((n, d)) < share, f32(0.5 - 0.1 * t), f32(0.0)).astype(f32))
+    sparse_steps(gpu, ora, fn, 3, method, f"{method} {share}")
+    gpu.destroy()
+
+
 # tk_final_short / tk_final at the boundary between them; more than 64 kept values in a wavefront's quarter, more than
 # one batch of eight workers
 @pytest.mark.parametrize("tiles,n,share", [(320, 9, 0.3), (321, 9, 0.3), (320, 1, 0.001)])
