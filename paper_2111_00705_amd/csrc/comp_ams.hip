@@ -24,6 +24,7 @@
 #include "blocksign_kernels.h"
 #include "topk_kernels.h"
 #include "plain_kernels.h"
+#include "launch_rules.h"
 
 using namespace cams;
 
@@ -751,7 +752,7 @@ void launch_final(comp_ams *h, hipStream_t st)
 {
     launch_timed(h, P_TK_FINAL, st, [&] {
         by_flag(h->params.stream_state, [&](auto ss) {
-            if (h->ge.n_tiles <= kShortFinalTiles)
+            if (short_final(h->n, h->ge.n_tiles))
                 KLAUNCH((tk_final_short<decltype(ss)::value>), 4 * h->ge.n_tiles, kThreads, st, h->ge, h->ws, h->cand,
                         h->tile_dir, h->theta, h->m, h->v, h->vhat, h->params);
             else

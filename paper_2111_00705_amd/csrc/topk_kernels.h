@@ -776,12 +776,9 @@ __global__ __launch_bounds__(kThreads) void tk_final(TkGeom ge, const TkWorker *
     }
 }
 
-// The same with a quarter of a tile per workgroup, for vectors of at most kShortFinalTiles tiles, which leave the chip
-// idle otherwise: quarter w holds the coordinates of the listing pass's wavefront w, and wavefront r here takes row r
-// of them (one float4 per lane, the state loaded before anything else).  The four wavefronts each read the quarter's
-// lists, which is what it costs.  Step plus get_theta, n = 8, k = 1 %, a tile per workgroup / a quarter, us:
-// d = 65 000 38.0 / 35.9, 262 144 49.1 / 47.0, 1 M 67.2 / 65.8, 2 M 89.5 / 92.0, 4 M 139.7 / 145.5; d = 110 M 2455 / 2497.
-constexpr int kShortFinalTiles = 320;
+// The same with a quarter of a tile per workgroup, for vectors that leave the chip idle otherwise (see short_final): quarter
+// w holds the coordinates of the listing pass's wavefront w, and wavefront r here takes row r of them (one float4 per lane,
+// the state loaded before anything else).  The four wavefronts each read the quarter's lists, which is what it costs.
 template <bool kStreamState>
 __global__ __launch_bounds__(kThreads) void tk_final_short(TkGeom ge, const TkWorker *__restrict__ ws,
                                                      const uint2 *__restrict__ cand,
