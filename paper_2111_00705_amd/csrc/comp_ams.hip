@@ -194,14 +194,6 @@ inline int tk_ef_chunk_for(const comp_ams *h)
     return tk_long_rows(h) ? 16 : 8;
 }
 
-// Grid of a kernel with one workgroup per tile (in x) under tile_of_block's mapping.
-inline unsigned grid_blocks(int64_t n_tiles, int chunk)
-{
-    if (chunk <= 0) return (unsigned)n_tiles;
-    const int64_t span = 8 * (int64_t)chunk;
-    return (unsigned)((n_tiles + span - 1) / span * span);
-}
-
 // Applies the caller's choices (comp_ams_set_streaming; -1 = by size) to the kernel parameters.
 inline void apply_streaming(comp_ams *h)
 {
@@ -869,11 +861,8 @@ int step_topk_naive(comp_ams *h, const G *g, hipStream_t st)
 template <typename G>
 int step_plain(comp_ams *h, const G *g, hipStream_t st)
 {
-    // Tile order: each XCD working through 16 consecutive tiles (64 quarters) of a row at a time is as fast as the plain
-    // order or faster at every size measured (d = 3 M to 110 M, n = 1 to 64: 0-6 %), as long as there are tiles enough to
-    // reach all XCDs: a vector of 65 536 coordinates, one chunk, would run on one of them.
     const int n_quarters = (int)(h->ld / kPlainCoords);
-    const int chunk = 4 * (h->chunk_choice >= 0 ? h->chunk_choice : n_quarters >= 8 * 64 ? 16 : 0);
+    const int chunk = plain_chunk(h->chunk_choice, n_quarters);
     launch_timed(h, P_PLAIN_UPDATE, st, [&] {
         by_flag(h->params.stream_state, [&](auto ss) {
             KLAUNCH((plain_update<G, decltype(ss)::value>), grid_blocks(n_quarters, chunk), kThreads, st, g, h->d, h->n,

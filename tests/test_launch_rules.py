@@ -25,3 +25,27 @@ def test_quarter_tile_update_only_where_the_lists_are_short(tmp_path):
              (64, 80): 1, (64, 128): 0, (65535, 1): 0, (65535, 524288): 0}
     got = evaluate(tmp_path, [f"short_final({n}, {tiles})" for n, tiles in cases])
     assert got == list(cases.values())
+
+
+def test_uncompressed_update_pads_its_grid_to_no_more_than_eight_vectors(tmp_path):
+    quarters = [1, 4, 64, 511, 512, 977, 100_000, 2_097_152]
+    choices = [-1, 0, 1, 16, 1024, 65_536]
+    pairs = [(c, q) for c in choices for q in quarters]
+    chunk = evaluate(tmp_path, [f"plain_chunk({c}, {q})" for c, q in pairs])
+    grid = evaluate(tmp_path, [f"grid_blocks({q}, plain_chunk({c}, {q}))" for c, q in pairs])
+
+    def tiles(n_blocks, ch):          # tile_of_block
+        if ch <= 0:
+            return list(range(n_blocks))
+        span = 8 * ch
+        return [b - b % span + (b % span & 7) * ch + (b % span >> 3) for b in range(n_blocks)]
+    for (c, q), ch, blocks in zip(pairs, chunk, grid):
+        wanted = 4 * c if c >= 0 else (64 if q >= 512 else 0)
+        assert ch == min(wanted, q) and q <= blocks <= max(8 * q, q + 8 * ch)
+        if q > 1000:
+            continue
+        # every quarter once, and on the same XCD and in the same order as with the chunk that was asked for
+        order = lambda c_, n_: [(b & 7, t) for b, t in enumerate(tiles(n_, c_)) if t < q]
+        asked = blocks if wanted <= 0 else (q + 8 * wanted - 1) // (8 * wanted) * 8 * wanted
+        assert sorted(t for _, t in order(ch, blocks)) == list(range(q))
+        assert order(ch, blocks) == order(wanted, asked)
