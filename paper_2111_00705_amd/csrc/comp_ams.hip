@@ -665,7 +665,7 @@ int step_blocksign_cd(comp_ams *h, const G *g, hipStream_t st)
     if (tb.small_log2 > 0 && tb.small_log2 <= 8) {
         // blocks inside a wavefront: lines 8-16 in one launch
         launch_timed(h, P_BS_SERVER, st, [&] {
-            const BsMarkov mk{h->ghat_srv, h->gtil, h->signs_srv, h->partial_srv, h->scales_srv, 1};
+            const BsMarkov mk{h->ghat_srv, h->gtil, h->signs_srv, h->partial_srv, h->scales_srv};
             launch_update<kBlocksShort, true>(h, st, h->params, mk);
         });
         h->pending = true;
@@ -679,7 +679,7 @@ int step_blocksign_cd(comp_ams *h, const G *g, hipStream_t st)
             KLAUNCH_LDS((bs_scale), dim3(tb.n_scale_list, h->n), scale_threads(h), scale_lds(h), st, h->partial, tb, h->scales);
         });
     launch_timed(h, P_BS_SERVER, st, [&] {
-        const BsMarkov mk{h->ghat_srv, h->gtil, h->signs_srv, h->partial_srv, h->scales_srv, whole ? 1 : 0};
+        const BsMarkov mk{h->ghat_srv, h->gtil, h->signs_srv, h->partial_srv, h->scales_srv};
         if (whole)
             by_flag(h->params.stream_state, [&](auto ss) {
                 KLAUNCH((bs_server<true, decltype(ss)::value>), ugrid, kThreads, st, h->d, h->ld,
@@ -772,13 +772,17 @@ unsigned tk_pass_lds(const comp_ams *h)
     return lists + (rows_exceed_caches(h) && !tk_long_rows(h) ? 7000u : 9u * 1024u);
 }
 
-// Calls f with what tk_pass1 may take for granted about the keys (see kKeyEither) as a compile-time constant.
-template <typename F>
-void by_key(const comp_ams *h, size_t grad_bytes, F &&f)
+// Calls f with what tk_pass1<kMode, ., G> may take for granted about the keys (see kKeyEither) as a compile-time constant.
+template <int kMode, typename G, typename F>
+void by_key(const comp_ams *h, F &&f)
 {
-    if (h->method == COMP_AMS_METHOD_EF && grad_bytes == 4 && tk_long_rows(h))
-        f(std::integral_constant<int, kKeyEither>{});
-    else if (h->compressor == COMP_AMS_RANDK)
+    if constexpr (kMode == kPassEf && std::is_same<G, float>::value) {
+        if (tk_long_rows(h)) {
+            f(std::integral_constant<int, kKeyEither>{});
+            return;
+        }
+    }
+    if (h->compressor == COMP_AMS_RANDK)
         f(std::integral_constant<int, kKeyScore>{});
     else
         f(std::integral_constant<int, kKeyMagnitude>{});
@@ -811,7 +815,7 @@ int step_topk(comp_ams *h, const G *g, hipStream_t st)
 {
     if (is_short(h)) {
         const TkGeom sge = short_geometry(h->ge);
-        launch_timed(h, P_TK_PASS1, st, [&] { by_key(h, sizeof(G), [&](auto key) {
+        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassEf, G>(h, [&](auto key) {
             KLAUNCH((tk_pass1<kPassEf, decltype(key)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
                     h->tile_dir);
         }); });
@@ -821,7 +825,7 @@ int step_topk(comp_ams *h, const G *g, hipStream_t st)
     }
     const TkGeom &ge = h->ge;
     const TkGeom pge = pass_geometry<G>(h);
-    launch_timed(h, P_TK_PASS1, st, [&] { by_key(h, sizeof(G), [&](auto key) {
+    launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassEf, G>(h, [&](auto key) {
         KLAUNCH_LDS((tk_pass1<kPassEf, decltype(key)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassEf, G>(h)), st, g, h->e, pge, h->ws,
                 h->cand, h->cursor, h->tile_dir);
     }); });
@@ -837,7 +841,7 @@ int step_topk_naive(comp_ams *h, const G *g, hipStream_t st)
 {
     if (is_short(h)) {
         const TkGeom sge = short_geometry(h->ge);
-        launch_timed(h, P_TK_PASS1, st, [&] { by_key(h, sizeof(G), [&](auto key) {
+        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassNaive, G>(h, [&](auto key) {
             KLAUNCH((tk_pass1<kPassNaive, decltype(key)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
                     h->tile_dir);
         }); });
@@ -847,7 +851,7 @@ int step_topk_naive(comp_ams *h, const G *g, hipStream_t st)
     }
     const TkGeom &ge = h->ge;
     const TkGeom pge = pass_geometry<G>(h);
-    launch_timed(h, P_TK_PASS1, st, [&] { by_key(h, sizeof(G), [&](auto key) {
+    launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassNaive, G>(h, [&](auto key) {
         KLAUNCH_LDS((tk_pass1<kPassNaive, decltype(key)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassNaive, G>(h)), st, g, h->e, pge, h->ws,
                 h->cand, h->cursor, h->tile_dir);
     }); });
@@ -882,13 +886,13 @@ int step_topk_cd(comp_ams *h, const G *g, hipStream_t st)
     const bool brief = is_short(h);
     if (brief) {
         const TkGeom sge = short_geometry(ge);
-        launch_timed(h, P_TK_PASS1, st, [&] { by_key(h, sizeof(G), [&](auto key) {
+        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassCd, G>(h, [&](auto key) {
             KLAUNCH((tk_pass1<kPassCd, decltype(key)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
                     h->tile_dir);
         }); });
         launch_short_select<kSrcGrad, G>(h, st, sge, h->ws, h->cand, h->small_ctr, h->tile_dir, g, h->e, P_TK_RESOLVE);
     } else {
-        launch_timed(h, P_TK_PASS1, st, [&] { by_key(h, sizeof(G), [&](auto key) {
+        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassCd, G>(h, [&](auto key) {
             KLAUNCH_LDS((tk_pass1<kPassCd, decltype(key)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassCd, G>(h)), st, g, h->e, pge, h->ws,
                     h->cand, h->cursor, h->tile_dir);
         }); });
@@ -902,14 +906,14 @@ int step_topk_cd(comp_ams *h, const G *g, hipStream_t st)
     if (brief) {
         const TkGeom sge = short_geometry(sv.ge);
         uint32_t *count = h->small_ctr + (size_t)h->n * kCursorStride;      // the server's, after the workers'
-        launch_timed(h, P_TK_PASS1_SERVER, st, [&] { by_key(h, sizeof(G), [&](auto key) {
+        launch_timed(h, P_TK_PASS1_SERVER, st, [&] { by_key<kPassDiff, float>(h, [&](auto key) {
             KLAUNCH((tk_pass1<kPassDiff, decltype(key)::value, float>), dim3(sge.n_tiles, 1), kThreads, st, h->ghat_srv, h->gtil, sge, sv.ws, sv.cand,
                     count, sv.tile_dir);
         }); });
         launch_short_select<kSrcDiff, float>(h, st, sge, sv.ws, sv.cand, count, sv.tile_dir, h->ghat_srv, h->gtil,
                                              P_TK_SELECT_SERVER);
     } else {
-        launch_timed(h, P_TK_PASS1_SERVER, st, [&] { by_key(h, sizeof(G), [&](auto key) {
+        launch_timed(h, P_TK_PASS1_SERVER, st, [&] { by_key<kPassDiff, float>(h, [&](auto key) {
             KLAUNCH((tk_pass1<kPassDiff, decltype(key)::value, float>), dim3(grid_blocks(ge.n_tiles, sv.ge.xcd_chunk), 1), kThreads, st, h->ghat_srv,
                     h->gtil, sv.ge, sv.ws, sv.cand, sv.cursor, sv.tile_dir);
         }); });

@@ -414,6 +414,44 @@ __device__ __forceinline__ void consider(float x, uint32_t j, uint32_t base, boo
 //        kPassNaive  naive compression (Section 4): x = g, the stored rows are not touched.
 enum { kPassEf = 0, kPassCd = 1, kPassDiff = 2, kPassNaive = 3 };
 
+// The gradients and the stored values of this thread's coordinates, base + 4 (tid + 256 r) + c.
+template <int kMode, typename G>
+__device__ __forceinline__ void load_pass_tile(float4 (&gv)[4], float4 (&xv)[4], const G *__restrict__ grow,
+                                               const float *__restrict__ xrow, uint32_t base, uint32_t d, int stream_rows)
+{
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const uint32_t j = base + 4 * (threadIdx.x + kThreads * r);
+        if constexpr (kMode == kPassDiff)
+            gv[r] = ld4_row(grow + j, stream_rows);
+        else
+            gv[r] = load_grad4(grow, j, d);
+        xv[r] = kMode == kPassNaive ? make_float4(0.f, 0.f, 0.f, 0.f) : ld4_row(xrow + j, stream_rows);
+    }
+}
+
+// The coordinates j .. j + 3 of the vector that is compressed; under error feedback they are stored as well.
+template <bool kFull, int kMode>
+__device__ __forceinline__ void form_coordinates(float (&x)[4], const float4 &g, const float4 &old, uint32_t j, uint32_t d,
+                                                 const KeptTest &kt, const SelKey &sk_prev, float *__restrict__ xrow)
+{
+    const float gg[4] = {g.x, g.y, g.z, g.w};
+    const float xo[4] = {old.x, old.y, old.z, old.w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        if (kMode == kPassNaive) {
+            x[c] = (kFull || j + c < d) ? gg[c] : 0.f;
+        } else if (kMode != kPassEf) {
+            x[c] = (kFull || j + c < d) ? fsub(gg[c], xo[c]) : 0.f;
+        } else {
+            // e = x_old - C(x_old): +0 where the previous step kept the coordinate
+            const float e = was_kept(kt, sel_key(sk_prev, xo[c], j + c), j + c) ? 0.f : xo[c];
+            x[c] = (kFull || j + c < d) ? fadd(gg[c], e) : 0.f;
+        }
+    }
+    if (kMode == kPassEf) st4_stream(xrow + j, make_float4(x[0], x[1], x[2], x[3]));
+}
+
 template <bool kFull, int kMode, typename G>
 __device__ __forceinline__ uint32_t pass1_tile(const G *__restrict__ grow, float *__restrict__ xrow,
                                                uint32_t base, uint32_t d, const KeptTest &kt, uint32_t guess,
@@ -422,35 +460,13 @@ __device__ __forceinline__ uint32_t pass1_tile(const G *__restrict__ grow, float
 {
     const int tid = threadIdx.x;
     float4 gv[4], xv[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const uint32_t j = base + 4 * (tid + kThreads * r);
-        if constexpr (kMode == kPassDiff)
-            gv[r] = ld4_row(grow + j, stream_rows);
-        else
-            gv[r] = load_grad4(grow, j, d);
-        xv[r] = kMode == kPassNaive ? make_float4(0.f, 0.f, 0.f, 0.f) : ld4_row(xrow + j, stream_rows);
-    }
+    load_pass_tile<kMode>(gv, xv, grow, xrow, base, d, stream_rows);
     uint32_t count = 0;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const uint32_t j = base + 4 * (tid + kThreads * r);
-        const float gg[4] = {gv[r].x, gv[r].y, gv[r].z, gv[r].w};
-        const float xo[4] = {xv[r].x, xv[r].y, xv[r].z, xv[r].w};
         float x[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            if (kMode == kPassNaive) {
-                x[c] = (kFull || j + c < d) ? gg[c] : 0.f;
-            } else if (kMode != kPassEf) {
-                x[c] = (kFull || j + c < d) ? fsub(gg[c], xo[c]) : 0.f;
-            } else {
-                // e = x_old - C(x_old): +0 where the previous step kept the coordinate
-                const float e = was_kept(kt, sel_key(sk_prev, xo[c], j + c), j + c) ? 0.f : xo[c];
-                x[c] = (kFull || j + c < d) ? fadd(gg[c], e) : 0.f;
-            }
-        }
-        if (kMode == kPassEf) st4_stream(xrow + j, make_float4(x[0], x[1], x[2], x[3]));
+        form_coordinates<kFull, kMode>(x, gv[r], xv[r], j, d, kt, sk_prev, xrow);
 #pragma unroll
         for (int c = 0; c < 4; ++c)
             consider<kMode == kPassEf>(x[c], j + c, base, kFull || j + c < d, guess, sk, stage, count, zeros);
@@ -512,8 +528,11 @@ constexpr bool kListDirect = (kMode == kPassEf && sizeof(G) == 4) || kMode == kP
 
 // What the listing pass knows at compile time about the keys: magnitudes (Top-k), scores (Rand-k), or nothing.  Without
 // a branch per element: step plus get_theta, us, n = 4, d = 65 536 33.5 / 32.7, n = 8, d = 2 M 89.3 / 87.9, n = 16, d = 11.2 M
-// 462 / 459, Rand-k n = 16, d = 1.2 M f16 92.5 / 90.9, naive n = 8, d = 3 M bf16 79.2 / 77.8 - but n = 8, d = 110 M 2345 / 2367:
-// the rows of tk_long_rows keep the branch.
+// 462 / 459, Rand-k n = 16, d = 1.2 M f16 92.5 / 90.9, naive n = 8, d = 3 M bf16 79.2 / 77.8.  The long rows of error feedback on
+// 32-bit gradients (tk_long_rows) keep the branch, as they want fewer workgroups per unit.  The pass alone, with / without the
+// branch, mean and range over eight shapes of 70 M to 200 M coordinates and 2 to 16 workers: Top-k with k = 0.03 % to 0.4 % 1.4 %
+// faster with it (4 % slower to 7 % faster), with 1 % equal (-2 to 1.4 %), Rand-k 0.1 % 2.6 % faster (-1.3 to 5 %), 1 % 1.7 % slower
+// (-4.5 to 0.5 %); n = 8, d = 110 M, k = 0.1 % 1652 / 1677 us.  Five shapes of 11 M to 55 M, Top-k: 0.2 % slower (-1.9 to 1.5 %).
 enum { kKeyMagnitude = 0, kKeyScore = 1, kKeyEither = 2 };
 
 // A tile listed straight from the registers.
@@ -526,34 +545,13 @@ __device__ __forceinline__ void pass1_direct(const G *__restrict__ grow, float *
 {
     const int tid = threadIdx.x, wave = tid >> 6;
     float4 gv[4], xv[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const uint32_t j = base + 4 * (tid + kThreads * r);
-        if constexpr (kMode == kPassDiff)
-            gv[r] = ld4_row(grow + j, stream_rows);
-        else
-            gv[r] = load_grad4(grow, j, d);
-        xv[r] = kMode == kPassNaive ? make_float4(0.f, 0.f, 0.f, 0.f) : ld4_row(xrow + j, stream_rows);
-    }
+    load_pass_tile<kMode>(gv, xv, grow, xrow, base, d, stream_rows);
     float x[4][4];
     uint32_t count = 0, zeros = 0, hits = 0;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const uint32_t j = base + 4 * (tid + kThreads * r);
-        const float gg[4] = {gv[r].x, gv[r].y, gv[r].z, gv[r].w};
-        const float xo[4] = {xv[r].x, xv[r].y, xv[r].z, xv[r].w};
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            if (kMode == kPassNaive) {
-                x[r][c] = (kFull || j + c < d) ? gg[c] : 0.f;
-            } else if (kMode != kPassEf) {
-                x[r][c] = (kFull || j + c < d) ? fsub(gg[c], xo[c]) : 0.f;
-            } else {
-                const float e = was_kept(kt, sel_key(sk_prev, xo[c], j + c), j + c) ? 0.f : xo[c];
-                x[r][c] = (kFull || j + c < d) ? fadd(gg[c], e) : 0.f;
-            }
-        }
-        if (kMode == kPassEf) st4_stream(xrow + j, make_float4(x[r][0], x[r][1], x[r][2], x[r][3]));
+        form_coordinates<kFull, kMode>(x[r], gv[r], xv[r], j, d, kt, sk_prev, xrow);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const bool valid = kFull || j + c < d;
