@@ -28,12 +28,11 @@ int comp_ams_set_streaming(comp_ams_t *h, int32_t rows, int32_t state);
  * Order in which the workgroups of the streaming pass take the 4096-coordinate tiles of a row, a tuning
  * aid (no effect on results).  The chip hands workgroups to its eight XCDs in turn; with chunk > 0
  * every XCD works through `chunk` consecutive tiles of each group of 8 * chunk tiles, with chunk = 0
- * consecutive tiles go to consecutive XCDs, -1 = chosen from the sizes (the default: 16 when the
- * stored rows exceed 1 GiB in total and the method keeps them - error feedback, CD-Adam - except for
- * CD-Adam's Top-k / Rand-k steps on 16-bit gradients; else 0; Top-k / Rand-k under error feedback: 0 while
- * the rows stay in the caches, else 8, or 16 for rows of 64 Mi coordinates or more; the update without
- * compression, which takes its tiles the same way: 16 from 128 tiles on).  chunk <= 65536.  May be called
- * between steps.
+ * consecutive tiles go to consecutive XCDs, -1 = chosen from the sizes (the default.  Error feedback and
+ * CD-Adam with stored rows of more than 512 MiB in total: 8, or 16 for rows of 16 Mi coordinates or more, but
+ * 0 in CD-Adam's Top-k / Rand-k steps on 16-bit gradients; Top-k / Rand-k under error feedback instead from
+ * 224 MiB of rows on: 8, or 16 for rows of 64 Mi coordinates or more; the update without compression, which
+ * takes its tiles the same way: 16 from 128 tiles on; else 0).  chunk <= 65536.  May be called between steps.
  */
 int comp_ams_set_tile_order(comp_ams_t *h, int32_t chunk);
 
@@ -42,10 +41,11 @@ int comp_ams_set_tile_order(comp_ams_t *h, int32_t chunk);
  * amount decides how many workgroups share a compute unit (160 KB each), to which the pass responds by a
  * few per cent.  -1 = chosen from the sizes, the method and the gradient type (the default), else
  * 0 .. 61440.  BLOCKSIGN: the pass always gets at least what its block table needs (24 KB when a tile
- * holds several blocks' pieces).  TOPK / RANDK: the amount is added to 24 KB (the size of the candidate
- * staging lists of a workgroup; default under error feedback with 32-bit gradients: 9 KB, or 7000 bytes
- * for rows under 64 Mi coordinates that exceed the caches; else nothing beyond what the pass uses itself);
- * no effect on vectors of at most 16 tiles.  May be called between steps.
+ * holds several blocks' pieces, but nothing for uniform blocks of 4, 8, ... 2048 coordinates).  TOPK / RANDK:
+ * the amount is added to 24 KB (the size of the candidate staging lists of a workgroup; default under error
+ * feedback with 32-bit gradients: 9 KB, or 7000 bytes for rows under 64 Mi coordinates that exceed 80 MiB in
+ * total; else nothing beyond what the pass uses itself);
+ * vectors of at most 16 tiles ignore it, but for a first step.  May be called between steps.
  */
 int comp_ams_set_pass_lds(comp_ams_t *h, int32_t bytes);
 

@@ -119,15 +119,17 @@ struct comp_ams {
 
 // What a step touches once per step - the n stored rows; theta, m, v, vhat - is accessed as a stream
 // (see ld4_row, ld4_state) when it could not stay in the 256 MB memory-side cache until the next step anyway.
-// Between two steps a training program runs a forward and a backward pass through that cache, so the line is drawn
-// where three handles stepped in turn measured it, not one handle stepped back to back (step plus get_theta, us,
-// cached / streamed, three in turn; one handle).  Rows, n = 16: error feedback Top-k 64 MB 84.4 / 85.3, 96 MB
-// 110.8 / 103.9 (104.0 / 103.5), 192 MB 174.6 / 158.1 (156.0 / 157.4); blocks of 4096 64 MB 57.3 / 59.5, 96 MB 79.2 / 76.9
-// (72.9 / 77.0), 192 MB 146.2 / 133.2 (127.5 / 132.3).  State: error feedback Top-k n = 16 64 MB 200 / 199, 96 MB 277 / 271
-// (266 / 273), 160 MB 438 / 423 (412 / 417); no compression n = 8 bf16 64 MB 52 / 54, 96 MB 75 / 71 (69 / 71), 160 MB
-// 118 / 108 (99 / 107); CD-Adam, whose server vectors are read and written next to the state, Top-k n = 8 64 MB
-// 172 / 169, 96 MB 222 / 212 (201 / 195).  Under error feedback with cached rows the state streams, since it would
-// compete with them.
+// Between two steps a training program runs a forward and a backward pass through that cache.  Step plus get_theta, us,
+// cached / streamed, three handles with their own gradients in turn: rows, n = 16, blocks of 4096 64 MiB 57.3 / 59.5, 96 MiB
+// 81.5 / 77.5, 192 MiB 148.7 / 135.2, Top-k 96 MiB 112.3 / 103.2, 192 MiB 182.8 / 157.8; state, no compression n = 8 bf16 64 MiB
+// 54.1 / 55.4, 96 MiB 72.0 / 73.0, 192 MiB 137.0 / 127.0, per-layer sign n = 8 192 MiB 323.9 / 313.9, CD-Adam whole sign n = 8 96 MiB
+// 205.6 / 193.1.  Whole iterations, timed together so that what a policy leaves in the cache to be written back later counts:
+// a sweep over 384 MiB, the gradients written anew, step and get_theta (in brackets with four 4096^3 bf16 matrix products for
+// the sweep): rows 192 MiB, blocks of 4096 357 / 349 (525 / 528), Top-k 394 / 380 (576 / 570), CD-Adam whole sign n = 16 389 / 382
+// (566 / 571); state 192 MiB, no compression 360 / 359 (517 / 524), per-layer sign 617 / 621 (785 / 797), CD-Adam whole sign
+// 674 / 668 (844 / 847).  One handle stepped back to back with nothing in between is the case that pays: blocks of 4096 96 MiB
+// 73.5 / 77.9, 192 MiB 128.5 / 134.9, no compression state 192 MiB 120.4 / 128.1 (comp_ams_set_streaming takes it back).
+// Under error feedback with cached rows the state streams, since it would compete with them.
 constexpr size_t kCacheResidentBytes = (size_t)80 << 20;
 inline size_t row_bytes(const comp_ams *h) { return (size_t)h->n * (size_t)h->ld * sizeof(float); }
 inline bool rows_exceed_caches(const comp_ams *h) { return row_bytes(h) > kCacheResidentBytes; }
@@ -143,8 +145,10 @@ constexpr size_t kWithinStepBytes = (size_t)224 << 20;
 // workload: 1.63 ms at 32 KB, 1.65 ms at 24 and at 40 KB); below about a GiB of rows up to 16 KB is best (n = 16,
 // d = 1.2 M: 36.4 us, against 37.7 at 24 KB and 42.1 at 40 KB; n = 8, d = 11.2 M: 177 against 184 us).  Where many
 // tiles hold several pieces (short blocks) they pass through barriers, more workgroups per unit hide those, and
-// the table gets just what it needs (n = 16, d = 11.2 M, blocks of 256: 0.37 ms at 24 KB, 0.43 at 32 KB, 0.51 at
-// 40 KB).  The block-to-tile mapping below does not move these optima.  Gradients of 16 bits are another matter:
+// the table gets just what it needs (n = 16, d = 11.2 M, blocks of 256 by the general road, which such blocks without a
+// power of two take: 0.37 ms at 24 KB, 0.43 at 32 KB, 0.51 at 40 KB).  Short blocks of a power of two (BsTable::small_log2) have
+// no table and one barrier at most, and follow the size rule (step plus get_theta, B = 256, n = 16, d = 11.2 M: error feedback
+// 504 us at 0 to 16 KB, 483 at 32, 471 at 40; CD-Adam 492, 475, 466; d = 4 M: 194 to 199 at every amount).  The block-to-tile mapping below does not move these optima.  Gradients of 16 bits are another matter:
 // that pass issues more instructions per byte and wants the workgroups (n = 32, d = 25.6 M, bfloat16 or half:
 // 1.32 ms up to 24 KB, 1.54 ms at 32 KB, 1.83 ms at 40 KB), so it never gets more than 16 KB beyond its need.
 inline unsigned pass_lds_bytes(const comp_ams *h, bool grads16)
@@ -768,7 +772,10 @@ unsigned tk_pass_lds(const comp_ams *h)
     const unsigned lists = kListDirect<kMode, G> ? kStageBytes : 0u;
     if (h->lds_choice >= 0) return lists + (unsigned)h->lds_choice;
     if (kMode != kPassEf || sizeof(G) != 4) return 0u;
-    // five workgroups per unit for rows that exceed the caches by far and are not long (see tk_ef_chunk_for), else four
+    // five workgroups per unit for rows that stream and are not long (with chunks of 8 tiles from kWithinStepBytes on, see
+    // tk_ef_chunk_for), else four.  Four / five without chunks, step plus get_theta, us: n = 8, rows of 96 MiB 109.6 / 109.4,
+    // 128 MiB 134.4 / 132.7, 192 MiB 178.0 / 177.4; n = 16, 160 MiB 141.0 / 139.0, 216 MiB 177.0 / 175.5; with chunks of 8 the same
+    // rows take up to 1.5 % longer
     return lists + (rows_exceed_caches(h) && !tk_long_rows(h) ? 7000u : 9u * 1024u);
 }
 

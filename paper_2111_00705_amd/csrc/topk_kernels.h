@@ -16,8 +16,9 @@
 //   tk_pass1    one workgroup per (tile, worker): streams g and the stored x once and writes the new
 //               x; lists "candidates" - elements whose fine magnitude bin (top 17 bits, 0.2 % wide)
 //               is >= the worker's guess, which is the previous step's threshold minus a little
-//               slack - as (index, value) pairs, staged in LDS (value and place in the tile, 6 bytes)
-//               and appended densely to one of 32 or 64 regions of the worker (one atomic add per tile).
+//               slack - as (index, value) pairs, appended densely to one of 32 or 64 regions of the worker
+//               (one atomic add per tile): straight from registers, or staged in LDS first (value and
+//               place in the tile, 6 bytes), see kListDirect.
 //               A workgroup per tile (instead of a loop over tiles) matters: on this chip a wave
 //               that loops must wait for its stores before it can use its next loads.
 //   tk_hist     histograms of the candidates: the fine bins of the eight coarse bins from the guess's on,
@@ -302,9 +303,9 @@ __device__ __forceinline__ void block_prefix(uint32_t v, uint32_t *pre, uint32_t
 // ---------------------------------------------------------------------------------------------
 // Where candidates live.  Each worker owns ge.slices regions of ge.region_cap entries in the candidate array,
 // one after the other; tile t appends to region t mod slices, so workgroups that run at the same time
-// (neighbouring tiles) use different cursors, on different lines (kCursorStride).  Atomic adds on one cursor serialise at
-// up to a microsecond each, so a kernel of T tiles per vector lasts at least T / slices microseconds: a single long vector
-// (CD-Adam's server) takes more regions than each of many workers.  A tile takes its space with one atomic add
+// (neighbouring tiles) use different cursors, on different lines (kCursorStride).  Atomic adds on one cursor are served one
+// after the other, on a busy chip at up to a microsecond each, so a single long vector (CD-Adam's server) takes more regions
+// than each of many workers.  A tile takes its space with one atomic add
 // on the region's cursor and records {offset from the worker's first region, counts of its four wavefronts,
 // zeros} in the tile directory; inside the tile's space the candidates stand wavefront by wavefront.  The
 // order of the tiles inside a region depends on timing; nothing downstream depends on it (comp values are
@@ -371,7 +372,7 @@ __device__ __forceinline__ void take_tile_space(uint32_t count, uint32_t zeros, 
     __syncthreads();
 }
 
-// A wavefront's staged candidates in tk_pass1: the value and the coordinate's place inside the tile, 6 bytes per
+// A wavefront's staged candidates, in the passes that stage them (kListDirect names those that do not): the value and the coordinate's place inside the tile, 6 bytes per
 // entry instead of the 8 of an (index, value) pair.  With room for every coordinate of the wavefront (so the list
 // cannot overflow) a workgroup's four lists take 24 KB, and six workgroups fit a compute unit where 32 KB allowed
 // four: the passes that only read (CD-Adam, naive compression) run 3-5 % faster with the additional loads in flight.
@@ -520,7 +521,8 @@ __device__ __forceinline__ void finish_tile(const float (*stage_val)[kSub], cons
 // many, and no LDS is held.  Step plus get_theta, staged / direct, us: error feedback fp32 n = 16, d = 11.2 M 488 / 475,
 // n = 8, d = 25 M 628 / 606, d = 110 M 2433 / 2418; naive compression (held at 64 registers: eight workgroups per unit
 // where the lists allowed six) n = 8, d = 3 M bf16 83 / 80, n = 4, d = 60 M bf16 613 / 574, Rand-k n = 16, d = 6 M fp32
-// 173 / 164.  Error feedback on 16-bit gradients loses (Rand-k n = 16, d = 1.2 M f16 92.8 / 94.1, Top-k n = 16, d = 11.2 M
+// 173 / 164 (Rand-k spills one or two registers for that, and gains by it on 16 bits all the same: n = 16, d = 11.2 M f16 300
+// without the bound, 294 with it, fp32 266 / 266).  Error feedback on 16-bit gradients loses (Rand-k n = 16, d = 1.2 M f16 92.8 / 94.1, Top-k n = 16, d = 11.2 M
 // bf16 439 / 441), and CD-Adam has no pattern (n = 8: d = 11.2 M bf16 374 / 369, d = 8 M f16 with 5 % kept 384 / 389, d = 25 M
 // fp32 695 / 697): those stage.
 template <int kMode, typename G>
@@ -1237,7 +1239,7 @@ static_assert(kMaxPieces <= 2 * kResolveThreads, "two pieces per thread in the p
 constexpr int kScanUnroll = 4;    // independent loads per thread in the scans of the dense set
 constexpr int kStaged = 8192;     // elements under the first digit of Tc that are collected in LDS for the further digits
 
-// LDS of the digit search, shared by tk_resolve and tk_select.
+// LDS of the digit search, in tk_resolve and tk_small_select.
 struct ResolveLds {
     uint32_t lh[kBins2];
     uint32_t part[kResolveThreads / kWave];
@@ -1251,11 +1253,11 @@ struct ResolveLds {
 // cnt comp values that fetch(q, comp) delivers kScanUnroll at a time (comp[u] = element q[u], anything for
 // q[u] >= cnt; q ascends with u), of which the one of 1-based rank `rank` (from the top) among those that
 // carry the prefix is wanted.  Once at most kFew elements carry the prefix they are fetched and
-// ranked against each other directly.  All threads of the workgroup (256 or 1024) call this; returns Tc.
+// ranked against each other directly.  All threads of the workgroup call this; returns Tc.
 // kWholeBins: a digit whose bin holds exactly the elements still wanted ends the search with the bin's lower edge as
 // Tc - right when every element of the vector that could fall into that bin is among the cnt delivered (the
 // threshold bin of tk_compact is), wrong when the elements are only those above some bound that may cut the bin
-// (the candidate list of tk_small_pass): then the search goes on to the k-th largest comp value itself.
+// (the list of tk_small_select): then the search goes on to the k-th largest comp value itself.
 // have_first: the first digit has kFirstBits bits and its counts are in L.lh[0 .. kBinsFirst) already (with a
 // barrier after them); the first scan is not made.
 template <bool kWholeBins = true, class Fetch>
@@ -1454,7 +1456,7 @@ struct ExactLds {
     uint32_t zeros;
 };
 
-// The digits of Tc by counting over the whole vector.  All threads of the workgroup (256 or 1024) call this.
+// The digits of Tc by counting over the whole vector.  All threads of the workgroup call this.
 __device__ __forceinline__ uint64_t exact_threshold(const ExactSource &es, const TkGeom &ge, int i, ResolveLds &L)
 {
     const int tid = threadIdx.x, nt = (int)blockDim.x;
@@ -1494,7 +1496,7 @@ __device__ __forceinline__ uint64_t exact_threshold(const ExactSource &es, const
 
 // Lists the kept elements (comp >= tc) of the vector, tile by tile, as one run from the start of the worker's
 // space, and writes every tile's record.  Coordinate 4 T + c of a tile (T = 0 .. 1023) belongs to the wavefront
-// (T mod 256) / 64 of the listing pass.  All threads of the workgroup (256 or 1024) call this.
+// (T mod 256) / 64 of the listing pass.  All threads of the workgroup call this.
 __device__ __forceinline__ void list_kept(const ExactSource &es, const TkGeom &ge, int i, uint64_t tc,
                                           uint2 *__restrict__ cand, uint4 *__restrict__ tile_dir, ExactLds &E)
 {
