@@ -81,12 +81,19 @@ def test_short_blocks(B, method):
             assert rel_close(gpu.get_scales(), ora.scales, 1e-7).all(), (d, n, t)
             if method == "cd":
                 assert rel_close(gpu.get_server_scales(), ora.server_scales, 1e-7).all(), (d, n, t)
-            for i in range(n):
-                bits = np.unpackbits(gpu.get_signs(i), bitorder="little")[:d]
-                row = ora.error[i] if method == "ef" else None
-                if row is not None:
-                    assert rel_close(gpu.get_error(i), row, STATE_RTOL).all(), (d, n, t, i)
-                assert bits.size == d
+            # the messages: every sign bit with its block's scale is the oracle's compressed vector (a wrong bit is off by
+            # twice the scale), and so is the server's
+            rows = [(i, gpu.get_scales()[i], ora.compressed[i]) for i in range(n)]
+            if method == "cd":
+                rows.append((n, gpu.get_server_scales(), ora.server_compressed))
+            for who, scales, want in rows:
+                negative = np.unpackbits(gpu.get_signs(who), bitorder="little")
+                assert not negative[d:].any(), (d, n, t, who)
+                spread = np.repeat(scales, B)[:d]
+                assert rel_close(np.where(negative[:d], -spread, spread), want, 1e-7).all(), (d, n, t, who)
+            if method == "ef":
+                for i in range(n):
+                    assert rel_close(gpu.get_error(i), ora.error[i], STATE_RTOL).all(), (d, n, t, i)
         for name, got, want in (("theta", gpu.get_theta(), ora.theta), ("m", gpu.get_m(), ora.m),
                                 ("v", gpu.get_v(), ora.v), ("vhat", gpu.get_vhat(), ora.vhat)):
             assert rel_close(got, want, STATE_RTOL).all(), (name, d, n)

@@ -208,10 +208,16 @@ def test_scaled_sign_message_rebuilt_from_bits_and_scales(method):
     gpu.destroy()
 
 
-@pytest.mark.parametrize("comp,kb,method", [(P.TOPK, 300, P.METHOD_EF), (P.BLOCKSIGN, 4096, P.METHOD_EF),
-                                            (P.TOPK, 300, P.METHOD_CD), (P.BLOCKSIGN, 1000, P.METHOD_CD),
-                                            (P.RANDK, 300, P.METHOD_EF), (P.RANDK, 300, P.METHOD_CD)])
-def test_a_step_can_be_captured_in_a_graph_and_replayed(comp, kb, method):
+# one selection kernel up to 65 536 coordinates, the chain of three beyond, the update a tile per workgroup beyond 320
+# tiles; short blocks of a power of two with the server's stage in one launch (16) or three (1024)
+@pytest.mark.parametrize("comp,kb,method,d", [(comp, 300, method, d) for comp in (P.TOPK, P.RANDK)
+                                              for method in (P.METHOD_EF, P.METHOD_CD, P.METHOD_NAIVE)
+                                              for d in (30_011, 70_003)] +
+                         [(P.TOPK, 14_000, P.METHOD_EF, 1_400_003), (P.TOPK, 14_000, P.METHOD_CD, 1_400_003),
+                          (P.BLOCKSIGN, 4096, P.METHOD_EF, 30_011), (P.BLOCKSIGN, 1000, P.METHOD_CD, 30_011),
+                          (P.BLOCKSIGN, 16, P.METHOD_EF, 30_011), (P.BLOCKSIGN, 16, P.METHOD_CD, 30_011),
+                          (P.BLOCKSIGN, 1024, P.METHOD_CD, 30_011)])
+def test_a_step_can_be_captured_in_a_graph_and_replayed(comp, kb, method, d):
     """comp_ams_step allocates nothing and clears its counters in kernels, so a caller may capture it.
     The captured step is replayed several times, with fresh gradients copied into the captured buffer
     by ordinary eager work in between, and every replay is checked against the oracle.
@@ -219,8 +225,8 @@ def test_a_step_can_be_captured_in_a_graph_and_replayed(comp, kb, method):
     that number; under error feedback the deferred error memory of each replay must then be read with
     the draw of its predecessor - the same draw from the second replay on."""
     import torch
-    announce(f"graph capture comp={comp} method={method}")
-    d, n = 30_011, 4
+    announce(f"graph capture comp={comp} method={method} d={d}")
+    n = 4
     gpu = P.CompAms(d, n, comp, kb, W.BETA1, W.BETA2, W.EPS, W.LR)
     ora = O.Oracle(d, n, comp, kb, W.BETA1, W.BETA2, W.EPS, W.LR, method=method)
     gpu.set_method(method)
@@ -255,21 +261,22 @@ def test_a_step_can_be_captured_in_a_graph_and_replayed(comp, kb, method):
             assert ok.all(), f"replay {t} {name}: {np.count_nonzero(~ok)} coordinates differ"
         if method == P.METHOD_EF:
             assert np.array_equal(bits(gpu.get_error(1)), bits(ora.error[1])), t
-        else:
+        elif method == P.METHOD_CD:
             assert np.array_equal(bits(gpu.get_ghat_worker(1)), bits(ora.ghat_workers[1])), t
         if comp != P.BLOCKSIGN:
             assert np.array_equal(gpu.get_selected(2)[0], ora.selected[2]), t
     gpu.destroy()
 
 
-@pytest.mark.parametrize("comp,kb", [(P.TOPK, 300), (P.BLOCKSIGN, 1000)])
+@pytest.mark.parametrize("comp,kb,d", [(P.TOPK, 300, 30_011), (P.TOPK, 14_000, 1_400_003), (P.BLOCKSIGN, 1000, 30_011),
+                                       (P.BLOCKSIGN, 64, 30_011), (P.BLOCKSIGN, 1024, 30_011)])
 @pytest.mark.parametrize("method", [P.METHOD_EF, P.METHOD_CD])
-def test_the_cache_policy_does_not_change_results(comp, kb, method):
+def test_the_cache_policy_does_not_change_results(comp, kb, d, method):
     """comp_ams_set_streaming only picks load / store flavours: every combination, also switched between
     steps, must leave bit-identical state."""
     import torch
-    announce(f"cache policy comp={comp} method={method}")
-    d, n = 30_011, 3
+    announce(f"cache policy comp={comp} method={method} d={d}")
+    n = 3
     gs = [np.random.default_rng([77, t]).standard_normal((n, d)).astype(f32) for t in range(4)]
     ref = None
     for rows, state in ((-1, -1), (0, 0), (1, 1), (0, 1), (1, 0)):
@@ -317,7 +324,8 @@ def test_the_tile_order_does_not_change_the_uncompressed_update():
             assert all(np.array_equal(a, b) for a, b in zip(ref, out)), chunk
 
 
-@pytest.mark.parametrize("comp,kb", [(P.TOPK, 3000), (P.RANDK, 3000), (P.BLOCKSIGN, 1000), (P.BLOCKSIGN, 4096)])
+@pytest.mark.parametrize("comp,kb", [(P.TOPK, 3000), (P.RANDK, 3000), (P.BLOCKSIGN, 1000), (P.BLOCKSIGN, 4096),
+                                     (P.BLOCKSIGN, 256)])
 @pytest.mark.parametrize("method", [P.METHOD_EF, P.METHOD_CD, P.METHOD_NAIVE])
 def test_the_tile_order_does_not_change_results(comp, kb, method):
     """comp_ams_set_tile_order only permutes which workgroup takes which tile, comp_ams_set_pass_lds only
@@ -381,7 +389,8 @@ def test_probe_copy_copies_exactly_what_it_is_given(count):
 
 @pytest.mark.parametrize("method", [P.METHOD_EF, P.METHOD_CD, P.METHOD_NAIVE])
 @pytest.mark.parametrize("comp,d,kb", [(P.BLOCKSIGN, 30_011, 1000), (P.BLOCKSIGN, 4096 * 3, 4096), (P.BLOCKSIGN, 37, 100),
-                                       (P.TOPK, 30_011, 300), (P.RANDK, 5_003, 77)])
+                                       (P.BLOCKSIGN, 30_011, 16), (P.BLOCKSIGN, 5_003, 256), (P.BLOCKSIGN, 70_001, 2048),
+                                       (P.TOPK, 30_011, 300), (P.TOPK, 90_001, 900), (P.RANDK, 5_003, 77)])
 def test_packed_messages_decode_to_the_oracles_compressed_vectors(method, comp, d, kb):
     """comp_ams_pack_message: the wire form of every worker's (and, for CD-Adam, the server's) message,
     decoded on the host, is C(.) of the oracle bit for bit; its size is the paper's bit count rounded up
