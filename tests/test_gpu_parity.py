@@ -112,6 +112,21 @@ def test_topk_degenerate_inputs(case):
     gpu.destroy()
 
 
+@pytest.mark.parametrize("d", [9_001, 70_001])
+@pytest.mark.parametrize("ulps,nonzero,k", [(900, 100, 100), (900, 100, 99), (10_000, 400, 400), (900, 100, 130), (200_000, 5000, 5000)])
+def test_topk_of_denormals_keeps_no_zero_beside_them(d, ulps, nonzero, k):
+    """The smallest keys share their leading digits with the zeros, which are not listed: a digit whose listed elements are
+    all kept must not take the zeros in."""
+    announce(f"topk denormals d={d} ulps={ulps} nonzero={nonzero} k={k}")
+    rng = np.random.default_rng([d, ulps, k])
+    g = np.zeros((2, d), np.uint32)
+    for i in range(2):
+        g[i, rng.choice(d, nonzero, replace=False)] = rng.integers(1, ulps, nonzero)
+    gpu, ora = make_pair(d, 2, P.TOPK, k)
+    run_steps(gpu, ora, lambda t: g.view(f32).copy(), steps=3, tag=f"d={d} k={k}")
+    gpu.destroy()
+
+
 def test_topk_k_equal_d_is_vanilla_amsgrad_on_gpu():
     announce("topk k=d")
     n, d = 4, 6000
