@@ -434,7 +434,7 @@ __device__ __forceinline__ void load_pass_tile(float4 (&gv)[4], float4 (&xv)[4],
 // The coordinates j .. j + 3 of the vector that is compressed; under error feedback they are stored as well.
 template <bool kFull, int kMode>
 __device__ __forceinline__ void form_coordinates(float (&x)[4], const float4 &g, const float4 &old, uint32_t j, uint32_t d,
-                                                 const KeptTest &kt, const SelKey &sk_prev, float *__restrict__ xrow)
+                                                 const KeptTest &kt, const SelKey &sk_prev, float *xrow)
 {
     const float gg[4] = {g.x, g.y, g.z, g.w};
     const float xo[4] = {old.x, old.y, old.z, old.w};
