@@ -93,12 +93,13 @@ def measured_traffic(workload: str, variant, slot: str):
     have = library_fingerprint()
     if not fp or fp.group(1) != have:
         return None, f"{rel} was taken with sources {fp.group(1) if fp else 'unrecorded'}, the tree holds {have}"
-    want = KERNEL_VARIANT.get((slot, variant), "cams::" + slot)
+    want = KERNEL_VARIANT.get((slot, variant), "cams::" + slot)      # on short vectors tk_final_short runs in tk_final's slot
     section = text.split("## HBM-side traffic", 1)[-1]
     for line in section.splitlines():
         cells = [c.strip() for c in line.strip().strip("|").split("|")]
         name = cells[0].strip("`")
-        if len(cells) == 7 and (name == want or name.startswith(want + "<") or ("<" in want and name.startswith(want))):
+        if len(cells) == 7 and (name == want or name.startswith((want + "<", want + "_short<")) or
+                                ("<" in want and name.startswith(want))):
             return float(cells[6]) * 1e6, rel
     return None, f"{rel} has no row for {want}"
 

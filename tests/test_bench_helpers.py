@@ -37,6 +37,14 @@ def test_counter_bytes_come_from_the_matching_summary_or_are_null(tmp_path, monk
     assert bench.measured_traffic(w, None, "tk_pass1")[0] is None
 
 
+def test_a_short_vectors_update_is_found_in_its_summary(monkeypatch):
+    path = os.path.join(ROOT, "profiles", "cfg0_topk_n4_d65536.md")
+    fp = open(path).read().split("Library source fingerprint: `", 1)[1][:12]
+    monkeypatch.setattr(bench, "library_fingerprint", lambda: fp)
+    got, source = bench.measured_traffic("cfg0_topk_n4_d65536", "ef", "tk_final")
+    assert source == "profiles/cfg0_topk_n4_d65536.md" and got > 0
+
+
 def test_which_summary_a_run_reads():
     assert bench.run_variant("ef", "f32", False) == "ef"
     assert bench.run_variant("cd", "f32", False) == "cd"
