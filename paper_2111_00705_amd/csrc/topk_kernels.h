@@ -1607,12 +1607,11 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
     hist2[(int64_t)i * kBinsFirst + tid] = 0;
     const int s_hi = (int)w.pshift + ge.idx_bits;
     uint64_t tc = (uint64_t)w.prefix << s_hi;
-    bool zero_tail = w.whole == kZeroTail;                       // the threshold lies among zeros
     const uint4 *dir_row = tile_dir + (int64_t)i * ge.n_tiles;
     if (w.overflow2) {
         tc = exact_select(es, ge, i, cand, tile_dir, L, U.exact);
         if (tid == 0) ws[i].whole = kExact;          // for the records (comp_ams_get_selection_info)
-    } else if (zero_tail) {
+    } else if (w.whole == kZeroTail) {
         tc = zero_tail_threshold(dir_row, xs + (int64_t)i * ge.ld, ge, w.rank, L);
     } else if (w.relisted && !w.whole) {
         // Lists made anew: the elements under the prefix stand in the worker's regions among those above it.  The first
@@ -1629,10 +1628,9 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
         if (tid == regions - 1) rpre[regions] = before + mine;
         __syncthreads();
         const uint32_t cnt = rpre[regions];
-        // the bin of the smallest keys is listed without its zeros, so the lists hold every non-zero element: where they
-        // are fewer than k, the k-th largest is a zero
-        zero_tail = xs != nullptr && w.prefix == 0u && cnt < ge.k;
-        if (zero_tail)
+        if (xs != nullptr && w.prefix == 0u && cnt < ge.k)
+            // the bin of the smallest keys is listed without its zeros, so the lists hold every non-zero element:
+            // fewer than k, and the k-th largest is a zero
             tc = zero_tail_threshold(dir_row, xs + (int64_t)i * ge.ld, ge, ge.k - cnt, L);
         else {
             const SelKey sk = sel_key_of(ge.rand, ge.rand.step_now, i);
@@ -1751,10 +1749,9 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
 #pragma unroll
             for (int u = 0; u < kScanUnroll; ++u) comp[u] = q[u] < cnt ? wdense[at[u]] : 0ull;
         };
-        // the threshold bin may be the one of the smallest keys and the k-th largest lie below its listed (non-zero)
-        // elements: among the zeros
-        zero_tail = xs != nullptr && w.prefix == 0u && w.rank > cnt;
-        if (zero_tail)
+        if (xs != nullptr && w.prefix == 0u && w.rank > cnt)
+            // the threshold bin is the one of the smallest keys and the k-th largest lies below its listed
+            // (non-zero) elements: among the zeros
             tc = zero_tail_threshold(dir_row, xs + (int64_t)i * ge.ld, ge, w.rank - cnt, L);
         else {
             // The first digit below the prefix from tk_compact's counts.  Usually at most kFew elements carry it:
@@ -1851,14 +1848,16 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
             }
         }
     }
-    // Zeros are neither listed nor counted among the candidates (xs): where a bin of candidates that reaches down to key 0 is
-    // kept whole, its lower edge must not take them in.  (After a miss the whole bin was counted with its zeros.)
-    if (xs != nullptr && !w.overflow2 && !zero_tail && !(w.relisted && w.whole)) tc = max(tc, (uint64_t)1 << ge.idx_bits);
     if (w.relisted) {                                          // tk_compact was the last reader of the full histogram
         if (tid < ge.slices) cursor_b[(i * ge.slices + tid) * kCursorStride] = 0;
         for (int q = tid; q < kBins1; q += kResolveThreads) hist_full[(int64_t)i * kBins1 + q] = 0;
     }
-    if (tid == 0) finish_worker(ws, i, w, tc, ge, w.relisted != 0);
+    if (tid == 0) {
+        // Tc = 0 keeps every coordinate.  Below k = d it is the lower edge of a bin of the smallest keys whose listed elements
+        // are all kept: zeros, which are not listed then (xs), must stay out.
+        if (xs != nullptr && tc == 0 && ge.k < ge.d) tc = 1ull << ge.idx_bits;
+        finish_worker(ws, i, w, tc, ge, w.relisted != 0);
+    }
 }
 
 
