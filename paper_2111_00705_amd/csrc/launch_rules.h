@@ -6,13 +6,18 @@ namespace cams {
 
 // Whether the update of kept values takes a quarter of a tile per workgroup (tk_final_short) instead of a tile (tk_final).
 // The quarter form fills the chip and loads the state first, but each of its four wavefronts reads the lists of all n
-// workers.  Up to 320 tiles its 1280 workgroups run at once, five on a compute unit; beyond, a second round starts.  With many
-// workers the reading is what counts.  Step plus get_theta, error feedback, k = 2 %, a tile / a quarter, us: n = 2, 288 tiles
-// 56.7 / 52.6, 384 tiles 60.6 / 60.7; n = 8, 128 tiles 56.7 / 54.7, 320 tiles 78.0 / 74.1, 352 tiles 80.9 / 81.7; n = 16, 319 tiles
-// 106.7 / 104.6; n = 20, 192 tiles 87.8 / 87.9, 319 tiles 107.9 / 109.0; n = 32, 128 tiles 92.6 / 92.1, 160 tiles 105.6 / 106.9,
-// 288 tiles 130.9 / 133.9; n = 64, 64 tiles 105.6 / 106.1 (k = 0.1 % 101.0 / 98.7), 256 tiles 197.4 / 203.6.
-constexpr int kShortFinalTiles = 320, kShortFinalLists = 16 * kShortFinalTiles;
-inline bool short_final(int64_t n, int64_t n_tiles) { return n_tiles <= kShortFinalTiles && n * n_tiles <= kShortFinalLists; }
+// workers and sorts out its own row.  Up to 320 tiles its 1280 workgroups run at once, five on a compute unit; beyond, a
+// second round starts.  With many workers the reading is what counts.  Step plus get_theta, error feedback, a tile / a
+// quarter, us: Top-k, k = 2 %, n = 2, 288 tiles 56.7 / 52.6, 384 tiles 60.6 / 60.7; n = 8, 128 tiles 56.7 / 54.7, 320 tiles
+// 78.0 / 74.1, 352 tiles 80.9 / 81.7; n = 16, 319 tiles 106.7 / 104.6; k = 5 %, n = 24, 128 tiles 84.8 / 85.2, 200 tiles
+// 108.0 / 111.3; n = 32, 64 tiles 77.8 / 77.8, 128 tiles 101.1 / 102.2; n = 48, 64 tiles 98.2 / 98.4, 100 tiles 119.4 / 122.4;
+// Rand-k, k = 1 %, n = 16, 2 tiles 37.5 / 37.1; n = 48, 2 tiles 49.1 / 50.5, 16 tiles 57.0 / 56.2; n = 256, 5 tiles 133.4 / 150.2,
+// n = 1000, 5 tiles 446.6 / 514.0 (k = 0.1 % of the values 360.8 / 338.5, 2 % 395.1 / 416.5).
+constexpr int kShortFinalTiles = 320, kShortFinalWorkers = 48, kShortFinalLists = 3072;
+inline bool short_final(int64_t n, int64_t n_tiles)
+{
+    return n_tiles <= kShortFinalTiles && n <= kShortFinalWorkers && (n <= 16 || n * n_tiles <= kShortFinalLists);
+}
 
 // Grid of a kernel with one workgroup per tile (in x) under tile_of_block's mapping.
 inline unsigned grid_blocks(int64_t n_tiles, int chunk)

@@ -190,7 +190,7 @@ def test_short_vectors_of_equal_values_or_few_nonzeros(method, share):
 
 # tk_final_short / tk_final at the boundary between them; more than 64 kept values in a wavefront's quarter, more than
 # one batch of eight workers
-@pytest.mark.parametrize("tiles,n,share", [(320, 9, 0.3), (321, 9, 0.3), (320, 1, 0.001), (80, 64, 0.01), (81, 64, 0.01)])
+@pytest.mark.parametrize("tiles,n,share", [(320, 9, 0.3), (321, 9, 0.3), (320, 1, 0.001), (64, 48, 0.01), (65, 48, 0.01)])
 def test_update_of_kept_values(tiles, n, share):
     d = tiles * TILE - 3
     print(f"[case] update of kept values, {tiles} tiles n={n} share={share}", flush=True)
