@@ -366,21 +366,25 @@ constexpr int kSignBatch = 8;       // workers whose sign words are loaded toget
 
 // CD-Adam's server stage (Algorithm 1, lines 8-9): the mean of the c_i goes into ghat, w = ghat - gtilde is formed, and
 // its sign bits and piece sums are written for the second compression.  One workgroup per tile: a piece of w is summed
-// by the workgroup that holds all of it.  kWholeBlocks: every tile is exactly one block (block t); the workers' scales are
-// then formed here from the piece sums and stored, the block's scale of w is known inside the workgroup, and lines 9-16 of
-// Algorithm 1 follow at once (no bs_scale, no bs_apply).  kStreamState: theta, m, v, vhat (touched only with kWholeBlocks) and
-// ghat, which nothing else in a step reads, are loaded and stored as streams; gtilde, which bs_apply reads again, is left
-// cached until its own last store.  (Whole-vector sign, step plus get_theta: n = 8, d = 11.2 M 336.5 -> 331.8 us, n = 2,
-// d = 60 M bf16 877 -> 831; blocks of 4096, n = 8, d = 8 M 236 -> 226.)
+// by the workgroup that holds all of it.  kFusedScale: every tile lies inside one block of at most kMaxFusedPieces
+// pieces; the workers' scales are then formed here from the partial sums (and stored by the tile at the block's
+// start).  kStreamState: theta, m, v, vhat (touched only with whole_blocks) and ghat, which nothing else in a step reads, are
+// loaded and stored as streams; gtilde, which bs_apply reads again, is left cached until its own last store.  (Whole-vector
+// sign, step plus get_theta: n = 8, d = 11.2 M 336.5 -> 331.8 us, n = 2, d = 60 M bf16 877 -> 831; blocks of 4096, n = 8,
+// d = 8 M 236 -> 226.)
 struct BsMarkov {
     float *ghat;            // [ld] the server's aggregate
-    float *gtil;            // [ld] gtilde of the step before (rewritten only by the variants that apply the message)
+    float *gtil;            // [ld] gtilde of the step before (rewritten here only when whole_blocks is set)
     uint16_t *signs;        // [n_tiles][256] sign bits of w
     double *partial;        // [n_pieces] piece sums of |w|
     float *scales;          // [n_blocks] scales of the server's message
+    int32_t whole_blocks;   // every tile is exactly one block: the block's scale of w is known inside the
+                            // workgroup, so lines 9-16 of Algorithm 1 follow at once (no bs_scale, no bs_apply).  Set
+                            // where kFusedScale is; known at compile time, with the LDS that such tiles do not need left
+                            // out, bs_server took longer (blocks of 4096, n = 8, d = 8 M 68.4 -> 72.1 us)
 };
 
-template <bool kWholeBlocks, bool kStreamState>
+template <bool kFusedScale, bool kStreamState>
 __global__ __launch_bounds__(kThreads) void bs_server(int64_t d, int64_t ld, int n, BsTable tb,
                                                       const double *__restrict__ partial,
                                                       float *__restrict__ scales,
@@ -391,8 +395,8 @@ __global__ __launch_bounds__(kThreads) void bs_server(int64_t d, int64_t ld, int
 {
     __shared__ float s_lds[kScaleChunk];
     __shared__ double scratch[4];
-    __shared__ float absx[kWholeBlocks ? 1 : kTile];        // piece_sums of the server's vector
-    __shared__ uint16_t bound[kWholeBlocks ? 1 : kTile];    // piece ends of a tile where several blocks meet
+    __shared__ float absx[kTile];                    // piece_sums of the server's vector
+    __shared__ uint16_t bound[kTile];                // piece ends of a tile where several blocks meet
     const int t = blockIdx.x;
     const int tid = threadIdx.x;
     const int64_t base = (int64_t)t * kTile;
@@ -409,32 +413,47 @@ __global__ __launch_bounds__(kThreads) void bs_server(int64_t d, int64_t ld, int
 #pragma unroll
     for (int u = 0; u < kSignBatch; ++u) bits[u] = (u < n) ? srow[u * sstride] : 0u;
 
-    int p0 = t, p1 = t + 1, b_single = t;
-    if (!kWholeBlocks) {
-        if (tb.uniform_tiles > 0) {
-            b_single = t / tb.uniform_tiles;
-        } else {
-            p0 = tb.tile_piece0[t];
-            p1 = tb.tile_piece0[t + 1];
-            b_single = tb.piece_blk[p0];
-        }
+    int p0, p1, b_single;
+    if (tb.uniform_tiles > 0) {
+        p0 = t;
+        p1 = t + 1;
+        b_single = t / tb.uniform_tiles;
+    } else {
+        p0 = tb.tile_piece0[t];
+        p1 = tb.tile_piece0[t + 1];
+        b_single = tb.piece_blk[p0];
     }
-    const bool single = kWholeBlocks || (p1 - p0 == 1);
-    const double len = (double)min((int64_t)kTile, d - base);       // of the tile's block, where it is the tile
+    const bool single = kFusedScale || (p1 - p0 == 1);
 
     if (single) {
+        int q0 = 0, q1 = 0;
+        double len = 1.0;
+        if (kFusedScale) {
+            if (tb.uniform_tiles > 0) {
+                q0 = b_single * tb.uniform_tiles;
+                q1 = min(q0 + tb.uniform_tiles, n_tiles);
+                len = (double)min((int64_t)tb.uniform_tiles * kTile, d - (int64_t)q0 * kTile);
+            } else {
+                q0 = tb.block_piece0[b_single];
+                q1 = tb.block_piece0[b_single + 1];
+                len = (double)(tb.offsets[b_single + 1] - tb.offsets[b_single]);
+            }
+        }
         for (int c0 = 0; c0 < n; c0 += kScaleChunk) {
             const int cn = min(kScaleChunk, n - c0);
             __syncthreads();
             // one thread per worker: the scale of this tile's block
             for (int u = tid; u < cn; u += kThreads) {
-                const int64_t i = c0 + u;
+                const int i = c0 + u;
                 float s;
-                if (kWholeBlocks) {
-                    s = (float)(partial[i * tb.n_pieces + t] / len);
-                    scales[i * tb.n_blocks + t] = s;
+                if (kFusedScale) {
+                    const double *prow = partial + (int64_t)i * tb.n_pieces;
+                    double S = 0.0;
+                    for (int q = q0; q < q1; ++q) S += prow[q];
+                    s = (float)(S / len);
+                    if (q0 == p0) scales[(int64_t)i * tb.n_blocks + b_single] = s;   // this tile starts the block
                 } else {
-                    s = scales[i * tb.n_blocks + b_single];
+                    s = scales[(int64_t)i * tb.n_blocks + b_single];
                 }
                 s_lds[u] = s;
             }
@@ -498,7 +517,7 @@ __global__ __launch_bounds__(kThreads) void bs_server(int64_t d, int64_t ld, int
     }
     mk.signs[(int64_t)t * kThreads + tid] = (uint16_t)sign_bits;
     __syncthreads();   // s_lds readers are done before scratch is used (separate arrays; keeps phases apart)
-    if constexpr (!kWholeBlocks) {
+    if (!mk.whole_blocks) {
         piece_sums(w, base, p0, p1, tb, scratch, absx, bound, mk.partial, mk.scales);
         return;
     }
@@ -509,8 +528,9 @@ __global__ __launch_bounds__(kThreads) void bs_server(int64_t d, int64_t ld, int
 #pragma unroll
         for (int c = 0; c < 4; ++c) a64 += (double)fabsf(w[r][c]);
     const double S = block_sum(a64, scratch);
-    const float s = (float)(S / len);
-    if (tid == 0) mk.scales[t] = s;
+    const double blen = (double)min((int64_t)kTile, d - base);
+    const float s = (float)(S / blen);
+    if (tid == 0) mk.scales[b_single] = s;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int64_t j = base + 4 * (tid + kThreads * r);

@@ -669,7 +669,7 @@ int step_blocksign_cd(comp_ams *h, const G *g, hipStream_t st)
     if (tb.small_log2 > 0 && tb.small_log2 <= 8) {
         // blocks inside a wavefront: lines 8-16 in one launch
         launch_timed(h, P_BS_SERVER, st, [&] {
-            const BsMarkov mk{h->ghat_srv, h->gtil, h->signs_srv, h->partial_srv, h->scales_srv};
+            const BsMarkov mk{h->ghat_srv, h->gtil, h->signs_srv, h->partial_srv, h->scales_srv, 1};
             launch_update<kBlocksShort, true>(h, st, h->params, mk);
         });
         h->pending = true;
@@ -683,7 +683,7 @@ int step_blocksign_cd(comp_ams *h, const G *g, hipStream_t st)
             KLAUNCH_LDS((bs_scale), dim3(tb.n_scale_list, h->n), scale_threads(h), scale_lds(h), st, h->partial, tb, h->scales);
         });
     launch_timed(h, P_BS_SERVER, st, [&] {
-        const BsMarkov mk{h->ghat_srv, h->gtil, h->signs_srv, h->partial_srv, h->scales_srv};
+        const BsMarkov mk{h->ghat_srv, h->gtil, h->signs_srv, h->partial_srv, h->scales_srv, whole ? 1 : 0};
         if (whole)
             by_flag(h->params.stream_state, [&](auto ss) {
                 KLAUNCH((bs_server<true, decltype(ss)::value>), ugrid, kThreads, st, h->d, h->ld,

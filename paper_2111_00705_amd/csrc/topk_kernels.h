@@ -40,7 +40,7 @@
 // The candidate regions are bounded (see region_base): a region that fills up is detected, and the step then
 // goes the way of a guess that was too high (whole-vector count, lists made anew) and, if the lists still do not
 // fit, selects without lists inside tk_resolve (exact_select).  In vectors of at most 16 tiles one kernel
-// (tk_small_select) takes the place of tk_hist, tk_compact and tk_resolve.
+// (tk_small_select) takes the place of tk_hist, tk_compact and tk_resolve, but for a first step beyond four tiles.
 //
 // Exact zeros under error feedback: when fewer than k coordinates are non-zero the k-th largest is a zero and
 // zeros are selected by lower index.  They are never listed as candidates (millions of equal keys would be);
@@ -372,13 +372,11 @@ __device__ __forceinline__ void take_tile_space(uint32_t count, uint32_t zeros, 
     __syncthreads();
 }
 
-// A wavefront's staged candidates, in the passes that stage them (kListDirect names those that do not): the value and the coordinate's place inside the tile, 6 bytes per
-// entry instead of the 8 of an (index, value) pair.  With room for every coordinate of the wavefront (so the list
-// cannot overflow) a workgroup's four lists take 24 KB, and six workgroups fit a compute unit where 32 KB allowed
-// four: the passes that only read (CD-Adam, naive compression) run 3-5 % faster with the additional loads in flight.
-// (Staging the places alone and reading the values again when the list is copied out - possible where the vector is
-// g itself, naive compression - was built: eight workgroups per unit, and slower, n = 16, d = 11.2 M 158 -> 202 us:
-// the scattered re-reads cost more than the workgroups bring.)
+// A wavefront's staged candidates, in the passes that stage them (all but those kListDirect names): the value and the
+// coordinate's place inside the tile, 6 bytes per entry instead of the 8 of an (index, value) pair.  With room for every
+// coordinate of the wavefront (so the list cannot overflow) a workgroup's four lists take 24 KB, and six workgroups fit a
+// compute unit where 32 KB allowed four: CD-Adam's passes, which only read, run 3-5 % faster with the additional loads in
+// flight.
 struct Stage {
     float *val;          // [kSub]
     uint16_t *at;        // [kSub] index - first index of the tile
@@ -475,7 +473,7 @@ __device__ __forceinline__ uint32_t pass1_tile(const G *__restrict__ grow, float
     return count;
 }
 
-// End of a tile in tk_pass1.  No workgroup barrier: a wavefront that is done registers itself, and
+// End of a tile whose candidates are staged.  No workgroup barrier: a wavefront that is done registers itself, and
 // whichever of the four comes last does the rest for the whole tile - takes the tile's space in its
 // region (one atomic add), writes the directory record and copies all staged candidates.  The other
 // three leave at once instead of waiting for the atomic.
