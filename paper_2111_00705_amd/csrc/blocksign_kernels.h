@@ -228,16 +228,17 @@ __global__ __launch_bounds__(kThreads) void bs_pass(const G *__restrict__ g, flo
     const int p0 = uni ? t : tb.tile_piece0[t], p1 = uni ? t + 1 : tb.tile_piece0[t + 1];
     const float *sp = s_prev + (int64_t)i * tb.n_blocks;
 
-    float4 gv[4], xv[4];
+    GradRaw<G> gv[4];
+    float4 xv[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int64_t j = base + 4 * (tid + kThreads * r);
         // The stored row goes first, except with short blocks.  The pass alone, n = 16, d = 11.2 M, gradients first / row first,
         // us: blocks of 100 400 / 396, 200 385 / 380, 1000 374 / 367, bf16 blocks of 100 415 / 408; 62 layers, n = 8 188.5 / 186.7;
         // short blocks of 16 371 / 380, of 256 353 / 360
-        if (kSmall) gv[r] = load_grad4(grow, j, d);
+        if (kSmall) gv[r] = load_raw4<false>(grow, j, d);
         xv[r] = kMode == kBsNaive ? make_float4(0.f, 0.f, 0.f, 0.f) : ld4_row(xrow + j, tb.stream_rows);
-        if (!kSmall) gv[r] = load_grad4(grow, j, d);
+        if (!kSmall) gv[r] = load_raw4<false>(grow, j, d);
     }
     uint16_t *word = signs + ((int64_t)i * (ld / kTile) + t) * kThreads + tid;
     const uint32_t old_bits = (kMode == kBsCd && kPending) ? (uint32_t)*word : 0u;   // sign bits of the pending c_i
@@ -258,7 +259,8 @@ __global__ __launch_bounds__(kThreads) void bs_pass(const G *__restrict__ g, flo
     for (int r = 0; r < 4; ++r) {
         const int64_t j = base + 4 * (tid + kThreads * r);
         const int l0 = 4 * (tid + kThreads * r);
-        const float gg[4] = {gv[r].x, gv[r].y, gv[r].z, gv[r].w};
+        const float4 g4 = widen4(gv[r]);
+        const float gg[4] = {g4.x, g4.y, g4.z, g4.w};
         const float xx[4] = {xv[r].x, xv[r].y, xv[r].z, xv[r].w};
         float keep[4];     // what goes back to the stored vector
         if (kSmall) s_single = s_row[r];
@@ -875,11 +877,12 @@ __global__ __launch_bounds__(kThreads) void bs_pass_update(const G *__restrict__
     const int i = blockIdx.y - 4;
     const G *grow = g + (int64_t)i * d;
     float *xrow = xs + (int64_t)i * ld;
-    float4 gv[4], xv[4];
+    GradRaw<G> gv[4];
+    float4 xv[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int64_t j = base + 4 * (tid + kThreads * r);
-        gv[r] = load_grad4(grow, j, d);
+        gv[r] = load_raw4<false>(grow, j, d);
         xv[r] = ld4_row(xrow + j, tb.stream_rows);
     }
     const float s_prev = kPending ? fused_block_scale(df.partial_prev + (int64_t)i * tb.n_pieces, b, tb, n_tiles, d) : 0.f;
@@ -889,7 +892,8 @@ __global__ __launch_bounds__(kThreads) void bs_pass_update(const G *__restrict__
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int64_t j = base + 4 * (tid + kThreads * r);
-        const float gg[4] = {gv[r].x, gv[r].y, gv[r].z, gv[r].w};
+        const float4 g4 = widen4(gv[r]);
+        const float gg[4] = {g4.x, g4.y, g4.z, g4.w};
         const float xx[4] = {xv[r].x, xv[r].y, xv[r].z, xv[r].w};
 #pragma unroll
         for (int c = 0; c < 4; ++c) {

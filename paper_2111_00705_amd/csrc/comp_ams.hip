@@ -148,21 +148,23 @@ constexpr size_t kWithinStepBytes = (size_t)224 << 20;
 // the table gets just what it needs (n = 16, d = 11.2 M, blocks of 256 by the general road, which such blocks without a
 // power of two take: 0.37 ms at 24 KB, 0.43 at 32 KB, 0.51 at 40 KB).  Short blocks of a power of two (BsTable::small_log2) have
 // no table and one barrier at most, and follow the size rule (step plus get_theta, B = 256, n = 16, d = 11.2 M: error feedback
-// 504 us at 0 to 16 KB, 483 at 32, 471 at 40; CD-Adam 492, 475, 466; d = 4 M: 194 to 199 at every amount).  The block-to-tile mapping below does not move these optima.  Gradients of 16 bits are another matter:
-// that pass issues more instructions per byte and wants the workgroups (n = 32, d = 25.6 M, bfloat16 or half:
-// 1.32 ms up to 24 KB, 1.54 ms at 32 KB, 1.83 ms at 40 KB), so it never gets more than 16 KB beyond its need.
+// 504 us at 0 to 16 KB, 483 at 32, 471 at 40; CD-Adam 492, 475, 466; d = 4 M: 194 to 199 at every amount).  The block-to-tile mapping below does not move these optima.  Gradients of 16
+// bits want 32 KB where their rows are shorter than 16 Mi coordinates (step plus get_theta, us, 16 / 32 / 40 KB, chunks of 16
+// tiles: bfloat16, n = 16, d = 11.2 M, 62 layers 405 / 390 / 399, blocks of 256 431 / 414 / 409) and the same as fp32 beyond
+// (n = 32, d = 25.6 M, 161 layers 1595 / 1536 / 1535, half precision, blocks of 4096 1627 / 1550 / 1501; CD-Adam, n = 16,
+// d = 25.6 M, 161 layers 1016 / 982 / 1021).
+inline bool rows_span_chunks(const comp_ams *h) { return h->d >= ((int64_t)16 << 20); }   // see xcd_chunk_for
 inline unsigned pass_lds_bytes(const comp_ams *h, bool grads16)
 {
     const unsigned need = h->has_split_tiles && !h->tb.small_log2 ? kPassTileLds : 0u;
     if (h->lds_choice >= 0) return std::max(need, (unsigned)h->lds_choice);
     if (h->mostly_split_tiles && !h->tb.small_log2) return need;
-    if (grads16) return std::max(need, 16u * 1024u);
     // (with the tile order of xcd_chunk_for the larger amount pays from about half a GiB of rows: n = 16, d = 11.2 M
     // 354 against 358-360 us, n = 8, d = 25.6 M 393-395 against 410 us)
     const bool far_beyond_caches = (size_t)h->n * h->ld * sizeof(float) > ((size_t)512 << 20);
     // naive compression reads g only and wants the workgroups as well (n = 32, d = 25.6 M: 0.55 ms up to 24 KB,
     // 0.66 ms at 32 KB, 0.78 ms at 40 KB)
-    const unsigned large = h->method == COMP_AMS_METHOD_EF ? 40u * 1024u
+    const unsigned large = h->method == COMP_AMS_METHOD_EF ? (grads16 && !rows_span_chunks(h) ? 32u : 40u) * 1024u
                            : h->method == COMP_AMS_METHOD_CD ? 32u * 1024u : 16u * 1024u;
     return std::max(need, far_beyond_caches ? large : 16u * 1024u);
 }
@@ -174,7 +176,7 @@ inline unsigned pass_lds_bytes(const comp_ams *h, bool grads16)
 // 715 MB (n = 16, d = 11.2 M) gain nothing (+-1 %), rows that stay cached lose 4-20 % (the few tiles of a short
 // row then also fall on few XCDs), and the kernels with one workgroup per tile (the updates) do not respond.
 // CD-Adam's passes gain 0.5-2 %; naive compression (g only) gains nothing or loses 0.5-3 %, and so does the
-// Top-k pass with 16-bit gradients (block sign with 16-bit gradients gains 2 %): those keep the plain order.
+// Top-k pass of CD-Adam with 16-bit gradients (block sign with 16-bit gradients gains 2 %): those keep the plain order.
 // Rows of 11 M coordinates, half a GiB to 1.5 GiB in all, do gain 1-3 % with chunks of 8 tiles once the pass runs
 // three workgroups per unit (block sign, n = 16: 354 against 358 us; n = 32: 697 against 709 us with chunks of 16;
 // Top-k under CD-Adam, n = 16: 254 against 257 us), so shorter rows get 8 from half a GiB on.
@@ -182,7 +184,7 @@ inline int xcd_chunk_for(const comp_ams *h)
 {
     if (h->method != COMP_AMS_METHOD_EF && h->method != COMP_AMS_METHOD_CD) return 0;
     if ((size_t)h->n * h->ld * sizeof(float) <= ((size_t)512 << 20)) return 0;
-    return h->d < ((int64_t)16 << 20) ? 8 : 16;
+    return rows_span_chunks(h) ? 16 : 8;
 }
 
 // The error-feedback listing pass of Top-k / Rand-k on 32-bit gradients has its own optimum, which goes with the
@@ -215,15 +217,24 @@ inline void apply_streaming(comp_ams *h)
     h->params.stream_state = h->state_choice < 0 ? ((state_exceeds_caches(h) || rows_cached) ? 1 : 0) : h->state_choice;
 }
 
-// Geometry handed to tk_pass1 for gradients of type G: with 16-bit gradients the automatic tile order is the
-// plain one unless the method is error feedback (n = 8, d = 110 M, bfloat16: error feedback 1.44 -> 1.38 ms with
-// chunks of 16, CD-Adam 1.09 -> 1.10 ms); a caller's choice holds for every type.
+// What the streaming passes are launched with for gradients of type G; a caller's choice of the tile order holds for every
+// type.  Top-k with 16-bit gradients: chunks of 8 under error feedback, whatever the length (step plus get_theta, us, no
+// chunks / 8 / 16: bfloat16, n = 16, d = 11.2 M 412.7 / 408.9 / 416.4, n = 8, d = 110 M 2134 / 2084 / 2098; half precision n = 4,
+// d = 50 M 671 / 663 / 668), the plain order otherwise (CD-Adam n = 8, d = 110 M 1.09 against 1.10 ms).  Block sign with 16-bit
+// gradients: chunks of 16, whatever the length (see pass_lds_bytes: n = 16, d = 11.2 M, 62 layers 397 with 8, 390 with 16).
 template <typename G>
 inline TkGeom pass_geometry(const comp_ams *h)
 {
     TkGeom ge = h->ge;
-    if (sizeof(G) == 2 && h->chunk_choice < 0 && h->method != COMP_AMS_METHOD_EF) ge.xcd_chunk = 0;
+    if (sizeof(G) == 2 && h->chunk_choice < 0 && ge.xcd_chunk) ge.xcd_chunk = h->method == COMP_AMS_METHOD_EF ? 8 : 0;
     return ge;
+}
+template <typename G>
+inline BsTable pass_table(const comp_ams *h)
+{
+    BsTable tb = h->tb;
+    if (sizeof(G) == 2 && h->chunk_choice < 0 && tb.xcd_chunk) tb.xcd_chunk = 16;
+    return tb;
 }
 
 // Top-k and Rand-k share every buffer and kernel (the key differs, see SelKey).
@@ -581,7 +592,7 @@ inline unsigned scale_lds(const comp_ams *h) { return h->long_blocks ? kScaleSta
 template <typename G>
 int step_blocksign(comp_ams *h, const G *g, hipStream_t st)
 {
-    const BsTable &tb = h->tb;
+    const BsTable tb = pass_table<G>(h);
     const dim3 grid(grid_blocks(h->ld / kTile, tb.xcd_chunk), h->n);
     const unsigned lds = sizeof(G) == 2 ? h->pass_lds16 : h->pass_lds;
     launch_timed(h, P_BS_PASS, st, [&] { by_flag(tb.small_log2 > 0, [&](auto sm) {
@@ -617,7 +628,7 @@ inline bool can_defer_blocksign(const comp_ams *h)
 template <typename G>
 int step_blocksign_deferred(comp_ams *h, const G *g, hipStream_t st)
 {
-    const BsTable &tb = h->tb;
+    const BsTable tb = pass_table<G>(h);
     const int prev = h->bs_set, cur = 1 - prev;
     const dim3 grid(grid_blocks(h->ld / kTile, tb.xcd_chunk), h->n + 4);
     const unsigned lds = sizeof(G) == 2 ? h->pass_lds16 : h->pass_lds;
@@ -654,7 +665,7 @@ int step_blocksign_deferred(comp_ams *h, const G *g, hipStream_t st)
 template <typename G>
 int step_blocksign_cd(comp_ams *h, const G *g, hipStream_t st)
 {
-    const BsTable &tb = h->tb;
+    const BsTable tb = pass_table<G>(h);
     const dim3 grid(grid_blocks(h->ld / kTile, tb.xcd_chunk), h->n);
     const unsigned ugrid = (unsigned)(h->ld / kTile);
     const unsigned lds = sizeof(G) == 2 ? h->pass_lds16 : h->pass_lds;
@@ -763,15 +774,17 @@ void launch_final(comp_ams *h, hipStream_t st)
 // that only read want as many as fit (staging: n = 16, d = 11.2 M, CD-Adam: 245 us with the six that the lists allow,
 // 257 with four; n = 8, d = 110 M: 1.134 against 1.173 ms).  The error-feedback pass, which also writes the row back,
 // is best with four or five on 32-bit gradients (n = 8, d = 110 M: step plus get_theta 2418 us, 2487 with seven) and
-// gets 9 KB, which leaves four (five for shorter rows, see tk_ef_chunk_for); on 16-bit gradients it issues more
-// instructions per byte and wants the six as well (same shape, bfloat16, the pass alone: 1.44 against 1.76 ms).
+// gets 9 KB, which leaves four (five for shorter rows, see tk_ef_chunk_for).  On 16-bit gradients it wants four as well where
+// the rows are taken in chunks, and does not respond below (step plus get_theta, six / four, us: bfloat16, n = 16, d = 11.2 M
+// 419 / 408, n = 8, d = 110 M 2182 / 2112, d = 11.2 M 265.5 / 262.8; n = 16, d = 5 M 216 / 216; three: 430 and 2141).
 // comp_ams_set_pass_lds overrides.
 template <int kMode, typename G>
 unsigned tk_pass_lds(const comp_ams *h)
 {
     const unsigned lists = kListDirect<kMode, G> ? kStageBytes : 0u;
     if (h->lds_choice >= 0) return lists + (unsigned)h->lds_choice;
-    if (kMode != kPassEf || sizeof(G) != 4) return 0u;
+    if (kMode != kPassEf) return 0u;
+    if (sizeof(G) == 2) return row_bytes(h) > kWithinStepBytes ? 9u * 1024u : 0u;
     // five workgroups per unit for rows that stream and are not long (with chunks of 8 tiles from kWithinStepBytes on, see
     // tk_ef_chunk_for), else four.  Four / five without chunks, step plus get_theta, us: n = 8, rows of 96 MiB 109.6 / 109.4,
     // 128 MiB 134.4 / 132.7, 192 MiB 178.0 / 177.4; n = 16, 160 MiB 141.0 / 139.0, 216 MiB 177.0 / 175.5; with chunks of 8 the same

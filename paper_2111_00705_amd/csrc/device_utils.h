@@ -81,72 +81,59 @@ __device__ __forceinline__ float4 stream_load4(const float *p)
     return make_float4(t.x, t.y, t.z, t.w);
 }
 
-// Four consecutive gradient coordinates row[j..j+3], j a multiple of 4.  The row is caller
-// memory of length d whose start may be 16-, 8- or 4-byte aligned (row i of a dense [n][d]
-// array starts at i*d floats); coordinates at or beyond d read as zero.
-__device__ __forceinline__ float4 load_grad4(const float *__restrict__ row, int64_t j, int64_t d)
-{
-    const float *p = row + j;
-    if (j + 4 <= d) return stream_load4(p);
-    float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (j < d) r.x = p[0];
-    if (j + 1 < d) r.y = p[1];
-    if (j + 2 < d) r.z = p[2];
-    if (j + 3 < d) r.w = p[3];
-    return r;
-}
-
-// Gradients handed over as bfloat16 (the upper 16 bits of the fp32 value): widened exactly, so every
-// formula downstream sees the same fp32 numbers as with an fp32 copy of them.  Rows start at any 2-byte
-// alignment.
-typedef uint32_t v2u __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ v2u stream_load_u2(const uint16_t *p)
-{
-    return __builtin_nontemporal_load(reinterpret_cast<const v2u_any *>(p));
-}
-
-__device__ __forceinline__ float bf16_to_float(uint32_t h) { return __uint_as_float(h << 16); }
-
-__device__ __forceinline__ float4 load_grad4(const uint16_t *__restrict__ row, int64_t j, int64_t d)
-{
-    const uint16_t *p = row + j;
-    if (j + 4 <= d) {
-        const v2u t = stream_load_u2(p);
-        return make_float4(__uint_as_float(t.x << 16), __uint_as_float(t.x & 0xffff0000u),
-                           __uint_as_float(t.y << 16), __uint_as_float(t.y & 0xffff0000u));
-    }
-    float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (j < d) r.x = bf16_to_float(p[0]);
-    if (j + 1 < d) r.y = bf16_to_float(p[1]);
-    if (j + 2 < d) r.z = bf16_to_float(p[2]);
-    if (j + 3 < d) r.w = bf16_to_float(p[3]);
-    return r;
-}
-
-// Gradients handed over as IEEE half precision: same layout and loads as bfloat16, widened exactly
-// by the hardware conversion.  The wrapper type only tells the two 16-bit formats apart.
-struct f16bits {
+// Gradients come as fp32, as bfloat16 (the upper 16 bits of the fp32 value) or as IEEE half precision.  16-bit values are
+// widened exactly, so every formula downstream sees the same fp32 numbers as with an fp32 copy of them.
+struct f16bits {          // only tells the two 16-bit formats apart
     uint16_t v;
 };
 static_assert(sizeof(f16bits) == 2, "f16bits is a plain 16-bit value");
 
+typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float bf16_to_float(uint32_t h) { return __uint_as_float(h << 16); }
 __device__ __forceinline__ float f16_to_float(uint32_t h) { return __half2float(__ushort_as_half((unsigned short)h)); }
 
-__device__ __forceinline__ float4 load_grad4(const f16bits *__restrict__ row, int64_t j, int64_t d)
+// Four consecutive gradient coordinates row[j..j+3] as they stand in memory, j a multiple of 4, and their fp32 values.
+// The row is caller memory of length d at any alignment of its element type (row i of a dense [n][d] array starts
+// at i*d elements); coordinates at or beyond d read as zero.  kInside: j + 4 <= d is known.
+// Loading and widening are apart so that a thread's loads all go out before it waits for the first: widened inside the
+// bounds check, each 16-bit load was waited for before the next was issued.
+template <typename G> struct GradRaw { v2u v; };
+template <> struct GradRaw<float> { v4f v; };
+
+template <bool kInside>
+__device__ __forceinline__ GradRaw<float> load_raw4(const float *__restrict__ row, int64_t j, int64_t d)
+{
+    const float *p = row + j;
+    if (kInside || j + 4 <= d) return {__builtin_nontemporal_load(reinterpret_cast<const v4f_any *>(p))};
+    v4f r = {0.f, 0.f, 0.f, 0.f};
+    if (j < d) r.x = p[0];
+    if (j + 1 < d) r.y = p[1];
+    if (j + 2 < d) r.z = p[2];
+    if (j + 3 < d) r.w = p[3];
+    return {r};
+}
+template <bool kInside, typename G>   // G: uint16_t (bfloat16 bits) or f16bits
+__device__ __forceinline__ GradRaw<G> load_raw4(const G *__restrict__ row, int64_t j, int64_t d)
 {
     const uint16_t *p = reinterpret_cast<const uint16_t *>(row) + j;
-    if (j + 4 <= d) {
-        const v2u t = stream_load_u2(p);
-        return make_float4(f16_to_float(t.x & 0xffffu), f16_to_float(t.x >> 16), f16_to_float(t.y & 0xffffu),
-                           f16_to_float(t.y >> 16));
-    }
-    float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (j < d) r.x = f16_to_float(p[0]);
-    if (j + 1 < d) r.y = f16_to_float(p[1]);
-    if (j + 2 < d) r.z = f16_to_float(p[2]);
-    if (j + 3 < d) r.w = f16_to_float(p[3]);
-    return r;
+    if (kInside || j + 4 <= d) return {__builtin_nontemporal_load(reinterpret_cast<const v2u_any *>(p))};
+    v2u r = {0u, 0u};
+    if (j < d) r.x = p[0];
+    if (j + 1 < d) r.x |= (uint32_t)p[1] << 16;
+    if (j + 2 < d) r.y = p[2];
+    if (j + 3 < d) r.y |= (uint32_t)p[3] << 16;
+    return {r};
+}
+__device__ __forceinline__ float4 widen4(const GradRaw<float> &r) { return make_float4(r.v.x, r.v.y, r.v.z, r.v.w); }
+__device__ __forceinline__ float4 widen4(const GradRaw<uint16_t> &r)
+{
+    return make_float4(__uint_as_float(r.v.x << 16), __uint_as_float(r.v.x & 0xffff0000u), __uint_as_float(r.v.y << 16),
+                       __uint_as_float(r.v.y & 0xffff0000u));
+}
+__device__ __forceinline__ float4 widen4(const GradRaw<f16bits> &r)
+{
+    return make_float4(f16_to_float(r.v.x & 0xffffu), f16_to_float(r.v.x >> 16), f16_to_float(r.v.y & 0xffffu),
+                       f16_to_float(r.v.y >> 16));
 }
 
 __device__ __forceinline__ float4 ld4(const float *p) { return *reinterpret_cast<const float4 *>(p); }

@@ -7,8 +7,8 @@
 // times as many workgroups, so a short vector fills the chip.  Against four float4 per thread with the loads of
 // four workers in flight (three sets of buffers in turn, us): n = 16, d = 11.2 M bf16 172 -> 125, fp32 188 -> 182;
 // n = 32, d = 25.6 M bf16 529 -> 425, fp32 734 -> 725; n = 8, d = 110 M bf16 912 -> 888, fp32 1.25 -> 1.23 ms;
-// n = 16, d = 1.2 M bf16 49 -> 22, fp32 33 -> 24.  Batches of 2 to 16 rows in flight lose up to 10 % on fp32 and gain
-// nothing on 16 bits; eight 16-bit gradients per lane (16-byte loads) take twice as long, because the state is then
+// n = 16, d = 1.2 M bf16 49 -> 22, fp32 33 -> 24.  Batches of 2 to 16 rows in flight lose up to 10 % on fp32 (16 bits:
+// see sum_rows); eight 16-bit gradients per lane (16-byte loads) take twice as long, because the state is then
 // written in half lines.
 #pragma once
 #include "device_utils.h"
@@ -16,6 +16,32 @@
 namespace cams {
 
 constexpr int kPlainCoords = 4 * kThreads;   // coordinates per workgroup: a quarter of a tile
+
+// acc += the coordinates j .. j + 3 of the n rows, in ascending order.  16-bit rows are loaded two at a time: step plus
+// get_theta, one / two / four at a time, us: n = 16, bf16 d = 1.2 M 39.7 / 38.3 / 38.0, d = 11.2 M 152.0 / 149.6 / 155.2; n = 4, f16
+// d = 50 M 408.6 / 411.0 / 416.7.
+template <bool kInside, typename G>
+__device__ __forceinline__ void sum_rows(float4 &acc, const G *__restrict__ row, int64_t j, int64_t d, int n)
+{
+    auto add = [&](const float4 &x) {
+        acc.x = fadd(acc.x, x.x);
+        acc.y = fadd(acc.y, x.y);
+        acc.z = fadd(acc.z, x.z);
+        acc.w = fadd(acc.w, x.w);
+    };
+    constexpr int kAhead = sizeof(G) == 2 ? 2 : 1;
+    int i = 0;
+#pragma unroll 1
+    for (; i + kAhead <= n; i += kAhead, row += kAhead * d) {
+        GradRaw<G> x[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) x[u] = load_raw4<kInside>(row + u * d, j, d);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) add(widen4(x[u]));
+    }
+#pragma unroll 1
+    for (; i < n; ++i, row += d) add(widen4(load_raw4<kInside>(row, j, d)));
+}
 
 template <typename G, bool kStreamState>   // G: float, uint16_t (bfloat16 bits) or f16bits
 __global__ __launch_bounds__(kThreads) void plain_update(const G *__restrict__ g, int64_t d, int n,
@@ -27,18 +53,13 @@ __global__ __launch_bounds__(kThreads) void plain_update(const G *__restrict__ g
     if (t >= n_quarters) return;
     const int64_t j = (int64_t)t * kPlainCoords + 4 * threadIdx.x;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    const G *row = g;
-#pragma unroll 1
-    for (int i = 0; i < n; ++i, row += d) {
-        const float4 x = load_grad4(row, j, d);
-        acc.x = fadd(acc.x, x.x);
-        acc.y = fadd(acc.y, x.y);
-        acc.z = fadd(acc.z, x.z);
-        acc.w = fadd(acc.w, x.w);
-    }
+    if (((int64_t)t + 1) * kPlainCoords <= d)
+        sum_rows<true>(acc, g, j, d, n);
+    else
+        sum_rows<false>(acc, g, j, d, n);
     float4 th = ld4_state<kStreamState>(theta + j), mm = ld4_state<kStreamState>(m + j),
            vv = ld4_state<kStreamState>(v + j), vh = ld4_state<kStreamState>(vhat + j);
-    // padding coordinates take no gradient (load_grad4 gives 0 past d)
+    // padding coordinates take no gradient (load_raw4 gives 0 past d)
     const float4 gbar = make_float4(fdiv(acc.x, p.n_workers), fdiv(acc.y, p.n_workers), fdiv(acc.z, p.n_workers),
                                     fdiv(acc.w, p.n_workers));
     amsgrad_update4(th, mm, vv, vh, gbar, p);

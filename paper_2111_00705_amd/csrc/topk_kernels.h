@@ -413,18 +413,21 @@ __device__ __forceinline__ void consider(float x, uint32_t j, uint32_t base, boo
 //        kPassNaive  naive compression (Section 4): x = g, the stored rows are not touched.
 enum { kPassEf = 0, kPassCd = 1, kPassDiff = 2, kPassNaive = 3 };
 
-// The gradients and the stored values of this thread's coordinates, base + 4 (tid + 256 r) + c.
-template <int kMode, typename G>
-__device__ __forceinline__ void load_pass_tile(float4 (&gv)[4], float4 (&xv)[4], const G *__restrict__ grow,
+// The gradients and the stored values of this thread's coordinates, base + 4 (tid + 256 r) + c.  kFull: the whole tile lies
+// below d.
+template <bool kFull, int kMode, typename G>
+__device__ __forceinline__ void load_pass_tile(GradRaw<G> (&gv)[4], float4 (&xv)[4], const G *__restrict__ grow,
                                                const float *__restrict__ xrow, uint32_t base, uint32_t d, int stream_rows)
 {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const uint32_t j = base + 4 * (threadIdx.x + kThreads * r);
-        if constexpr (kMode == kPassDiff)
-            gv[r] = ld4_row(grow + j, stream_rows);
-        else
-            gv[r] = load_grad4(grow, j, d);
+        if constexpr (kMode == kPassDiff) {
+            const float4 a = ld4_row(grow + j, stream_rows);
+            gv[r].v = {a.x, a.y, a.z, a.w};
+        } else {
+            gv[r] = load_raw4<kFull>(grow, j, d);
+        }
         xv[r] = kMode == kPassNaive ? make_float4(0.f, 0.f, 0.f, 0.f) : ld4_row(xrow + j, stream_rows);
     }
 }
@@ -458,14 +461,15 @@ __device__ __forceinline__ uint32_t pass1_tile(const G *__restrict__ grow, float
                                                int stream_rows, uint32_t &zeros)
 {
     const int tid = threadIdx.x;
-    float4 gv[4], xv[4];
-    load_pass_tile<kMode>(gv, xv, grow, xrow, base, d, stream_rows);
+    GradRaw<G> gv[4];
+    float4 xv[4];
+    load_pass_tile<kFull, kMode>(gv, xv, grow, xrow, base, d, stream_rows);
     uint32_t count = 0;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const uint32_t j = base + 4 * (tid + kThreads * r);
         float x[4];
-        form_coordinates<kFull, kMode>(x, gv[r], xv[r], j, d, kt, sk_prev, xrow);
+        form_coordinates<kFull, kMode>(x, widen4(gv[r]), xv[r], j, d, kt, sk_prev, xrow);
 #pragma unroll
         for (int c = 0; c < 4; ++c)
             consider<kMode == kPassEf>(x[c], j + c, base, kFull || j + c < d, guess, sk, stage, count, zeros);
@@ -544,14 +548,15 @@ __device__ __forceinline__ void pass1_direct(const G *__restrict__ grow, float *
                                              uint4 *__restrict__ tile_dir, uint32_t *overflow_flag)
 {
     const int tid = threadIdx.x, wave = tid >> 6;
-    float4 gv[4], xv[4];
-    load_pass_tile<kMode>(gv, xv, grow, xrow, base, d, stream_rows);
+    GradRaw<G> gv[4];
+    float4 xv[4];
+    load_pass_tile<kFull, kMode>(gv, xv, grow, xrow, base, d, stream_rows);
     float x[4][4];
     uint32_t count = 0, zeros = 0, hits = 0;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const uint32_t j = base + 4 * (tid + kThreads * r);
-        form_coordinates<kFull, kMode>(x[r], gv[r], xv[r], j, d, kt, sk_prev, xrow);
+        form_coordinates<kFull, kMode>(x[r], widen4(gv[r]), xv[r], j, d, kt, sk_prev, xrow);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const bool valid = kFull || j + c < d;
@@ -833,32 +838,42 @@ __device__ __forceinline__ Piece piece_of(const TkGeom &ge, const uint32_t *__re
 //   kSrcGradOnly  a = g itself (naive compression)
 enum { kSrcStored = 0, kSrcGrad = 1, kSrcDiff = 2, kSrcGradOnly = 3 };
 
-// The coordinates j .. j + 3 of vector i (j a multiple of 4).  a: for kSrcGrad / kSrcGradOnly the gradients (elements of
-// type G), else padded float rows; brow: row i of b.
+// The coordinates j .. j + 3 of vector i (j a multiple of 4) as they are stored, and their values.  a: for kSrcGrad /
+// kSrcGradOnly the gradients (elements of type G), else padded float rows; brow: row i of b.
 template <int kSrc, typename G>
-__device__ __forceinline__ float4 load_source4(const void *__restrict__ a, int i, const TkGeom &ge,
-                                               const float *__restrict__ brow, uint32_t j, uint32_t d)
-{
-    float4 av;
-    if constexpr (kSrc == kSrcGrad || kSrc == kSrcGradOnly)
-        av = load_grad4(static_cast<const G *>(a) + (int64_t)i * ge.d, j, d);
-    else
-        av = ld4(static_cast<const float *>(a) + (int64_t)i * ge.ld + j);
-    if (kSrc == kSrcGrad || kSrc == kSrcDiff) {
-        const float4 bv = ld4(brow + j);
-        av = make_float4(fsub(av.x, bv.x), fsub(av.y, bv.y), fsub(av.z, bv.z), fsub(av.w, bv.w));
+struct Source4 {
+    static constexpr bool kGrad = kSrc == kSrcGrad || kSrc == kSrcGradOnly, kTwo = kSrc == kSrcGrad || kSrc == kSrcDiff;
+    GradRaw<std::conditional_t<kGrad, G, float>> a;
+    float4 b;
+    __device__ __forceinline__ void load(const void *__restrict__ av, int i, const TkGeom &ge, const float *__restrict__ brow,
+                                         uint32_t j, uint32_t d)
+    {
+        if constexpr (kGrad) {
+            a = load_raw4<false>(static_cast<const G *>(av) + (int64_t)i * ge.d, j, d);
+        } else {
+            const float4 x = ld4(static_cast<const float *>(av) + (int64_t)i * ge.ld + j);
+            a.v = {x.x, x.y, x.z, x.w};
+        }
+        if (kTwo) b = ld4(brow + j);
     }
-    return av;
-}
+    __device__ __forceinline__ float4 value() const
+    {
+        const float4 x = widen4(a);
+        return kTwo ? make_float4(fsub(x.x, b.x), fsub(x.y, b.y), fsub(x.z, b.z), fsub(x.w, b.w)) : x;
+    }
+};
 
 // The 16 values of this thread in the tile at `base` (coordinates base + 4 (tid + 256 r) + c).
 template <int kSrc, typename G>
 __device__ __forceinline__ void load_source_tile(float (&x)[4][4], const void *__restrict__ a, int i, const TkGeom &ge,
                                                  const float *__restrict__ brow, uint32_t base, uint32_t d)
 {
+    Source4<kSrc, G> s[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s[r].load(a, i, ge, brow, base + 4 * (threadIdx.x + kThreads * r), d);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const float4 v = load_source4<kSrc, G>(a, i, ge, brow, base + 4 * (threadIdx.x + kThreads * r), d);
+        const float4 v = s[r].value();
         x[r][0] = v.x;
         x[r][1] = v.y;
         x[r][2] = v.z;
@@ -1912,14 +1927,15 @@ __device__ __forceinline__ uint32_t list_short_again(const TkGeom &ge, int i, co
     for (int q = tid; q < kBins1; q += kResolveThreads) L.lh[q] = 0;
     __syncthreads();
     for (int t0 = 0; t0 < ge.n_tiles; t0 += kShortBatch) {
-        float4 v[kShortBatch];
+        Source4<kSrc, G> v[kShortBatch];
 #pragma unroll
         for (int u = 0; u < kShortBatch; ++u)
-            if (t0 + u < ge.n_tiles) v[u] = load_source4<kSrc, G>(a, i, ge, brow, (uint32_t)(t0 + u) * kTile + 4 * tid, d);
+            if (t0 + u < ge.n_tiles) v[u].load(a, i, ge, brow, (uint32_t)(t0 + u) * kTile + 4 * tid, d);
 #pragma unroll
         for (int u = 0; u < kShortBatch; ++u) {
             if (t0 + u >= ge.n_tiles) continue;
-            const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+            const float4 v4 = v[u].value();
+            const float x[4] = {v4.x, v4.y, v4.z, v4.w};
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const uint32_t j = (uint32_t)(t0 + u) * kTile + 4 * tid + c;
@@ -1936,10 +1952,13 @@ __device__ __forceinline__ uint32_t list_short_again(const TkGeom &ge, int i, co
     for (int t0 = 0; t0 < ge.n_tiles; t0 += kShortBatch) {              // uniform over the workgroup
         float x[kShortBatch][4];
         uint32_t hits = 0, count[kShortBatch];
+        Source4<kSrc, G> s[kShortBatch] = {};
+#pragma unroll
+        for (int u = 0; u < kShortBatch; ++u)
+            if (t0 + u < ge.n_tiles) s[u].load(a, i, ge, brow, (uint32_t)(t0 + u) * kTile + 4 * tid, d);
 #pragma unroll
         for (int u = 0; u < kShortBatch; ++u) {
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (t0 + u < ge.n_tiles) v = load_source4<kSrc, G>(a, i, ge, brow, (uint32_t)(t0 + u) * kTile + 4 * tid, d);
+            const float4 v = s[u].value();
             x[u][0] = v.x;
             x[u][1] = v.y;
             x[u][2] = v.z;
@@ -2009,7 +2028,7 @@ __device__ __forceinline__ uint32_t list_short_again(const TkGeom &ge, int i, co
 }
 
 // sge: the vectors' geometry with slices = 1 and region_cap = all of a vector's space.  count: entries listed per
-// vector, kCursorStride words apart (cleared here for the next step).  a, b: how a vector is re-formed (load_source4).
+// vector, kCursorStride words apart (cleared here for the next step).  a, b: how a vector is re-formed (Source4).
 template <int kSrc, typename G>
 __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom sge, TkWorker *__restrict__ ws,
                                                                    uint2 *__restrict__ cand, uint32_t *__restrict__ count,
