@@ -236,8 +236,10 @@ __global__ __launch_bounds__(kThreads) void bs_pass(const G *__restrict__ g, flo
         // The stored row goes first, except with short blocks.  The pass alone, n = 16, d = 11.2 M, gradients first / row first,
         // us: blocks of 100 400 / 396, 200 385 / 380, 1000 374 / 367, bf16 blocks of 100 415 / 408; 62 layers, n = 8 188.5 / 186.7;
         // short blocks of 16 371 / 380, of 256 353 / 360
+        // (ld4_row<kSmall>: with short blocks the compiler had merged the two kinds of row load, and rows that should stream were
+        // read through the caches; n = 16, d = 11.2 M, step plus get_theta 462 -> 424 us with blocks of 256, 488 -> 450 of 16)
         if (kSmall) gv[r] = load_raw4<false>(grow, j, d);
-        xv[r] = kMode == kBsNaive ? make_float4(0.f, 0.f, 0.f, 0.f) : ld4_row(xrow + j, tb.stream_rows);
+        xv[r] = kMode == kBsNaive ? make_float4(0.f, 0.f, 0.f, 0.f) : ld4_row<kSmall>(xrow + j, tb.stream_rows);
         if (!kSmall) gv[r] = load_raw4<false>(grow, j, d);
     }
     uint16_t *word = signs + ((int64_t)i * (ld / kTile) + t) * kThreads + tid;

@@ -152,7 +152,21 @@ __device__ __forceinline__ void st4_stream(float *p, const float4 &v)
 // larger than the caches cannot survive from one step to the next, so they are loaded as a stream; small
 // ones (stream == 0) are loaded normally, since part of them is still cached from the step before.  (They
 // are stored as a stream in both cases: that measured faster or equal at every size.)
-__device__ __forceinline__ float4 ld4_row(const float *p, int stream) { return stream ? stream_load4(p) : ld4(p); }
+// kApart: empty asm statements keep the two loads apart where the compiler would merge them into one without the hint.
+template <bool kApart = false>
+__device__ __forceinline__ float4 ld4_row(const float *p, int stream)
+{
+    if (!kApart) return stream ? stream_load4(p) : ld4(p);
+    float4 v;
+    if (stream) {
+        asm volatile("");
+        v = stream_load4(p);
+        asm volatile("");
+    } else {
+        v = ld4(p);
+    }
+    return v;
+}
 // theta, m, v, vhat are read and written once per step: streamed when they are too large to stay in the
 // memory-side cache until the next step (AmsParams::stream_state).
 // A compile-time choice: with a run-time flag the compiler merges the two stores and drops the hint.
