@@ -191,13 +191,14 @@ inline int xcd_chunk_for(const comp_ams *h)
 // length of a row rather than with the total (one session; pass times with four workgroups per unit and no chunks /
 // the choice below): rows of 11 M coordinates, n = 8, 12, 16, 24, 32: 179 / 173, 266 / 259, 353 / 341, 527 / 513,
 // 700 / 688 us with five workgroups per unit and chunks of 8 tiles (chunks of 4, 12 or 32 lose, 16 gains half as
-// much); 25 M coordinates, n = 16: 783 / 763 us; rows of 110 M coordinates want four workgroups and chunks of 16
-// or 8 (n = 8: 1.68 ms against 1.69-1.71 ms with five; n = 4: 846-850 against 860 us).
+// much); 25 M coordinates, n = 16: 783 / 763 us; rows of 64 Mi coordinates or more want four workgroups
+// (n = 8, d = 110 M: 1.68 ms against 1.69-1.71 ms with five; n = 4: 846-850 against 860 us) and the same chunks (step plus get_theta,
+// chunks of 16 / 8, us: n = 8, d = 110 M 2375 / 2347, n = 4, d = 70 M 1000 / 998, Rand-k n = 8, d = 70 M 1523 / 1525; bfloat16 n = 8,
+// d = 110 M 2098 / 2083).
 inline bool tk_long_rows(const comp_ams *h) { return h->d >= ((int64_t)64 << 20); }
 inline int tk_ef_chunk_for(const comp_ams *h)
 {
-    if (row_bytes(h) <= kWithinStepBytes) return 0;
-    return tk_long_rows(h) ? 16 : 8;
+    return row_bytes(h) > kWithinStepBytes ? 8 : 0;
 }
 
 // Applies the caller's choices (comp_ams_set_streaming; -1 = by size) to the kernel parameters.
@@ -218,15 +219,15 @@ inline void apply_streaming(comp_ams *h)
 }
 
 // What the streaming passes are launched with for gradients of type G; a caller's choice of the tile order holds for every
-// type.  Top-k with 16-bit gradients: chunks of 8 under error feedback, whatever the length (step plus get_theta, us, no
-// chunks / 8 / 16: bfloat16, n = 16, d = 11.2 M 412.7 / 408.9 / 416.4, n = 8, d = 110 M 2134 / 2084 / 2098; half precision n = 4,
-// d = 50 M 671 / 663 / 668), the plain order otherwise (CD-Adam n = 8, d = 110 M 1.09 against 1.10 ms).  Block sign with 16-bit
+// type.  Top-k with 16-bit gradients: the plain order but for error feedback (CD-Adam n = 8, d = 110 M 1.09 against 1.10 ms;
+// error feedback, step plus get_theta, us, no chunks / 8 / 16: bfloat16, n = 16, d = 11.2 M 412.7 / 408.9 / 416.4, n = 8, d = 110 M
+// 2134 / 2084 / 2098; half precision n = 4, d = 50 M 671 / 663 / 668).  Block sign with 16-bit
 // gradients: chunks of 16, whatever the length (see pass_lds_bytes: n = 16, d = 11.2 M, 62 layers 397 with 8, 390 with 16).
 template <typename G>
 inline TkGeom pass_geometry(const comp_ams *h)
 {
     TkGeom ge = h->ge;
-    if (sizeof(G) == 2 && h->chunk_choice < 0 && ge.xcd_chunk) ge.xcd_chunk = h->method == COMP_AMS_METHOD_EF ? 8 : 0;
+    if (sizeof(G) == 2 && h->chunk_choice < 0 && h->method != COMP_AMS_METHOD_EF) ge.xcd_chunk = 0;
     return ge;
 }
 template <typename G>
