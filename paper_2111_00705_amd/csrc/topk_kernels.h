@@ -680,8 +680,9 @@ __device__ __forceinline__ void sum_kept_tile(float *acc, const TkGeom &ge, cons
                 const int w = min(wb + u, nw - 1);           // clamped: the copies past nw are not used
                 cnt[u] = wb + u < nw ? (uint32_t)__shfl((int)my_count, w, kWave) : 0u;
                 const uint32_t start = (uint32_t)__shfl((int)my_start, w, kWave);
-                e[u] = make_uint2(0u, 0u);
-                if ((uint32_t)lane < cnt[u]) e[u] = cand[worker_base(ge, w0 + w) + start + lane];
+                // no branch around the load (lanes past the list read the worker's first entry): in one, the compiler waits for
+                // each load before the next is issued
+                e[u] = cand[worker_base(ge, w0 + w) + ((uint32_t)lane < cnt[u] ? start + lane : 0u)];
             }
 #pragma unroll
             for (int u = 0; u < kFinBatch; ++u) {
