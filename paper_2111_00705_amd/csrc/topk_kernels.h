@@ -195,6 +195,45 @@ __device__ __forceinline__ bool was_kept(const KeptTest &k, uint32_t key, uint32
     return key >= k.tkey && (key > k.tkey || j <= k.tj);
 }
 
+// The first digit below the prefix of Tc (kFirstBits bits): a function of comp that does not decrease, over the elements
+// that carry the prefix.
+// Where the prefix is a fine bin (kFineShift magnitude bits open) one bit of the digit is the top open bit, and half of the
+// values that leaves go to the elements whose further open bits are all zero, by the top bits of their index; the others
+// share the rest by magnitude.  16-bit gradients have no further bits: what ties there are told apart by their index in this
+// digit already, where with the top kFirstBits open bits all of them carried the same one (tk_resolve, naive n = 8,
+// d = 3 M bf16, 12.6 -> 8.3 us; step plus get_theta 73.8 -> 71.3, CD-Adam n = 8, d = 11.2 M bf16 342.5 -> 336, naive n = 16,
+// d = 11 M f16 with 5 % kept 285 -> 279).  Elsewhere, and for scores (Rand-k), which have no ties, the digit is the top
+// kFirstBits open bits.
+struct FirstDigit {
+    int idx_bits, s_lo;         // s_lo: comp bits below the digit, when it is a run of bits
+    bool split;
+};
+constexpr uint32_t kTieBins = kBinsFirst / 4;      // per value of the top open bit
+constexpr int kTieBits = kFirstBits - 2;
+static_assert(kFineShift - 1 - kTieBits >= 0, "magnitudes of a half in kTieBins bins");
+__device__ __forceinline__ FirstDigit first_digit(const TkGeom &ge, uint32_t pshift)
+{
+    return {ge.idx_bits, (int)pshift + ge.idx_bits - kFirstBits, pshift == (uint32_t)kFineShift && !ge.rand.on};   // pshift > kFirstBits
+}
+__device__ __forceinline__ uint32_t digit_of(const FirstDigit &f, uint64_t comp)
+{
+    if (!f.split) return (uint32_t)(comp >> f.s_lo) & (uint32_t)(kBinsFirst - 1);
+    const uint32_t open = (uint32_t)(comp >> f.idx_bits) & ((1u << kFineShift) - 1u);
+    const uint32_t half = open >> (kFineShift - 1), low = open & ((1u << (kFineShift - 1)) - 1u);
+    const uint32_t inv = (uint32_t)comp & (uint32_t)((1ull << f.idx_bits) - 1ull);
+    // vectors of this selection have more than kShortBatch tiles: idx_bits > kTieBits
+    return half * 2u * kTieBins + (low == 0u ? inv >> (f.idx_bits - kTieBits) : kTieBins + ((low - 1u) >> (kFineShift - 1 - kTieBits)));
+}
+// The smallest comp of that digit under the prefix.
+__device__ __forceinline__ uint64_t digit_edge(const FirstDigit &f, uint32_t prefix, uint32_t digit)
+{
+    if (!f.split) return (((uint64_t)prefix << kFirstBits) | digit) << f.s_lo;
+    const uint32_t half = digit / (2u * kTieBins), rest = digit % (2u * kTieBins);
+    const uint32_t low = rest < kTieBins ? 0u : ((rest - kTieBins) << (kFineShift - 1 - kTieBits)) + 1u;
+    const uint64_t key = ((uint64_t)prefix << kFineShift) | (half << (kFineShift - 1)) | low;
+    return (key << f.idx_bits) | (rest < kTieBins ? (uint64_t)rest << (f.idx_bits - kTieBits) : 0ull);
+}
+
 // Finds, in a histogram held in LDS (`bins` counters, a multiple of the workgroup size), the bin
 // of the element of 1-based rank `rank` counted from the top bin downwards, and leaves
 // {bin, elements in higher bins, the bin's count} in res[0..2] for every thread (res[3] = 1 if
@@ -1112,8 +1151,7 @@ __global__ __launch_bounds__(kThreads) void tk_compact(TkGeom ge, TkWorker *__re
             ws[i].relisted = 0u;
         }
         if (whole) return;
-        // the digit of comp right below the prefix (tk_resolve's first digit)
-        const int s_lo = (int)pshift + ge.idx_bits - kFirstBits;      // pshift >= kFineShift > kFirstBits
+        const FirstDigit fd = first_digit(ge, pshift);
         const uint32_t quarter = (pc.q1 - pc.q0 + 3) / 4;
         const uint32_t w0 = min(pc.q0 + wave * quarter, pc.q1), w1 = min(w0 + quarter, pc.q1);
         const int64_t rbase = region_base(ge, i, pc.slice);
@@ -1135,7 +1173,7 @@ __global__ __launch_bounds__(kThreads) void tk_compact(TkGeom ge, TkWorker *__re
                 if (hit) {
                     const uint64_t comp = composite(key, c[u].x, ge.idx_bits);
                     out[slot] = comp;
-                    const uint32_t digit = (uint32_t)(comp >> s_lo) & (uint32_t)(kBinsFirst - 1);
+                    const uint32_t digit = digit_of(fd, comp);
                     atomicAdd(&lh2[digit], 1u);
                     atomicOr(&bits[wave][digit >> 5], 1u << (digit & 31u));
                 }
@@ -1771,13 +1809,12 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
             // The first digit below the prefix from tk_compact's counts.  Usually at most kFew elements carry it:
             // they sit in at most as many pieces, which the pieces' bitmaps name, so only those pieces are read
             // (a few hundred elements instead of the whole threshold bin) and the elements ranked directly.
-            const int s_lo = s_hi - kFirstBits;
+            const FirstDigit fd = first_digit(ge, w.pshift);
             find_rank_bin(L.lh, L.part, L.res, kBinsFirst, w.rank);          // barriers since L.lh was filled
             const uint32_t digit = L.res[0], left = L.res[2], rank1 = w.rank - L.res[1];
             const bool found = L.res[3] != 0u;
-            const uint64_t prefix1 = ((uint64_t)w.prefix << kFirstBits) | digit;
             if (found && left == rank1) {
-                tc = prefix1 << s_lo;                                         // all under this prefix are kept
+                tc = digit_edge(fd, w.prefix, digit);                         // all with this digit are kept
             } else if (found && left <= (uint32_t)min(kFew, kResolveThreads)) {
                 if (tid == 0) {
                     U.pieces.n_plist = 0;
@@ -1798,7 +1835,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
                     const uint32_t first = rstart[p], count = rpre[p + 1] - rpre[p];
                     for (uint32_t e = lane; e < count; e += kWave) {
                         const uint64_t comp = wdense[first + e];
-                        if ((comp >> s_lo) == prefix1) {
+                        if (digit_of(fd, comp) == digit) {
                             const uint32_t slot = atomicAdd(&L.n_few, 1u);
                             if (slot < (uint32_t)kFew) L.few[slot] = comp;
                         }
@@ -1814,8 +1851,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
                 __syncthreads();
                 tc = L.tc_sh;
             } else if (found && left <= (uint32_t)kStaged) {
-                // Many elements under the first digit: exact ties, which 16-bit gradients produce by the thousand (a fine
-                // bin holds two of their values), are told apart only by the index bits at the far end of comp.  The
+                // Many elements under the first digit, for instance ties by the hundred thousand.  The
                 // elements are collected in LDS once, a piece per team of 8 lanes and four pieces of a team in flight,
                 // and the further digits scan LDS; through the piece table every digit was a scan of the whole bin.
                 constexpr int kTeam = 8, kTeams = kResolveThreads / kTeam;
@@ -1823,7 +1859,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
                 if (tid == 0) L.n_few = 0;
                 __syncthreads();
                 auto collect = [&](uint64_t comp, bool valid) {
-                    const bool hit = valid && (comp >> s_lo) == prefix1;
+                    const bool hit = valid && digit_of(fd, comp) == digit;
                     const uint64_t hm = __ballot(hit);
                     if (!hm) return;
                     uint32_t at = 0;
@@ -1856,9 +1892,10 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
 #pragma unroll
                     for (int u = 0; u < kScanUnroll; ++u) comp[u] = q[u] < left ? U.pieces.staged[q[u]] : 0ull;
                 };
-                tc = resolve_digits(staged, left, prefix1, rank1, s_lo, L);
+                // (a bin of the further digits may hold elements of another first digit, which are not among these)
+                tc = resolve_digits<false>(staged, left, w.prefix, rank1, s_hi, L);
             } else {
-                tc = resolve_digits(fetch, cnt, w.prefix, w.rank, s_hi, L, true);
+                tc = resolve_digits(fetch, cnt, w.prefix, w.rank, s_hi, L, !fd.split);
             }
         }
     }

@@ -216,6 +216,30 @@ def test_ties_in_the_threshold_bin(method, values):
     gpu.destroy()
 
 
+# the threshold's fine bin split by its top open bit, by index where the further bits are zero and by magnitude elsewhere:
+# six magnitudes at the edges of those shares, spread over the vector or packed into few indices (more than 8192 elements
+# under one digit are scanned in place, some hundred to 8192 collected in LDS)
+@pytest.mark.parametrize("method", ["ef", "naive", "cd"])
+@pytest.mark.parametrize("crowd,k", [("spread", 9_000), ("spread", 101), ("packed", 9_500), ("packed", 4_000), ("one value", 9_999)])
+def test_split_of_the_threshold_bin(method, crowd, k):
+    d, n = 4_000_003, 1                        # 22 index bits: a digit's share of the indices is 2^14
+    print(f"[case] threshold bin {crowd} {method} k={k}", flush=True)
+    gpu, ora = sparse_pair(d, n, k, method)
+    low = np.array([0, 1, 32, 33, 0x1fff, 0x2000, 0x2001, 0x3fff], dtype=np.uint32)
+
+    def fn(t):
+        r = np.random.default_rng([k, t])
+        g = (r.standard_normal((n, d), dtype=f32) * f32(1e-6))
+        size = 12_000
+        at = np.arange(t, t + size) if crowd == "packed" else r.choice(d, size, replace=False)
+        bits = np.uint32(0x3e8000 << 8) + (low[r.integers(0, low.size, size)] if crowd == "spread" else np.where(
+            r.random(size) < 0.9, np.uint32(0x2000 * (t % 2)), low[r.integers(0, low.size, size)] if crowd == "packed" else np.uint32(0x2000 * (t % 2))))
+        g[0, at] = np.where(r.random(size) < 0.5, bits.astype(np.uint32).view(f32), -bits.astype(np.uint32).view(f32))
+        return np.ascontiguousarray(g)
+    sparse_steps(gpu, ora, fn, 3, method, f"{crowd} {k}")
+    gpu.destroy()
+
+
 # CD-Adam on a vector long enough for more than 64 candidate regions on the server, with a drop that makes every
 # selection list anew
 def test_cd_lists_anew_on_a_long_vector():
