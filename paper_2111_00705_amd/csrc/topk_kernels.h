@@ -59,7 +59,7 @@ constexpr int kBins1 = 2048;      // coarse bin: top 11 of the 31 magnitude bits
 constexpr int kShift1 = 20;
 constexpr int kFineShift = 14;    // fine bin: top 17 bits; 64 fine bins per coarse bin
 constexpr int kFinePerCoarse = 1 << (kShift1 - kFineShift);
-constexpr int kWindowCoarse = 8;  // coarse bins whose fine bins are counted, from the guess's on: one octave of
+constexpr int kWindowCoarse = 8;  // coarse bins whose fine bins are counted (see window_start): one octave of
                                   // magnitudes.  In the first steps of a run the threshold climbs by tens of fine
                                   // bins per step; beyond the window only the coarse bin is known and the threshold
                                   // bin holds 64 times the elements (with two coarse bins, n = 8, d = 110 M: steps
@@ -955,9 +955,20 @@ __device__ __forceinline__ uint32_t candidates_listed(const TkGeom &ge, const ui
     return *total_sh;
 }
 
+// First coarse bin of the window whose fine bins are counted: the guess's, but no more than kWindowBelow fine bins below the
+// previous threshold.  With a wide slack (after a fall, or for Rand-k) a window that began at the guess ended before the
+// thresholds of the next steps, and the threshold bin held 64 times the elements: CD-Adam n = 8, d = 11.2 M bf16, on two
+// batches in turn, tk_resolve took 36 us in every second step and takes 10.
+constexpr uint32_t kWindowBelow = 224;
+__device__ __forceinline__ uint32_t window_start(uint32_t guess, uint32_t last)
+{
+    if (last != kNoGuess && last > guess + kWindowBelow) guess = last - kWindowBelow;
+    return guess >> (kShift1 - kFineShift);
+}
+
 // First kernel of the selection.  Grid (slices * parts, n).
 // Usual case (kCaseListed): histograms of the candidates of a worker - the fine bins of the kWindowCoarse coarse bins
-// that start with the guess's, and the coarse bins of the candidates beyond that window (those inside it would
+// from window_start on, and the coarse bins of the candidates beyond that window (those inside it would
 // draw most LDS atomics to eight words; tk_compact adds them up from the fine bins).  Loads are issued four at a
 // time.
 // After a miss (kCaseMiss) the workgroups of the worker count the whole vector, re-formed from what is stored
@@ -977,7 +988,7 @@ __global__ __launch_bounds__(kThreads) void tk_hist(TkGeom ge, const TkWorker *_
     __shared__ uint32_t total_sh;
     const int i = blockIdx.y;
     const int tid = threadIdx.x;
-    const uint32_t guess = ws[i].guess;
+    const uint32_t guess = ws[i].guess, last = ws[i].last_fine;
     const uint32_t total = candidates_listed(ge, cursor, i, &total_sh);
     const int which = selection_case<kSrc>(ge, total, guess, ws[i].overflow != 0u);
     if (which == kCaseZeroTail) return;
@@ -1011,7 +1022,7 @@ __global__ __launch_bounds__(kThreads) void tk_hist(TkGeom ge, const TkWorker *_
     }
     for (int q = tid; q < kFineWindow; q += kThreads) lf[q] = 0;
     __syncthreads();
-    const uint32_t wbase = guess & ~(uint32_t)(kFinePerCoarse - 1);   // first fine bin of the guess's coarse bin
+    const uint32_t wbase = window_start(guess, last) * kFinePerCoarse;
     const uint2 *src = cand + region_base(ge, i, pc.slice);
     for (uint32_t qb = pc.q0; qb < pc.q1; qb += 4 * kThreads) {
         uint2 y[4];
@@ -1090,7 +1101,7 @@ __global__ __launch_bounds__(kThreads) void tk_compact(TkGeom ge, TkWorker *__re
     const uint4 own1 = *reinterpret_cast<const uint4 *>(hist1 + (int64_t)i * kBins1 + 8 * tid + 4);
     const uint32_t f0 = histf[(int64_t)i * kFineWindow + tid], f1 = histf[(int64_t)i * kFineWindow + kThreads + tid];
     const Piece pc = piece_of(ge, cursor, i, min(bx, per - 1));
-    const uint32_t guess = ws[i].guess;
+    const uint32_t guess = ws[i].guess, last = ws[i].last_fine;
     const bool overflow = ws[i].overflow != 0u;
     {
         lf[tid] = f0;
@@ -1114,7 +1125,7 @@ __global__ __launch_bounds__(kThreads) void tk_compact(TkGeom ge, TkWorker *__re
 
     if (which == kCaseListed) {
         if (bx >= per) return;                      // workgroups beyond the pieces are there for the lists after a miss
-        const uint32_t wb = guess >> (kShift1 - kFineShift);      // first coarse bin of the fine window
+        const uint32_t wb = window_start(guess, last);            // first coarse bin of the fine window
         uint32_t own[8] = {own0.x, own0.y, own0.z, own0.w, own1.x, own1.y, own1.z, own1.w};
 #pragma unroll
         for (int q = 0; q < 8; ++q) {               // the window's coarse bins are counted in the fine histogram alone
