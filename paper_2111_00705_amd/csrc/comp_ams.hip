@@ -761,8 +761,10 @@ void launch_final(comp_ams *h, hipStream_t st)
     launch_timed(h, P_TK_FINAL, st, [&] {
         by_flag(h->params.stream_state, [&](auto ss) {
             if (short_final(h->n, h->ge.n_tiles))
-                KLAUNCH((tk_final_short<decltype(ss)::value>), 4 * h->ge.n_tiles, kThreads, st, h->ge, h->ws, h->cand,
-                        h->tile_dir, h->theta, h->m, h->v, h->vhat, h->params);
+                by_flag(short_final_batch(h->ge.n_tiles) == 8, [&](auto eight) {
+                    KLAUNCH((tk_final_short<decltype(ss)::value, decltype(eight)::value ? 8 : 5>), 4 * h->ge.n_tiles, kThreads, st, h->ge,
+                            h->ws, h->cand, h->tile_dir, h->theta, h->m, h->v, h->vhat, h->params);
+                });
             else
                 KLAUNCH((tk_final<decltype(ss)::value>), h->ge.n_tiles, kThreads, st, h->ge, h->ws, h->cand, h->tile_dir,
                         h->theta, h->m, h->v, h->vhat, h->params);

@@ -5,10 +5,9 @@
 namespace cams {
 
 // Whether the update of kept values takes a quarter of a tile per workgroup (tk_final_short) instead of a tile (tk_final).
-// The quarter form fills the chip and loads the state first, but each of its four wavefronts reads the lists of all n
-// workers and sorts out its own row.  Up to 320 tiles its 1280 workgroups run at once, five on a compute unit; beyond, a
-// second round starts.  With many workers the reading is what counts.  Step plus get_theta, error feedback, a tile / a
-// quarter, us: Top-k, k = 2 %, n = 2, 288 tiles 56.7 / 52.6, 384 tiles 60.6 / 60.7; n = 8, 128 tiles 56.7 / 54.7, 320 tiles
+// The quarter form fills the chip and loads the state first.  Up to 320 tiles its 1280 workgroups run at once.  Step plus
+// get_theta, error feedback, a tile / a quarter, us, when each of the four wavefronts of a quarter still went through all lists
+// for itself (the quarter has gained 1-4 % since with 16 workers or more): Top-k, k = 2 %, n = 2, 288 tiles 56.7 / 52.6, 384 tiles 60.6 / 60.7; n = 8, 128 tiles 56.7 / 54.7, 320 tiles
 // 78.0 / 74.1, 352 tiles 80.9 / 81.7; n = 16, 319 tiles 106.7 / 104.6; k = 5 %, n = 24, 128 tiles 84.8 / 85.2, 200 tiles
 // 108.0 / 111.3; n = 32, 64 tiles 77.8 / 77.8, 128 tiles 101.1 / 102.2; n = 48, 64 tiles 98.2 / 98.4, 100 tiles 119.4 / 122.4;
 // Rand-k, k = 1 %, n = 16, 2 tiles 37.5 / 37.1; n = 48, 2 tiles 49.1 / 50.5, 16 tiles 57.0 / 56.2; n = 256, 5 tiles 133.4 / 150.2,
@@ -18,6 +17,11 @@ inline bool short_final(int64_t n, int64_t n_tiles)
 {
     return n_tiles <= kShortFinalTiles && n <= kShortFinalWorkers && (n <= 16 || n * n_tiles <= kShortFinalLists);
 }
+
+// Workers whose kept values a workgroup of tk_final_short holds at a time.  Eight take 36 KB of LDS, which leaves four
+// workgroups on a compute unit, enough for 256 tiles; five take 23 KB.  Step plus get_theta, us, five / eight: n = 48,
+// d = 250 000 81.8 / 79.6, n = 32, d = 350 000 bf16 80.7 / 79.2; 293 tiles, n = 16 88.7 / 93.5, 318 tiles, n = 2 46.5 / 48.8.
+inline int short_final_batch(int64_t n_tiles) { return n_tiles <= 256 ? 8 : 5; }
 
 // Grid of a kernel with one workgroup per tile (in x) under tile_of_block's mapping.
 inline unsigned grid_blocks(int64_t n_tiles, int chunk)

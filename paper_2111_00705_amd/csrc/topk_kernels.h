@@ -52,6 +52,7 @@
 // bins, digits, thresholds, the deferred error - is unchanged.
 #pragma once
 #include "device_utils.h"
+#include "launch_rules.h"
 
 namespace cams {
 
@@ -683,17 +684,14 @@ constexpr int kFinBatch = 8;   // workers whose candidates a wavefront has in fl
 // worker order.  ws: the records that hold the selection's thresholds (and, for Rand-k, the draw they were made
 // with).  kScatter (CD-Adam, Algorithm 1, line 6): the kept value u = c_i[j] is also added to
 // ghat_i[j] in `rows` ([n][ld]); the old values are fetched for a whole batch before they are used.
-// wave: the wavefront of the listing pass whose list is read.  kRow: only the coordinates of row `row` of its quarter are
-// summed, into acc of 256 floats.
-template <bool kScatter, bool kRow>
+// wave: the wavefront of the listing pass whose list is read.
+template <bool kScatter>
 __device__ __forceinline__ void sum_kept_tile(float *acc, const TkGeom &ge, const TkWorker *__restrict__ ws,
                                               const uint2 *__restrict__ cand, const uint4 *__restrict__ tile_dir,
-                                              int t, float *__restrict__ rows, int wave, int row)
+                                              int t, float *__restrict__ rows, int wave)
 {
     const uint32_t base = (uint32_t)t * kTile;
     const int lane = threadIdx.x & 63;
-    auto mine = [&](uint32_t j) { return !kRow || (int)((j - base) >> 10) == row; };
-    auto place = [&](uint32_t j) { return kRow ? ((j - base) & 1023u) - 256u * (uint32_t)wave : j - base; };
     for (int w0 = 0; w0 < ge.n; w0 += kWave) {
         const int nw = min(kWave, ge.n - w0);
         // lane l: where worker w0 + l keeps this wavefront's candidates of the tile, and its threshold
@@ -731,7 +729,7 @@ __device__ __forceinline__ void sum_kept_tile(float *acc, const TkGeom &ge, cons
                 const uint64_t tc = ((uint64_t)tc_hi << 32) | tc_lo;
                 SelKey sk = {0u, 0u, 0u};
                 if (ge.rand.on) sk = {1u, (uint32_t)__shfl((int)my_sk.a, w, kWave), (uint32_t)__shfl((int)my_sk.b, w, kWave)};
-                keep[u] = (uint32_t)lane < cnt[u] && mine(e[u].x) &&
+                keep[u] = (uint32_t)lane < cnt[u] &&
                           composite(sel_key(sk, __uint_as_float(e[u].y), e[u].x), e[u].x, ge.idx_bits) >= tc;
                 old[u] = 0.f;
                 if (kScatter && keep[u]) old[u] = rows[(int64_t)(w0 + w) * ge.ld + e[u].x];
@@ -741,7 +739,7 @@ __device__ __forceinline__ void sum_kept_tile(float *acc, const TkGeom &ge, cons
                 const int w = min(wb + u, nw - 1);
                 if (keep[u]) {
                     const float x = __uint_as_float(e[u].y);
-                    const uint32_t l = place(e[u].x);
+                    const uint32_t l = e[u].x - base;
                     acc[l] = fadd(acc[l], x);
                     if (kScatter) rows[(int64_t)(w0 + w) * ge.ld + e[u].x] = fadd(old[u], x);
                 }
@@ -757,8 +755,8 @@ __device__ __forceinline__ void sum_kept_tile(float *acc, const TkGeom &ge, cons
                     for (uint32_t q = kWave + lane; q < cnt[u]; q += kWave) {
                         const uint2 c = src[q];
                         const float x = __uint_as_float(c.y);
-                        if (mine(c.x) && composite(sel_key(sk, x, c.x), c.x, ge.idx_bits) >= tc) {
-                            const uint32_t l = place(c.x);
+                        if (composite(sel_key(sk, x, c.x), c.x, ge.idx_bits) >= tc) {
+                            const uint32_t l = c.x - base;
                             acc[l] = fadd(acc[l], x);
                             if (kScatter) {
                                 float *gh = rows + (int64_t)(w0 + w) * ge.ld + c.x;
@@ -789,7 +787,7 @@ __global__ __launch_bounds__(kThreads) void tk_final(TkGeom ge, const TkWorker *
 #pragma unroll
     for (int r = 0; r < 4; ++r) st4(acc + 4 * (tid + kThreads * r), make_float4(0.f, 0.f, 0.f, 0.f));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    sum_kept_tile<false, false>(acc, ge, ws, cand, tile_dir, t, nullptr, tid >> 6, 0);
+    sum_kept_tile<false>(acc, ge, ws, cand, tile_dir, t, nullptr, tid >> 6);
 
     // the state is loaded only now: fewer live registers above (more workgroups per compute unit),
     // which measured faster than loading it first
@@ -820,28 +818,133 @@ __global__ __launch_bounds__(kThreads) void tk_final(TkGeom ge, const TkWorker *
 }
 
 // The same with a quarter of a tile per workgroup, for vectors that leave the chip idle otherwise (see short_final): quarter
-// w holds the coordinates of the listing pass's wavefront w, and wavefront r here takes row r of them (one float4 per lane,
-// the state loaded before anything else).  The four wavefronts each read the quarter's lists, which is what it costs.
-template <bool kStreamState>
+// w holds the coordinates of the listing pass's wavefront w, and wavefront r here updates row r of them (one float4 per lane,
+// the state loaded before anything else).
+// Bound by a chain of latencies: the records of all workers, then the candidates, are each loaded at once.  The candidates
+// are dealt out to the 256 threads together, since a worker's list holds a dozen of them in a quarter; the kept values of
+// kBatch workers at a time then go to a row of LDS each, with a bit per coordinate, and every thread adds its own
+// coordinates in ascending worker order.  A wavefront that went through the lists
+// worker by worker, eight workers' candidates in flight, each of the four for its own row, took (step plus get_theta, us, that / this)
+// Rand-k n = 16, d = 1.2 M f16 84.5 / 81.6, n = 48, d = 200 000 with 5 % kept 84.2 / 81.6, Top-k n = 16, d = 1.2 M 89.9 / 88.5,
+// n = 20, d = 600 000 with 5 % kept bf16 82.4 / 79.6, n = 2, d = 1.3 M 45.8 / 45.4; n = 4, d = 65 536 the same.
+constexpr int kShortHeld = 2;         // candidates a thread holds from the start
+template <bool kStreamState, int kBatch>   // kBatch: workers whose kept values are in LDS at a time
 __global__ __launch_bounds__(kThreads) void tk_final_short(TkGeom ge, const TkWorker *__restrict__ ws,
                                                      const uint2 *__restrict__ cand,
                                                      const uint4 *__restrict__ tile_dir,
                                                      float *__restrict__ theta, float *__restrict__ m,
                                                      float *__restrict__ v, float *__restrict__ vhat, AmsParams p)
 {
-    __shared__ float acc4[4][4 * kWave];
+    __shared__ float val[kBatch][4 * kThreads];
+    __shared__ uint32_t kept[kBatch][kWave];     // a word per thread of the listing pass: bit 4 r + c for row r, component c
+    __shared__ uint32_t start[kShortFinalWorkers], upto[kShortFinalWorkers + 1], key_a[kShortFinalWorkers], key_b[kShortFinalWorkers];
+    __shared__ uint64_t tc[kShortFinalWorkers];
+    static_assert(kShortFinalWorkers <= kWave, "a worker per lane");
     const int t = blockIdx.x >> 2, w = blockIdx.x & 3;
-    const int lane = threadIdx.x & 63, r = threadIdx.x >> 6;
-    const int64_t j = (int64_t)t * kTile + 1024 * r + 256 * w + 4 * lane;
-    float *acc = acc4[r];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, r = tid >> 6;
+    const uint32_t base = (uint32_t)t * kTile;
+    const int64_t j = (int64_t)base + 1024 * r + 256 * w + 4 * lane;
     float4 th = ld4_state<kStreamState>(theta + j), mm = ld4_state<kStreamState>(m + j),
            vv = ld4_state<kStreamState>(v + j), vh = ld4_state<kStreamState>(vhat + j);
-    st4(acc + 4 * lane, make_float4(0.f, 0.f, 0.f, 0.f));
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    sum_kept_tile<false, true>(acc, ge, ws, cand, tile_dir, t, nullptr, w, r);
-    const float4 a = ld4(acc + 4 * lane);
-    const float4 gbar = make_float4(fdiv(a.x, p.n_workers), fdiv(a.y, p.n_workers), fdiv(a.z, p.n_workers),
-                                    fdiv(a.w, p.n_workers));
+    if (r == 0) {
+        // lane i: where worker i keeps the quarter's candidates, and its threshold
+        uint32_t count = 0;
+        if (lane < ge.n) {
+            const uint4 rec = tile_dir[(int64_t)lane * ge.n_tiles + t];
+            const TkWorker *wk = ws + lane;
+            const uint32_t c[4] = {rec.y & 0xffffu, rec.y >> 16, rec.z & 0xffffu, rec.z >> 16};
+            uint32_t at = rec.x;
+            for (int q = 0; q < w; ++q) at += c[q];
+            count = c[w];
+            start[lane] = at;
+            tc[lane] = wk->tc;
+            const SelKey sk = sel_key_of(ge.rand, wk->step_word, lane);
+            key_a[lane] = sk.a;
+            key_b[lane] = sk.b;
+        }
+        uint32_t incl = count;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const uint32_t up = __shfl_up(incl, off, kWave);
+            if (lane >= off) incl += up;
+        }
+        if (lane < ge.n) upto[lane + 1] = incl;
+        if (lane == 0) upto[0] = 0u;
+    }
+    __syncthreads();
+    const uint32_t total = upto[ge.n];
+    // the worker of entry q of the quarter: the last one whose entries start at or before it
+    auto owner = [&](uint32_t q) {
+        int i = 0;
+#pragma unroll
+        for (int bit = 32; bit > 0; bit >>= 1)
+            if (i + bit < ge.n && upto[min(i + bit, kShortFinalWorkers)] <= q) i += bit;
+        return i;
+    };
+    auto fetch = [&](uint32_t q, int i) { return cand[worker_base(ge, i) + start[i] + (q - upto[i])]; };
+    auto is_kept = [&](const uint2 &e, int i) {
+        const SelKey sk = {ge.rand.on, key_a[i], key_b[i]};
+        return composite(sel_key(sk, __uint_as_float(e.y), e.x), e.x, ge.idx_bits) >= tc[i];
+    };
+    auto put = [&](const uint2 &e, int u) {
+        const uint32_t l = e.x - base;
+        val[u][(l >> 10) * 256u + (l & 255u)] = __uint_as_float(e.y);
+        atomicOr(&kept[u][(l >> 2) & 63u], 1u << ((l >> 10) * 4u + (l & 3u)));
+    };
+    uint2 e[kShortHeld];
+    int of[kShortHeld];
+#pragma unroll
+    for (int s = 0; s < kShortHeld; ++s) {
+        const uint32_t q = tid + s * kThreads;
+        of[s] = q < total ? owner(q) : -1;
+        e[s] = make_uint2(0u, 0u);
+        if (of[s] >= 0) e[s] = fetch(q, of[s]);
+    }
+#pragma unroll
+    for (int s = 0; s < kShortHeld; ++s)
+        if (of[s] >= 0 && !is_kept(e[s], of[s])) of[s] = -1;
+    // entries beyond those: the first of each thread in the batch that begins with worker w0 is read a batch ahead
+    uint32_t more = 0;
+    int more_of = -1;
+    uint2 more_e = make_uint2(0u, 0u);
+    auto read_ahead = [&](int w0) {
+        more = max(upto[w0], (uint32_t)(kShortHeld * kThreads)) + tid;
+        more_of = more < upto[min(w0 + kBatch, ge.n)] ? owner(more) : -1;
+        if (more_of >= 0) more_e = fetch(more, more_of);
+    };
+    read_ahead(0);
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int w0 = 0; w0 < ge.n; w0 += kBatch) {
+        const int nw = min(kBatch, ge.n - w0);
+        if (w0) __syncthreads();                             // the bits of the batch before have been read
+        for (int q = tid; q < kBatch * kWave; q += kThreads) (&kept[0][0])[q] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < kShortHeld; ++s)
+            if ((uint32_t)(of[s] - w0) < (uint32_t)nw) put(e[s], of[s] - w0);
+        if (more_of >= 0 && is_kept(more_e, more_of)) put(more_e, more_of - w0);
+        for (uint32_t q = more + kThreads; q < upto[w0 + nw]; q += kThreads) {
+            const int i = owner(q);
+            const uint2 x = fetch(q, i);
+            if (is_kept(x, i)) put(x, i - w0);
+        }
+        if (w0 + kBatch < ge.n) read_ahead(w0 + kBatch);
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            if (u < nw) {
+                const uint32_t bits = kept[u][lane] >> (4 * r);
+                const float4 x = ld4(&val[u][256 * r + 4 * lane]);      // anything where nothing was kept
+                if (bits & 1u) acc[0] = fadd(acc[0], x.x);
+                if (bits & 2u) acc[1] = fadd(acc[1], x.y);
+                if (bits & 4u) acc[2] = fadd(acc[2], x.z);
+                if (bits & 8u) acc[3] = fadd(acc[3], x.w);
+            }
+        }
+    }
+    const float4 gbar = make_float4(fdiv(acc[0], p.n_workers), fdiv(acc[1], p.n_workers), fdiv(acc[2], p.n_workers),
+                                    fdiv(acc[3], p.n_workers));
     const float4 vh0 = vh;
     amsgrad_update4(th, mm, vv, vh, gbar, p);
     st4_state<kStreamState>(theta + j, th);
@@ -2177,7 +2280,7 @@ __global__ __launch_bounds__(kThreads) void tk_merge(TkGeom ge, const TkWorker *
 #pragma unroll
     for (int r = 0; r < 4; ++r) st4(acc + 4 * (tid + kThreads * r), make_float4(0.f, 0.f, 0.f, 0.f));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    sum_kept_tile<true, false>(acc, ge, ws, cand, tile_dir, t, ghat_rows, tid >> 6, 0);
+    sum_kept_tile<true>(acc, ge, ws, cand, tile_dir, t, ghat_rows, tid >> 6);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int l = 4 * (tid + kThreads * r);

@@ -199,6 +199,18 @@ def test_update_of_kept_values(tiles, n, share):
     gpu.destroy()
 
 
+# tk_final_short: eight or five workers' kept values at a time (256 / 257 tiles), candidates beyond the two that a thread
+# holds, all of a quarter kept
+@pytest.mark.parametrize("comp", [P.TOPK, P.RANDK])
+@pytest.mark.parametrize("tiles,n,share", [(256, 9, 0.1), (257, 11, 0.02), (17, 48, 0.3), (2, 16, 1.0), (18, 6, 0.12)])
+def test_update_of_kept_values_by_quarters(tiles, n, share, comp):
+    d = tiles * TILE - 5
+    print(f"[case] update by quarters, {tiles} tiles n={n} share={share} comp={comp}", flush=True)
+    gpu, ora = sparse_pair(d, n, int(d * share), "ef", comp)
+    sparse_steps(gpu, ora, grads_of(tiles + n, n, d), 2, "ef", f"tiles={tiles}")
+    gpu.destroy()
+
+
 # exact ties in the threshold bin: `values` magnitudes, d / values coordinates each - ranked directly, collected in LDS
 # (up to 8192 under the first digit), or scanned in place
 @pytest.mark.parametrize("method", ["ef", "naive", "cd"])
