@@ -1073,7 +1073,8 @@ __device__ __forceinline__ uint32_t window_start(uint32_t guess, uint32_t last)
 // Usual case (kCaseListed): histograms of the candidates of a worker - the fine bins of the kWindowCoarse coarse bins
 // from window_start on, and the coarse bins of the candidates beyond that window (those inside it would
 // draw most LDS atomics to eight words; tk_compact adds them up from the fine bins).  Loads are issued four at a
-// time.
+// time, without a branch around them (past the end the last element is read again): in one the compiler waits for each load
+// before it issues the next.
 // After a miss (kCaseMiss) the workgroups of the worker count the whole vector, re-formed from what is stored
 // (a, b: see load_source_tile), into the worker's full coarse histogram instead; tk_compact takes the coarse bin of
 // the k-th largest from it and lists again.  Bin 0 (zeros and the smallest denormals) is not counted there but
@@ -1132,7 +1133,7 @@ __global__ __launch_bounds__(kThreads) void tk_hist(TkGeom ge, const TkWorker *_
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const uint32_t q = qb + u * kThreads + tid;
-            y[u] = q < pc.q1 ? src[q] : make_uint2(0u, 0u);
+            y[u] = src[min(q, pc.q1 - 1u)];
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -1277,7 +1278,7 @@ __global__ __launch_bounds__(kThreads) void tk_compact(TkGeom ge, TkWorker *__re
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const uint32_t q = qb + u * kWave + lane;
-                c[u] = q < w1 ? src[q] : make_uint2(0u, 0u);
+                c[u] = src[min(q, w1 - 1u)];
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -1819,7 +1820,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
 #pragma unroll
                         for (int u = 0; u < 8; ++u) {
                             const uint32_t q = q0 + u * kWave + lane;
-                            e[u] = q < count ? src[q] : make_uint2(0u, 0u);
+                            e[u] = src[min(q, count - 1u)];
                         }
 #pragma unroll
                         for (int u = 0; u < 8; ++u) {
@@ -1843,19 +1844,23 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
                 auto fetch = [&](const uint32_t (&q)[kScanUnroll], uint64_t (&comp)[kScanUnroll]) {
                     if (q[0] >= cnt) return;
                     int r[kScanUnroll];
+                    uint32_t in[kScanUnroll];
 #pragma unroll
-                    for (int u = 0; u < kScanUnroll; ++u) r[u] = 0;
+                    for (int u = 0; u < kScanUnroll; ++u) {
+                        r[u] = 0;
+                        in[u] = min(q[u], cnt - 1u);
+                    }
                     for (int bit = top; bit > 0; bit >>= 1) {
                         uint32_t start[kScanUnroll];
 #pragma unroll
                         for (int u = 0; u < kScanUnroll; ++u) start[u] = rpre[min(r[u] + bit, regions)];
 #pragma unroll
-                        for (int u = 0; u < kScanUnroll; ++u) r[u] = (start[u] <= q[u] && r[u] + bit < regions) ? r[u] + bit : r[u];
+                        for (int u = 0; u < kScanUnroll; ++u) r[u] = (start[u] <= in[u] && r[u] + bit < regions) ? r[u] + bit : r[u];
                     }
                     uint2 e[kScanUnroll];
 #pragma unroll
                     for (int u = 0; u < kScanUnroll; ++u)
-                        e[u] = q[u] < cnt ? list[(uint32_t)r[u] * ge.region_cap + (q[u] - rpre[r[u]])] : make_uint2(0u, 0u);
+                        e[u] = list[(uint32_t)r[u] * ge.region_cap + (in[u] - rpre[r[u]])];
 #pragma unroll
                     for (int u = 0; u < kScanUnroll; ++u)
                         comp[u] = composite(sel_key(sk, __uint_as_float(e[u].y), e[u].x), e[u].x, ge.idx_bits);
@@ -1900,20 +1905,24 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
         auto fetch = [&](const uint32_t (&q)[kScanUnroll], uint64_t (&comp)[kScanUnroll]) {
             if (q[0] >= cnt) return;                       // nothing for this thread in the batch
             int r[kScanUnroll];
+            uint32_t in[kScanUnroll];
 #pragma unroll
-            for (int u = 0; u < kScanUnroll; ++u) r[u] = 0;
+            for (int u = 0; u < kScanUnroll; ++u) {
+                r[u] = 0;
+                in[u] = min(q[u], cnt - 1u);               // no branch around the loads: see tk_hist
+            }
             for (int bit = top; bit > 0; bit >>= 1) {
                 uint32_t start[kScanUnroll];
 #pragma unroll
                 for (int u = 0; u < kScanUnroll; ++u) start[u] = rpre[min(r[u] + bit, pieces)];   // rpre[pieces] = cnt
 #pragma unroll
-                for (int u = 0; u < kScanUnroll; ++u) r[u] = (start[u] <= q[u] && r[u] + bit < pieces) ? r[u] + bit : r[u];
+                for (int u = 0; u < kScanUnroll; ++u) r[u] = (start[u] <= in[u] && r[u] + bit < pieces) ? r[u] + bit : r[u];
             }
             uint32_t at[kScanUnroll];
 #pragma unroll
-            for (int u = 0; u < kScanUnroll; ++u) at[u] = rstart[r[u]] + (q[u] - rpre[r[u]]);
+            for (int u = 0; u < kScanUnroll; ++u) at[u] = rstart[r[u]] + (in[u] - rpre[r[u]]);
 #pragma unroll
-            for (int u = 0; u < kScanUnroll; ++u) comp[u] = q[u] < cnt ? wdense[at[u]] : 0ull;
+            for (int u = 0; u < kScanUnroll; ++u) comp[u] = wdense[at[u]];
         };
         if (xs != nullptr && w.prefix == 0u && w.rank > cnt)
             // the threshold bin is the one of the smallest keys and the k-th largest lies below its listed
@@ -1923,6 +1932,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
             // The first digit below the prefix from tk_compact's counts.  Usually at most kFew elements carry it:
             // they sit in at most as many pieces, which the pieces' bitmaps name, so only those pieces are read
             // (a few hundred elements instead of the whole threshold bin) and the elements ranked directly.
+            constexpr int kTeam = 8, kTeams = kResolveThreads / kTeam;
             const FirstDigit fd = first_digit(ge, w.pshift);
             find_rank_bin(L.lh, L.part, L.res, kBinsFirst, w.rank);          // barriers since L.lh was filled
             const uint32_t digit = L.res[0], left = L.res[2], rank1 = w.rank - L.res[1];
@@ -1944,10 +1954,12 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
                 }
                 __syncthreads();
                 const uint32_t n_listed = min(U.pieces.n_plist, (uint32_t)kFew);   // <= left: each names an element
-                for (uint32_t q = wave; q < n_listed; q += kResolveThreads / kWave) {
+                // a piece per team of 8 lanes: a piece holds a handful of the bin's elements (a piece per wavefront took its 16
+                // wavefronts through the pieces one after the other, a memory latency each)
+                for (uint32_t q = tid / kTeam; q < n_listed; q += kTeams) {
                     const uint32_t p = U.pieces.plist[q];
                     const uint32_t first = rstart[p], count = rpre[p + 1] - rpre[p];
-                    for (uint32_t e = lane; e < count; e += kWave) {
+                    for (uint32_t e = tid % kTeam; e < count; e += kTeam) {
                         const uint64_t comp = wdense[first + e];
                         if (digit_of(fd, comp) == digit) {
                             const uint32_t slot = atomicAdd(&L.n_few, 1u);
@@ -1968,7 +1980,6 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
                 // Many elements under the first digit, for instance ties by the hundred thousand.  The
                 // elements are collected in LDS once, a piece per team of 8 lanes and four pieces of a team in flight,
                 // and the further digits scan LDS; through the piece table every digit was a scan of the whole bin.
-                constexpr int kTeam = 8, kTeams = kResolveThreads / kTeam;
                 const int team = tid / kTeam, tl = tid % kTeam;
                 if (tid == 0) L.n_few = 0;
                 __syncthreads();
@@ -1989,14 +2000,14 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
                         const int p = p0 + u * kTeams + team;
                         first[u] = p < pieces ? rstart[p] : 0u;
                         count[u] = p < pieces ? rpre[p + 1] - rpre[p] : 0u;
-                        comp[u] = (uint32_t)tl < count[u] ? wdense[first[u] + tl] : 0ull;
+                        comp[u] = wdense[(uint32_t)tl < count[u] ? first[u] + tl : 0u];
                         most = max(most, count[u]);
                     }
 #pragma unroll
                     for (int u = 0; u < 4; ++u) collect(comp[u], (uint32_t)tl < count[u]);
                     for (uint32_t e = kTeam; __any(e < most); e += kTeam) {    // uniform over the wavefront
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) comp[u] = e + tl < count[u] ? wdense[first[u] + e + tl] : 0ull;
+                        for (int u = 0; u < 4; ++u) comp[u] = wdense[e + tl < count[u] ? first[u] + e + tl : 0u];
 #pragma unroll
                         for (int u = 0; u < 4; ++u) collect(comp[u], e + tl < count[u]);
                     }
