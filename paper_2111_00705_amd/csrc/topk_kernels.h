@@ -21,7 +21,7 @@
 //               place in the tile, 6 bytes), see kListDirect.
 //               A workgroup per tile (instead of a loop over tiles) matters: on this chip a wave
 //               that loops must wait for its stores before it can use its next loads.
-//   tk_hist     histograms of the candidates: the fine bins of the eight coarse bins from the guess's on,
+//   tk_hist     histograms of the candidates: the fine bins of eight coarse bins (see window_start),
 //               coarse bins (top 11 bits) beyond; with fewer than k candidates (always on the first
 //               step) the guess was too high: then the workgroups count the whole vector into a
 //               full coarse histogram instead
