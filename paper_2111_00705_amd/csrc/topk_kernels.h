@@ -741,7 +741,11 @@ __device__ __forceinline__ void sum_kept_tile(float *acc, const TkGeom &ge, cons
                     const float x = __uint_as_float(e[u].y);
                     const uint32_t l = e[u].x - base;
                     acc[l] = fadd(acc[l], x);
-                    if (kScatter) rows[(int64_t)(w0 + w) * ge.ld + e[u].x] = fadd(old[u], x);
+                    // stored as a stream: the row is not read again before the next step (step plus get_theta, us, ordinary store /
+                    // this: CD-Adam n = 8, d = 11.2 M bf16 336.0 / 330.8, n = 16 fp32 501.5 / 493.8, Rand-k n = 8, d = 25 M 686 / 676, Top-k
+                    // 0.1 % of d = 60 M 1152 / 1154; loaded as a stream as well 343.5, 511, 691, 1158)
+                    if (kScatter)
+                        __builtin_nontemporal_store(fadd(old[u], x), rows + (int64_t)(w0 + w) * ge.ld + e[u].x);
                 }
                 if (cnt[u] > (uint32_t)kWave) {
                     // more than 64 candidates of this worker in the wavefront's quarter of the tile (rare)
