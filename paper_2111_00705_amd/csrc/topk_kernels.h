@@ -22,7 +22,7 @@
 //               A workgroup per tile (instead of a loop over tiles) matters: on this chip a wave
 //               that loops must wait for its stores before it can use its next loads.
 //   tk_hist     histograms of the candidates: the fine bins of eight coarse bins (see window_start),
-//               coarse bins (top 11 bits) beyond; with fewer than k candidates (always on the first
+//               coarse bins (top 11 bits) outside; with fewer than k candidates (always on the first
 //               step) the guess was too high: then the workgroups count the whole vector into a
 //               full coarse histogram instead
 //   tk_compact  coarse and fine bin of the k-th largest (every workgroup for itself); candidates in
@@ -212,6 +212,7 @@ struct FirstDigit {
 constexpr uint32_t kTieBins = kBinsFirst / 4;      // per value of the top open bit
 constexpr int kTieBits = kFirstBits - 2;
 static_assert(kFineShift - 1 - kTieBits >= 0, "magnitudes of a half in kTieBins bins");
+static_assert(kShift1 - kFirstBits <= kFineShift, "a first digit below a coarse bin lies in one fine bin");
 __device__ __forceinline__ FirstDigit first_digit(const TkGeom &ge, uint32_t pshift)
 {
     return {ge.idx_bits, (int)pshift + ge.idx_bits - kFirstBits, pshift == (uint32_t)kFineShift && !ge.rand.on};   // pshift > kFirstBits
@@ -1066,6 +1067,10 @@ __device__ __forceinline__ uint32_t candidates_listed(const TkGeom &ge, const ui
 // previous threshold.  With a wide slack (after a fall, or for Rand-k) a window that began at the guess ended before the
 // thresholds of the next steps, and the threshold bin held 64 times the elements: CD-Adam n = 8, d = 11.2 M bf16, on two
 // batches in turn, tk_resolve took 36 us in every second step and takes 10.
+// So coarse bins may lie between the guess and the window, and the guess's own is listed only from the guess on: a coarse
+// prefix does not mean that all elements of the bin are among the candidates, and the bin's lower edge, which lies below the
+// guess, is no threshold (tk_compact's `whole`).  The digits below such a prefix (kFirstBits bits and more) are narrower than
+// a fine bin, and no candidate lies below the guess: the lower edge of the digit of the k-th largest does not either.
 constexpr uint32_t kWindowBelow = 224;
 __device__ __forceinline__ uint32_t window_start(uint32_t guess, uint32_t last)
 {
@@ -1075,7 +1080,7 @@ __device__ __forceinline__ uint32_t window_start(uint32_t guess, uint32_t last)
 
 // First kernel of the selection.  Grid (slices * parts, n).
 // Usual case (kCaseListed): histograms of the candidates of a worker - the fine bins of the kWindowCoarse coarse bins
-// from window_start on, and the coarse bins of the candidates beyond that window (those inside it would
+// from window_start on, and the coarse bins of the candidates outside that window (those inside it would
 // draw most LDS atomics to eight words; tk_compact adds them up from the fine bins).  Loads are issued four at a
 // time, without a branch around them (past the end the last element is read again): in one the compiler waits for each load
 // before it issues the next.
@@ -1261,7 +1266,8 @@ __global__ __launch_bounds__(kThreads) void tk_compact(TkGeom ge, TkWorker *__re
             prefix = (prefix << (kShift1 - kFineShift)) | (uint32_t)top;
             pshift = kFineShift;
         }
-        const bool whole = count == rank;
+        // every element with this prefix is kept: only where all of them were listed (see window_start)
+        const bool whole = count == rank && (pshift == (uint32_t)kFineShift || prefix * kFinePerCoarse >= guess);
         if (bx == 0 && tid == 0) {
             ws[i].prefix = prefix;
             ws[i].pshift = pshift;
@@ -1426,8 +1432,8 @@ struct ResolveLds {
 // carry the prefix is wanted.  Once at most kFew elements carry the prefix they are fetched and
 // ranked against each other directly.  All threads of the workgroup call this; returns Tc.
 // kWholeBins: a digit whose bin holds exactly the elements still wanted ends the search with the bin's lower edge as
-// Tc - right when every element of the vector that could fall into that bin is among the cnt delivered (the
-// threshold bin of tk_compact is), wrong when the elements are only those above some bound that may cut the bin
+// Tc - right when every element of the vector that could fall into that bin is among the cnt delivered (a digit of
+// tk_compact's threshold bin lies in one fine bin, and those are listed whole), wrong when the elements are only those above some bound that may cut the bin
 // (the list of tk_small_select): then the search goes on to the k-th largest comp value itself.
 // have_first: the first digit has kFirstBits bits and its counts are in L.lh[0 .. kBinsFirst) already (with a
 // barrier after them); the first scan is not made.

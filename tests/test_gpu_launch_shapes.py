@@ -252,6 +252,69 @@ def test_split_of_the_threshold_bin(method, crowd, k):
     gpu.destroy()
 
 
+# the window of fine bins may start above the guess's coarse bin, which then is known by its count alone but listed only from the
+# guess on: what lies below the guess in that bin is not kept.  A worker each: k values at fine bin 65224, k at `second` (a fall
+# of 150 to 200 bins: the window starts 224 below), then `sizes` values at `bins`, then no gradient, so that the error memory is
+# read again.  (A value at the foot of their coarse bin goes with the first two and is taken back: with the k values alone the
+# threshold is the lower edge of the bin.)
+WINDOW_CASES = {
+    "k listed in the guess's bin": (65074, (64773, 64770), (4, 20)),
+    "k + 1 listed in the guess's bin": (65074, (64773, 64770), (5, 20)),
+    "k listed, the k-th alone in the guess's bin": (65074, (64900, 64773, 64768), (3, 1, 20)),
+    "k listed, four coarse bins below the window": (65024, (64630, 64600), (4, 20)),
+    "a whole bin between the guess's and the window": (65024, (64700, 64630), (4, 20)),
+    "a cut in a bin between the guess's and the window": (65024, (64700, 64690), (4, 20)),
+    "the guess on the edge of its bin": (65030, (64641, 64639), (4, 20)),
+}
+
+
+def test_threshold_below_the_window():
+    d, k, n = 18 * TILE - 3728, 4, len(WINDOW_CASES)
+    print(f"[case] thresholds below the window of fine bins, d={d} n={n}", flush=True)
+    gpu, ora = sparse_pair(d, n, k, "ef")
+    r = np.random.default_rng(5)
+    guesses, foot = {}, {}
+
+    def fn(t):
+        if t == 2:
+            guesses.update({i: gpu.get_selection_info(i)["next_guess"] for i in range(n)})
+        g = np.zeros((n, d), dtype=f32)
+        for i, (second, bins, sizes) in enumerate(WINDOW_CASES.values()):
+            top = [65224, second][t] if t < 2 else 0
+            fine = np.repeat(bins, sizes) if t == 2 else np.repeat(top, k if t < 2 else 0)
+            at = r.choice(d, fine.size + 1, replace=False)
+            low = r.integers(1, 1 << 14, fine.size)
+            g[i, at[1:]] = ((fine.astype(np.uint32) << np.uint32(14)) + low.astype(np.uint32)).view(f32)
+            if i in foot:
+                g[i, foot[i][0]] -= foot.pop(i)[1]
+            if t < 2:
+                foot[i] = at[0], np.uint32((top & ~63) << 14).view(f32)
+                g[i, foot[i][0]] += foot[i][1]
+        return g
+    for t in range(5):
+        sparse_steps(gpu, ora, lambda _: fn(t), 1, "ef", f"step {t}")
+        for i, name in enumerate(WINDOW_CASES):
+            info = gpu.get_selection_info(i)
+            if t == 2:                         # the case is what it says: listed, and only the coarse bin known at first
+                assert info["relisted"] == 0 and info["open_bits"] == 20, (name, info)
+                assert info["threshold_fine_bin"] >= guesses[i], (name, info, guesses[i])
+    gpu.destroy()
+
+
+# the same for Rand-k, whose slack is that wide where k is large: draws found on the host in which exactly k scores reach
+# the guess and the k-th lies in the guess's coarse bin (worker 3 at the second step, worker 7 at the third)
+@pytest.mark.parametrize("seed,n,steps", [(111, 4, 3), (63, 8, 4)])
+@pytest.mark.parametrize("method", ["ef", "naive", "cd"])
+def test_randk_threshold_below_the_window(method, seed, n, steps):
+    d, k = 70_000, 20_000
+    print(f"[case] Rand-k thresholds below the window, {method} seed={seed}", flush=True)
+    gpu, ora = sparse_pair(d, n, k, method, P.RANDK)
+    gpu.set_rand(seed)
+    ora.set_rand(seed)
+    sparse_steps(gpu, ora, grads_of(seed, n, d), steps, method, f"seed {seed}")
+    gpu.destroy()
+
+
 # CD-Adam on a vector long enough for more than 64 candidate regions on the server, with a drop that makes every
 # selection list anew
 def test_cd_lists_anew_on_a_long_vector():
