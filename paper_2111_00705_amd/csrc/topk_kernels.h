@@ -211,7 +211,8 @@ struct FirstDigit {
 };
 constexpr uint32_t kTieBins = kBinsFirst / 4;      // per value of the top open bit
 constexpr int kTieBits = kFirstBits - 2;
-static_assert(kFineShift - 1 - kTieBits >= 0, "magnitudes of a half in kTieBins bins");
+constexpr int kRestShift = kFineShift - 1 - kTieBits;      // magnitude bits below the digit of the others
+static_assert(kRestShift >= 0, "magnitudes of a half in kTieBins bins");
 static_assert(kShift1 - kFirstBits <= kFineShift, "a first digit below a coarse bin lies in one fine bin");
 __device__ __forceinline__ FirstDigit first_digit(const TkGeom &ge, uint32_t pshift)
 {
@@ -223,17 +224,30 @@ __device__ __forceinline__ uint32_t digit_of(const FirstDigit &f, uint64_t comp)
     const uint32_t open = (uint32_t)(comp >> f.idx_bits) & ((1u << kFineShift) - 1u);
     const uint32_t half = open >> (kFineShift - 1), low = open & ((1u << (kFineShift - 1)) - 1u);
     const uint32_t inv = (uint32_t)comp & (uint32_t)((1ull << f.idx_bits) - 1ull);
-    // vectors of this selection have more than kShortBatch tiles: idx_bits > kTieBits
-    return half * 2u * kTieBins + (low == 0u ? inv >> (f.idx_bits - kTieBits) : kTieBins + ((low - 1u) >> (kFineShift - 1 - kTieBits)));
+    return half * 2u * kTieBins + (low == 0u ? inv >> (f.idx_bits - kTieBits) : kTieBins + (low >> kRestShift));
+}
+// The bits of comp, above the `open` lowest, that all elements with that digit under the prefix share; no element of a greater
+// digit does.  (Ties share those of the smallest other magnitudes, which are greater: an element's rank from the top among those
+// with its digit is its rank among those with these bits.)
+struct DigitBits {
+    uint64_t prefix;
+    int open;
+};
+__device__ __forceinline__ DigitBits digit_bits(const FirstDigit &f, uint32_t prefix, uint32_t digit)
+{
+    if (!f.split) return {((uint64_t)prefix << kFirstBits) | digit, f.s_lo};
+    const uint32_t half = digit / (2u * kTieBins), rest = digit % (2u * kTieBins);
+    const uint64_t top = (uint64_t)prefix << 1 | half;
+    if (rest < kTieBins) return {top << (kFineShift - 1 + kTieBits) | rest, f.idx_bits - kTieBits};
+    return {top << kTieBits | (rest - kTieBins), f.idx_bits + kRestShift};
 }
 // The smallest comp of that digit under the prefix.
 __device__ __forceinline__ uint64_t digit_edge(const FirstDigit &f, uint32_t prefix, uint32_t digit)
 {
-    if (!f.split) return (((uint64_t)prefix << kFirstBits) | digit) << f.s_lo;
-    const uint32_t half = digit / (2u * kTieBins), rest = digit % (2u * kTieBins);
-    const uint32_t low = rest < kTieBins ? 0u : ((rest - kTieBins) << (kFineShift - 1 - kTieBits)) + 1u;
-    const uint64_t key = ((uint64_t)prefix << kFineShift) | (half << (kFineShift - 1)) | low;
-    return (key << f.idx_bits) | (rest < kTieBins ? (uint64_t)rest << (f.idx_bits - kTieBits) : 0ull);
+    const DigitBits b = digit_bits(f, prefix, digit);
+    // the others' first digit begins above the ties
+    const bool above_ties = f.split && digit % (2u * kTieBins) == kTieBins;
+    return (b.prefix << b.open) + (above_ties ? 1ull << f.idx_bits : 0ull);
 }
 
 // Finds, in a histogram held in LDS (`bins` counters, a multiple of the workgroup size), the bin
@@ -1435,37 +1449,32 @@ struct ResolveLds {
 // Tc - right when every element of the vector that could fall into that bin is among the cnt delivered (a digit of
 // tk_compact's threshold bin lies in one fine bin, and those are listed whole), wrong when the elements are only those above some bound that may cut the bin
 // (the list of tk_small_select): then the search goes on to the k-th largest comp value itself.
-// have_first: the first digit has kFirstBits bits and its counts are in L.lh[0 .. kBinsFirst) already (with a
-// barrier after them); the first scan is not made.
 template <bool kWholeBins = true, class Fetch>
 __device__ __forceinline__ uint64_t resolve_digits(Fetch fetch, uint32_t cnt, uint64_t prefix, uint32_t rank, int s_hi,
-                                                   ResolveLds &L, bool have_first = false)
+                                                   ResolveLds &L)
 {
     const int tid = threadIdx.x;
     const int nt = (int)blockDim.x;
     uint64_t tc = prefix << s_hi;
     bool done = false;
     while (!done) {
-        const int s_lo = max(s_hi - (have_first ? kFirstBits : kDigitBits), 0);
+        const int s_lo = max(s_hi - kDigitBits, 0);
         const uint32_t mask = (1u << (s_hi - s_lo)) - 1u;
-        if (!have_first) {
-            for (int b = tid; b < kBins2; b += nt) L.lh[b] = 0;
-            __syncthreads();
-            for (uint32_t qb = 0; qb < cnt; qb += kScanUnroll * nt) {
-                uint32_t q[kScanUnroll];
-                uint64_t comp[kScanUnroll];
+        for (int b = tid; b < kBins2; b += nt) L.lh[b] = 0;
+        __syncthreads();
+        for (uint32_t qb = 0; qb < cnt; qb += kScanUnroll * nt) {
+            uint32_t q[kScanUnroll];
+            uint64_t comp[kScanUnroll];
 #pragma unroll
-                for (int u = 0; u < kScanUnroll; ++u) q[u] = qb + u * nt + tid;
-                fetch(q, comp);                                 // independent loads: all in flight at once
+            for (int u = 0; u < kScanUnroll; ++u) q[u] = qb + u * nt + tid;
+            fetch(q, comp);                                     // independent loads: all in flight at once
 #pragma unroll
-                for (int u = 0; u < kScanUnroll; ++u)
-                    if (q[u] < cnt && (comp[u] >> s_hi) == prefix)
-                        atomicAdd(&L.lh[(uint32_t)(comp[u] >> s_lo) & mask], 1u);
-            }
-            __syncthreads();
+            for (int u = 0; u < kScanUnroll; ++u)
+                if (q[u] < cnt && (comp[u] >> s_hi) == prefix)
+                    atomicAdd(&L.lh[(uint32_t)(comp[u] >> s_lo) & mask], 1u);
         }
-        find_rank_bin(L.lh, L.part, L.res, have_first ? kBinsFirst : kBins2, rank);
-        have_first = false;
+        __syncthreads();
+        find_rank_bin(L.lh, L.part, L.res, kBins2, rank);
         if (!L.res[3]) break;                                  // cannot happen: rank <= matching elements
         prefix = (prefix << (s_hi - s_lo)) | L.res[0];
         rank -= L.res[1];
@@ -1848,7 +1857,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
                     for (int u = 0; u < kScanUnroll; ++u) comp[u] = q[u] < left ? U.pieces.staged[q[u]] : 0ull;
                 };
                 tc = resolve_digits(staged, left, prefix1, rank1, s_lo, L);
-            } else {
+            } else if (found) {
                 int top = 1;
                 while (2 * top < regions) top *= 2;
                 auto fetch = [&](const uint32_t (&q)[kScanUnroll], uint64_t (&comp)[kScanUnroll]) {
@@ -1875,7 +1884,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
                     for (int u = 0; u < kScanUnroll; ++u)
                         comp[u] = composite(sel_key(sk, __uint_as_float(e[u].y), e[u].x), e[u].x, ge.idx_bits);
                 };
-                tc = resolve_digits(fetch, cnt, w.prefix, w.rank, s_hi, L, true);
+                tc = resolve_digits(fetch, cnt, prefix1, rank1, s_lo, L);
             }
         }
     } else if (!w.whole) {
@@ -1946,7 +1955,8 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
             const FirstDigit fd = first_digit(ge, w.pshift);
             find_rank_bin(L.lh, L.part, L.res, kBinsFirst, w.rank);          // barriers since L.lh was filled
             const uint32_t digit = L.res[0], left = L.res[2], rank1 = w.rank - L.res[1];
-            const bool found = L.res[3] != 0u;
+            const bool found = L.res[3] != 0u;                                // always: rank <= elements under the prefix
+            const DigitBits known = digit_bits(fd, w.prefix, digit);
             if (found && left == rank1) {
                 tc = digit_edge(fd, w.prefix, digit);                         // all with this digit are kept
             } else if (found && left <= (uint32_t)min(kFew, kResolveThreads)) {
@@ -2027,10 +2037,10 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
 #pragma unroll
                     for (int u = 0; u < kScanUnroll; ++u) comp[u] = q[u] < left ? U.pieces.staged[q[u]] : 0ull;
                 };
-                // (a bin of the further digits may hold elements of another first digit, which are not among these)
-                tc = resolve_digits<false>(staged, left, w.prefix, rank1, s_hi, L);
-            } else {
-                tc = resolve_digits(fetch, cnt, w.prefix, w.rank, s_hi, L, !fd.split);
+                // (a bin of the further digits may hold ties, which are not among the smallest other magnitudes)
+                tc = resolve_digits<false>(staged, left, known.prefix, rank1, known.open, L);
+            } else if (found) {
+                tc = resolve_digits(fetch, cnt, known.prefix, rank1, known.open, L);
             }
         }
     }
@@ -2068,6 +2078,7 @@ constexpr int kSmallTiles = 16;
 // vectors / exact_select at every miss / this: naive 46.8 / 48.1 / 36.9, CD-Adam 74.4 / 129.0 / 67.8; fresh gradients, n = 32,
 // d = 60 000: naive 55.0 / 59.0 / 45.2, error feedback (which had exact_select before) 69.6 / 65.9 / 52.5.
 constexpr int kShortBatch = 4;
+static_assert((int64_t)kShortBatch * kTile >= (int64_t)1 << kTieBits, "digit_of: longer vectors have at least kTieBits index bits");
 constexpr int kRankAll = 128;     // a list of at most this many entries is ranked as it is, without digits (Rand-k under error
                                   // feedback, n = 8, d = 5000, k = 50: 34.3 -> 32.2 us; at 200 to 256 entries digits are
                                   // faster, d = 20 000, k = 200: 33.9 ranked, 33.5)
