@@ -1748,6 +1748,10 @@ __device__ __forceinline__ uint64_t exact_select(const ExactSource &es, const Tk
 // xs: the stored rows under error feedback with magnitude keys (where zeros are counted instead of listed and
 // the threshold may lie among them), else null.  es: how the compressed vector is re-formed, for a worker whose
 // lists did not fit.
+//
+// Bound by latency: one workgroup per vector, and its instructions come from memory after every long pass.  The branches that
+// a usual step does not take are marked, so that what it runs lies together (us, unmarked / marked, teams of 8 in both:
+// n = 8, d = 110 M, k = 0.1 % 9.0 / 8.0, n = 16, d = 11.2 M, k = 1 % 7.9 / 7.1, Rand-k n = 16, d = 1.2 M 5.5 / 4.8).
 __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorker *__restrict__ ws,
                                                               const uint64_t *__restrict__ dense,
                                                               const uint2 *__restrict__ dense_dir,
@@ -1794,12 +1798,12 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
     const int s_hi = (int)w.pshift + ge.idx_bits;
     uint64_t tc = (uint64_t)w.prefix << s_hi;
     const uint4 *dir_row = tile_dir + (int64_t)i * ge.n_tiles;
-    if (w.overflow2) {
+    if (__builtin_expect(w.overflow2 != 0u, 0)) {
         tc = exact_select(es, ge, i, cand, tile_dir, L, U.exact);
         if (tid == 0) ws[i].whole = kExact;          // for the records (comp_ams_get_selection_info)
-    } else if (w.whole == kZeroTail) {
+    } else if (__builtin_expect(w.whole == kZeroTail, 0)) {
         tc = zero_tail_threshold(dir_row, xs + (int64_t)i * ge.ld, ge, w.rank, L);
-    } else if (w.relisted && !w.whole) {
+    } else if (__builtin_expect(w.relisted && !w.whole, 0)) {
         // Lists made anew: the elements under the prefix stand in the worker's regions among those above it.  The first
         // digit is known as in the usual case; the elements under it are collected in LDS (one pass over the regions, a
         // region per wavefront) and searched there, or, where they are too many, found by digits over all regions.
@@ -1887,7 +1891,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
                 tc = resolve_digits(fetch, cnt, prefix1, rank1, s_lo, L);
             }
         }
-    } else if (!w.whole) {
+    } else if (__builtin_expect(!w.whole, 1)) {
         // tk_compact counted the first digit below the prefix while it copied: take its counts
         L.lh[tid] = first_count;
         const uint64_t *wdense = dense + region_base(ge, i, 0);
@@ -1943,7 +1947,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
 #pragma unroll
             for (int u = 0; u < kScanUnroll; ++u) comp[u] = wdense[at[u]];
         };
-        if (xs != nullptr && w.prefix == 0u && w.rank > cnt)
+        if (__builtin_expect(xs != nullptr && w.prefix == 0u && w.rank > cnt, 0))
             // the threshold bin is the one of the smallest keys and the k-th largest lies below its listed
             // (non-zero) elements: among the zeros
             tc = zero_tail_threshold(dir_row, xs + (int64_t)i * ge.ld, ge, w.rank - cnt, L);
@@ -1951,15 +1955,14 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
             // The first digit below the prefix from tk_compact's counts.  Usually at most kFew elements carry it:
             // they sit in at most as many pieces, which the pieces' bitmaps name, so only those pieces are read
             // (a few hundred elements instead of the whole threshold bin) and the elements ranked directly.
-            constexpr int kTeam = 8, kTeams = kResolveThreads / kTeam;
+            constexpr int kTeam = 16, kTeams = kResolveThreads / kTeam;
             const FirstDigit fd = first_digit(ge, w.pshift);
             find_rank_bin(L.lh, L.part, L.res, kBinsFirst, w.rank);          // barriers since L.lh was filled
             const uint32_t digit = L.res[0], left = L.res[2], rank1 = w.rank - L.res[1];
             const bool found = L.res[3] != 0u;                                // always: rank <= elements under the prefix
-            const DigitBits known = digit_bits(fd, w.prefix, digit);
-            if (found && left == rank1) {
+            if (__builtin_expect(found && left == rank1, 0)) {
                 tc = digit_edge(fd, w.prefix, digit);                         // all with this digit are kept
-            } else if (found && left <= (uint32_t)min(kFew, kResolveThreads)) {
+            } else if (__builtin_expect(found && left <= (uint32_t)min(kFew, kResolveThreads), 1)) {
                 if (tid == 0) {
                     U.pieces.n_plist = 0;
                     L.n_few = 0;
@@ -1974,16 +1977,23 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
                 }
                 __syncthreads();
                 const uint32_t n_listed = min(U.pieces.n_plist, (uint32_t)kFew);   // <= left: each names an element
-                // a piece per team of 8 lanes: a piece holds a handful of the bin's elements (a piece per wavefront took its 16
-                // wavefronts through the pieces one after the other, a memory latency each)
+                // A piece per team of 16 lanes, four loads of a lane in flight: where few pieces are named they are read in one
+                // round trip, and where many are (ties) the teams take them at once.  us, n = 8, d = 110 M without ties, and
+                // n = 16, d = 11.2 M bf16: a piece per wavefront 8.4 and 13.9, teams of 8 with four loads 8.0 and 10.2, teams of 16
+                // with one load 7.9 and 10.2, with four 7.4 and 10.5.
                 for (uint32_t q = tid / kTeam; q < n_listed; q += kTeams) {
                     const uint32_t p = U.pieces.plist[q];
                     const uint32_t first = rstart[p], count = rpre[p + 1] - rpre[p];
-                    for (uint32_t e = tid % kTeam; e < count; e += kTeam) {
-                        const uint64_t comp = wdense[first + e];
-                        if (digit_of(fd, comp) == digit) {
-                            const uint32_t slot = atomicAdd(&L.n_few, 1u);
-                            if (slot < (uint32_t)kFew) L.few[slot] = comp;
+                    for (uint32_t e = tid % kTeam; e < count; e += 4 * kTeam) {
+                        uint64_t comp[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) comp[u] = wdense[first + min(e + u * kTeam, count - 1u)];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            if (e + u * kTeam < count && digit_of(fd, comp[u]) == digit) {
+                                const uint32_t slot = atomicAdd(&L.n_few, 1u);
+                                if (slot < (uint32_t)kFew) L.few[slot] = comp[u];
+                            }
                         }
                     }
                 }
@@ -1998,7 +2008,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
                 tc = L.tc_sh;
             } else if (found && left <= (uint32_t)kStaged) {
                 // Many elements under the first digit, for instance ties by the hundred thousand.  The
-                // elements are collected in LDS once, a piece per team of 8 lanes and four pieces of a team in flight,
+                // elements are collected in LDS once, a piece per team of lanes and four pieces of a team in flight,
                 // and the further digits scan LDS; through the piece table every digit was a scan of the whole bin.
                 const int team = tid / kTeam, tl = tid % kTeam;
                 if (tid == 0) L.n_few = 0;
@@ -2037,14 +2047,16 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
 #pragma unroll
                     for (int u = 0; u < kScanUnroll; ++u) comp[u] = q[u] < left ? U.pieces.staged[q[u]] : 0ull;
                 };
+                const DigitBits known = digit_bits(fd, w.prefix, digit);
                 // (a bin of the further digits may hold ties, which are not among the smallest other magnitudes)
                 tc = resolve_digits<false>(staged, left, known.prefix, rank1, known.open, L);
             } else if (found) {
+                const DigitBits known = digit_bits(fd, w.prefix, digit);
                 tc = resolve_digits(fetch, cnt, known.prefix, rank1, known.open, L);
             }
         }
     }
-    if (w.relisted) {                                          // tk_compact was the last reader of the full histogram
+    if (__builtin_expect(w.relisted != 0u, 0)) {               // tk_compact was the last reader of the full histogram
         if (tid < ge.slices) cursor_b[(i * ge.slices + tid) * kCursorStride] = 0;
         for (int q = tid; q < kBins1; q += kResolveThreads) hist_full[(int64_t)i * kBins1 + q] = 0;
     }
