@@ -891,10 +891,10 @@ int step_plain(comp_ams *h, const G *g, hipStream_t st)
     const int n_quarters = (int)(h->ld / kPlainCoords);
     const int chunk = plain_chunk(h->chunk_choice, n_quarters);
     launch_timed(h, P_PLAIN_UPDATE, st, [&] {
-        by_flag(h->params.stream_state, [&](auto ss) {
-            KLAUNCH((plain_update<G, decltype(ss)::value>), grid_blocks(n_quarters, chunk), kThreads, st, g, h->d, h->n,
-                    h->theta, h->m, h->v, h->vhat, h->params, chunk, n_quarters);
-        });
+        by_flag(h->params.stream_state, [&](auto ss) { by_flag(plain_rows_ahead(h->n, h->d, sizeof(G)) == 2, [&](auto two) {
+            KLAUNCH((plain_update<G, decltype(ss)::value, sizeof(G) == 2 && decltype(two)::value ? 2 : 1>), grid_blocks(n_quarters, chunk), kThreads,
+                    st, g, h->d, h->n, h->theta, h->m, h->v, h->vhat, h->params, chunk, n_quarters);
+        }); });
     });
     return COMP_AMS_OK;
 }

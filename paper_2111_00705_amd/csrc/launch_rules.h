@@ -43,4 +43,16 @@ inline int plain_chunk(int choice, int n_quarters)
     return chunk < n_quarters ? chunk : n_quarters;
 }
 
+// Workers' rows of which the update without compression has a load in flight at a time.  16-bit gradients: two where one leaves
+// few bytes in flight, on vectors below 8 Mi coordinates, and up to 16 Mi where the rows of more than eight workers are most of
+// what is read; beyond, where the chip streams from memory all the time, two lose.  Step plus get_theta, us, one / two: n = 2,
+// d = 1 M 23.9 / 23.6, 4 M 43.9 / 43.0, 14 M 110.9 / 111.5, 60 M 446 / 450; n = 4, 1 M 24.9 / 24.1, 8 M 76.5 / 76.5, 11.2 M 99.9 / 100.8,
+// 14 M 118.6 / 119.9, 60 M 484 / 484; n = 8, 1 M 27.0 / 25.5, 8 M 87.6 / 86.5, 14 M 137.1 / 137.7, 30 M 281.6 / 288.1, 60 M 559 / 574;
+// n = 16, 1 M 31.2 / 29.8, 8 M 109.1 / 107.0, 11.2 M 150.0 / 147.9, 15.9 M 198.5 / 197.2, 18 M 220.9 / 219.2, 30 M 361 / 372; n = 32, 1 M
+// 39.8 / 38.4, 11.2 M 216.9 / 210.5.  (Four at a time, n = 16: 1.2 M 38.0 against 38.3, 11.2 M 155.2 against 149.6.)
+inline int plain_rows_ahead(int64_t n, int64_t d, int bytes_per_gradient)
+{
+    return bytes_per_gradient == 2 && d < ((int64_t)(n > 8 ? 16 : 8) << 20) ? 2 : 1;
+}
+
 }  // namespace cams

@@ -8,7 +8,7 @@
 // four workers in flight (three sets of buffers in turn, us): n = 16, d = 11.2 M bf16 172 -> 125, fp32 188 -> 182;
 // n = 32, d = 25.6 M bf16 529 -> 425, fp32 734 -> 725; n = 8, d = 110 M bf16 912 -> 888, fp32 1.25 -> 1.23 ms;
 // n = 16, d = 1.2 M bf16 49 -> 22, fp32 33 -> 24.  Batches of 2 to 16 rows in flight lose up to 10 % on fp32 (16 bits:
-// see sum_rows); eight 16-bit gradients per lane (16-byte loads) take twice as long, because the state is then
+// see plain_rows_ahead); eight 16-bit gradients per lane (16-byte loads) take twice as long, because the state is then
 // written in half lines.
 #pragma once
 #include "device_utils.h"
@@ -17,10 +17,8 @@ namespace cams {
 
 constexpr int kPlainCoords = 4 * kThreads;   // coordinates per workgroup: a quarter of a tile
 
-// acc += the coordinates j .. j + 3 of the n rows, in ascending order.  16-bit rows are loaded two at a time: step plus
-// get_theta, one / two / four at a time, us: n = 16, bf16 d = 1.2 M 39.7 / 38.3 / 38.0, d = 11.2 M 152.0 / 149.6 / 155.2; n = 4, f16
-// d = 50 M 408.6 / 411.0 / 416.7.
-template <bool kInside, typename G>
+// acc += the coordinates j .. j + 3 of the n rows, in ascending order, kAhead rows loaded at a time (see plain_rows_ahead).
+template <bool kInside, int kAhead, typename G>
 __device__ __forceinline__ void sum_rows(float4 &acc, const G *__restrict__ row, int64_t j, int64_t d, int n)
 {
     auto add = [&](const float4 &x) {
@@ -29,7 +27,6 @@ __device__ __forceinline__ void sum_rows(float4 &acc, const G *__restrict__ row,
         acc.z = fadd(acc.z, x.z);
         acc.w = fadd(acc.w, x.w);
     };
-    constexpr int kAhead = sizeof(G) == 2 ? 2 : 1;
     int i = 0;
 #pragma unroll 1
     for (; i + kAhead <= n; i += kAhead, row += kAhead * d) {
@@ -43,7 +40,7 @@ __device__ __forceinline__ void sum_rows(float4 &acc, const G *__restrict__ row,
     for (; i < n; ++i, row += d) add(widen4(load_raw4<kInside>(row, j, d)));
 }
 
-template <typename G, bool kStreamState>   // G: float, uint16_t (bfloat16 bits) or f16bits
+template <typename G, bool kStreamState, int kAhead>   // G: float, uint16_t (bfloat16 bits) or f16bits
 __global__ __launch_bounds__(kThreads) void plain_update(const G *__restrict__ g, int64_t d, int n,
                                                          float *__restrict__ theta, float *__restrict__ m,
                                                          float *__restrict__ v, float *__restrict__ vhat, AmsParams p, int chunk,
@@ -54,9 +51,9 @@ __global__ __launch_bounds__(kThreads) void plain_update(const G *__restrict__ g
     const int64_t j = (int64_t)t * kPlainCoords + 4 * threadIdx.x;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     if (((int64_t)t + 1) * kPlainCoords <= d)
-        sum_rows<true>(acc, g, j, d, n);
+        sum_rows<true, kAhead>(acc, g, j, d, n);
     else
-        sum_rows<false>(acc, g, j, d, n);
+        sum_rows<false, kAhead>(acc, g, j, d, n);
     float4 th = ld4_state<kStreamState>(theta + j), mm = ld4_state<kStreamState>(m + j),
            vv = ld4_state<kStreamState>(v + j), vh = ld4_state<kStreamState>(vhat + j);
     // padding coordinates take no gradient (load_raw4 gives 0 past d)

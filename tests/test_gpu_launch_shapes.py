@@ -5,7 +5,7 @@ import pytest
 
 import paper_2111_00705_amd as P
 from oracle import oracle as O
-from parity_util import STATE_RTOL, make_pair, rel_close, run_steps
+from parity_util import STATE_RTOL, bits, make_pair, rel_close, run_steps
 
 pytestmark = pytest.mark.gpu
 f32 = np.float32
@@ -55,6 +55,27 @@ def test_uncompressed_at_quarter_tiles(d, n):
                             ("vhat", gpu.get_vhat(), ora.vhat)):
         assert rel_close(got, want, STATE_RTOL).all(), name
     gpu.destroy()
+
+
+# 16-bit gradients on both sides of the line between two rows in flight and one: the fp32 entry point, which always has one,
+# gives the same bits for the widened values
+@pytest.mark.parametrize("n,d", [(1, 2**23 - 1), (3, 2**23 - 1), (3, 2**23), (9, 2**23), (9, 2**24 - 1), (9, 2**24)])
+def test_uncompressed_16_bit_rows_in_flight(n, d):
+    import torch
+    print(f"[case] no compression, 16-bit gradients, d={d} n={n}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(d + n)
+    for dtype, entry in ((torch.bfloat16, "step_bf16"), (torch.float16, "step_f16")):
+        narrow, wide = (P.CompAms(d, n, P.TOPK, 1) for _ in range(2))
+        for h in (narrow, wide):
+            h.set_method(P.METHOD_NONE)
+        for _ in range(2):
+            g = torch.randn((n, d), device="cuda", generator=gen).to(dtype)
+            getattr(narrow, entry)(g)
+            wide.step(g.float())
+        for name in ("get_theta", "get_m", "get_v", "get_vhat"):
+            assert np.array_equal(bits(getattr(narrow, name)()), bits(getattr(wide, name)())), (name, dtype)
+        narrow.destroy()
+        wide.destroy()
 
 
 # short blocks (a power of two below a tile): butterfly sums inside a wavefront, across the wavefronts of a row, across rows;

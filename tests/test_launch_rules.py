@@ -50,3 +50,10 @@ def test_uncompressed_update_pads_its_grid_to_no_more_than_eight_vectors(tmp_pat
         asked = blocks if wanted <= 0 else (q + 8 * wanted - 1) // (8 * wanted) * 8 * wanted
         assert sorted(t for _, t in order(ch, blocks)) == list(range(q))
         assert order(ch, blocks) == order(wanted, asked)
+
+
+def test_uncompressed_update_loads_two_rows_at_a_time_on_short_16_bit_vectors_alone(tmp_path):
+    cases = {(1, 1, 2): 2, (8, 2**23 - 1, 2): 2, (8, 2**23, 2): 1, (9, 2**23, 2): 2, (9, 2**24 - 1, 2): 2, (9, 2**24, 2): 1,
+             (32, 60_000_000, 2): 1, (1, 1, 4): 1, (16, 2**23, 4): 1, (16, 2**24, 4): 1}
+    got = evaluate(tmp_path, [f"plain_rows_ahead({n}, {d}, {size})" for n, d, size in cases])
+    assert got == list(cases.values())
