@@ -844,8 +844,12 @@ __global__ __launch_bounds__(kThreads) void tk_final(TkGeom ge, const TkWorker *
 // kBatch workers at a time then go to a row of LDS each, with a bit per coordinate, and every thread adds its own
 // coordinates in ascending worker order.  A wavefront that went through the lists
 // worker by worker, eight workers' candidates in flight, each of the four for its own row, took (step plus get_theta, us, that / this)
-// Rand-k n = 16, d = 1.2 M f16 84.5 / 81.6, n = 48, d = 200 000 with 5 % kept 84.2 / 81.6, Top-k n = 16, d = 1.2 M 89.9 / 88.5,
-// n = 20, d = 600 000 with 5 % kept bf16 82.4 / 79.6, n = 2, d = 1.3 M 45.8 / 45.4; n = 4, d = 65 536 the same.
+// Rand-k n = 16, d = 1.2 M f16 89.8 / 80.9, d = 300 000 with 20 % kept 80.6 / 66.5, n = 32, d = 21 000 f16 44.9 / 37.0, Top-k n = 16,
+// d = 1.2 M 91.0 / 86.9, n = 48, d = 200 000 with 5 % kept 93.2 / 81.4, n = 20, d = 600 000 with 5 % kept bf16 87.6 / 74.2, n = 2,
+// d = 1.3 M 52.5 / 51.6, n = 4, d = 65 536 33.0 / 32.8 (the whole step's gain where other kernels changed as well).  The bits are cleared
+// before the first barrier and the search for an entry's worker takes as many steps as n or the batch needs: with six steps
+// for any n and a barrier more, the smallest vectors lost (n = 4, d = 730 bf16 27.6 -> 27.9, now 27.7; naive d = 994 26.1 -> 26.3,
+// now 26.1; n = 48 above 84.6, 20 % kept 69.1).
 constexpr int kShortHeld = 2;         // candidates a thread holds from the start
 template <bool kStreamState, int kBatch>   // kBatch: workers whose kept values are in LDS at a time
 __global__ __launch_bounds__(kThreads) void tk_final_short(TkGeom ge, const TkWorker *__restrict__ ws,
@@ -866,6 +870,7 @@ __global__ __launch_bounds__(kThreads) void tk_final_short(TkGeom ge, const TkWo
     const int64_t j = (int64_t)base + 1024 * r + 256 * w + 4 * lane;
     float4 th = ld4_state<kStreamState>(theta + j), mm = ld4_state<kStreamState>(m + j),
            vv = ld4_state<kStreamState>(v + j), vh = ld4_state<kStreamState>(vhat + j);
+    for (int q = tid; q < kBatch * kWave; q += kThreads) (&kept[0][0])[q] = 0u;
     if (r == 0) {
         // lane i: where worker i keeps the quarter's candidates, and its threshold
         uint32_t count = 0;
@@ -893,14 +898,16 @@ __global__ __launch_bounds__(kThreads) void tk_final_short(TkGeom ge, const TkWo
     }
     __syncthreads();
     const uint32_t total = upto[ge.n];
-    // the worker of entry q of the quarter: the last one whose entries start at or before it
-    auto owner = [&](uint32_t q) {
-        int i = 0;
+    // The worker of entry q < total of the quarter is the last one whose entries start at or before it (upto[ge.n] = total lies
+    // beyond every q).  A thread's first entries are looked for together, those of a batch among its workers.
+    auto last_before = [&](int i, int bit, uint32_t q) { return upto[min(i + bit, ge.n)] <= q ? i + bit : i; };
+    auto owner = [&](uint32_t q, int w0) {
+        int i = w0;
 #pragma unroll
-        for (int bit = 32; bit > 0; bit >>= 1)
-            if (i + bit < ge.n && upto[min(i + bit, kShortFinalWorkers)] <= q) i += bit;
+        for (int bit = 4; bit > 0; bit >>= 1) i = last_before(i, bit, q);
         return i;
     };
+    static_assert(kBatch <= 8, "three steps");
     auto fetch = [&](uint32_t q, int i) { return cand[worker_base(ge, i) + start[i] + (q - upto[i])]; };
     auto is_kept = [&](const uint2 &e, int i) {
         const SelKey sk = {ge.rand.on, key_a[i], key_b[i]};
@@ -914,9 +921,14 @@ __global__ __launch_bounds__(kThreads) void tk_final_short(TkGeom ge, const TkWo
     uint2 e[kShortHeld];
     int of[kShortHeld];
 #pragma unroll
+    for (int s = 0; s < kShortHeld; ++s) of[s] = 0;
+    for (int bit = ge.n > 1 ? 1 << (31 - __clz(ge.n - 1)) : 0; bit > 0; bit >>= 1)      // from the greatest power of two below n
+#pragma unroll
+        for (int s = 0; s < kShortHeld; ++s) of[s] = last_before(of[s], bit, tid + s * kThreads);
+#pragma unroll
     for (int s = 0; s < kShortHeld; ++s) {
         const uint32_t q = tid + s * kThreads;
-        of[s] = q < total ? owner(q) : -1;
+        if (q >= total) of[s] = -1;
         e[s] = make_uint2(0u, 0u);
         if (of[s] >= 0) e[s] = fetch(q, of[s]);
     }
@@ -929,22 +941,24 @@ __global__ __launch_bounds__(kThreads) void tk_final_short(TkGeom ge, const TkWo
     uint2 more_e = make_uint2(0u, 0u);
     auto read_ahead = [&](int w0) {
         more = max(upto[w0], (uint32_t)(kShortHeld * kThreads)) + tid;
-        more_of = more < upto[min(w0 + kBatch, ge.n)] ? owner(more) : -1;
+        more_of = more < upto[min(w0 + kBatch, ge.n)] ? owner(more, w0) : -1;
         if (more_of >= 0) more_e = fetch(more, more_of);
     };
     read_ahead(0);
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
     for (int w0 = 0; w0 < ge.n; w0 += kBatch) {
         const int nw = min(kBatch, ge.n - w0);
-        if (w0) __syncthreads();                             // the bits of the batch before have been read
-        for (int q = tid; q < kBatch * kWave; q += kThreads) (&kept[0][0])[q] = 0u;
-        __syncthreads();
+        if (w0) {
+            __syncthreads();                                 // the bits of the batch before have been read
+            for (int q = tid; q < kBatch * kWave; q += kThreads) (&kept[0][0])[q] = 0u;
+            __syncthreads();
+        }
 #pragma unroll
         for (int s = 0; s < kShortHeld; ++s)
             if ((uint32_t)(of[s] - w0) < (uint32_t)nw) put(e[s], of[s] - w0);
         if (more_of >= 0 && is_kept(more_e, more_of)) put(more_e, more_of - w0);
         for (uint32_t q = more + kThreads; q < upto[w0 + nw]; q += kThreads) {
-            const int i = owner(q);
+            const int i = owner(q, w0);
             const uint2 x = fetch(q, i);
             if (is_kept(x, i)) put(x, i - w0);
         }
