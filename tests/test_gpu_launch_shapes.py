@@ -130,11 +130,12 @@ def sparse_pair(d, n, k, method, compressor=P.TOPK):
     return gpu, ora
 
 
-def sparse_steps(gpu, ora, fn, steps, method, tag):
+def sparse_steps(gpu, ora, fn, steps, method, tag, dtype="float32"):
     import torch
+    step = {"float32": gpu.step, "bfloat16": gpu.step_bf16, "float16": gpu.step_f16}[dtype]
     for t in range(steps):
         g = fn(t)
-        gpu.step(torch.from_numpy(g).cuda())
+        step(torch.from_numpy(g).cuda().to(getattr(torch, dtype)))
         ora.step(g)
         for i in range(gpu.n):
             assert np.array_equal(gpu.get_selected(i)[0], ora.selected[i]), f"{tag} step {t} worker {i}: kept set"
@@ -270,6 +271,42 @@ def test_split_of_the_threshold_bin(method, crowd, k):
         g[0, at] = np.where(r.random(size) < 0.5, bits.astype(np.uint32).view(f32), -bits.astype(np.uint32).view(f32))
         return np.ascontiguousarray(g)
     sparse_steps(gpu, ora, fn, 3, method, f"{crowd} {k}")
+    gpu.destroy()
+
+
+# the same crowds as 16-bit gradients of several workers: ties at the foot of the fine bin (bfloat16) and of its upper half too
+# (half precision).  The first step keeps k values of that magnitude elsewhere, which sets the guess; the second has the crowd,
+# at every fourth index, so that a digit's share holds 512 of it: the k-th ends a share, or is one before or after that.
+@pytest.mark.parametrize("method", ["ef", "naive", "cd"])
+@pytest.mark.parametrize("dtype", ["bfloat16", "float16"])
+@pytest.mark.parametrize("crowd,k", [("run", 6 * 512), ("run", 6 * 512 - 1), ("run", 6 * 512 + 1), ("one value", 5000),
+                                     ("two values", 7001)])
+def test_split_of_the_threshold_bin_16_bit(method, dtype, crowd, k):
+    import torch
+    d, n, size = 300_003, 3, 12_000            # 19 index bits: a digit's share of the indices is 2^11
+    print(f"[case] threshold bin {crowd} {method} {dtype} k={k}", flush=True)
+    gpu, ora = sparse_pair(d, n, k, method)
+    upper = f32(1 + 2**-10) if dtype == "float16" else f32(1)         # the upper half of the fine bin that starts at 1
+
+    def fn(t):
+        r = np.random.default_rng([k, t])
+        g = torch.from_numpy(r.standard_normal((n, d), dtype=f32) * f32(1e-3)).to(getattr(torch, dtype)).float().numpy()
+        g[:, :150_000] = 0                                     # the crowd's: no error memory
+        for i in range(n):
+            if t == 0 or (t == 1 and method == "cd"):          # (CD-Adam: what was kept is subtracted)
+                g[i, d - k:] = 1
+            if t == 1:
+                # from a share's first index on, but worker 2 from inside one
+                at = 4 * np.arange(size) + (0, 2048, 1000)[i] if crowd == "run" else r.choice(150_000, size, replace=False)
+                value = np.where(r.random(size) < 0.5, f32(1), upper) if crowd == "two values" else (f32(1), upper, upper)[i]
+                g[i, at] = np.where(r.random(size) < 0.5, value, -value)
+        return np.ascontiguousarray(g)
+    for t in range(3):
+        sparse_steps(gpu, ora, lambda _: fn(t), 1, method, f"{crowd} {k} step {t}", dtype)
+        if t == 1:
+            for i in range(n):                 # the case is what it says: listed, a fine bin that more than one share fills
+                info = gpu.get_selection_info(i)
+                assert info["relisted"] == 0 and info["open_bits"] == 14 and info["whole_bin"] == 0, (i, sorted(info.items()))
     gpu.destroy()
 
 

@@ -28,6 +28,12 @@ def test_quarter_tile_update_only_where_the_lists_are_short(tmp_path):
     assert got == list(cases.values())
 
 
+def test_quarter_tile_update_holds_eight_workers_up_to_256_tiles(tmp_path):
+    cases = {1: 8, 256: 8, 257: 5, 320: 5}
+    got = evaluate(tmp_path, [f"short_final_batch({tiles})" for tiles in cases])
+    assert got == list(cases.values())
+
+
 def test_uncompressed_update_pads_its_grid_to_no_more_than_eight_vectors(tmp_path):
     quarters = [1, 4, 64, 511, 512, 977, 100_000, 2_097_152]
     choices = [-1, 0, 1, 16, 1024, 65_536]
