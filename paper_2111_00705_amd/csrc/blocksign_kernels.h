@@ -237,7 +237,9 @@ __global__ __launch_bounds__(kThreads) void bs_pass(const G *__restrict__ g, flo
         // us: blocks of 100 400 / 396, 200 385 / 380, 1000 374 / 367, bf16 blocks of 100 415 / 408; 62 layers, n = 8 188.5 / 186.7;
         // short blocks of 16 371 / 380, of 256 353 / 360
         // (ld4_row<kSmall>: with short blocks the compiler had merged the two kinds of row load, and rows that should stream were
-        // read through the caches; n = 16, d = 11.2 M, step plus get_theta 462 -> 424 us with blocks of 256, 488 -> 450 of 16)
+        // read through the caches; n = 16, d = 11.2 M, step plus get_theta, us, merged / apart: blocks of 256 462 / 429, bf16
+        // 412 / 377, of 16 488 / 454, bf16 436 / 400.  Rows that stay cached do not notice the branch: n = 16, d = 1.2 M 64.9 / 64.5 and
+        // 66.7 / 66.7, n = 8, d = 1 M 42.1 / 41.9 and 42.2 / 42.0, n = 4, d = 100 000 23.3 / 23.4 and 23.1 / 23.1)
         if (kSmall) gv[r] = load_raw4<false>(grow, j, d);
         xv[r] = kMode == kBsNaive ? make_float4(0.f, 0.f, 0.f, 0.f) : ld4_row<kSmall>(xrow + j, tb.stream_rows);
         if (!kSmall) gv[r] = load_raw4<false>(grow, j, d);
@@ -511,7 +513,8 @@ __global__ __launch_bounds__(kThreads) void bs_server(int64_t d, int64_t ld, int
     // All four rows' loads go out before the first row is stored, and below the next row's state before a row is stored: the
     // compiler does not take a load past a store that might write what it reads, and a workgroup waited for memory row by
     // row.  Step plus get_theta, us, before / after: whole-vector sign n = 8, d = 11.2 M 319.6 / 317.6, n = 4, d = 30 M bf16 539 /
-    // 532, 62 layers n = 8 bf16 310.6 / 306.6, blocks of 4096 n = 8, d = 8 M 219.5 / 216.2, n = 4, d = 60 000 28.4 / 27.8.
+    // 532, 62 layers n = 8 bf16 310.6 / 306.6, blocks of 4096 n = 8, d = 8 M 219.5 / 216.2, n = 4, d = 60 000 28.4 / 27.8.  The
+    // one-launch form pays for it with 104 registers instead of 77, four wavefronts per SIMD instead of five.
     float4 gh_row[4], gt_row[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {

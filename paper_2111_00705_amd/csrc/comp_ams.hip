@@ -192,9 +192,9 @@ inline int xcd_chunk_for(const comp_ams *h)
 // the choice below): rows of 11 M coordinates, n = 8, 12, 16, 24, 32: 179 / 173, 266 / 259, 353 / 341, 527 / 513,
 // 700 / 688 us with five workgroups per unit and chunks of 8 tiles (chunks of 4, 12 or 32 lose, 16 gains half as
 // much); 25 M coordinates, n = 16: 783 / 763 us; rows of 64 Mi coordinates or more want four workgroups
-// (n = 8, d = 110 M: 1.68 ms against 1.69-1.71 ms with five; n = 4: 846-850 against 860 us) and the same chunks (step plus get_theta,
-// chunks of 16 / 8, us: n = 8, d = 110 M 2375 / 2347, n = 4, d = 70 M 1000 / 998, Rand-k n = 8, d = 70 M 1523 / 1525; bfloat16 n = 8,
-// d = 110 M 2098 / 2083).
+// (n = 8, d = 110 M: 1.68 ms against 1.69-1.71 ms with five; n = 4: 846-850 against 860 us) and the same chunks (step plus get_theta of
+// one handle, in turn in one process, chunks of 16 / 8, us: n = 8, d = 110 M 2371 / 2340, bfloat16 2108 / 2092, n = 2 1116 / 1119, n = 4,
+// d = 70 M 1001 / 996, Rand-k n = 8, d = 70 M 1506 / 1499; three handles in turn at n = 8, d = 110 M show no difference).
 inline bool tk_long_rows(const comp_ams *h) { return h->d >= ((int64_t)64 << 20); }
 inline int tk_ef_chunk_for(const comp_ams *h)
 {

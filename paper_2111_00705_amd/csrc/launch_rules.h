@@ -7,7 +7,9 @@ namespace cams {
 // Whether the update of kept values takes a quarter of a tile per workgroup (tk_final_short) instead of a tile (tk_final).
 // The quarter form fills the chip and loads the state first.  Up to 320 tiles its 1280 workgroups run at once.  Step plus
 // get_theta, error feedback, a tile / a quarter, us, when each of the four wavefronts of a quarter still went through all lists
-// for itself (the quarter has gained 1-4 % since with 16 workers or more): Top-k, k = 2 %, n = 2, 288 tiles 56.7 / 52.6, 384 tiles 60.6 / 60.7; n = 8, 128 tiles 56.7 / 54.7, 320 tiles
+// for itself (the quarter has gained since, 1 % of the step with 2 workers, 2-4 % with 16, up to 13 % with many kept values;
+// beyond the line it gained in places, n = 8, 342 tiles 77.0 / 72.5, and lost in others, 440 tiles 2-6 %, before its search got
+// shorter): Top-k, k = 2 %, n = 2, 288 tiles 56.7 / 52.6, 384 tiles 60.6 / 60.7; n = 8, 128 tiles 56.7 / 54.7, 320 tiles
 // 78.0 / 74.1, 352 tiles 80.9 / 81.7; n = 16, 319 tiles 106.7 / 104.6; k = 5 %, n = 24, 128 tiles 84.8 / 85.2, 200 tiles
 // 108.0 / 111.3; n = 32, 64 tiles 77.8 / 77.8, 128 tiles 101.1 / 102.2; n = 48, 64 tiles 98.2 / 98.4, 100 tiles 119.4 / 122.4;
 // Rand-k, k = 1 %, n = 16, 2 tiles 37.5 / 37.1; n = 48, 2 tiles 49.1 / 50.5, 16 tiles 57.0 / 56.2; n = 256, 5 tiles 133.4 / 150.2,
