@@ -102,6 +102,22 @@ __device__ __forceinline__ void small_block_sums(const float (&x)[4][4], int log
     }
 }
 
+// 2^-k, k below 1023: the product with it is the quotient by 2^k (sums of magnitudes of fp32 are far from fp64's subnormals).
+__device__ __forceinline__ double inverse_power(int k) { return __longlong_as_double((long long)(1023 - k) << 52); }
+
+// The scale of the short block (at most 256 coordinates: inside a wavefront's row) that holds the float4 x at coordinate j, in
+// every lane of the block; the sums in small_block_sums' order.
+__device__ __forceinline__ float short_block_scale(const float (&x)[4], const BsTable &tb, int64_t d, int64_t j)
+{
+    double S = ((double)fabsf(x[0]) + (double)fabsf(x[1])) + ((double)fabsf(x[2]) + (double)fabsf(x[3]));
+    const int lanes = 1 << (tb.small_log2 - 2);
+    for (int off = 1; off < lanes; off <<= 1) S += __shfl_xor(S, off, kWave);
+    const int64_t len = (int64_t)1 << tb.small_log2;
+    const int64_t first = j & ~(len - 1);
+    if (__all(first + len <= d)) return (float)(S * inverse_power(tb.small_log2));
+    return (float)(S / (double)max((int64_t)1, min(len, d - first)));
+}
+
 // Sign bits: per worker, per tile, one 16-bit word per thread of the workgroup.  Bit r*4 + c of
 // word `tid` is the sign of the coordinate  tile*4096 + 4*(tid + 256*r) + c,  i.e. of the c-th
 // component of the r-th float4 that thread tid handles in the tile (same mapping in bs_pass and
@@ -582,6 +598,31 @@ __global__ __launch_bounds__(kThreads) void bs_server(int64_t d, int64_t ld, int
     }
 }
 
+// Lines 8-12 of Algorithm 1 for short blocks inside a wavefront: gb, the mean of the c_i on the float4 at coordinate j, becomes
+// gtilde; ghat, gtilde and the server's scales are written.  gh4, gt4: ghat and gtilde there; blk: the float4's block.  Returns
+// the sign bits of the server's vector.
+template <bool kStreamState>
+__device__ __forceinline__ uint32_t short_server(float (&gb)[4], const float4 &gh4, const float4 &gt4, const BsMarkov &mk,
+                                                 const BsTable &tb, int64_t d, int64_t j, int blk)
+{
+    const float gh[4] = {gh4.x, gh4.y, gh4.z, gh4.w}, gt[4] = {gt4.x, gt4.y, gt4.z, gt4.w};
+    float nh[4], w[4];
+    uint32_t neg = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        nh[c] = (j + c < d) ? fadd(gh[c], gb[c]) : gh[c];          // padding coordinates stay 0
+        w[c] = (j + c < d) ? fsub(nh[c], gt[c]) : 0.f;
+        neg |= (__float_as_uint(w[c]) >> 31) << c;
+    }
+    st4_state<kStreamState>(mk.ghat + j, make_float4(nh[0], nh[1], nh[2], nh[3]));
+    const float s = short_block_scale(w, tb, d, j);
+    if ((j & (((int64_t)1 << tb.small_log2) - 1)) == 0 && j < d) mk.scales[blk] = s;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) gb[c] = (j + c < d) ? fadd(gt[c], signed_scale(s, neg, c)) : gt[c];   // gtilde
+    st4_state<kStreamState>(mk.gtil + j, make_float4(gb[0], gb[1], gb[2], gb[3]));
+    return neg;
+}
+
 // Server average and AMSGrad update, a quarter of a tile per workgroup, one float4 per thread.  Workgroup 4 t + w takes the
 // words of the threads 64 w .. 64 w + 63 of tile t, wavefront r of it their nibble r, so the four wavefronts share the
 // sign words they read.  With one float4 the registers leave room for many wavefronts, and the sign words (and scales)
@@ -749,37 +790,16 @@ __global__ __launch_bounds__(kThreads) void bs_update(int64_t d, int64_t ld, int
     float gb[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) gb[c] = j + c < d ? fdiv(acc[c], p.n_workers) : 0.f;
-    if (kMarkov) {
+    if constexpr (kMarkov) {
         const float4 gh4 = ld4_state<kStreamState>(mk.ghat + j), gt4 = ld4_state<kStreamState>(mk.gtil + j);
-        const float gh[4] = {gh4.x, gh4.y, gh4.z, gh4.w}, gt[4] = {gt4.x, gt4.y, gt4.z, gt4.w};
-        float nh[4], w[4];
-        uint32_t neg = 0;
-        double S = 0.0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            nh[c] = (j + c < d) ? fadd(gh[c], gb[c]) : gh[c];          // padding coordinates stay 0
-            w[c] = (j + c < d) ? fsub(nh[c], gt[c]) : 0.f;
-            neg |= (__float_as_uint(w[c]) >> 31) << c;
-        }
-        st4_state<kStreamState>(mk.ghat + j, make_float4(nh[0], nh[1], nh[2], nh[3]));
-        S = ((double)fabsf(w[0]) + (double)fabsf(w[1])) + ((double)fabsf(w[2]) + (double)fabsf(w[3]));
-        const int lanes = 1 << (tb.small_log2 - 2);
-        for (int off = 1; off < lanes; off <<= 1) S += __shfl_xor(S, off, kWave);
-        const int64_t len = (int64_t)1 << tb.small_log2;
-        const int64_t first = j & ~(len - 1);
-        const float s = (float)(S / (double)max((int64_t)1, min(len, d - first)));
-        if (j == first && j < d) mk.scales[blk] = s;
         // the server's sign words: the four wavefronts hold a nibble each
         __shared__ uint32_t nib[4][kWave];
-        nib[r][lane] = neg;
+        nib[r][lane] = short_server<kStreamState>(gb, gh4, gt4, mk, tb, d, j, blk);
         __syncthreads();
         if (r == 0) {
             mk.signs[(int64_t)t * kThreads + slot] =
                 (uint16_t)(nib[0][lane] | (nib[1][lane] << 4) | (nib[2][lane] << 8) | (nib[3][lane] << 12));
         }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) gb[c] = (j + c < d) ? fadd(gt[c], signed_scale(s, neg, c)) : gt[c];   // gtilde
-        st4_state<kStreamState>(mk.gtil + j, make_float4(gb[0], gb[1], gb[2], gb[3]));
     }
     if (!kEarlyState) {
         th = ld4_state<kStreamState>(theta + j);
@@ -800,6 +820,171 @@ __global__ __launch_bounds__(kThreads) void bs_update(int64_t d, int64_t ld, int
             if (j + 2 < d) theta_out[j + 2] = th.z;
         }
     }
+    st4_state<kStreamState>(m + j, mm);
+    st4_state<kStreamState>(v + j, vv);
+    st4_state<kStreamState>(vhat + j, vh);
+}
+
+// A whole step with short blocks of at most 256 coordinates in one launch, for vectors that leave the chip idle (one_launch_sign):
+// a quarter of a tile per workgroup, words and coordinates as in bs_update.  Twelve wavefronts share the (row, worker) pairs, each
+// with a row of its own; a block lies inside a row, so a worker's scale and sign bits are known where its row was read, and go
+// through LDS to four more wavefronts, which add the c_i up in ascending worker order and update the state.
+// Bound by latency: the state and kStepBatch pairs of every wavefront are in flight together, one barrier, and nothing waits for a
+// store; rows of padding are left out.
+// CD-Adam n = 20, d = 300, blocks of 16: bs_pass 4.7 us and bs_update 5.7 with a gap between them, this 6.2; step plus
+// get_theta 24.2 -> 20.5.  (Eight workers a wavefront, four rows always and everything unrolled, 9.3 us: its instructions took longer
+// to fetch and issue than the loads.)
+constexpr int kStepWaves = 12, kStepThreads = (kStepWaves + 4) * kWave;     // 12: a multiple of 1, 2, 3 and 4 rows
+constexpr int kStepBatch = 4;
+constexpr unsigned kStepLdsPerWorker = kThreads * (sizeof(float) + sizeof(uint8_t));   // dynamic LDS
+template <bool kPending, int kMode, typename G, bool kStreamState>
+__global__ __launch_bounds__(kStepThreads) void bs_step_short(const G *__restrict__ g, float *__restrict__ xs, int64_t d, int64_t ld,
+                                                              int n, BsTable tb, float *__restrict__ scales,
+                                                              uint16_t *__restrict__ signs, float *__restrict__ theta,
+                                                              float *__restrict__ m, float *__restrict__ v,
+                                                              float *__restrict__ vhat, AmsParams p, BsMarkov mk)
+{
+    constexpr bool kMarkov = kMode == kBsCd;
+    extern __shared__ __align__(16) unsigned char step_lds[];
+    float (*s_lds)[kThreads] = reinterpret_cast<float (*)[kThreads]>(step_lds);           // [n] a worker's scale for each float4
+    uint8_t (*nib)[4][kWave] = reinterpret_cast<uint8_t (*)[4][kWave]>(s_lds + n);        // [n] its sign bits there
+    __shared__ uint8_t server_nib[4][kWave];
+    const int t = blockIdx.x >> 2;
+    const uint32_t lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t quarter = (int64_t)t * kTile + 4 * kWave * (blockIdx.x & 3);
+    if (quarter >= d) return;                              // padding: all of it stays 0
+    const int rows = (int)min((int64_t)4, (d - quarter + 4 * kThreads - 1) / (4 * kThreads));    // the others are padding
+    const bool updates = wave >= kStepWaves;
+    // wave / rows and wave % rows without a division; step: wavefronts of a row
+    const int of = rows == 1 ? wave : rows == 2 ? wave >> 1 : rows == 3 ? (wave * 11) >> 5 : wave >> 2;
+    const int step = rows == 1 ? 12 : rows == 2 ? 6 : rows == 3 ? 4 : 3;
+    const int r = updates ? wave - kStepWaves : wave - of * rows;
+    const uint32_t at = 4u * (lane + kThreads * r);
+    const int64_t j = quarter + at;
+    const int64_t sstride = (int64_t)(ld / kTile) * kThreads;
+    const int64_t word0 = (int64_t)t * kThreads + (blockIdx.x & 3) * kWave;
+    const int blk = min((int)(j >> tb.small_log2), tb.n_blocks - 1);
+    auto word = [&](const uint8_t (*q)[kWave]) {
+        uint32_t w = q[0][lane];
+        if (rows > 1) w |= q[1][lane] << 4;
+        if (rows > 2) w |= q[2][lane] << 8;
+        if (rows > 3) w |= q[3][lane] << 12;
+        return (uint16_t)w;
+    };
+    if (!updates) {
+        const GradPlace place = grad_place(j, d);          // two short blocks at least: d > 4
+        const int64_t len64 = (int64_t)1 << tb.small_log2;
+        const int64_t first = j & ~(len64 - 1);
+        const bool heads = j == first && j < d;            // the block's first float4
+        const bool whole = quarter + 4 * kThreads * r + 4 * kWave <= d;       // no block of the row is cut
+        const int lanes = 1 << (tb.small_log2 - 2);
+        for (int w0 = of; w0 < n; w0 += kStepBatch * step) {
+            GradRaw<G> gv[kStepBatch];
+            float4 xv[kStepBatch];
+            float s_old[kStepBatch];
+            uint32_t old_bits[kStepBatch], neg[kStepBatch];
+            double S[kStepBatch];
+#pragma unroll
+            for (int u = 0; u < kStepBatch; ++u) {
+                const int i = min(w0 + u * step, n - 1);   // clamped: the copies past n are not used
+                gv[u] = load_place4(g + (int64_t)i * d, place);
+                xv[u] = kMode == kBsNaive ? make_float4(0.f, 0.f, 0.f, 0.f) : ld4(at_offset(xs + (int64_t)i * ld + quarter, at));
+                s_old[u] = kPending ? scales[(int64_t)i * tb.n_blocks + blk] : 0.f;
+                old_bits[u] = kMarkov && kPending ? (uint32_t)*at_offset(signs + (int64_t)i * sstride + word0, lane) >> (4 * r) : 0u;
+            }
+            // stage by stage over the batch: what one worker does is a chain of latencies
+#pragma unroll
+            for (int u = 0; u < kStepBatch; ++u) {
+                const float4 g4 = shift4(widen4(gv[u]), place.shift);
+                const float gg[4] = {g4.x, g4.y, g4.z, g4.w};
+                const float xx[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w};
+                float x[4], keep[4] = {0.f, 0.f, 0.f, 0.f};
+                neg[u] = 0;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const bool in = j + c < d;
+                    if (kMarkov) {
+                        const float gh = kPending ? fadd(xx[c], signed_scale(s_old[u], old_bits[u], c)) : xx[c];
+                        keep[c] = in ? gh : xx[c];
+                        x[c] = in ? fsub(gg[c], gh) : 0.f;
+                    } else if (kMode == kBsNaive) {
+                        x[c] = in ? gg[c] : 0.f;
+                    } else {
+                        const float sum = fadd(gg[c], kPending ? deferred_sign_error(xx[c], s_old[u]) : xx[c]);
+                        keep[c] = x[c] = in ? sum : 0.f;
+                    }
+                    neg[u] |= (__float_as_uint(x[c]) >> 31) << c;
+                }
+                xv[u] = make_float4(keep[0], keep[1], keep[2], keep[3]);
+                S[u] = ((double)fabsf(x[0]) + (double)fabsf(x[1])) + ((double)fabsf(x[2]) + (double)fabsf(x[3]));
+            }
+            for (int off = 1; off < lanes; off <<= 1) {
+#pragma unroll
+                for (int u = 0; u < kStepBatch; ++u) S[u] += __shfl_xor(S[u], off, kWave);
+            }
+            if (whole) {
+                const double inv = inverse_power(tb.small_log2);
+#pragma unroll
+                for (int u = 0; u < kStepBatch; ++u) S[u] *= inv;
+            } else {
+                const double len = (double)max((int64_t)1, min(len64, d - first));
+#pragma unroll
+                for (int u = 0; u < kStepBatch; ++u) S[u] /= len;
+            }
+#pragma unroll
+            for (int u = 0; u < kStepBatch; ++u) {
+                const int i = w0 + u * step;
+                if (i < n) {
+                    const float s = (float)S[u];
+                    s_lds[i][r * kWave + lane] = s;
+                    nib[i][r][lane] = (uint8_t)neg[u];
+                    if (kMode != kBsNaive) st4_stream(at_offset(xs + (int64_t)i * ld + quarter, at), xv[u]);
+                    if (heads) scales[(int64_t)i * tb.n_blocks + blk] = s;
+                }
+            }
+        }
+        lds_barrier();
+        // the words of the workers in turn; the old ones, which all rows needed, have been read
+        for (int i = wave; i < n; i += kStepWaves) *at_offset(signs + (int64_t)i * sstride + word0, lane) = word(nib[i]);
+        if (kMarkov) lds_barrier();
+        return;
+    }
+    float4 th, mm, vv, vh, gh4, gt4;
+    const bool live = r < rows;
+    if (live) {
+        th = ld4_state<kStreamState>(theta + j);
+        mm = ld4_state<kStreamState>(m + j);
+        vv = ld4_state<kStreamState>(v + j);
+        vh = ld4_state<kStreamState>(vhat + j);
+        if (kMarkov) {
+            gh4 = ld4_state<kStreamState>(mk.ghat + j);
+            gt4 = ld4_state<kStreamState>(mk.gtil + j);
+        }
+    }
+    lds_barrier();
+    float gb[4];
+    if (live) {
+        float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (int i = 0; i < n; ++i) {
+            const float s = s_lds[i][r * kWave + lane];
+            const uint32_t bits = nib[i][r][lane];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[c] = fadd(acc[c], signed_scale(s, bits, c));
+        }
+        // padding coordinates take no gradient
+#pragma unroll
+        for (int c = 0; c < 4; ++c) gb[c] = j + c < d ? fdiv(acc[c], p.n_workers) : 0.f;
+        if (kMarkov) server_nib[r][lane] = (uint8_t)short_server<kStreamState>(gb, gh4, gt4, mk, tb, d, j, blk);
+    }
+    if (kMarkov) {
+        lds_barrier();
+        if (r == 0) *at_offset(mk.signs + word0, lane) = word(server_nib);
+    }
+    if (!live) return;
+    amsgrad_update4(th, mm, vv, vh, make_float4(gb[0], gb[1], gb[2], gb[3]), p);
+    st4_state<kStreamState>(theta + j, th);
     st4_state<kStreamState>(m + j, mm);
     st4_state<kStreamState>(v + j, vv);
     st4_state<kStreamState>(vhat + j, vh);

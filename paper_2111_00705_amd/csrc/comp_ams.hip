@@ -258,11 +258,11 @@ namespace {
 
 enum ProfSlot { P_BS_PASS, P_BS_SCALE, P_BS_UPDATE, P_TK_PASS1, P_TK_HIST, P_TK_COMPACT,
                 P_TK_RESOLVE, P_TK_FINAL, P_BS_SERVER, P_BS_SCALE_SERVER, P_BS_APPLY, P_TK_MERGE, P_TK_PASS1_SERVER,
-                P_TK_SELECT_SERVER, P_TK_APPLY, P_PLAIN_UPDATE, P_BS_PASS_UPDATE, P_SLOTS };
+                P_TK_SELECT_SERVER, P_TK_APPLY, P_PLAIN_UPDATE, P_BS_PASS_UPDATE, P_BS_STEP, P_SLOTS };
 const char *const kProfNames[P_SLOTS] = {"bs_pass", "bs_scale", "bs_update", "tk_pass1", "tk_hist",
                                          "tk_compact", "tk_resolve", "tk_final", "bs_server",
                                          "bs_scale_server", "bs_apply", "tk_merge", "tk_pass1_server", "tk_select_server",
-                                         "tk_apply", "plain_update", "bs_pass_update"};
+                                         "tk_apply", "plain_update", "bs_pass_update", "bs_step_short"};
 
 // Kernel launches of a step go through KLAUNCH.  With profiling on, launch_timed hands the launch a
 // pair of events through t_ev0 / t_ev1 and the kernel is started with hipExtLaunchKernel, which stamps
@@ -589,6 +589,20 @@ void launch_bs_update(comp_ams *h, hipStream_t st, const AmsParams &p, float *th
 // Workgroup size of bs_scale: the staging wavefronts only where some block is long enough to use them.
 inline unsigned scale_threads(const comp_ams *h) { return h->long_blocks ? kThreads : kWave; }
 inline unsigned scale_lds(const comp_ams *h) { return h->long_blocks ? kScaleStage * sizeof(double) : 0u; }
+
+// Short blocks inside a wavefront on vectors that leave the chip idle: every method in one launch, the same in a captured step.
+template <int kMode, typename G>
+int step_blocksign_one_launch(comp_ams *h, const G *g, hipStream_t st)
+{
+    const BsMarkov mk{h->ghat_srv, h->gtil, h->signs_srv, h->partial_srv, h->scales_srv, 1};
+    launch_timed(h, P_BS_STEP, st, [&] { by_flag(h->params.stream_state, [&](auto ss) { by_flag(h->pending, [&](auto pend) {
+        KLAUNCH_LDS((bs_step_short<kMode != kBsNaive && decltype(pend)::value, kMode, G, decltype(ss)::value>),
+                (unsigned)(h->ld / kTile * 4), kStepThreads, h->n * kStepLdsPerWorker, st, g, h->e, h->d, h->ld, h->n, h->tb, h->scales, h->signs, h->theta, h->m,
+                h->v, h->vhat, h->params, mk);
+    }); }); });
+    h->pending = kMode != kBsNaive;
+    return COMP_AMS_OK;
+}
 
 template <typename G>
 int step_blocksign(comp_ams *h, const G *g, hipStream_t st)
@@ -1086,6 +1100,10 @@ int step_any(comp_ams *h, const G *grads_dev, void *hip_stream)
         rc = (h->method == COMP_AMS_METHOD_CD)      ? step_topk_cd(h, grads_dev, st)
              : (h->method == COMP_AMS_METHOD_NAIVE) ? step_topk_naive(h, grads_dev, st)
                                                     : step_topk(h, grads_dev, st);
+    else if (h->tb.small_log2 > 0 && h->tb.small_log2 <= 8 && one_launch_sign(h->n, h->d, h->ld / kTile))
+        rc = (h->method == COMP_AMS_METHOD_CD)      ? step_blocksign_one_launch<kBsCd>(h, grads_dev, st)
+             : (h->method == COMP_AMS_METHOD_NAIVE) ? step_blocksign_one_launch<kBsNaive>(h, grads_dev, st)
+                                                    : step_blocksign_one_launch<kBsEf>(h, grads_dev, st);
     else
         rc = (h->method == COMP_AMS_METHOD_CD)            ? step_blocksign_cd(h, grads_dev, st)
              : (!capturing && can_defer_blocksign(h))     ? step_blocksign_deferred(h, grads_dev, st)

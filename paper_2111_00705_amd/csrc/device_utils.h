@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace cams {
 
@@ -124,6 +125,34 @@ __device__ __forceinline__ GradRaw<G> load_raw4(const G *__restrict__ row, int64
     if (j + 3 < d) r.y |= (uint32_t)p[3] << 16;
     return {r};
 }
+// The same without a branch, for d >= 4: a float4 that ends past d is read from the row's last four coordinates and shifted, so
+// that the loads of several rows go out together whatever the lane (a branch around a load that ends early waits for the loads
+// before it).
+struct GradPlace {
+    int64_t at;      // where the four are read: j, or d - 4
+    int shift;       // j - at, no more than 4
+};
+__device__ __forceinline__ GradPlace grad_place(int64_t j, int64_t d)
+{
+    const int64_t at = min(j, d - 4);
+    return {at, (int)min(j - at, (int64_t)4)};
+}
+__device__ __forceinline__ GradRaw<float> load_place4(const float *__restrict__ row, const GradPlace &q)
+{
+    return {__builtin_nontemporal_load(reinterpret_cast<const v4f_any *>(row + q.at))};
+}
+template <typename G>
+__device__ __forceinline__ GradRaw<G> load_place4(const G *__restrict__ row, const GradPlace &q)
+{
+    return {__builtin_nontemporal_load(reinterpret_cast<const v2u_any *>(reinterpret_cast<const uint16_t *>(row) + q.at))};
+}
+// Components past d come out as anything.
+__device__ __forceinline__ float4 shift4(float4 x, int shift)
+{
+    if (shift & 1) x = make_float4(x.y, x.z, x.w, x.w);
+    if (shift & 2) x = make_float4(x.z, x.w, x.w, x.w);
+    return x;
+}
 __device__ __forceinline__ float4 widen4(const GradRaw<float> &r) { return make_float4(r.v.x, r.v.y, r.v.z, r.v.w); }
 __device__ __forceinline__ float4 widen4(const GradRaw<uint16_t> &r)
 {
@@ -134,6 +163,15 @@ __device__ __forceinline__ float4 widen4(const GradRaw<f16bits> &r)
 {
     return make_float4(f16_to_float(r.v.x & 0xffffu), f16_to_float(r.v.x >> 16), f16_to_float(r.v.y & 0xffffu),
                        f16_to_float(r.v.y >> 16));
+}
+
+// base + at for a base that is uniform over the wavefront: the offset stays a 32-bit number of bytes (at * sizeof(T) < 2^32), so that
+// the access takes it beside a scalar base instead of a 64-bit sum per lane.
+template <typename T>
+__device__ __forceinline__ T *at_offset(T *base, uint32_t at)
+{
+    using Bytes = std::conditional_t<std::is_const<T>::value, const char, char>;
+    return reinterpret_cast<T *>(reinterpret_cast<Bytes *>(base) + (uint32_t)(at * (uint32_t)sizeof(T)));
 }
 
 __device__ __forceinline__ float4 ld4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
@@ -197,6 +235,14 @@ __device__ __forceinline__ void st4_if_changed(float *p, const float4 &v, const 
 }
 
 __device__ __forceinline__ uint32_t mag_key(float x) { return __float_as_uint(x) & 0x7fffffffu; }
+
+// A workgroup barrier that orders LDS only: unlike __syncthreads it does not wait for stores to memory that are in flight.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
 // Sum over the 64 lanes with a fixed butterfly; every lane receives the same result, and the
 // result depends only on the lane values, not on timing.

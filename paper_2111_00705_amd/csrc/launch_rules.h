@@ -25,6 +25,20 @@ inline bool short_final(int64_t n, int64_t n_tiles)
 // d = 250 000 81.8 / 79.6, n = 32, d = 350 000 bf16 80.7 / 79.2; 293 tiles, n = 16 88.7 / 93.5, 318 tiles, n = 2 46.5 / 48.8.
 inline int short_final_batch(int64_t n_tiles) { return n_tiles <= 256 ? 8 : 5; }
 
+// Whether a step with short blocks of at most 256 coordinates is one launch (bs_step_short), with rows = those of a quarter of a tile
+// that hold coordinates.  A workgroup goes through all workers of its quarter: beyond 80 (worker, row) pairs the two launches, which
+// spread the workers over the chip, are as fast or faster, and beyond 64 tiles the chip is full without that.  Step plus
+// get_theta, us, two launches / one: CD-Adam n = 20, d = 300 25.3 / 21.2; n = 48, d = 300 27.4 / 21.1, n = 96 33.7 / 24.8; n = 4,
+// d = 4000 21.9 / 20.1, n = 32 (CD-Adam) 26.6 / 26.8, n = 64 30.0 / 34.6; d = 65 536, n = 1 22.6 / 20.1, n = 8 23.9 / 22.2, n = 16
+// 25.0 / 24.6, n = 32 29.5 / 29.5; d = 250 000, n = 16 32.3 / 29.3, CD-Adam 33.1 / 31.2; d = 500 000, n = 4 27.8 / 26.3, CD-Adam
+// 30.1 / 31.3; d = 1 M, n = 2 31.3 / 32.0, CD-Adam 33.0 / 39.8.
+constexpr int kOneLaunchPairs = 80, kOneLaunchTiles = 64;
+inline bool one_launch_sign(int64_t n, int64_t d, int64_t n_tiles)
+{
+    const int64_t rows = d > 3072 ? 4 : (d + 1023) / 1024;
+    return n_tiles <= kOneLaunchTiles && n * rows <= kOneLaunchPairs;
+}
+
 // Grid of a kernel with one workgroup per tile (in x) under tile_of_block's mapping.
 inline unsigned grid_blocks(int64_t n_tiles, int chunk)
 {

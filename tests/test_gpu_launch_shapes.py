@@ -121,6 +121,51 @@ def test_short_blocks(B, method):
         gpu.destroy()
 
 
+# bs_step_short on both sides of its lines: one to four rows of a quarter with coordinates, more workers than a wavefront has in
+# flight, 64 and 65 tiles; 16-bit gradients through the same kernel are widened exactly, so both entry points agree bit for bit
+@pytest.mark.parametrize("method", ["ef", "naive", "cd"])
+@pytest.mark.parametrize("d,n,B", [(5, 80, 4), (1023, 80, 256), (1023, 81, 256), (1026, 40, 8), (3071, 26, 64), (3073, 20, 128),
+                                   (3073, 21, 128), (64 * TILE - 3, 2, 32), (64 * TILE + 1, 2, 32)])
+def test_short_blocks_in_one_launch(d, n, B, method):
+    import torch
+    print(f"[case] one launch, blocks of {B}, {method}, d={d} n={n}", flush=True)
+    code = {"ef": (P.METHOD_EF, O.EF), "naive": (P.METHOD_NAIVE, O.NAIVE), "cd": (P.METHOD_CD, O.CD)}[method]
+    handles = [P.CompAms(d, n, P.BLOCKSIGN, B) for _ in range(3)]
+    ora = O.Oracle(d, n, P.BLOCKSIGN, B, 0.9, 0.999, 1e-8, 1e-3, method=code[1])
+    for h in handles:
+        if code[0] != P.METHOD_EF:
+            h.set_method(code[0])
+    gpu, b16, wide = handles
+    fn = grads_of(B + d, n, d)
+    for t in range(3):
+        g = fn(t)
+        gd = torch.from_numpy(g).cuda()
+        gpu.step(gd)
+        ora.step(g)
+        b16.step_bf16(gd.bfloat16())
+        wide.step(gd.bfloat16().float())
+        assert rel_close(gpu.get_scales(), ora.scales, 1e-7).all(), t           # fp64 sums in another order
+        for name, got, want in (("theta", gpu.get_theta(), ora.theta), ("m", gpu.get_m(), ora.m), ("v", gpu.get_v(), ora.v),
+                                ("vhat", gpu.get_vhat(), ora.vhat)):
+            assert rel_close(got, want, STATE_RTOL).all(), (name, t)
+        for get in ("get_theta", "get_m", "get_v", "get_vhat", "get_scales"):
+            assert np.array_equal(bits(getattr(b16, get)()), bits(getattr(wide, get)())), (get, t)
+        for i in (0, n - 1):
+            assert np.array_equal(b16.get_signs(i), wide.get_signs(i)), (i, t)
+            negative = np.unpackbits(gpu.get_signs(i), bitorder="little")
+            assert not negative[d:].any()
+            spread = np.repeat(gpu.get_scales()[i], B)[:d]
+            assert rel_close(np.where(negative[:d], -spread, spread), ora.compressed[i], 1e-7).all(), (i, t)
+            if method == "ef":
+                assert rel_close(gpu.get_error(i), ora.error[i], STATE_RTOL).all(), (i, t)
+            if method == "cd":
+                assert rel_close(gpu.get_ghat_worker(i), ora.ghat_workers[i], STATE_RTOL).all(), (i, t)
+        if method == "cd":
+            assert rel_close(gpu.get_gtilde(), ora.gtilde, STATE_RTOL).all(), t
+    for h in handles:
+        h.destroy()
+
+
 def sparse_pair(d, n, k, method, compressor=P.TOPK):
     code = {"ef": (P.METHOD_EF, O.EF), "naive": (P.METHOD_NAIVE, O.NAIVE), "cd": (P.METHOD_CD, O.CD)}[method]
     gpu = P.CompAms(d, n, compressor, k)

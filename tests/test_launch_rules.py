@@ -34,6 +34,13 @@ def test_quarter_tile_update_holds_eight_workers_up_to_256_tiles(tmp_path):
     assert got == list(cases.values())
 
 
+def test_one_launch_sign_step_only_where_few_workers_share_a_quarter(tmp_path):
+    cases = {(80, 1): 1, (80, 1024): 1, (81, 300): 0, (40, 1025): 1, (41, 2048): 0, (26, 2049): 1, (27, 3072): 0, (20, 3073): 1,
+             (21, 3073): 0, (20, 64 * 4096): 1, (1, 64 * 4096 + 1): 0, (65535, 1): 0}
+    got = evaluate(tmp_path, [f"one_launch_sign({n}, {d}, {(d + 4095) // 4096})" for n, d in cases])
+    assert got == list(cases.values())
+
+
 def test_uncompressed_update_pads_its_grid_to_no_more_than_eight_vectors(tmp_path):
     quarters = [1, 4, 64, 511, 512, 977, 100_000, 2_097_152]
     choices = [-1, 0, 1, 16, 1024, 65_536]
