@@ -244,6 +244,22 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Sum over lanes 0 .. this one, by the lane permutes that ride in a vector instruction (a row of 16 lanes in four steps, then the
+// rows before): six __shfl_up are six round trips through the LDS unit, one after the other.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v)
+{
+    int x = (int)v;
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);      // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);      // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);      // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);      // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);      // row_bcast:15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);      // row_bcast:31 into rows 2 and 3
+    return (uint32_t)x;
+}
+// The sum over all 64 lanes, uniform, from wave_scan's result.
+__device__ __forceinline__ uint32_t scan_total(uint32_t scan) { return (uint32_t)__builtin_amdgcn_readlane((int)scan, kWave - 1); }
+
 // Sum over the 64 lanes with a fixed butterfly; every lane receives the same result, and the
 // result depends only on the lane values, not on timing.
 __device__ __forceinline__ double wave_sum(double v)

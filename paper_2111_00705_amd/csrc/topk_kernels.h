@@ -250,40 +250,56 @@ __device__ __forceinline__ uint64_t digit_edge(const FirstDigit &f, uint32_t pre
     return (b.prefix << b.open) + (above_ties ? 1ull << f.idx_bits : 0ull);
 }
 
-// Finds, in a histogram held in LDS (`bins` counters, a multiple of the workgroup size), the bin
+// Sums of the wavefronts of a workgroup of kWaves (a power of two up to 16) in part[]: the sum over those behind `wave`, uniform.
+template <int kWaves>
+__device__ __forceinline__ uint32_t waves_behind(const uint32_t *part, int wave)
+{
+    const int lane = threadIdx.x & 63;
+    return scan_total(wave_scan(lane < kWaves && lane > wave ? part[lane & (kWaves - 1)] : 0u));
+}
+
+// The same over those before `wave`, of a workgroup of kResolveThreads.
+__device__ __forceinline__ uint32_t waves_before(const uint32_t *part, int wave)
+{
+    const int lane = threadIdx.x & 63;
+    return scan_total(wave_scan(lane < wave ? part[lane & (kResolveThreads / kWave - 1)] : 0u));
+}
+
+// Finds, in a histogram of kBins counters held in LDS by a workgroup of kResolveThreads, the bin
 // of the element of 1-based rank `rank` counted from the top bin downwards, and leaves
 // {bin, elements in higher bins, the bin's count} in res[0..2] for every thread (res[3] = 1 if
-// found, which needs 1 <= rank <= total).  `part` holds one LDS counter per wavefront.
-__device__ __forceinline__ void find_rank_bin(const uint32_t *lh, uint32_t *part, uint32_t *res, int bins,
-                                              uint32_t rank)
+// found, which needs 1 <= rank <= total).  `part` holds one LDS counter per wavefront.  Bound by latency (wave_scan; tk_compact
+// and tk_resolve together, us, with shuffles and the wavefronts' counters read one after the other / now: Rand-k n = 16, d = 1.2 M f16
+// 11.1 / 9.8, naive n = 8, d = 3 M bf16 14.1 / 12.1).
+template <int kBins>
+__device__ __forceinline__ void find_rank_bin(const uint32_t *lh, uint32_t *part, uint32_t *res, uint32_t rank)
 {
-    const int nt = blockDim.x;
-    const int per = bins / nt;
+    constexpr int per = kBins / kResolveThreads;
+    static_assert(per * kResolveThreads == kBins, "the same number of bins for every thread");
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t mine = 0;
-    for (int q = 0; q < per; ++q) mine += lh[threadIdx.x * per + q];
-    uint32_t suffix = mine;                       // sum over lanes >= this one
+    uint32_t own[per], mine = 0;
 #pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const uint32_t t = __shfl_down(suffix, off, kWave);
-        if (lane + off < kWave) suffix += t;
+    for (int q = 0; q < per; ++q) {
+        own[q] = lh[threadIdx.x * per + q];
+        mine += own[q];
     }
-    if (lane == 0) part[wave] = suffix;
+    const uint32_t incl = wave_scan(mine), total = scan_total(incl);
+    if (lane == 0) part[wave] = total;
     if (threadIdx.x == 0) res[3] = 0;
     __syncthreads();
-    uint32_t above = suffix - mine;
-    for (int w = wave + 1; w < (nt >> 6); ++w) above += part[w];
+    uint32_t above = waves_behind<kResolveThreads / kWave>(part, wave) + total - incl;
     if (above < rank && above + mine >= rank) {
+        bool found = false;
+#pragma unroll
         for (int q = per - 1; q >= 0; --q) {
-            const uint32_t c = lh[threadIdx.x * per + q];
-            if (above + c >= rank) {
+            if (!found && above + own[q] >= rank) {
                 res[0] = threadIdx.x * per + q;
                 res[1] = above;
-                res[2] = c;
+                res[2] = own[q];
                 res[3] = 1;
-                break;
+                found = true;
             }
-            above += c;
+            above += own[q];
         }
     }
     __syncthreads();
@@ -297,16 +313,10 @@ __device__ __forceinline__ void find_rank_owned(const uint32_t (&own)[8], uint32
     uint32_t mine = 0;
 #pragma unroll
     for (int q = 0; q < 8; ++q) mine += own[q];
-    uint32_t suffix = mine;                       // sum over lanes >= this one
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const uint32_t t = __shfl_down(suffix, off, kWave);
-        if (lane + off < kWave) suffix += t;
-    }
-    if (lane == 0) part[wave] = suffix;
+    const uint32_t incl = wave_scan(mine), total = scan_total(incl);
+    if (lane == 0) part[wave] = total;
     __syncthreads();
-    uint32_t above = suffix - mine;
-    for (int w = wave + 1; w < kThreads / kWave; ++w) above += part[w];
+    uint32_t above = waves_behind<kThreads / kWave>(part, wave) + total - incl;
     if (above < rank && above + mine >= rank) {
         bool found = false;
 #pragma unroll
@@ -332,27 +342,6 @@ __device__ __forceinline__ uint32_t wave_append(bool flag, uint32_t &count)
     const uint32_t slot = count + __popcll(mask & ((1ull << lane) - 1ull));
     count += __popcll(mask);
     return slot;
-}
-
-// Exclusive prefix sum of one value per thread over a 256-thread workgroup, left in pre[0..256]
-// (pre[256] = total).  `part` holds 4 LDS counters.  Three barriers.
-__device__ __forceinline__ void block_prefix(uint32_t v, uint32_t *pre, uint32_t *part)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t incl = v;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const uint32_t up = __shfl_up(incl, off, kWave);
-        if (lane >= off) incl += up;
-    }
-    __syncthreads();                       // readers of an earlier pre/part are done
-    if (lane == kWave - 1) part[wave] = incl;
-    __syncthreads();
-    uint32_t before = 0;
-    for (int w = 0; w < wave; ++w) before += part[w];
-    pre[threadIdx.x] = before + incl - v;
-    if (threadIdx.x == kThreads - 1) pre[kThreads] = before + incl;
-    __syncthreads();
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -887,12 +876,7 @@ __global__ __launch_bounds__(kThreads) void tk_final_short(TkGeom ge, const TkWo
             key_a[lane] = sk.a;
             key_b[lane] = sk.b;
         }
-        uint32_t incl = count;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const uint32_t up = __shfl_up(incl, off, kWave);
-            if (lane >= off) incl += up;
-        }
+        const uint32_t incl = wave_scan(count);
         if (lane < ge.n) upto[lane + 1] = incl;
         if (lane == 0) upto[0] = 0u;
     }
@@ -1074,21 +1058,12 @@ __device__ __forceinline__ int selection_case(const TkGeom &ge, uint32_t total, 
     return kCaseMiss;
 }
 
-// Number of candidates of worker i = sum of its region cursors.  Wavefront 0 adds them up; total_sh: one LDS
-// word; ends with a barrier.  All threads of the workgroup call this.
-__device__ __forceinline__ uint32_t candidates_listed(const TkGeom &ge, const uint32_t *__restrict__ cursor, int i,
-                                                      uint32_t *total_sh)
+// Number of candidates of worker i = sum of its region cursors; every wavefront adds them up for itself.
+__device__ __forceinline__ uint32_t candidates_listed(const TkGeom &ge, const uint32_t *__restrict__ cursor, int i)
 {
-    const int lane = threadIdx.x & 63;
-    if ((threadIdx.x >> 6) == 0) {
-        uint32_t c = 0;
-        for (int q = lane; q < ge.slices; q += kWave) c += cursor[(i * ge.slices + q) * kCursorStride];
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off, kWave);
-        if (lane == 0) *total_sh = c;
-    }
-    __syncthreads();
-    return *total_sh;
+    uint32_t c = 0;
+    for (int q = threadIdx.x & 63; q < ge.slices; q += kWave) c += cursor[(i * ge.slices + q) * kCursorStride];
+    return scan_total(wave_scan(c));
 }
 
 // First coarse bin of the window whose fine bins are counted: the guess's, but no more than kWindowBelow fine bins below the
@@ -1131,11 +1106,10 @@ __global__ __launch_bounds__(kThreads) void tk_hist(TkGeom ge, const TkWorker *_
 {
     __shared__ uint32_t lh[kBins1];
     __shared__ uint32_t lf[kFineWindow];
-    __shared__ uint32_t total_sh;
     const int i = blockIdx.y;
     const int tid = threadIdx.x;
     const uint32_t guess = ws[i].guess, last = ws[i].last_fine;
-    const uint32_t total = candidates_listed(ge, cursor, i, &total_sh);
+    const uint32_t total = candidates_listed(ge, cursor, i);
     const int which = selection_case<kSrc>(ge, total, guess, ws[i].overflow != 0u);
     if (which == kCaseZeroTail) return;
     const Piece pc = piece_of(ge, cursor, i, (int)blockIdx.x);
@@ -1233,7 +1207,6 @@ __global__ __launch_bounds__(kThreads) void tk_compact(TkGeom ge, TkWorker *__re
     __shared__ uint32_t part[kThreads / kWave];
     __shared__ uint32_t res[3];
     __shared__ uint32_t sh[9];
-    __shared__ uint32_t total_sh;
     static_assert(kBins1 == 8 * kThreads && kFineWindow == 2 * kThreads, "bins owned per thread");
     static_assert(kFinePerCoarse == kWave && kWindowCoarse == 2 * (kThreads / kWave), "fine bins of two coarse bins per wavefront");
     const int i = blockIdx.y;
@@ -1252,12 +1225,7 @@ __global__ __launch_bounds__(kThreads) void tk_compact(TkGeom ge, TkWorker *__re
     {
         lf[tid] = f0;
         lf[kThreads + tid] = f1;
-        uint32_t s0 = f0, s1 = f1;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            s0 += __shfl_xor(s0, off, kWave);
-            s1 += __shfl_xor(s1, off, kWave);
-        }
+        const uint32_t s0 = scan_total(wave_scan(f0)), s1 = scan_total(wave_scan(f1));
         if (lane == 0) {
             win[wave] = s0;
             win[wave + kThreads / kWave] = s1;
@@ -1265,7 +1233,8 @@ __global__ __launch_bounds__(kThreads) void tk_compact(TkGeom ge, TkWorker *__re
         for (int q = tid; q < kBinsFirst; q += kThreads) lh2[q] = 0;
         if (lane < kPieceWords) bits[wave][lane] = 0;
     }
-    const uint32_t total = candidates_listed(ge, cursor, i, &total_sh);      // ends with a barrier
+    const uint32_t total = candidates_listed(ge, cursor, i);
+    __syncthreads();                                                         // what was put into LDS
     const int which = selection_case<kSrc>(ge, total, guess, overflow);
     const SelKey sk = sel_key_of(ge.rand, ge.rand.step_now, i);
 
@@ -1286,12 +1255,8 @@ __global__ __launch_bounds__(kThreads) void tk_compact(TkGeom ge, TkWorker *__re
         if (prefix - wb < (uint32_t)kWindowCoarse) {
             // the fine histogram covers this coarse bin: pick the fine bin as well (every wavefront for itself)
             const uint32_t c = lf[(prefix - wb) * kFinePerCoarse + lane];
-            uint32_t suffix = c;                    // candidates of this coarse bin in fine bins >= lane
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) {
-                const uint32_t t = __shfl_down(suffix, off, kWave);
-                if (lane + off < kWave) suffix += t;
-            }
+            const uint32_t incl = wave_scan(c);
+            const uint32_t suffix = scan_total(incl) - incl + c;      // candidates of this coarse bin in fine bins >= lane
             const uint64_t reach = __ballot(suffix >= rank);      // lane 0 reaches: suffix(0) = count >= rank
             const int top = reach ? 63 - __builtin_clzll(reach) : 0;
             count = (uint32_t)__shfl((int)c, top, kWave);
@@ -1459,6 +1424,20 @@ struct ResolveLds {
     uint64_t tc_sh;
 };
 
+// The comp value of 1-based rank `rank` from the top among the n <= kFew in L.few (unique; a barrier after they were put there);
+// ends with a barrier.
+__device__ __forceinline__ uint64_t rank_few(uint32_t n, uint32_t rank, ResolveLds &L)
+{
+    if (threadIdx.x < n) {
+        const uint64_t mine = L.few[threadIdx.x];
+        uint32_t greater = 0;
+        for (uint32_t u = 0; u < n; ++u) greater += L.few[u] > mine ? 1u : 0u;
+        if (greater + 1 == rank) L.tc_sh = mine;              // comp values are unique: exactly one thread
+    }
+    __syncthreads();
+    return L.tc_sh;
+}
+
 // The digits of Tc below `prefix` (which leaves s_hi low bits of comp open), 12 bits at a time, over the
 // cnt comp values that fetch(q, comp) delivers kScanUnroll at a time (comp[u] = element q[u], anything for
 // q[u] >= cnt; q ascends with u), of which the one of 1-based rank `rank` (from the top) among those that
@@ -1493,7 +1472,7 @@ __device__ __forceinline__ uint64_t resolve_digits(Fetch fetch, uint32_t cnt, ui
                     atomicAdd(&L.lh[(uint32_t)(comp[u] >> s_lo) & mask], 1u);
         }
         __syncthreads();
-        find_rank_bin(L.lh, L.part, L.res, kBins2, rank);
+        find_rank_bin<kBins2>(L.lh, L.part, L.res, rank);
         if (!L.res[3]) break;                                  // cannot happen: rank <= matching elements
         prefix = (prefix << (s_hi - s_lo)) | L.res[0];
         rank -= L.res[1];
@@ -1517,15 +1496,8 @@ __device__ __forceinline__ uint64_t resolve_digits(Fetch fetch, uint32_t cnt, ui
                         L.few[atomicAdd(&L.n_few, 1u)] = comp[u];
             }
             __syncthreads();
-            if ((uint32_t)tid < left) {
-                const uint64_t mine = L.few[tid];
-                uint32_t greater = 0;
-                for (uint32_t u = 0; u < left; ++u) greater += L.few[u] > mine ? 1u : 0u;
-                if (greater + 1 == rank) L.tc_sh = mine;      // comp values are unique: exactly one thread
-            }
-            __syncthreads();
             done = true;
-            tc = L.tc_sh;
+            tc = rank_few(left, rank, L);
         }
         __syncthreads();
     }
@@ -1559,17 +1531,11 @@ __device__ __forceinline__ void finish_worker(TkWorker *ws, int i, const TkWorke
 __device__ __forceinline__ uint32_t resolve_scan(uint32_t v, uint32_t *part, uint32_t *total_sh)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t incl = v;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const uint32_t up = __shfl_up(incl, off, kWave);
-        if (lane >= off) incl += up;
-    }
+    const uint32_t incl = wave_scan(v);
     __syncthreads();                       // readers of an earlier part are done
     if (lane == kWave - 1) part[wave] = incl;
     __syncthreads();
-    uint32_t before = 0;
-    for (int q = 0; q < wave; ++q) before += part[q];
+    const uint32_t before = waves_before(part, wave);
     if (threadIdx.x == kResolveThreads - 1) *total_sh = before + incl;
     return before + incl - v;
 }
@@ -1689,7 +1655,7 @@ __device__ __forceinline__ uint64_t exact_threshold(const ExactSource &es, const
             }
         }
         __syncthreads();
-        find_rank_bin(L.lh, L.part, L.res, kBins2, rank);          // rank <= elements under the prefix
+        find_rank_bin<kBins2>(L.lh, L.part, L.res, rank);          // rank <= elements under the prefix
         prefix = (prefix << (s_hi - s_lo)) | L.res[0];
         rank -= L.res[1];
         const uint32_t left = L.res[2];
@@ -1844,7 +1810,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
         else {
             const SelKey sk = sel_key_of(ge.rand, ge.rand.step_now, i);
             const uint2 *list = cand + worker_base(ge, i);
-            find_rank_bin(L.lh, L.part, L.res, kBinsFirst, w.rank);
+            find_rank_bin<kBinsFirst>(L.lh, L.part, L.res, w.rank);
             const int s_lo = s_hi - kFirstBits;
             const uint32_t left = L.res[2], rank1 = w.rank - L.res[1];
             const bool found = L.res[3] != 0u;
@@ -1916,16 +1882,10 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
         const uint64_t *wdense = dense + region_base(ge, i, 0);
         // exclusive prefix sum of the piece counts, two pieces per thread
         const uint2 a = make_uint2(two.x, two.y), b = make_uint2(two.z, two.w);
-        uint32_t incl = a.y + b.y;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const uint32_t up = __shfl_up(incl, off, kWave);
-            if (lane >= off) incl += up;
-        }
+        const uint32_t incl = wave_scan(a.y + b.y);
         if (lane == kWave - 1) L.part[wave] = incl;
         __syncthreads();
-        uint32_t before = 0;
-        for (int q = 0; q < wave; ++q) before += L.part[q];
+        const uint32_t before = waves_before(L.part, wave);
         const uint32_t excl = before + incl - (a.y + b.y);
         if (2 * tid < pieces) {
             rpre[2 * tid] = excl;
@@ -1976,7 +1936,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
             // (a few hundred elements instead of the whole threshold bin) and the elements ranked directly.
             constexpr int kTeam = 16, kTeams = kResolveThreads / kTeam;
             const FirstDigit fd = first_digit(ge, w.pshift);
-            find_rank_bin(L.lh, L.part, L.res, kBinsFirst, w.rank);          // barriers since L.lh was filled
+            find_rank_bin<kBinsFirst>(L.lh, L.part, L.res, w.rank);          // barriers since L.lh was filled
             const uint32_t digit = L.res[0], left = L.res[2], rank1 = w.rank - L.res[1];
             const bool found = L.res[3] != 0u;                                // always: rank <= elements under the prefix
             if (__builtin_expect(found && left == rank1, 0)) {
@@ -2017,14 +1977,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
                     }
                 }
                 __syncthreads();
-                if ((uint32_t)tid < left) {
-                    const uint64_t mine = L.few[tid];
-                    uint32_t greater = 0;
-                    for (uint32_t u = 0; u < left; ++u) greater += L.few[u] > mine ? 1u : 0u;
-                    if (greater + 1 == rank1) L.tc_sh = mine;                 // comp values are unique: exactly one thread
-                }
-                __syncthreads();
-                tc = L.tc_sh;
+                tc = rank_few(left, rank1, L);
             } else if (found && left <= (uint32_t)kStaged) {
                 // Many elements under the first digit, for instance ties by the hundred thousand.  The
                 // elements are collected in LDS once, a piece per team of lanes and four pieces of a team in flight,
@@ -2099,7 +2052,12 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
 // on this multi-XCD part cost more than the launch they save - 21.6 us against 6 + 5.)
 // Bound by latency: a list of up to kScanUnroll entries per thread (a vector of 65 536 coordinates lists 1.2 k) is read
 // once, into registers, and the digits are found from those.
+// The first digit is the fine bin, counted from the guess's, so that a few entries are left to rank.  (With the top 12 bits of comp,
+// 6 % wide, up to 256 were left, and ranking those against each other took 3.5 us of 9.3.  Kernel, and step plus get_theta, us, that
+// / this, with the scans by lane permutes as well: error feedback n = 4, d = 65 536, k = 1 % 10.4 / 6.8, 33.9 / 29.3, n = 8,
+// d = 20 000, k = 2 % 9.1 / 5.6, 34.5 / 30.3; naive n = 8, d = 40 000, k = 5 % bf16 8.0 / 5.6, 32.9 / 29.2.)
 constexpr int kSmallTiles = 16;
+constexpr int kShortFine = 2048;  // fine bins of the first digit: four octaves above the guess
 
 // After a miss (a guess that was too high, a full region, the first step of a vector of few tiles) the workgroup lists the
 // vector again by itself: one pass counts the coarse bins, a second lists what lies in the k-th largest's bin or above,
@@ -2160,7 +2118,7 @@ __device__ __forceinline__ uint32_t list_short_again(const TkGeom &ge, int i, co
         }
     }
     __syncthreads();
-    find_rank_bin(L.lh, L.part, L.res, kBins1, ge.k);
+    find_rank_bin<kBins1>(L.lh, L.part, L.res, ge.k);
     const uint32_t prefix = L.res[3] ? L.res[0] : 0u;                   // fewer than k counted: bin 0
     if (L.res[3]) top = {prefix, ge.k - L.res[1], kShift1 + ge.idx_bits};
     uint32_t run = 0;
@@ -2206,14 +2164,7 @@ __device__ __forceinline__ uint32_t list_short_again(const TkGeom &ge, int i, co
         }
         __syncthreads();
         // every wavefront adds the counts up for itself
-        const uint32_t mine = S.count[lane];
-        uint32_t incl = mine;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const uint32_t up = __shfl_up(incl, off, kWave);
-            if (lane >= off) incl += up;
-        }
-        const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
+        const uint32_t mine = S.count[lane], incl = wave_scan(mine), total = scan_total(incl);
         if (total > ge.region_cap - run) return kNoSpace;               // uniform over the workgroup
         if (wave == 0) {
             // lane 16 u + 4 w: the first of the four counts of wavefront w of tile t0 + u
@@ -2260,6 +2211,9 @@ __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom sge, T
     const uint2 *list = cand + worker_base(sge, i);
     uint32_t total = count[i * kCursorStride];
     const TkWorker w = ws[i];
+    for (int q = tid; q < kShortFine; q += kResolveThreads) L.lh[q] = 0;
+    if (tid == 0) L.n_few = 0;
+    __syncthreads();                                                  // nothing waits for memory yet
     const SelKey sk = sel_key_of(sge.rand, sge.rand.step_now, i);
     const bool zeros_listed = kSrc != kSrcStored || sk.on;           // see tk_pass1
     const ExactSource es{kSrc, std::is_same<G, float>::value ? 0 : std::is_same<G, uint16_t>::value ? 1 : 2, a, b};
@@ -2281,14 +2235,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom sge, T
         if (total <= (uint32_t)kRankAll) {
             if ((uint32_t)tid < total) L.few[tid] = comp_of(tid);
             __syncthreads();
-            if ((uint32_t)tid < total) {
-                const uint64_t mine = L.few[tid];
-                uint32_t greater = 0;
-                for (uint32_t u = 0; u < total; ++u) greater += L.few[u] > mine ? 1u : 0u;
-                if (greater + 1 == sge.k) L.tc_sh = mine;             // comp values are unique: exactly one thread
-            }
-            __syncthreads();
-            tc = L.tc_sh;
+            tc = rank_few(total, sge.k, L);
         } else if (total <= (uint32_t)(kScanUnroll * kResolveThreads)) {
             uint64_t held[kScanUnroll];
 #pragma unroll
@@ -2297,7 +2244,33 @@ __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom sge, T
 #pragma unroll
                 for (int u = 0; u < kScanUnroll; ++u) comp[u] = held[u];       // one batch: q[u] = u * kResolveThreads + tid
             };
-            tc = resolve_digits<false>(fetch, total, top.prefix, top.rank, top.open, L);
+            // The first digit: the fine bin, counted from the guess's, below which nothing is listed, up to kShortFine bins.
+            // The threshold lies a little above the guess, so its bin is among them and holds a few entries.
+            bool found = false;
+            if (!missed) {
+                const uint32_t guess = w.guess;
+                const int open = kFineShift + sge.idx_bits;
+#pragma unroll
+                for (int u = 0; u < kScanUnroll; ++u)
+                    if (u * kResolveThreads + tid < total)
+                        atomicAdd(&L.lh[min((uint32_t)(held[u] >> open) - guess, (uint32_t)kShortFine - 1u)], 1u);
+                __syncthreads();
+                find_rank_bin<kShortFine>(L.lh, L.part, L.res, sge.k);
+                const uint32_t bin = L.res[0], left = L.res[2];
+                top = {guess + bin, sge.k - L.res[1], open};
+                if (bin == (uint32_t)kShortFine - 1u) {                          // holds all beyond as well
+                    top = {0ull, sge.k, 31 + sge.idx_bits};
+                } else if (left <= (uint32_t)kFew) {
+#pragma unroll
+                    for (int u = 0; u < kScanUnroll; ++u)
+                        if (u * kResolveThreads + tid < total && (held[u] >> open) == top.prefix)
+                            L.few[atomicAdd(&L.n_few, 1u)] = held[u];
+                    __syncthreads();
+                    tc = rank_few(left, top.rank, L);
+                    found = true;
+                }
+            }
+            if (!found) tc = resolve_digits<false>(fetch, total, top.prefix, top.rank, top.open, L);
         } else {
             auto fetch = [&](const uint32_t (&q)[kScanUnroll], uint64_t (&comp)[kScanUnroll]) {
 #pragma unroll

@@ -255,6 +255,28 @@ def test_short_vectors_of_equal_values_or_few_nonzeros(method, share):
     gpu.destroy()
 
 
+# tk_small_select's first digit, the fine bin above the guess: a scale that jumps 2**11 up leaves the threshold beyond the bins
+# counted one by one, a dozen magnitudes leave more than 256 entries in the threshold's bin, the others a few
+@pytest.mark.parametrize("method", ["ef", "naive", "cd"])
+@pytest.mark.parametrize("comp", [P.TOPK, P.RANDK])
+@pytest.mark.parametrize("kind", ["jump", "grid", "plain"])
+def test_short_vectors_first_digit(method, comp, kind):
+    d, n, k = 3 * 1024 + 5, 3, 400
+    print(f"[case] first digit of a short vector, {kind}, {method}, comp={comp}", flush=True)
+    gpu, ora = sparse_pair(d, n, k, method, comp)
+    if comp == P.RANDK:
+        gpu.set_rand(5)
+        ora.set_rand(5)
+
+    def fn(t):
+        x = grads_of(17, n, d)(t) * f32(100.0)
+        if kind == "grid":
+            x = np.round(x * f32(64.0 / 16.0)) / f32(4.0)        # a dozen magnitudes, thousands of ties
+        return np.ascontiguousarray(x * f32(2.0 ** (11 * (t % 2)) if kind == "jump" else 1.0), dtype=f32)
+    sparse_steps(gpu, ora, fn, 5, method, f"{kind} {method}")
+    gpu.destroy()
+
+
 # tk_final_short / tk_final at the boundary between them; more than 64 kept values in a wavefront's quarter, more than
 # one batch of eight workers
 @pytest.mark.parametrize("tiles,n,share", [(320, 9, 0.3), (321, 9, 0.3), (320, 1, 0.001), (64, 48, 0.01), (65, 48, 0.01)])
