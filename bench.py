@@ -123,8 +123,7 @@ def kernel_algorithmic_bytes(name: str, n: int, d: int, method: str = "ef") -> i
         "tk_final": 32 * d,
         "bs_server": 12 * d,
         "bs_apply": 40 * d,
-        "tk_merge": 8 * d,
-        "tk_pass1_server": 8 * d,
+        "tk_merge": 12 * d,       # ghat read and written, gtilde read for the server's candidates
         "tk_apply": 40 * d,
         "plain_update": 4 * nd + 32 * d,
     }.get(name, 0)

@@ -257,11 +257,11 @@ inline uint32_t per_step_word(const comp_ams *h, uint32_t draw) { return host_mi
 namespace {
 
 enum ProfSlot { P_BS_PASS, P_BS_SCALE, P_BS_UPDATE, P_TK_PASS1, P_TK_HIST, P_TK_COMPACT,
-                P_TK_RESOLVE, P_TK_FINAL, P_BS_SERVER, P_BS_SCALE_SERVER, P_BS_APPLY, P_TK_MERGE, P_TK_PASS1_SERVER,
+                P_TK_RESOLVE, P_TK_FINAL, P_BS_SERVER, P_BS_SCALE_SERVER, P_BS_APPLY, P_TK_MERGE,
                 P_TK_SELECT_SERVER, P_TK_APPLY, P_PLAIN_UPDATE, P_BS_PASS_UPDATE, P_BS_STEP, P_SLOTS };
 const char *const kProfNames[P_SLOTS] = {"bs_pass", "bs_scale", "bs_update", "tk_pass1", "tk_hist",
                                          "tk_compact", "tk_resolve", "tk_final", "bs_server",
-                                         "bs_scale_server", "bs_apply", "tk_merge", "tk_pass1_server", "tk_select_server",
+                                         "bs_scale_server", "bs_apply", "tk_merge", "tk_select_server",
                                          "tk_apply", "plain_update", "bs_pass_update", "bs_step_short"};
 
 // Kernel launches of a step go through KLAUNCH.  With profiling on, launch_timed hands the launch a
@@ -913,7 +913,7 @@ int step_plain(comp_ams *h, const G *g, hipStream_t st)
     return COMP_AMS_OK;
 }
 
-// One iteration of Algorithm 1 (CD-Adam) with Top-k in both directions: ten launches, six on a short vector.
+// One iteration of Algorithm 1 (CD-Adam) with Top-k in both directions: nine launches, five on a short vector.
 template <typename G>
 int step_topk_cd(comp_ams *h, const G *g, hipStream_t st)
 {
@@ -936,28 +936,23 @@ int step_topk_cd(comp_ams *h, const G *g, hipStream_t st)
         launch_select<kSrcGrad, G>(h, st, ge, h->ws, h->cand, h->cursor, h->cursor_b, h->tile_dir, h->hist1, h->histf,
                                    h->hist_full, h->hist2, h->piece_bits, h->dense, h->dense_dir, g, h->e, kWorkerSelectSlots);
     }
-    launch_timed(h, P_TK_MERGE, st, [&] {
-        KLAUNCH((tk_merge), ge.n_tiles, kThreads, st, ge, h->ws, h->cand, h->tile_dir, h->e, h->ghat_srv,
-                                                  h->params.n_workers);
-    });
+    // the server's side: merge lists its candidates as well
+    TkSide side = sv;
     if (brief) {
-        const TkGeom sge = short_geometry(sv.ge);
-        uint32_t *count = h->small_ctr + (size_t)h->n * kCursorStride;      // the server's, after the workers'
-        launch_timed(h, P_TK_PASS1_SERVER, st, [&] { by_key<kPassDiff, float>(h, [&](auto key) {
-            KLAUNCH((tk_pass1<kPassDiff, decltype(key)::value, float>), dim3(sge.n_tiles, 1), kThreads, st, h->ghat_srv, h->gtil, sge, sv.ws, sv.cand,
-                    count, sv.tile_dir);
-        }); });
-        launch_short_select<kSrcDiff, float>(h, st, sge, sv.ws, sv.cand, count, sv.tile_dir, h->ghat_srv, h->gtil,
+        side.ge = short_geometry(sv.ge);
+        side.cursor = h->small_ctr + (size_t)h->n * kCursorStride;          // the server's, after the workers'
+    }
+    launch_timed(h, P_TK_MERGE, st, [&] { by_key<kPassCd, G>(h, [&](auto key) { by_flag(merge_loads_early(ge.n_tiles), [&](auto early) {
+        KLAUNCH((tk_merge<decltype(key)::value, decltype(early)::value>), ge.n_tiles, kThreads, st, ge, h->ws, h->cand, h->tile_dir,
+                h->e, h->ghat_srv, h->gtil, h->params.n_workers, side);
+    }); }); });
+    if (brief)
+        launch_short_select<kSrcDiff, float>(h, st, side.ge, sv.ws, sv.cand, side.cursor, sv.tile_dir, h->ghat_srv, h->gtil,
                                              P_TK_SELECT_SERVER);
-    } else {
-        launch_timed(h, P_TK_PASS1_SERVER, st, [&] { by_key<kPassDiff, float>(h, [&](auto key) {
-            KLAUNCH((tk_pass1<kPassDiff, decltype(key)::value, float>), dim3(grid_blocks(ge.n_tiles, sv.ge.xcd_chunk), 1), kThreads, st, h->ghat_srv,
-                    h->gtil, sv.ge, sv.ws, sv.cand, sv.cursor, sv.tile_dir);
-        }); });
+    else
         launch_select<kSrcDiff, float>(h, st, sv.ge, sv.ws, sv.cand, sv.cursor, h->cursor_b_s, sv.tile_dir, h->hist1_s, h->histf_s,
                                        h->hist_full_s, h->hist2_s, h->piece_bits_s, h->dense_s, h->dense_dir_s, h->ghat_srv, h->gtil,
                                        kServerSelectSlots);
-    }
     launch_timed(h, P_TK_APPLY, st, [&] {
         by_flag(h->params.stream_state, [&](auto ss) {
             KLAUNCH((tk_apply<decltype(ss)::value>), ge.n_tiles, kThreads, st, sv, h->gtil, h->theta, h->m, h->v,

@@ -39,6 +39,12 @@ inline bool one_launch_sign(int64_t n, int64_t d, int64_t n_tiles)
     return n_tiles <= kOneLaunchTiles && n * rows <= kOneLaunchPairs;
 }
 
+// Whether tk_merge loads the server's vectors before the kept values: on few tiles nothing else hides that latency, on many the
+// registers (102 against 68) cost more wavefronts.  CD-Adam, step plus get_theta, us, late / early: Top-k n = 2, d = 600 000
+// 64.2 / 62.0, n = 8, d = 300 000 65.2 / 63.7, d = 2 M 107.7 / 104.3, Rand-k d = 5 M 188.3 / 188.1, Top-k d = 11.2 M bf16 334 / 337, n = 16
+// 502 / 510, n = 8, d = 40 M 861 / 889.
+inline bool merge_loads_early(int64_t n_tiles) { return n_tiles < 1024; }
+
 // Grid of a kernel with one workgroup per tile (in x) under tile_of_block's mapping.
 inline unsigned grid_blocks(int64_t n_tiles, int chunk)
 {

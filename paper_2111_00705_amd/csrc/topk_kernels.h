@@ -453,9 +453,8 @@ __device__ __forceinline__ void consider(float x, uint32_t j, uint32_t base, boo
 // Modes: kPassEf  error feedback: x = g + e, written back over the stored vector;
 //        kPassCd  CD-Adam worker (Algorithm 1, line 5): u = g - ghat_i, nothing written back (ghat_i
 //                 changes only where c_i is not zero; tk_merge does that);
-//        kPassDiff  CD-Adam server (line 9): w = ghat - gtilde, both padded rows, nothing written back;
 //        kPassNaive  naive compression (Section 4): x = g, the stored rows are not touched.
-enum { kPassEf = 0, kPassCd = 1, kPassDiff = 2, kPassNaive = 3 };
+enum { kPassEf = 0, kPassCd = 1, kPassNaive = 3 };
 
 // The gradients and the stored values of this thread's coordinates, base + 4 (tid + 256 r) + c.  kFull: the whole tile lies
 // below d.
@@ -466,12 +465,7 @@ __device__ __forceinline__ void load_pass_tile(GradRaw<G> (&gv)[4], float4 (&xv)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const uint32_t j = base + 4 * (threadIdx.x + kThreads * r);
-        if constexpr (kMode == kPassDiff) {
-            const float4 a = ld4_row(grow + j, stream_rows);
-            gv[r].v = {a.x, a.y, a.z, a.w};
-        } else {
-            gv[r] = load_raw4<kFull>(grow, j, d);
-        }
+        gv[r] = load_raw4<kFull>(grow, j, d);
         xv[r] = kMode == kPassNaive ? make_float4(0.f, 0.f, 0.f, 0.f) : ld4_row(xrow + j, stream_rows);
     }
 }
@@ -583,29 +577,24 @@ constexpr bool kListDirect = (kMode == kPassEf && sizeof(G) == 4) || kMode == kP
 // (-4.5 to 0.5 %); n = 8, d = 110 M, k = 0.1 % 1652 / 1677 us.  Five shapes of 11 M to 55 M, Top-k: 0.2 % slower (-1.9 to 1.5 %).
 enum { kKeyMagnitude = 0, kKeyScore = 1, kKeyEither = 2 };
 
-// A tile listed straight from the registers.
-template <bool kFull, int kMode, typename G>
-__device__ __forceinline__ void pass1_direct(const G *__restrict__ grow, float *__restrict__ xrow, uint32_t base, uint32_t d,
-                                             const KeptTest &kt, uint32_t guess, const SelKey &sk, const SelKey &sk_prev,
-                                             int stream_rows, uint32_t *sh, const TkGeom &ge, int i, int t,
-                                             uint2 *__restrict__ cand, uint32_t *__restrict__ cursor,
-                                             uint4 *__restrict__ tile_dir, uint32_t *overflow_flag)
+// Lists the candidates among this thread's 16 values of tile t straight from the registers (x[r][c]: coordinate
+// base + 4 (tid + 256 r) + c).  kSkipZeros: see consider.  All threads of the workgroup call this.
+template <bool kFull, bool kSkipZeros>
+__device__ __forceinline__ void list_registers(const float (&x)[4][4], uint32_t base, uint32_t d, uint32_t guess, const SelKey &sk,
+                                               uint32_t *sh, const TkGeom &ge, int i, int t, uint2 *__restrict__ cand,
+                                               uint32_t *__restrict__ cursor, uint4 *__restrict__ tile_dir,
+                                               uint32_t *overflow_flag)
 {
     const int tid = threadIdx.x, wave = tid >> 6;
-    GradRaw<G> gv[4];
-    float4 xv[4];
-    load_pass_tile<kFull, kMode>(gv, xv, grow, xrow, base, d, stream_rows);
-    float x[4][4];
     uint32_t count = 0, zeros = 0, hits = 0;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const uint32_t j = base + 4 * (tid + kThreads * r);
-        form_coordinates<kFull, kMode>(x[r], widen4(gv[r]), xv[r], j, d, kt, sk_prev, xrow);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const bool valid = kFull || j + c < d;
             bool hit = valid && (sel_key(sk, x[r][c], j + c) >> kFineShift) >= guess;
-            if (kMode == kPassEf && !sk.on) {
+            if (kSkipZeros && !sk.on) {
                 const bool zero = valid && mag_key(x[r][c]) == 0u;
                 zeros += (uint32_t)__popcll(__ballot(zero));
                 hit = hit && !zero;
@@ -627,6 +616,24 @@ __device__ __forceinline__ void pass1_direct(const G *__restrict__ grow, float *
             const uint32_t slot = wave_append(hit, at);
             if (hit) dst[slot] = make_uint2(base + 4 * (tid + kThreads * r) + c, __float_as_uint(x[r][c]));
         }
+}
+
+// A tile of the listing pass listed straight from the registers.
+template <bool kFull, int kMode, typename G>
+__device__ __forceinline__ void pass1_direct(const G *__restrict__ grow, float *__restrict__ xrow, uint32_t base, uint32_t d,
+                                             const KeptTest &kt, uint32_t guess, const SelKey &sk, const SelKey &sk_prev,
+                                             int stream_rows, uint32_t *sh, const TkGeom &ge, int i, int t,
+                                             uint2 *__restrict__ cand, uint32_t *__restrict__ cursor,
+                                             uint4 *__restrict__ tile_dir, uint32_t *overflow_flag)
+{
+    GradRaw<G> gv[4];
+    float4 xv[4];
+    load_pass_tile<kFull, kMode>(gv, xv, grow, xrow, base, d, stream_rows);
+    float x[4][4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        form_coordinates<kFull, kMode>(x[r], widen4(gv[r]), xv[r], base + 4 * (threadIdx.x + kThreads * r), d, kt, sk_prev, xrow);
+    list_registers<kFull, kMode == kPassEf>(x, base, d, guess, sk, sh, ge, i, t, cand, cursor, tile_dir, overflow_flag);
 }
 
 // G: element type of g - float, or uint16_t (bfloat16 bits) for gradients handed over as bfloat16.
@@ -651,7 +658,7 @@ __global__ __launch_bounds__(kThreads, kMode == kPassNaive ? 8 : 1) void tk_pass
     if constexpr (kKey != kKeyEither) sk.on = sk_prev.on = kKey == kKeyScore ? 1u : 0u;
     const uint32_t d = (uint32_t)ge.d;
     const uint32_t base = (uint32_t)t * kTile;
-    const G *grow = g + (int64_t)i * (kMode == kPassDiff ? ge.ld : ge.d);
+    const G *grow = g + (int64_t)i * ge.d;
     float *xrow = xs + (int64_t)i * ge.ld;
     if constexpr (kDirect) {
         if (base + kTile <= d)
@@ -2301,31 +2308,58 @@ struct TkSide {
     uint4 *tile_dir;
 };
 
-// Per tile: ghat_i += c_i (line 6) and ghat += mean of the c_i (line 8).  The server's vector
-// w = ghat - gtilde (line 9) is then listed by tk_pass1<kPassDiff>.
+// Per tile: ghat_i += c_i (line 6), ghat += mean of the c_i (line 8), and the server's vector w = ghat - gtilde (line 9), whose
+// candidates are listed straight from the registers; sv: the server's selection.  The scattered additions are most of it on long
+// rows, each the read and the write of a whole line in memory (n = 8, d = 11.2 M, 1.4 M kept values: 51 of 77 us); the listing here
+// saves a launch that read ghat and gtilde again (two kernels / one, us: the same bf16 94.8 / 91.4, d = 2 M 17.5 / 14.4, step plus
+// get_theta 342 / 334 and 112 / 104).  kEarly: ghat and gtilde are loaded first, see merge_loads_early.
+template <int kKey, bool kEarly>
 __global__ __launch_bounds__(kThreads) void tk_merge(TkGeom ge, const TkWorker *__restrict__ ws,
                                                      const uint2 *__restrict__ cand,
                                                      const uint4 *__restrict__ tile_dir,
                                                      float *__restrict__ ghat_rows, float *__restrict__ ghat,
-                                                     float n_workers)
+                                                     const float *__restrict__ gtil, float n_workers, TkSide sv)
 {
     __shared__ float acc[kTile];
+    __shared__ uint32_t sh[9];
     const int t = blockIdx.x;
-    const int64_t base = (int64_t)t * kTile;
+    const uint32_t base = (uint32_t)t * kTile, d = (uint32_t)ge.d;
     const int tid = threadIdx.x;
+    float4 gh[4], gt[4];
+    auto load_server = [&] {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            gh[r] = ld4(ghat + base + 4 * (tid + kThreads * r));
+            gt[r] = ld4(gtil + base + 4 * (tid + kThreads * r));
+        }
+    };
+    if (kEarly) load_server();
 #pragma unroll
     for (int r = 0; r < 4; ++r) st4(acc + 4 * (tid + kThreads * r), make_float4(0.f, 0.f, 0.f, 0.f));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     sum_kept_tile<true>(acc, ge, ws, cand, tile_dir, t, ghat_rows, tid >> 6);
+    if (!kEarly) load_server();
+    float w[4][4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int l = 4 * (tid + kThreads * r);
-        const float4 a = ld4(acc + l), gh = ld4(ghat + base + l);
+        const float4 a = ld4(acc + l);
         // padding coordinates: 0 + 0 / n; ghat moves only where some worker kept a coordinate
-        st4_if_changed<false>(ghat + base + l,
-                              make_float4(fadd(gh.x, fdiv(a.x, n_workers)), fadd(gh.y, fdiv(a.y, n_workers)),
-                                          fadd(gh.z, fdiv(a.z, n_workers)), fadd(gh.w, fdiv(a.w, n_workers))), gh);
+        const float4 nh = make_float4(fadd(gh[r].x, fdiv(a.x, n_workers)), fadd(gh[r].y, fdiv(a.y, n_workers)),
+                                      fadd(gh[r].z, fdiv(a.z, n_workers)), fadd(gh[r].w, fdiv(a.w, n_workers)));
+        st4_if_changed<false>(ghat + base + l, nh, gh[r]);
+        w[r][0] = fsub(nh.x, gt[r].x);
+        w[r][1] = fsub(nh.y, gt[r].y);
+        w[r][2] = fsub(nh.z, gt[r].z);
+        w[r][3] = fsub(nh.w, gt[r].w);
     }
+    SelKey sk = sel_key_of(sv.ge.rand, sv.ge.rand.step_now, 0);
+    sk.on = kKey == kKeyScore ? 1u : 0u;
+    const uint32_t guess = sv.ws[0].guess;
+    if (base + kTile <= d)
+        list_registers<true, false>(w, base, d, guess, sk, sh, sv.ge, 0, t, sv.cand, sv.cursor, sv.tile_dir, &sv.ws[0].overflow);
+    else
+        list_registers<false, false>(w, base, d, guess, sk, sh, sv.ge, 0, t, sv.cand, sv.cursor, sv.tile_dir, &sv.ws[0].overflow);
 }
 
 // CD-Adam (Algorithm 1), lines 10 and 12-16: gtilde += c, c = the kept coordinates of w, then the

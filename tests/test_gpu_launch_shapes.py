@@ -255,6 +255,20 @@ def test_short_vectors_of_equal_values_or_few_nonzeros(method, share):
     gpu.destroy()
 
 
+# tk_merge lists the server's candidates: its vectors loaded before the kept values up to 1023 tiles, after them beyond; a first
+# step without a guess, ragged last tiles, one tile and one more than the short path takes
+@pytest.mark.parametrize("comp", [P.TOPK, P.RANDK])
+@pytest.mark.parametrize("d,n,k", [(1, 3, 1), (TILE - 1, 3, 200), (17 * TILE + 3, 3, 900), (1023 * TILE, 2, 5000), (1023 * TILE + 6, 2, 5000)])
+def test_server_candidates_listed_by_the_merge(comp, d, n, k):
+    print(f"[case] merge d={d} n={n} k={k} comp={comp}", flush=True)
+    gpu, ora = sparse_pair(d, n, k, "cd", comp)
+    if comp == P.RANDK:
+        gpu.set_rand(9)
+        ora.set_rand(9)
+    sparse_steps(gpu, ora, grads_of(d, n, d), 3, "cd", f"merge {d}")
+    gpu.destroy()
+
+
 # tk_small_select's first digit, the fine bin above the guess: a scale that jumps 2**11 up leaves the threshold beyond the bins
 # counted one by one, a dozen magnitudes leave more than 256 entries in the threshold's bin, the others a few
 @pytest.mark.parametrize("method", ["ef", "naive", "cd"])

@@ -41,6 +41,10 @@ def test_one_launch_sign_step_only_where_few_workers_share_a_quarter(tmp_path):
     assert got == list(cases.values())
 
 
+def test_merge_loads_the_server_first_on_few_tiles(tmp_path):
+    assert evaluate(tmp_path, [f"merge_loads_early({t})" for t in (1, 1023, 1024, 500_000)]) == [1, 1, 0, 0]
+
+
 def test_uncompressed_update_pads_its_grid_to_no_more_than_eight_vectors(tmp_path):
     quarters = [1, 4, 64, 511, 512, 977, 100_000, 2_097_152]
     choices = [-1, 0, 1, 16, 1024, 65_536]
