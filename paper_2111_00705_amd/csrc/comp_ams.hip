@@ -809,20 +809,27 @@ unsigned tk_pass_lds(const comp_ams *h)
     return lists + (rows_exceed_caches(h) && !tk_long_rows(h) ? 7000u : 9u * 1024u);
 }
 
-// Calls f with what tk_pass1<kMode, ., G> may take for granted about the keys (see kKeyEither) as a compile-time constant.
+// Calls f with two compile-time constants of tk_pass1<kMode, ., ., G>: what it may take for granted about the keys (see kKeyEither),
+// and whether it lists with few instructions, which the long rows of error feedback do not want (see list_registers).
 template <int kMode, typename G, typename F>
 void by_key(const comp_ams *h, F &&f)
 {
     if constexpr (kMode == kPassEf && std::is_same<G, float>::value) {
         if (tk_long_rows(h)) {
-            f(std::integral_constant<int, kKeyEither>{});
+            f(std::integral_constant<int, kKeyEither>{}, std::false_type{});
             return;
         }
     }
-    if (h->compressor == COMP_AMS_RANDK)
-        f(std::integral_constant<int, kKeyScore>{});
-    else
-        f(std::integral_constant<int, kKeyMagnitude>{});
+    const bool few = kListDirect<kMode, G> && !(kMode == kPassEf && row_bytes(h) > kWithinStepBytes);
+    by_flag(h->compressor == COMP_AMS_RANDK, [&](auto score) {
+        constexpr int key = decltype(score)::value ? kKeyScore : kKeyMagnitude;
+        if constexpr (!kListDirect<kMode, G>)
+            f(std::integral_constant<int, key>{}, std::false_type{});
+        else if constexpr (kMode != kPassEf)
+            f(std::integral_constant<int, key>{}, std::true_type{});
+        else
+            by_flag(few, [&](auto fw) { f(std::integral_constant<int, key>{}, fw); });
+    });
 }
 
 // Short vectors: the geometry with one region per vector (all of its space), and the selection in one launch.  Without a
@@ -852,8 +859,8 @@ int step_topk(comp_ams *h, const G *g, hipStream_t st)
 {
     if (is_short(h)) {
         const TkGeom sge = short_geometry(h->ge);
-        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassEf, G>(h, [&](auto key) {
-            KLAUNCH((tk_pass1<kPassEf, decltype(key)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
+        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassEf, G>(h, [&](auto key, auto few) {
+            KLAUNCH((tk_pass1<kPassEf, decltype(key)::value, decltype(few)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
                     h->tile_dir);
         }); });
         launch_short_select<kSrcStored, float>(h, st, sge, h->ws, h->cand, h->small_ctr, h->tile_dir, h->e, nullptr, P_TK_RESOLVE);
@@ -862,8 +869,8 @@ int step_topk(comp_ams *h, const G *g, hipStream_t st)
     }
     const TkGeom &ge = h->ge;
     const TkGeom pge = pass_geometry<G>(h);
-    launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassEf, G>(h, [&](auto key) {
-        KLAUNCH_LDS((tk_pass1<kPassEf, decltype(key)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassEf, G>(h)), st, g, h->e, pge, h->ws,
+    launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassEf, G>(h, [&](auto key, auto few) {
+        KLAUNCH_LDS((tk_pass1<kPassEf, decltype(key)::value, decltype(few)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassEf, G>(h)), st, g, h->e, pge, h->ws,
                 h->cand, h->cursor, h->tile_dir);
     }); });
     launch_select<kSrcStored, float>(h, st, ge, h->ws, h->cand, h->cursor, h->cursor_b, h->tile_dir, h->hist1, h->histf,
@@ -878,8 +885,8 @@ int step_topk_naive(comp_ams *h, const G *g, hipStream_t st)
 {
     if (is_short(h)) {
         const TkGeom sge = short_geometry(h->ge);
-        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassNaive, G>(h, [&](auto key) {
-            KLAUNCH((tk_pass1<kPassNaive, decltype(key)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
+        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassNaive, G>(h, [&](auto key, auto few) {
+            KLAUNCH((tk_pass1<kPassNaive, decltype(key)::value, decltype(few)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
                     h->tile_dir);
         }); });
         launch_short_select<kSrcGradOnly, G>(h, st, sge, h->ws, h->cand, h->small_ctr, h->tile_dir, g, nullptr, P_TK_RESOLVE);
@@ -888,8 +895,8 @@ int step_topk_naive(comp_ams *h, const G *g, hipStream_t st)
     }
     const TkGeom &ge = h->ge;
     const TkGeom pge = pass_geometry<G>(h);
-    launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassNaive, G>(h, [&](auto key) {
-        KLAUNCH_LDS((tk_pass1<kPassNaive, decltype(key)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassNaive, G>(h)), st, g, h->e, pge, h->ws,
+    launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassNaive, G>(h, [&](auto key, auto few) {
+        KLAUNCH_LDS((tk_pass1<kPassNaive, decltype(key)::value, decltype(few)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassNaive, G>(h)), st, g, h->e, pge, h->ws,
                 h->cand, h->cursor, h->tile_dir);
     }); });
     launch_select<kSrcGradOnly, G>(h, st, ge, h->ws, h->cand, h->cursor, h->cursor_b, h->tile_dir, h->hist1, h->histf,
@@ -923,14 +930,14 @@ int step_topk_cd(comp_ams *h, const G *g, hipStream_t st)
     const bool brief = is_short(h);
     if (brief) {
         const TkGeom sge = short_geometry(ge);
-        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassCd, G>(h, [&](auto key) {
-            KLAUNCH((tk_pass1<kPassCd, decltype(key)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
+        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassCd, G>(h, [&](auto key, auto few) {
+            KLAUNCH((tk_pass1<kPassCd, decltype(key)::value, decltype(few)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
                     h->tile_dir);
         }); });
         launch_short_select<kSrcGrad, G>(h, st, sge, h->ws, h->cand, h->small_ctr, h->tile_dir, g, h->e, P_TK_RESOLVE);
     } else {
-        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassCd, G>(h, [&](auto key) {
-            KLAUNCH_LDS((tk_pass1<kPassCd, decltype(key)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassCd, G>(h)), st, g, h->e, pge, h->ws,
+        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassCd, G>(h, [&](auto key, auto few) {
+            KLAUNCH_LDS((tk_pass1<kPassCd, decltype(key)::value, decltype(few)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassCd, G>(h)), st, g, h->e, pge, h->ws,
                     h->cand, h->cursor, h->tile_dir);
         }); });
         launch_select<kSrcGrad, G>(h, st, ge, h->ws, h->cand, h->cursor, h->cursor_b, h->tile_dir, h->hist1, h->histf,
@@ -942,7 +949,7 @@ int step_topk_cd(comp_ams *h, const G *g, hipStream_t st)
         side.ge = short_geometry(sv.ge);
         side.cursor = h->small_ctr + (size_t)h->n * kCursorStride;          // the server's, after the workers'
     }
-    launch_timed(h, P_TK_MERGE, st, [&] { by_key<kPassCd, G>(h, [&](auto key) { by_flag(merge_loads_early(ge.n_tiles), [&](auto early) {
+    launch_timed(h, P_TK_MERGE, st, [&] { by_key<kPassCd, G>(h, [&](auto key, auto) { by_flag(merge_loads_early(ge.n_tiles), [&](auto early) {
         KLAUNCH((tk_merge<decltype(key)::value, decltype(early)::value>), ge.n_tiles, kThreads, st, ge, h->ws, h->cand, h->tile_dir,
                 h->e, h->ghat_srv, h->gtil, h->params.n_workers, side);
     }); }); });

@@ -579,47 +579,84 @@ enum { kKeyMagnitude = 0, kKeyScore = 1, kKeyEither = 2 };
 
 // Lists the candidates among this thread's 16 values of tile t straight from the registers (x[r][c]: coordinate
 // base + 4 (tid + 256 r) + c).  kSkipZeros: see consider.  All threads of the workgroup call this.
-template <bool kFull, bool kSkipZeros>
+// kFew: with few instructions - a value takes a subtraction, whose top bit says that its key lies below the guess, and a shift of
+// that bit into a mask; a thread's candidates follow one another in the list.  Else slot by slot of the wavefront.  Step plus
+// get_theta, us, slot by slot / with few: naive Rand-k n = 8, d = 3 M bf16 73.9 / 71.6, Top-k 68.2 / 68.2, d = 100 M 1105 / 1097, error
+// feedback n = 4, d = 65 536 29.3 / 28.9, n = 8, d = 300 000 44.6 / 44.1, d = 2 M 83.4 / 82.2, Rand-k n = 16, d = 1.2 M 84.9 / 84.1; long rows
+// under error feedback lose: n = 16, d = 11.2 M 455.1 / 457.2, n = 8, d = 25 M 587 / 592, d = 110 M 2374 / 2416.
+template <bool kFull, bool kSkipZeros, bool kFew>
 __device__ __forceinline__ void list_registers(const float (&x)[4][4], uint32_t base, uint32_t d, uint32_t guess, const SelKey &sk,
                                                uint32_t *sh, const TkGeom &ge, int i, int t, uint2 *__restrict__ cand,
                                                uint32_t *__restrict__ cursor, uint4 *__restrict__ tile_dir,
                                                uint32_t *overflow_flag)
 {
-    const int tid = threadIdx.x, wave = tid >> 6;
-    uint32_t count = 0, zeros = 0, hits = 0;
+    if constexpr (kFew) {
+        const int tid = threadIdx.x, wave = tid >> 6;
+        const uint32_t first = guess << kFineShift;      // the smallest key that is listed; kNoGuess gives 2^31, above every key
+        uint32_t below = 0, zero = 0;                    // bit 15 - (4 r + c)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const uint32_t j = base + 4 * (tid + kThreads * r);
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t j = base + 4 * (tid + kThreads * r);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const bool valid = kFull || j + c < d;
-            bool hit = valid && (sel_key(sk, x[r][c], j + c) >> kFineShift) >= guess;
-            if (kSkipZeros && !sk.on) {
-                const bool zero = valid && mag_key(x[r][c]) == 0u;
-                zeros += (uint32_t)__popcll(__ballot(zero));
-                hit = hit && !zero;
+            for (int c = 0; c < 4; ++c) {
+                const bool valid = kFull || j + c < d;
+                const uint32_t under = sel_key(sk, x[r][c], j + c) - first;
+                below = __builtin_amdgcn_alignbit(below, valid ? under : ~0u, 31);
+                if (kSkipZeros && !sk.on) zero = __builtin_amdgcn_alignbit(zero, valid ? mag_key(x[r][c]) - 1u : 0u, 31);
             }
-            count += (uint32_t)__popcll(__ballot(hit));
-            hits |= (hit ? 1u : 0u) << (r * 4 + c);
         }
+        const uint32_t hits = ~(below | zero) & 0xffffu;
+        // this thread's counts and the wavefront's, zeros in the upper half (a wavefront owns 1024 coordinates)
+        const uint32_t mine = __popc(hits) | (kSkipZeros ? (uint32_t)__popc(zero) << 16 : 0u);
+        const uint32_t incl = wave_scan(mine), both = scan_total(incl);
+        take_tile_space(both & 0xffffu, both >> 16, sh, ge, i, t, cursor, tile_dir, overflow_flag);
+        uint32_t at = sh[4];
+        if (at == kNoSpace) return;
+        at += (wave > 0 ? sh[0] : 0u) + (wave > 1 ? sh[1] : 0u) + (wave > 2 ? sh[2] : 0u) + ((incl - mine) & 0xffffu);
+        uint2 *dst = cand + worker_base(ge, i);          // uniform
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (hits & (0x8000u >> (r * 4 + c)))
+                    *at_offset(dst, at++) = make_uint2(base + 4 * (tid + kThreads * r) + c, __float_as_uint(x[r][c]));
+    } else {
+        const int tid = threadIdx.x, wave = tid >> 6;
+        uint32_t count = 0, zeros = 0, hits = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t j = base + 4 * (tid + kThreads * r);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const bool valid = kFull || j + c < d;
+                bool hit = valid && (sel_key(sk, x[r][c], j + c) >> kFineShift) >= guess;
+                if (kSkipZeros && !sk.on) {
+                    const bool zero = valid && mag_key(x[r][c]) == 0u;
+                    zeros += (uint32_t)__popcll(__ballot(zero));
+                    hit = hit && !zero;
+                }
+                count += (uint32_t)__popcll(__ballot(hit));
+                hits |= (hit ? 1u : 0u) << (r * 4 + c);
+            }
+        }
+        take_tile_space(count, zeros, sh, ge, i, t, cursor, tile_dir, overflow_flag);
+        uint32_t at = sh[4];
+        if (at == kNoSpace) return;
+        for (int w = 0; w < wave; ++w) at += sh[w];
+        uint2 *dst = cand + worker_base(ge, i);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const bool hit = (hits >> (r * 4 + c)) & 1u;
+                const uint32_t slot = wave_append(hit, at);
+                if (hit) dst[slot] = make_uint2(base + 4 * (tid + kThreads * r) + c, __float_as_uint(x[r][c]));
+            }
     }
-    take_tile_space(count, zeros, sh, ge, i, t, cursor, tile_dir, overflow_flag);
-    uint32_t at = sh[4];
-    if (at == kNoSpace) return;
-    for (int w = 0; w < wave; ++w) at += sh[w];
-    uint2 *dst = cand + worker_base(ge, i);
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const bool hit = (hits >> (r * 4 + c)) & 1u;
-            const uint32_t slot = wave_append(hit, at);
-            if (hit) dst[slot] = make_uint2(base + 4 * (tid + kThreads * r) + c, __float_as_uint(x[r][c]));
-        }
 }
 
 // A tile of the listing pass listed straight from the registers.
-template <bool kFull, int kMode, typename G>
+template <bool kFull, int kMode, bool kFew, typename G>
 __device__ __forceinline__ void pass1_direct(const G *__restrict__ grow, float *__restrict__ xrow, uint32_t base, uint32_t d,
                                              const KeptTest &kt, uint32_t guess, const SelKey &sk, const SelKey &sk_prev,
                                              int stream_rows, uint32_t *sh, const TkGeom &ge, int i, int t,
@@ -633,11 +670,11 @@ __device__ __forceinline__ void pass1_direct(const G *__restrict__ grow, float *
 #pragma unroll
     for (int r = 0; r < 4; ++r)
         form_coordinates<kFull, kMode>(x[r], widen4(gv[r]), xv[r], base + 4 * (threadIdx.x + kThreads * r), d, kt, sk_prev, xrow);
-    list_registers<kFull, kMode == kPassEf>(x, base, d, guess, sk, sh, ge, i, t, cand, cursor, tile_dir, overflow_flag);
+    list_registers<kFull, kMode == kPassEf, kFew>(x, base, d, guess, sk, sh, ge, i, t, cand, cursor, tile_dir, overflow_flag);
 }
 
 // G: element type of g - float, or uint16_t (bfloat16 bits) for gradients handed over as bfloat16.
-template <int kMode, int kKey, typename G>
+template <int kMode, int kKey, bool kFew, typename G>     // kFew: see list_registers; false where the candidates are staged
 __global__ __launch_bounds__(kThreads, kMode == kPassNaive ? 8 : 1) void tk_pass1(const G *__restrict__ g, float *__restrict__ xs, TkGeom ge,
                                                      TkWorker *ws, uint2 *__restrict__ cand,
                                                      uint32_t *__restrict__ cursor, uint4 *__restrict__ tile_dir)
@@ -662,10 +699,10 @@ __global__ __launch_bounds__(kThreads, kMode == kPassNaive ? 8 : 1) void tk_pass
     float *xrow = xs + (int64_t)i * ge.ld;
     if constexpr (kDirect) {
         if (base + kTile <= d)
-            pass1_direct<true, kMode, G>(grow, xrow, base, d, kt, guess, sk, sk_prev, ge.stream_rows, sh, ge, i, t, cand,
+            pass1_direct<true, kMode, kFew, G>(grow, xrow, base, d, kt, guess, sk, sk_prev, ge.stream_rows, sh, ge, i, t, cand,
                                          cursor, tile_dir, &ws[i].overflow);
         else
-            pass1_direct<false, kMode, G>(grow, xrow, base, d, kt, guess, sk, sk_prev, ge.stream_rows, sh, ge, i, t, cand,
+            pass1_direct<false, kMode, kFew, G>(grow, xrow, base, d, kt, guess, sk, sk_prev, ge.stream_rows, sh, ge, i, t, cand,
                                           cursor, tile_dir, &ws[i].overflow);
     } else {
         if (tid == 0) sh[4] = 0;
@@ -2357,9 +2394,9 @@ __global__ __launch_bounds__(kThreads) void tk_merge(TkGeom ge, const TkWorker *
     sk.on = kKey == kKeyScore ? 1u : 0u;
     const uint32_t guess = sv.ws[0].guess;
     if (base + kTile <= d)
-        list_registers<true, false>(w, base, d, guess, sk, sh, sv.ge, 0, t, sv.cand, sv.cursor, sv.tile_dir, &sv.ws[0].overflow);
+        list_registers<true, false, true>(w, base, d, guess, sk, sh, sv.ge, 0, t, sv.cand, sv.cursor, sv.tile_dir, &sv.ws[0].overflow);
     else
-        list_registers<false, false>(w, base, d, guess, sk, sh, sv.ge, 0, t, sv.cand, sv.cursor, sv.tile_dir, &sv.ws[0].overflow);
+        list_registers<false, false, true>(w, base, d, guess, sk, sh, sv.ge, 0, t, sv.cand, sv.cursor, sv.tile_dir, &sv.ws[0].overflow);
 }
 
 // CD-Adam (Algorithm 1), lines 10 and 12-16: gtilde += c, c = the kept coordinates of w, then the
