@@ -20,6 +20,19 @@ inline bool short_final(int64_t n, int64_t n_tiles)
     return n_tiles <= kShortFinalTiles && n <= kShortFinalWorkers && (n <= 16 || n * n_tiles <= kShortFinalLists);
 }
 
+// The same kernel pays beyond that line as well since its candidates are dealt out to all threads: up to 320 tiles whatever the
+// lists hold, and up to 448 with no more than eight workers.  Error feedback, step plus get_theta, us, a tile / a quarter: n = 2,
+// d = 1.5 M, k = 1 % 54.7 / 50.2, 1.8 M 56.8 / 52.5; n = 8, 1.5 M 73.6 / 69.8, k = 5 % 83.0 / 78.7, 1.8 M 78.8 / 74.8, naive bf16
+// 55.8 / 56.3, 2.1 M k = 0.1 % 82.4 / 83.5, naive bf16 60.2 / 62.3, 2.5 M 96.1 / 96.9; n = 12, 1.8 M 89.2 / 89.7, 2.1 M 97.8 / 100.2;
+// n = 16, 1.5 M 95.2 / 95.1, 2.5 M 130.8 / 134.7; n = 24, 800 000 85.2 / 83.0; n = 32, 400 000 73.4 / 69.5, k = 5 % bf16 81.5 / 76.7,
+// 800 000 99.8 / 96.5, 1.3 M 131.4 / 132.2, 1.5 M 144.2 / 144.5; n = 48, 400 000 93.0 / 88.0, 800 000 130.6 / 126.5, 1.3 M 177.8 / 177.8.
+constexpr int kQuarterTiles = 448, kQuarterWorkers = 8;
+inline bool quarter_final(int64_t n, int64_t n_tiles)
+{
+    return short_final(n, n_tiles) ||
+           n_tiles <= (n <= kQuarterWorkers ? kQuarterTiles : n <= kShortFinalWorkers ? kShortFinalTiles : 0);
+}
+
 // Workers whose kept values a workgroup of tk_final_short holds at a time.  Eight take 36 KB of LDS, which leaves four
 // workgroups on a compute unit, enough for 256 tiles; five take 23 KB.  Step plus get_theta, us, five / eight: n = 48,
 // d = 250 000 81.8 / 79.6, n = 32, d = 350 000 bf16 80.7 / 79.2; 293 tiles, n = 16 88.7 / 93.5, 318 tiles, n = 2 46.5 / 48.8.

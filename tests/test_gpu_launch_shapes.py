@@ -302,6 +302,17 @@ def test_update_of_kept_values(tiles, n, share):
     gpu.destroy()
 
 
+# the same by quarters of up to 448 tiles, and beyond; many workers with long lists on 320 tiles
+@pytest.mark.parametrize("tiles,n,share", [(448, 8, 0.02), (449, 8, 0.02), (448, 1, 0.3), (448, 9, 0.01), (320, 48, 0.002), (97, 32, 0.1)])
+def test_update_of_kept_values_by_quarters_of_more_tiles(tiles, n, share):
+    d = tiles * TILE - 5
+    k = max(1, int(share * d))
+    print(f"[case] quarters of {tiles} tiles, n={n} k={k}", flush=True)
+    gpu, ora = sparse_pair(d, n, k, "ef")
+    sparse_steps(gpu, ora, grads_of(tiles + n, n, d), 2, "ef", f"quarters {tiles} {n}")
+    gpu.destroy()
+
+
 # tk_final_short: eight or five workers' kept values at a time (256 / 257 tiles), candidates beyond the two that a thread
 # holds, all of a quarter kept
 @pytest.mark.parametrize("comp", [P.TOPK, P.RANDK])

@@ -28,6 +28,13 @@ def test_quarter_tile_update_only_where_the_lists_are_short(tmp_path):
     assert got == list(cases.values())
 
 
+def test_quarter_tile_update_of_few_workers_or_few_tiles(tmp_path):
+    cases = {(1, 448): 1, (8, 448): 1, (8, 449): 0, (9, 320): 1, (9, 321): 0, (48, 320): 1, (48, 321): 0, (49, 1): 0, (65535, 1): 0,
+             (1, 524288): 0}
+    got = evaluate(tmp_path, [f"quarter_final({n}, {tiles})" for n, tiles in cases])
+    assert got == list(cases.values())
+
+
 def test_quarter_tile_update_holds_eight_workers_up_to_256_tiles(tmp_path):
     cases = {1: 8, 256: 8, 257: 5, 320: 5}
     got = evaluate(tmp_path, [f"short_final_batch({tiles})" for tiles in cases])
