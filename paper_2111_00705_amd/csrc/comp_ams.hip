@@ -786,6 +786,16 @@ void launch_final(comp_ams *h, hipStream_t st)
     });
 }
 
+// How the listing pass lists (see kListStaged): thread by thread, but for long rows under error feedback, and under CD-Adam beyond
+// the short vectors.
+template <int kMode, typename G>
+int list_mode(const comp_ams *h)
+{
+    if (kMode == kPassNaive) return kListThreads;
+    if (kMode == kPassCd) return h->ge.n_tiles <= kSmallTiles ? kListThreads : kListStaged;
+    return row_bytes(h) <= kWithinStepBytes ? kListThreads : sizeof(G) == 4 ? kListSlots : kListStaged;
+}
+
 // Dynamic LDS handed to tk_pass1: unused by the kernel, it only sets how many workgroups share a compute unit, counted
 // on top of the 24 KB of staging lists (which the variants that list from registers reserve here instead).  The passes
 // that only read want as many as fit (staging: n = 16, d = 11.2 M, CD-Adam: 245 us with the six that the lists allow,
@@ -798,7 +808,7 @@ void launch_final(comp_ams *h, hipStream_t st)
 template <int kMode, typename G>
 unsigned tk_pass_lds(const comp_ams *h)
 {
-    const unsigned lists = kListDirect<kMode, G> ? kStageBytes : 0u;
+    const unsigned lists = list_mode<kMode, G>(h) != kListStaged ? kStageBytes : 0u;
     if (h->lds_choice >= 0) return lists + (unsigned)h->lds_choice;
     if (kMode != kPassEf) return 0u;
     if (sizeof(G) == 2) return row_bytes(h) > kWithinStepBytes ? 9u * 1024u : 0u;
@@ -809,26 +819,24 @@ unsigned tk_pass_lds(const comp_ams *h)
     return lists + (rows_exceed_caches(h) && !tk_long_rows(h) ? 7000u : 9u * 1024u);
 }
 
-// Calls f with two compile-time constants of tk_pass1<kMode, ., ., G>: what it may take for granted about the keys (see kKeyEither),
-// and whether it lists with few instructions, which the long rows of error feedback do not want (see list_registers).
+// Calls f with two compile-time constants of tk_pass1<kMode, ., ., G>: what it may take for granted about the keys (see kKeyEither)
+// and how it lists.
 template <int kMode, typename G, typename F>
 void by_key(const comp_ams *h, F &&f)
 {
-    if constexpr (kMode == kPassEf && std::is_same<G, float>::value) {
+    constexpr int kOther = kMode == kPassNaive ? kListThreads : kMode == kPassEf && sizeof(G) == 4 ? kListSlots : kListStaged;
+    if constexpr (kMode == kPassEf && sizeof(G) == 4) {
         if (tk_long_rows(h)) {
-            f(std::integral_constant<int, kKeyEither>{}, std::false_type{});
+            f(std::integral_constant<int, kKeyEither>{}, std::integral_constant<int, kListSlots>{});
             return;
         }
     }
-    const bool few = kListDirect<kMode, G> && !(kMode == kPassEf && row_bytes(h) > kWithinStepBytes);
     by_flag(h->compressor == COMP_AMS_RANDK, [&](auto score) {
-        constexpr int key = decltype(score)::value ? kKeyScore : kKeyMagnitude;
-        if constexpr (!kListDirect<kMode, G>)
-            f(std::integral_constant<int, key>{}, std::false_type{});
-        else if constexpr (kMode != kPassEf)
-            f(std::integral_constant<int, key>{}, std::true_type{});
-        else
-            by_flag(few, [&](auto fw) { f(std::integral_constant<int, key>{}, fw); });
+        constexpr std::integral_constant<int, decltype(score)::value ? kKeyScore : kKeyMagnitude> key{};
+        if (list_mode<kMode, G>(h) == kListThreads)
+            f(key, std::integral_constant<int, kListThreads>{});
+        else if constexpr (kOther != kListThreads)
+            f(key, std::integral_constant<int, kOther>{});
     });
 }
 
@@ -859,8 +867,8 @@ int step_topk(comp_ams *h, const G *g, hipStream_t st)
 {
     if (is_short(h)) {
         const TkGeom sge = short_geometry(h->ge);
-        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassEf, G>(h, [&](auto key, auto few) {
-            KLAUNCH((tk_pass1<kPassEf, decltype(key)::value, decltype(few)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
+        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassEf, G>(h, [&](auto key, auto list) {
+            KLAUNCH((tk_pass1<kPassEf, decltype(key)::value, decltype(list)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
                     h->tile_dir);
         }); });
         launch_short_select<kSrcStored, float>(h, st, sge, h->ws, h->cand, h->small_ctr, h->tile_dir, h->e, nullptr, P_TK_RESOLVE);
@@ -869,8 +877,8 @@ int step_topk(comp_ams *h, const G *g, hipStream_t st)
     }
     const TkGeom &ge = h->ge;
     const TkGeom pge = pass_geometry<G>(h);
-    launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassEf, G>(h, [&](auto key, auto few) {
-        KLAUNCH_LDS((tk_pass1<kPassEf, decltype(key)::value, decltype(few)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassEf, G>(h)), st, g, h->e, pge, h->ws,
+    launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassEf, G>(h, [&](auto key, auto list) {
+        KLAUNCH_LDS((tk_pass1<kPassEf, decltype(key)::value, decltype(list)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassEf, G>(h)), st, g, h->e, pge, h->ws,
                 h->cand, h->cursor, h->tile_dir);
     }); });
     launch_select<kSrcStored, float>(h, st, ge, h->ws, h->cand, h->cursor, h->cursor_b, h->tile_dir, h->hist1, h->histf,
@@ -885,8 +893,8 @@ int step_topk_naive(comp_ams *h, const G *g, hipStream_t st)
 {
     if (is_short(h)) {
         const TkGeom sge = short_geometry(h->ge);
-        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassNaive, G>(h, [&](auto key, auto few) {
-            KLAUNCH((tk_pass1<kPassNaive, decltype(key)::value, decltype(few)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
+        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassNaive, G>(h, [&](auto key, auto list) {
+            KLAUNCH((tk_pass1<kPassNaive, decltype(key)::value, decltype(list)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
                     h->tile_dir);
         }); });
         launch_short_select<kSrcGradOnly, G>(h, st, sge, h->ws, h->cand, h->small_ctr, h->tile_dir, g, nullptr, P_TK_RESOLVE);
@@ -895,8 +903,8 @@ int step_topk_naive(comp_ams *h, const G *g, hipStream_t st)
     }
     const TkGeom &ge = h->ge;
     const TkGeom pge = pass_geometry<G>(h);
-    launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassNaive, G>(h, [&](auto key, auto few) {
-        KLAUNCH_LDS((tk_pass1<kPassNaive, decltype(key)::value, decltype(few)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassNaive, G>(h)), st, g, h->e, pge, h->ws,
+    launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassNaive, G>(h, [&](auto key, auto list) {
+        KLAUNCH_LDS((tk_pass1<kPassNaive, decltype(key)::value, decltype(list)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassNaive, G>(h)), st, g, h->e, pge, h->ws,
                 h->cand, h->cursor, h->tile_dir);
     }); });
     launch_select<kSrcGradOnly, G>(h, st, ge, h->ws, h->cand, h->cursor, h->cursor_b, h->tile_dir, h->hist1, h->histf,
@@ -930,14 +938,14 @@ int step_topk_cd(comp_ams *h, const G *g, hipStream_t st)
     const bool brief = is_short(h);
     if (brief) {
         const TkGeom sge = short_geometry(ge);
-        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassCd, G>(h, [&](auto key, auto few) {
-            KLAUNCH((tk_pass1<kPassCd, decltype(key)::value, decltype(few)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
+        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassCd, G>(h, [&](auto key, auto list) {
+            KLAUNCH((tk_pass1<kPassCd, decltype(key)::value, decltype(list)::value, G>), dim3(sge.n_tiles, h->n), kThreads, st, g, h->e, sge, h->ws, h->cand, h->small_ctr,
                     h->tile_dir);
         }); });
         launch_short_select<kSrcGrad, G>(h, st, sge, h->ws, h->cand, h->small_ctr, h->tile_dir, g, h->e, P_TK_RESOLVE);
     } else {
-        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassCd, G>(h, [&](auto key, auto few) {
-            KLAUNCH_LDS((tk_pass1<kPassCd, decltype(key)::value, decltype(few)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassCd, G>(h)), st, g, h->e, pge, h->ws,
+        launch_timed(h, P_TK_PASS1, st, [&] { by_key<kPassCd, G>(h, [&](auto key, auto list) {
+            KLAUNCH_LDS((tk_pass1<kPassCd, decltype(key)::value, decltype(list)::value, G>), dim3(grid_blocks(ge.n_tiles, pge.xcd_chunk), h->n), kThreads, (tk_pass_lds<kPassCd, G>(h)), st, g, h->e, pge, h->ws,
                     h->cand, h->cursor, h->tile_dir);
         }); });
         launch_select<kSrcGrad, G>(h, st, ge, h->ws, h->cand, h->cursor, h->cursor_b, h->tile_dir, h->hist1, h->histf,

@@ -18,7 +18,7 @@
 //               is >= the worker's guess, which is the previous step's threshold minus a little
 //               slack - as (index, value) pairs, appended densely to one of 32 or 64 regions of the worker
 //               (one atomic add per tile): straight from registers, or staged in LDS first (value and
-//               place in the tile, 6 bytes), see kListDirect.
+//               place in the tile, 6 bytes), see kListStaged.
 //               A workgroup per tile (instead of a loop over tiles) matters: on this chip a wave
 //               that loops must wait for its stores before it can use its next loads.
 //   tk_hist     histograms of the candidates: the fine bins of eight coarse bins (see window_start),
@@ -416,7 +416,7 @@ __device__ __forceinline__ void take_tile_space(uint32_t count, uint32_t zeros, 
     __syncthreads();
 }
 
-// A wavefront's staged candidates, in the passes that stage them (all but those kListDirect names): the value and the
+// A wavefront's staged candidates, in the passes that stage them (kListStaged): the value and the
 // coordinate's place inside the tile, 6 bytes per entry instead of the 8 of an (index, value) pair.  With room for every
 // coordinate of the wavefront (so the list cannot overflow) a workgroup's four lists take 24 KB, and six workgroups fit a
 // compute unit where 32 KB allowed four: CD-Adam's passes, which only read, run 3-5 % faster with the additional loads in
@@ -555,18 +555,18 @@ __device__ __forceinline__ void finish_tile(const float (*stage_val)[kSub], cons
     }
 }
 
-// Whether tk_pass1 lists straight from its registers: each wavefront counts its candidates, the workgroup takes the
-// tile's space, and each wavefront writes its own - against staging lists in LDS that the last wavefront to finish copies
-// out alone.  A store then carries one or two candidates instead of a run of them, which costs nothing until they are
-// many, and no LDS is held.  Step plus get_theta, staged / direct, us: error feedback fp32 n = 16, d = 11.2 M 488 / 475,
-// n = 8, d = 25 M 628 / 606, d = 110 M 2433 / 2418; naive compression (held at 64 registers: eight workgroups per unit
-// where the lists allowed six) n = 8, d = 3 M bf16 83 / 80, n = 4, d = 60 M bf16 613 / 574, Rand-k n = 16, d = 6 M fp32
-// 173 / 164 (Rand-k spills one or two registers for that, and gains by it on 16 bits all the same: n = 16, d = 11.2 M f16 300
-// without the bound, 294 with it, fp32 266 / 266).  Error feedback on 16-bit gradients loses (Rand-k n = 16, d = 1.2 M f16 92.8 / 94.1, Top-k n = 16, d = 11.2 M
-// bf16 439 / 441), and CD-Adam has no pattern (n = 8: d = 11.2 M bf16 374 / 369, d = 8 M f16 with 5 % kept 384 / 389, d = 25 M
-// fp32 695 / 697): those stage.
-template <int kMode, typename G>
-constexpr bool kListDirect = (kMode == kPassEf && sizeof(G) == 4) || kMode == kPassNaive;
+// How tk_pass1 lists.  Staged: in LDS, and the last wavefront of a workgroup to finish copies all lists out alone.  Or straight from
+// its registers: each wavefront counts its candidates, the workgroup takes the tile's space, and each wavefront writes its own, slot
+// by slot of the wavefront or thread by thread with few instructions (list_registers).  A store then carries one or two candidates
+// instead of a run of them, which costs nothing until they are many, and no LDS is held.  Step plus get_theta, us, staged / slot by
+// slot: error feedback fp32 n = 16, d = 11.2 M 488 / 475, n = 8, d = 25 M 628 / 606, d = 110 M 2433 / 2418; naive compression (held at
+// 64 registers: eight workgroups per unit where the lists allowed six) n = 8, d = 3 M bf16 83 / 80, n = 4, d = 60 M bf16 613 / 574,
+// Rand-k n = 16, d = 6 M fp32 173 / 164 (Rand-k spilled one or two registers for that, and gained by it on 16 bits all the same:
+// n = 16, d = 11.2 M f16 300 without the bound, 294 with it, fp32 266 / 266).  Staged / thread by thread: error feedback on 16 bits
+// Rand-k n = 16, d = 1.2 M f16 80.4 / 79.6, Top-k bf16 80.1 / 79.4, n = 8, d = 300 000 f16 44.8 / 43.9, n = 4, d = 65 536 29.4 / 28.5,
+// n = 8, d = 4 M 115.8 / 114.4, but n = 16, d = 11.2 M 398.5 / 399.1, n = 8, d = 60 M 1171 / 1202; CD-Adam n = 8, d = 20 000
+// 41.0 / 40.1, but d = 2 M 103.4 / 106.6, d = 11.2 M bf16 335 / 345, n = 16 502 / 517.  The host's list_mode draws the lines.
+enum { kListStaged = 0, kListSlots = 1, kListThreads = 2 };
 
 // What the listing pass knows at compile time about the keys: magnitudes (Top-k), scores (Rand-k), or nothing.  Without
 // a branch per element: step plus get_theta, us, n = 4, d = 65 536 33.5 / 32.7, n = 8, d = 2 M 89.3 / 87.9, n = 16, d = 11.2 M
@@ -579,18 +579,18 @@ enum { kKeyMagnitude = 0, kKeyScore = 1, kKeyEither = 2 };
 
 // Lists the candidates among this thread's 16 values of tile t straight from the registers (x[r][c]: coordinate
 // base + 4 (tid + 256 r) + c).  kSkipZeros: see consider.  All threads of the workgroup call this.
-// kFew: with few instructions - a value takes a subtraction, whose top bit says that its key lies below the guess, and a shift of
-// that bit into a mask; a thread's candidates follow one another in the list.  Else slot by slot of the wavefront.  Step plus
-// get_theta, us, slot by slot / with few: naive Rand-k n = 8, d = 3 M bf16 73.9 / 71.6, Top-k 68.2 / 68.2, d = 100 M 1105 / 1097, error
+// kListThreads: a value takes a subtraction, whose top bit says that its key lies below the guess, and a shift of that bit into a
+// mask; a thread's candidates follow one another in the list.  kListSlots: a ballot and a prefix per slot.  Step plus
+// get_theta, us, by slots / by threads: naive Rand-k n = 8, d = 3 M bf16 73.9 / 71.6, Top-k 68.2 / 68.2, d = 100 M 1105 / 1097, error
 // feedback n = 4, d = 65 536 29.3 / 28.9, n = 8, d = 300 000 44.6 / 44.1, d = 2 M 83.4 / 82.2, Rand-k n = 16, d = 1.2 M 84.9 / 84.1; long rows
 // under error feedback lose: n = 16, d = 11.2 M 455.1 / 457.2, n = 8, d = 25 M 587 / 592, d = 110 M 2374 / 2416.
-template <bool kFull, bool kSkipZeros, bool kFew>
+template <bool kFull, bool kSkipZeros, int kList>
 __device__ __forceinline__ void list_registers(const float (&x)[4][4], uint32_t base, uint32_t d, uint32_t guess, const SelKey &sk,
                                                uint32_t *sh, const TkGeom &ge, int i, int t, uint2 *__restrict__ cand,
                                                uint32_t *__restrict__ cursor, uint4 *__restrict__ tile_dir,
                                                uint32_t *overflow_flag)
 {
-    if constexpr (kFew) {
+    if constexpr (kList == kListThreads) {
         const int tid = threadIdx.x, wave = tid >> 6;
         const uint32_t first = guess << kFineShift;      // the smallest key that is listed; kNoGuess gives 2^31, above every key
         uint32_t below = 0, zero = 0;                    // bit 15 - (4 r + c)
@@ -656,7 +656,7 @@ __device__ __forceinline__ void list_registers(const float (&x)[4][4], uint32_t 
 }
 
 // A tile of the listing pass listed straight from the registers.
-template <bool kFull, int kMode, bool kFew, typename G>
+template <bool kFull, int kMode, int kList, typename G>
 __device__ __forceinline__ void pass1_direct(const G *__restrict__ grow, float *__restrict__ xrow, uint32_t base, uint32_t d,
                                              const KeptTest &kt, uint32_t guess, const SelKey &sk, const SelKey &sk_prev,
                                              int stream_rows, uint32_t *sh, const TkGeom &ge, int i, int t,
@@ -670,16 +670,16 @@ __device__ __forceinline__ void pass1_direct(const G *__restrict__ grow, float *
 #pragma unroll
     for (int r = 0; r < 4; ++r)
         form_coordinates<kFull, kMode>(x[r], widen4(gv[r]), xv[r], base + 4 * (threadIdx.x + kThreads * r), d, kt, sk_prev, xrow);
-    list_registers<kFull, kMode == kPassEf, kFew>(x, base, d, guess, sk, sh, ge, i, t, cand, cursor, tile_dir, overflow_flag);
+    list_registers<kFull, kMode == kPassEf, kList>(x, base, d, guess, sk, sh, ge, i, t, cand, cursor, tile_dir, overflow_flag);
 }
 
 // G: element type of g - float, or uint16_t (bfloat16 bits) for gradients handed over as bfloat16.
-template <int kMode, int kKey, bool kFew, typename G>     // kFew: see list_registers; false where the candidates are staged
+template <int kMode, int kKey, int kList, typename G>
 __global__ __launch_bounds__(kThreads, kMode == kPassNaive ? 8 : 1) void tk_pass1(const G *__restrict__ g, float *__restrict__ xs, TkGeom ge,
                                                      TkWorker *ws, uint2 *__restrict__ cand,
                                                      uint32_t *__restrict__ cursor, uint4 *__restrict__ tile_dir)
 {
-    constexpr bool kDirect = kListDirect<kMode, G>;   // the lists are not used then, and take no LDS
+    constexpr bool kDirect = kList != kListStaged;   // the lists are not used then, and take no LDS
     __shared__ float stage_val[kDirect ? 1 : 4][kSub];
     __shared__ uint16_t stage_at[kDirect ? 1 : 4][kSub];
     __shared__ uint32_t sh[9];
@@ -699,10 +699,10 @@ __global__ __launch_bounds__(kThreads, kMode == kPassNaive ? 8 : 1) void tk_pass
     float *xrow = xs + (int64_t)i * ge.ld;
     if constexpr (kDirect) {
         if (base + kTile <= d)
-            pass1_direct<true, kMode, kFew, G>(grow, xrow, base, d, kt, guess, sk, sk_prev, ge.stream_rows, sh, ge, i, t, cand,
+            pass1_direct<true, kMode, kList, G>(grow, xrow, base, d, kt, guess, sk, sk_prev, ge.stream_rows, sh, ge, i, t, cand,
                                          cursor, tile_dir, &ws[i].overflow);
         else
-            pass1_direct<false, kMode, kFew, G>(grow, xrow, base, d, kt, guess, sk, sk_prev, ge.stream_rows, sh, ge, i, t, cand,
+            pass1_direct<false, kMode, kList, G>(grow, xrow, base, d, kt, guess, sk, sk_prev, ge.stream_rows, sh, ge, i, t, cand,
                                           cursor, tile_dir, &ws[i].overflow);
     } else {
         if (tid == 0) sh[4] = 0;
@@ -2394,9 +2394,9 @@ __global__ __launch_bounds__(kThreads) void tk_merge(TkGeom ge, const TkWorker *
     sk.on = kKey == kKeyScore ? 1u : 0u;
     const uint32_t guess = sv.ws[0].guess;
     if (base + kTile <= d)
-        list_registers<true, false, true>(w, base, d, guess, sk, sh, sv.ge, 0, t, sv.cand, sv.cursor, sv.tile_dir, &sv.ws[0].overflow);
+        list_registers<true, false, kListThreads>(w, base, d, guess, sk, sh, sv.ge, 0, t, sv.cand, sv.cursor, sv.tile_dir, &sv.ws[0].overflow);
     else
-        list_registers<false, false, true>(w, base, d, guess, sk, sh, sv.ge, 0, t, sv.cand, sv.cursor, sv.tile_dir, &sv.ws[0].overflow);
+        list_registers<false, false, kListThreads>(w, base, d, guess, sk, sh, sv.ge, 0, t, sv.cand, sv.cursor, sv.tile_dir, &sv.ws[0].overflow);
 }
 
 // CD-Adam (Algorithm 1), lines 10 and 12-16: gtilde += c, c = the kept coordinates of w, then the
