@@ -742,11 +742,22 @@ int step_blocksign_cd(comp_ams *h, const G *g, hipStream_t st)
 // last digits (or, rarest, the selection without lists).  kSrc / a / b say how the compressed vector is formed
 // again where that is needed.  cursor_b: the second set of region cursors, which the lists made anew count in.
 template <int kSrc, typename G>
-void launch_select(comp_ams *h, hipStream_t st, const TkGeom &ge, TkWorker *ws, uint2 *cand, uint32_t *cursor,
+void launch_select(comp_ams *h, hipStream_t st, TkGeom ge, TkWorker *ws, uint2 *cand, uint32_t *cursor,
                    uint32_t *cursor_b, uint4 *tile_dir, uint32_t *hist1, uint32_t *histf, uint32_t *hist_full,
                    uint32_t *hist2, uint32_t *piece_bits, uint64_t *dense, uint2 *dense_dir, const void *a,
                    const float *b, const int (&slot)[3])
 {
+    // entries listed in steady state: 1.2 k for magnitudes; the slack of the guess above the k-th largest for scores
+    const int64_t entries = ge.rand.on ? (int64_t)ge.k + (((int64_t)ge.rand.min_slack * ge.d) >> 17) : (int64_t)ge.k * 5 / 4;
+    if (h->has_guess && one_launch_select(entries, ge.n_tiles, ge.slices, h->method == COMP_AMS_METHOD_CD, ge.rand.on != 0)) {
+        // One workgroup lists a vector again after a miss, so the guess keeps a wider slack (misses of a worker or more in 150 steps,
+        // 8 / 16 bins: error feedback n = 8, d = 300 000 1 / 0, n = 4, d = 500 000 bf16 4 / 1, n = 32, d = 400 000 2 / 0)
+        ge.rand.min_slack = std::max(ge.rand.min_slack, kOneSelectSlack);
+        launch_timed(h, slot[2], st, [&] {
+            KLAUNCH((tk_small_select<kSrc, G, true>), (unsigned)ge.n, kResolveThreads, st, ge, ws, cand, cursor, tile_dir, a, b);
+        });
+        return;
+    }
     const int per = ge.slices * ge.parts;
     // tk_compact: one workgroup per piece in the usual case; more (they leave at once then) where listing the vector
     // again after a miss wants them, up to about four per compute unit in total
@@ -858,7 +869,7 @@ void launch_short_select(comp_ams *h, hipStream_t st, const TkGeom &sge, TkWorke
                          uint4 *tile_dir, const void *a, const float *b, int slot)
 {
     launch_timed(h, slot, st, [&] {
-        KLAUNCH((tk_small_select<kSrc, G>), (unsigned)sge.n, kResolveThreads, st, sge, ws, cand, count, tile_dir, a, b);
+        KLAUNCH((tk_small_select<kSrc, G, false>), (unsigned)sge.n, kResolveThreads, st, sge, ws, cand, count, tile_dir, a, b);
     });
 }
 

@@ -52,6 +52,21 @@ inline bool one_launch_sign(int64_t n, int64_t d, int64_t n_tiles)
     return n_tiles <= kOneLaunchTiles && n * rows <= kOneLaunchPairs;
 }
 
+// Whether one workgroup per vector selects from lists that lie in several regions (tk_small_select) instead of the three selection
+// launches; entries: what is expected to be listed.  It holds kHeldEntries, and a quarter is left for uneven regions.  After a miss
+// that workgroup lists the vector again by itself (d = 500 000: 340 us where many workgroups take tens), so magnitudes, whose
+// threshold may fall, stop at 64 tiles, and at 128 under CD-Adam, which selects twice and missed nothing; scores do not fall.  Fewer
+// than 16 entries were not measured and stay.  Step plus get_theta, us, three launches / one: error feedback n = 8, d = 100 000
+// 38.6 / 34.7, d = 300 000, k = 0.1 % 42.8 / 38.9, k = 1 % 44.2 / 39.9, Rand-k 44.8 / 41.9, n = 16, d = 1.2 M f16 79.0 / 74.7, n = 8, d = 11 M bf16,
+// k = 0.1 % 246.2 / 245.0; naive n = 8, d = 3 M bf16, k = 0.3 % (Rand-k) 69.5 / 66.3; CD-Adam n = 8, d = 300 000 67.5 / 56.0,
+// d = 500 000 bf16 69.8 / 59.5, n = 2, d = 200 000 62.6 / 50.2, Rand-k d = 400 000 71.3 / 63.7.
+constexpr int kHeldEntries = 24 * 1024, kOneSelectTiles = 64, kOneSelectMin = 16;
+inline bool one_launch_select(int64_t entries, int64_t n_tiles, int slices, bool cd, bool scores)
+{
+    return (slices == 32 || slices == 64) && entries >= kOneSelectMin && entries <= kHeldEntries * 3 / 4 &&
+           (scores || n_tiles <= (cd ? 2 : 1) * kOneSelectTiles);
+}
+
 // Whether tk_merge loads the server's vectors before the kept values: on few tiles nothing else hides that latency, on many the
 // registers (102 against 68) cost more wavefronts.  CD-Adam, step plus get_theta, us, late / early: Top-k n = 2, d = 600 000
 // 64.2 / 62.0, n = 8, d = 300 000 65.2 / 63.7, d = 2 M 107.7 / 104.3, Rand-k d = 5 M 188.3 / 188.1, Top-k d = 11.2 M bf16 334 / 337, n = 16

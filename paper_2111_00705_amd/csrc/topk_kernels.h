@@ -90,6 +90,7 @@ constexpr int kResolveThreads = 1024;
 constexpr uint32_t kNoGuess = 1u << 17;      // fine-bin guess that lists nothing (before the first step)
 constexpr uint64_t kNoThreshold = ~0ull;     // Tc that keeps nothing (no pending selection)
 constexpr uint32_t kMinSlack = 8, kMaxSlack = 512, kFirstSlack = 8;   // in fine bins (0.2 % each)
+constexpr uint32_t kOneSelectSlack = 16;     // kMinSlack where one workgroup selects from several regions
 constexpr uint32_t kZeroTail = 2;            // value of TkWorker::whole
 constexpr uint32_t kExact = 3;               // value of TkWorker::whole: exact_select has found Tc and listed the kept set
 
@@ -2237,10 +2238,98 @@ __device__ __forceinline__ uint32_t list_short_again(const TkGeom &ge, int i, co
     return run;
 }
 
-// sge: the vectors' geometry with slices = 1 and region_cap = all of a vector's space.  count: entries listed per
-// vector, kCursorStride words apart (cleared here for the next step).  a, b: how a vector is re-formed (Source4).
-template <int kSrc, typename G>
-__global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom sge, TkWorker *__restrict__ ws,
+// The k-th largest comp value of a list that lies in the regions of vector i (lane q holds the count `mine` of region q, `total` in
+// all, at least k), every element at or above the guess's fine bin.  A wavefront holds the entries of two or four regions in
+// registers, all loads in flight at once, and the first digit is the fine bin above the guess (see tk_small_select).  Many entries
+// in the threshold's bin, or a threshold beyond the bins, are searched by digits through the regions' prefix sums.  top: what the
+// first digit tells.  Bound by one round trip for the entries and their LDS atomics.
+constexpr int kHeldRegions = 32, kHeldPerLane = 24;
+static_assert(kHeldPerLane * kResolveThreads == kHeldEntries, "launch_rules.h");
+__device__ __forceinline__ uint64_t select_in_regions(const TkGeom &ge, int i, const uint2 *__restrict__ list, uint32_t mine,
+                                                      uint32_t total, uint32_t guess, const SelKey &sk, uint32_t *rpre,
+                                                      ResolveLds &L, ShortDigits &top)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool four = ge.slices > kHeldRegions;                          // regions of a wavefront: four or two
+    const int open = kFineShift + ge.idx_bits;
+    uint2 e[kHeldPerLane];
+    uint32_t held = 0;                                                   // bit u: e[u] is an entry
+#pragma unroll
+    for (int u = 0; u < kHeldPerLane; ++u) {
+        const int region = four ? 4 * wave + u / (kHeldPerLane / 4) : 2 * wave + u / (kHeldPerLane / 2);
+        const uint32_t at = (four ? u % (kHeldPerLane / 4) : u % (kHeldPerLane / 2)) * kWave + lane;
+        const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)mine, region);
+        held |= (at < cnt ? 1u : 0u) << u;
+        e[u] = list[(uint32_t)region * ge.region_cap + (at < cnt ? at : 0u)];       // no branch around the load
+    }
+    auto bin_of = [&](const uint2 &c) {
+        return min((sel_key(sk, __uint_as_float(c.y), c.x) >> kFineShift) - guess, (uint32_t)kShortFine - 1u);
+    };
+    // entries of the wavefront's regions beyond those held (uneven lists)
+    auto others = [&](auto &&f) {
+        const int regions = four ? 4 : 2;
+        for (int r = regions * wave; r < regions * (wave + 1); ++r) {
+            const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)mine, r);
+            for (uint32_t at = kHeldPerLane * kWave / regions + lane; at < cnt; at += kWave) f(list[(uint32_t)r * ge.region_cap + at]);
+        }
+    };
+    uint32_t bins[kHeldPerLane];
+#pragma unroll
+    for (int u = 0; u < kHeldPerLane; ++u) {
+        bins[u] = bin_of(e[u]);
+        if ((held >> u) & 1u) atomicAdd(&L.lh[bins[u]], 1u);
+    }
+    others([&](const uint2 &c) { atomicAdd(&L.lh[bin_of(c)], 1u); });
+    __syncthreads();
+    find_rank_bin<kShortFine>(L.lh, L.part, L.res, ge.k);
+    const uint32_t bin = L.res[0], left = L.res[2], rank = ge.k - L.res[1];
+    if (bin != (uint32_t)kShortFine - 1u) {                              // the last one holds all beyond as well
+        top = {guess + bin, rank, open};
+        if (left <= (uint32_t)kFew) {
+            auto take = [&](const uint2 &c) {
+                L.few[atomicAdd(&L.n_few, 1u)] = composite(sel_key(sk, __uint_as_float(c.y), c.x), c.x, ge.idx_bits);
+            };
+#pragma unroll
+            for (int u = 0; u < kHeldPerLane; ++u)
+                if (((held >> u) & 1u) && bins[u] == bin) take(e[u]);
+            others([&](const uint2 &c) {
+                if (bin_of(c) == bin) take(c);
+            });
+            __syncthreads();
+            return rank_few(left, rank, L);
+        }
+    }
+    const uint32_t before = wave_scan(mine) - mine;
+    if (tid < ge.slices) rpre[tid] = before;
+    if (tid == 0) rpre[ge.slices] = total;
+    __syncthreads();
+    auto fetch = [&](const uint32_t (&q)[kScanUnroll], uint64_t (&comp)[kScanUnroll]) {
+        if (q[0] >= total) return;
+        int r[kScanUnroll];
+        uint32_t in[kScanUnroll];
+#pragma unroll
+        for (int u = 0; u < kScanUnroll; ++u) {
+            r[u] = 0;
+            in[u] = min(q[u], total - 1u);
+        }
+        for (int bit = ge.slices / 2; bit > 0; bit >>= 1) {
+#pragma unroll
+            for (int u = 0; u < kScanUnroll; ++u) r[u] = rpre[r[u] + bit] <= in[u] ? r[u] + bit : r[u];
+        }
+        uint2 c[kScanUnroll];
+#pragma unroll
+        for (int u = 0; u < kScanUnroll; ++u) c[u] = list[(uint32_t)r[u] * ge.region_cap + (in[u] - rpre[r[u]])];
+#pragma unroll
+        for (int u = 0; u < kScanUnroll; ++u) comp[u] = composite(sel_key(sk, __uint_as_float(c[u].y), c[u].x), c[u].x, ge.idx_bits);
+    };
+    return resolve_digits<false>(fetch, total, top.prefix, top.rank, top.open, L);
+}
+
+// ge: the geometry the vectors were listed with, and so `count`: the regions' cursors, kCursorStride words apart (cleared here for
+// the next step).  kRegions: kHeldRegions regions or twice as many (lists of up to kHeldEntries entries, see one_launch_select);
+// else a single one per vector (short vectors).  a, b: how a vector is re-formed (Source4).
+template <int kSrc, typename G, bool kRegions>
+__global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom ge, TkWorker *__restrict__ ws,
                                                                    uint2 *__restrict__ cand, uint32_t *__restrict__ count,
                                                                    uint4 *__restrict__ tile_dir, const void *__restrict__ a,
                                                                    const float *__restrict__ b)
@@ -2250,10 +2339,20 @@ __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom sge, T
         ShortLds again;
         ExactLds exact;
     } U;
+    __shared__ uint32_t rpre[kRegions ? kWave + 1 : 1];
     const int i = blockIdx.x;
     const int tid = threadIdx.x;
+    TkGeom sge = ge;                 // a vector's whole space as one region, which it becomes where it is listed again
+    sge.region_cap = (uint32_t)ge.slices * ge.region_cap;
+    sge.slices = 1;
     const uint2 *list = cand + worker_base(sge, i);
-    uint32_t total = count[i * kCursorStride];
+    uint32_t total, mine = 0;        // kRegions: lane q's own region holds `mine`
+    if constexpr (kRegions) {
+        if ((tid & 63) < ge.slices) mine = count[(i * ge.slices + (tid & 63)) * kCursorStride];
+        total = scan_total(wave_scan(mine));
+    } else {
+        total = count[i * kCursorStride];
+    }
     const TkWorker w = ws[i];
     for (int q = tid; q < kShortFine; q += kResolveThreads) L.lh[q] = 0;
     if (tid == 0) L.n_few = 0;
@@ -2268,6 +2367,8 @@ __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom sge, T
     uint64_t tc;
     if (missed && total == kNoSpace) {
         tc = exact_select(es, sge, i, cand, tile_dir, L, U.exact);
+    } else if (kRegions && !missed && total >= sge.k) {
+        tc = select_in_regions(ge, i, list, mine, total, w.guess, sk, rpre, L, top);
     } else if (total >= sge.k) {
         // every element at or above the guess is listed and there are at least k: Tc is the k-th largest of the
         // list (the comp value itself: a digit's bin may reach below the guess, where nothing is listed)
@@ -2324,14 +2425,24 @@ __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom sge, T
         }
     } else {
         // every non-zero element is listed and they are fewer than k: the threshold lies among the zeros, which the
-        // list leaves out - all candidates are kept, and Tc comes from counting over the vector
-        tc = exact_threshold(es, sge, i, L);
+        // list leaves out - all candidates are kept, and Tc comes from counting over the vector (a long one: from the tiles' counts)
+        if constexpr (kRegions)
+            tc = zero_tail_threshold(tile_dir + (int64_t)i * ge.n_tiles, static_cast<const float *>(a) + (int64_t)i * ge.ld, ge,
+                                     ge.k - total, L);
+        else
+            tc = exact_threshold(es, sge, i, L);
     }
+    if (kRegions && tid < ge.slices) count[(i * ge.slices + tid) * kCursorStride] = 0;
     if (tid == 0) {
         ws[i].relisted = missed ? 1u : 0u;
         ws[i].whole = missed && total == kNoSpace ? kExact : 0u;
+        if (kRegions) {                                                // for the records, as tk_compact leaves them
+            ws[i].prefix = (uint32_t)top.prefix;
+            ws[i].pshift = (uint32_t)(top.open - ge.idx_bits);
+            ws[i].rank = top.rank;
+        }
         finish_worker(ws, i, w, tc, sge, missed);
-        count[i * kCursorStride] = 0;
+        if (!kRegions) count[i * kCursorStride] = 0;
     }
 }
 

@@ -255,6 +255,39 @@ def test_short_vectors_of_equal_values_or_few_nonzeros(method, share):
     gpu.destroy()
 
 
+# one launch for the selection from several regions, and three on the other side of its lines: 32 and 64 regions (scores), the
+# largest list, a scale that collapses or jumps (listed again), fewer non-zeros than k, one crowded region
+@pytest.mark.parametrize("method", ["ef", "naive", "cd"])
+@pytest.mark.parametrize("comp,d,n,k,kind", [
+    (P.TOPK, 16 * TILE + 1, 3, 700, "plain"), (P.TOPK, 64 * TILE, 2, 14_745, "plain"), (P.TOPK, 64 * TILE + 1, 2, 2000, "plain"),
+    (P.TOPK, 128 * TILE - 3, 2, 3000, "plain"), (P.TOPK, 33 * TILE, 2, 900, "collapse"), (P.TOPK, 40 * TILE - 1, 2, 900, "jump"),
+    (P.TOPK, 20 * TILE + 7, 2, 900, "sparse"), (P.TOPK, 40 * TILE, 2, 1500, "crowd"), (P.TOPK, 50 * TILE, 2, 1500, "ties"),
+    (P.RANDK, 513 * TILE + 9, 2, 9000, "plain"), (P.RANDK, 300 * TILE, 2, 12_000, "jump"), (P.RANDK, 20 * TILE, 2, 30, "plain")])
+def test_selection_in_regions(method, comp, d, n, k, kind):
+    print(f"[case] selection in regions {kind} {method} comp={comp} d={d} n={n} k={k}", flush=True)
+    gpu, ora = sparse_pair(d, n, k, method, comp)
+    if comp == P.RANDK:
+        gpu.set_rand(3)
+        ora.set_rand(3)
+
+    def fn(t):
+        x = grads_of(d + k, n, d)(t)
+        r = np.random.default_rng([d, t])
+        if kind == "collapse":
+            x *= f32(1e-3 if t == 2 else 1.0)
+        elif kind == "jump":
+            x *= f32(2.0 ** 13 if t == 2 else 1.0)
+        elif kind == "sparse":
+            x *= (np.arange(d) % 211 == 5).astype(f32)                # about 400 coordinates that are ever non-zero
+        elif kind == "crowd":
+            x[:, 5 * TILE:6 * TILE] *= f32(50.0)                       # most candidates in one tile, and so in one region
+        elif kind == "ties":
+            x = np.where(r.random((n, d)) < 0.2, f32(1.0), x * f32(0.01)).astype(f32)
+        return np.ascontiguousarray(x, dtype=f32)
+    sparse_steps(gpu, ora, fn, 4, method, f"{kind} {method}")
+    gpu.destroy()
+
+
 # tk_merge lists the server's candidates: its vectors loaded before the kept values up to 1023 tiles, after them beyond; a first
 # step without a guess, ragged last tiles, one tile and one more than the short path takes
 @pytest.mark.parametrize("comp", [P.TOPK, P.RANDK])

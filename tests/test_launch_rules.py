@@ -48,6 +48,14 @@ def test_one_launch_sign_step_only_where_few_workers_share_a_quarter(tmp_path):
     assert got == list(cases.values())
 
 
+def test_one_launch_selection_of_lists_that_one_workgroup_holds(tmp_path):
+    cases = {(1000, 64, 32, 0, 0): 1, (1000, 65, 32, 0, 0): 0, (1000, 128, 32, 1, 0): 1, (1000, 129, 32, 1, 0): 0, (15, 20, 32, 0, 0): 0,
+             (16, 20, 32, 0, 0): 1, (18432, 60, 32, 0, 0): 1, (18433, 60, 32, 0, 0): 0, (18432, 20000, 64, 0, 1): 1,
+             (18432, 20000, 128, 1, 1): 0, (1000, 20, 16, 0, 0): 0}
+    calls = [f"one_launch_select({e}, {t}, {s}, {c}, {r})" for e, t, s, c, r in cases]
+    assert evaluate(tmp_path, calls) == list(cases.values())
+
+
 def test_merge_loads_the_server_first_on_few_tiles(tmp_path):
     assert evaluate(tmp_path, [f"merge_loads_early({t})" for t in (1, 1023, 1024, 500_000)]) == [1, 1, 0, 0]
 
