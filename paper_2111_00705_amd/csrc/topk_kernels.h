@@ -579,59 +579,74 @@ enum { kListStaged = 0, kListSlots = 1, kListThreads = 2 };
 enum { kKeyMagnitude = 0, kKeyScore = 1, kKeyEither = 2 };
 
 // Lists the candidates among this thread's 16 values of tile t straight from the registers (x[r][c]: coordinate
-// base + 4 (tid + 256 r) + c).  kSkipZeros: see consider.  All threads of the workgroup call this.
-// kListThreads: a value takes a subtraction, whose top bit says that its key lies below the guess, and a shift of that bit into a
-// mask; a thread's candidates follow one another in the list.  kListSlots: a ballot and a prefix per slot.  Step plus
-// get_theta, us, by slots / by threads: naive Rand-k n = 8, d = 3 M bf16 73.9 / 71.6, Top-k 68.2 / 68.2, d = 100 M 1105 / 1097, error
-// feedback n = 4, d = 65 536 29.3 / 28.9, n = 8, d = 300 000 44.6 / 44.1, d = 2 M 83.4 / 82.2, Rand-k n = 16, d = 1.2 M 84.9 / 84.1; long rows
+// base + 4 (tid + 256 r) + c), thread by thread.  kSkipZeros: see consider.  All threads of the workgroup call this.
+// A value takes a subtraction, whose top bit says that its key lies below the guess, and a shift of that bit into a mask; one scan
+// places a thread's candidates, which follow one another in the list.  Step plus get_theta, us, slot by slot / thread by thread:
+// naive Rand-k n = 8, d = 3 M bf16 74.4 / 72.0, Top-k 68.4 / 68.2, d = 100 M 1110 / 1095, error
+// feedback n = 4, d = 65 536 29.3 / 28.7, n = 8, d = 300 000 44.6 / 43.8, d = 2 M 83.2 / 81.8, Rand-k n = 16, d = 1.2 M 85.0 / 83.9; long rows
 // under error feedback lose: n = 16, d = 11.2 M 455.1 / 457.2, n = 8, d = 25 M 587 / 592, d = 110 M 2374 / 2416.
-template <bool kFull, bool kSkipZeros, int kList>
+template <bool kFull, bool kSkipZeros>
 __device__ __forceinline__ void list_registers(const float (&x)[4][4], uint32_t base, uint32_t d, uint32_t guess, const SelKey &sk,
                                                uint32_t *sh, const TkGeom &ge, int i, int t, uint2 *__restrict__ cand,
                                                uint32_t *__restrict__ cursor, uint4 *__restrict__ tile_dir,
                                                uint32_t *overflow_flag)
 {
-    if constexpr (kList == kListThreads) {
-        const int tid = threadIdx.x, wave = tid >> 6;
-        const uint32_t first = guess << kFineShift;      // the smallest key that is listed; kNoGuess gives 2^31, above every key
-        uint32_t below = 0, zero = 0;                    // bit 15 - (4 r + c)
+    const int tid = threadIdx.x, wave = tid >> 6;
+    const uint32_t first = guess << kFineShift;      // the smallest key that is listed; kNoGuess gives 2^31, above every key
+    uint32_t below = 0, zero = 0;                    // bit 15 - (4 r + c)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const uint32_t j = base + 4 * (tid + kThreads * r);
+    for (int r = 0; r < 4; ++r) {
+        const uint32_t j = base + 4 * (tid + kThreads * r);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const bool valid = kFull || j + c < d;
-                const uint32_t under = sel_key(sk, x[r][c], j + c) - first;
-                below = __builtin_amdgcn_alignbit(below, valid ? under : ~0u, 31);
-                if (kSkipZeros && !sk.on) zero = __builtin_amdgcn_alignbit(zero, valid ? mag_key(x[r][c]) - 1u : 0u, 31);
-            }
+        for (int c = 0; c < 4; ++c) {
+            const bool valid = kFull || j + c < d;
+            const uint32_t under = sel_key(sk, x[r][c], j + c) - first;
+            below = __builtin_amdgcn_alignbit(below, valid ? under : ~0u, 31);
+            if (kSkipZeros && !sk.on) zero = __builtin_amdgcn_alignbit(zero, valid ? mag_key(x[r][c]) - 1u : 0u, 31);
         }
-        const uint32_t hits = ~(below | zero) & 0xffffu;
-        // this thread's counts and the wavefront's, zeros in the upper half (a wavefront owns 1024 coordinates)
-        const uint32_t mine = __popc(hits) | (kSkipZeros ? (uint32_t)__popc(zero) << 16 : 0u);
-        const uint32_t incl = wave_scan(mine), both = scan_total(incl);
-        take_tile_space(both & 0xffffu, both >> 16, sh, ge, i, t, cursor, tile_dir, overflow_flag);
-        uint32_t at = sh[4];
-        if (at == kNoSpace) return;
-        at += (wave > 0 ? sh[0] : 0u) + (wave > 1 ? sh[1] : 0u) + (wave > 2 ? sh[2] : 0u) + ((incl - mine) & 0xffffu);
-        uint2 *dst = cand + worker_base(ge, i);          // uniform
+    }
+    const uint32_t hits = ~(below | zero) & 0xffffu;
+    // this thread's counts and the wavefront's, zeros in the upper half (a wavefront owns 1024 coordinates)
+    const uint32_t mine = __popc(hits) | (kSkipZeros ? (uint32_t)__popc(zero) << 16 : 0u);
+    const uint32_t incl = wave_scan(mine), both = scan_total(incl);
+    take_tile_space(both & 0xffffu, both >> 16, sh, ge, i, t, cursor, tile_dir, overflow_flag);
+    uint32_t at = sh[4];
+    if (at == kNoSpace) return;
+    at += (wave > 0 ? sh[0] : 0u) + (wave > 1 ? sh[1] : 0u) + (wave > 2 ? sh[2] : 0u) + ((incl - mine) & 0xffffu);
+    uint2 *dst = cand + worker_base(ge, i);          // uniform
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (hits & (0x8000u >> (r * 4 + c)))
-                    *at_offset(dst, at++) = make_uint2(base + 4 * (tid + kThreads * r) + c, __float_as_uint(x[r][c]));
-    } else {
-        const int tid = threadIdx.x, wave = tid >> 6;
-        uint32_t count = 0, zeros = 0, hits = 0;
+        for (int c = 0; c < 4; ++c)
+            if (hits & (0x8000u >> (r * 4 + c)))
+                *at_offset(dst, at++) = make_uint2(base + 4 * (tid + kThreads * r) + c, __float_as_uint(x[r][c]));
+}
+
+// A tile of the listing pass listed straight from the registers, thread by thread (list_registers) or slot by slot: a ballot and a
+// prefix for each of a wavefront's 16 slots, beside the row's stores.
+template <bool kFull, int kMode, int kList, typename G>
+__device__ __forceinline__ void pass1_direct(const G *__restrict__ grow, float *__restrict__ xrow, uint32_t base, uint32_t d,
+                                             const KeptTest &kt, uint32_t guess, const SelKey &sk, const SelKey &sk_prev,
+                                             int stream_rows, uint32_t *sh, const TkGeom &ge, int i, int t,
+                                             uint2 *__restrict__ cand, uint32_t *__restrict__ cursor,
+                                             uint4 *__restrict__ tile_dir, uint32_t *overflow_flag)
+{
+    const int tid = threadIdx.x, wave = tid >> 6;
+    GradRaw<G> gv[4];
+    float4 xv[4];
+    load_pass_tile<kFull, kMode>(gv, xv, grow, xrow, base, d, stream_rows);
+    float x[4][4];
+    uint32_t count = 0, zeros = 0, hits = 0;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const uint32_t j = base + 4 * (tid + kThreads * r);
+    for (int r = 0; r < 4; ++r) {
+        const uint32_t j = base + 4 * (tid + kThreads * r);
+        form_coordinates<kFull, kMode>(x[r], widen4(gv[r]), xv[r], j, d, kt, sk_prev, xrow);
+        if constexpr (kList == kListSlots) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const bool valid = kFull || j + c < d;
                 bool hit = valid && (sel_key(sk, x[r][c], j + c) >> kFineShift) >= guess;
-                if (kSkipZeros && !sk.on) {
+                if (kMode == kPassEf && !sk.on) {
                     const bool zero = valid && mag_key(x[r][c]) == 0u;
                     zeros += (uint32_t)__popcll(__ballot(zero));
                     hit = hit && !zero;
@@ -640,6 +655,10 @@ __device__ __forceinline__ void list_registers(const float (&x)[4][4], uint32_t 
                 hits |= (hit ? 1u : 0u) << (r * 4 + c);
             }
         }
+    }
+    if constexpr (kList != kListSlots) {
+        list_registers<kFull, kMode == kPassEf>(x, base, d, guess, sk, sh, ge, i, t, cand, cursor, tile_dir, overflow_flag);
+    } else {
         take_tile_space(count, zeros, sh, ge, i, t, cursor, tile_dir, overflow_flag);
         uint32_t at = sh[4];
         if (at == kNoSpace) return;
@@ -654,24 +673,6 @@ __device__ __forceinline__ void list_registers(const float (&x)[4][4], uint32_t 
                 if (hit) dst[slot] = make_uint2(base + 4 * (tid + kThreads * r) + c, __float_as_uint(x[r][c]));
             }
     }
-}
-
-// A tile of the listing pass listed straight from the registers.
-template <bool kFull, int kMode, int kList, typename G>
-__device__ __forceinline__ void pass1_direct(const G *__restrict__ grow, float *__restrict__ xrow, uint32_t base, uint32_t d,
-                                             const KeptTest &kt, uint32_t guess, const SelKey &sk, const SelKey &sk_prev,
-                                             int stream_rows, uint32_t *sh, const TkGeom &ge, int i, int t,
-                                             uint2 *__restrict__ cand, uint32_t *__restrict__ cursor,
-                                             uint4 *__restrict__ tile_dir, uint32_t *overflow_flag)
-{
-    GradRaw<G> gv[4];
-    float4 xv[4];
-    load_pass_tile<kFull, kMode>(gv, xv, grow, xrow, base, d, stream_rows);
-    float x[4][4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-        form_coordinates<kFull, kMode>(x[r], widen4(gv[r]), xv[r], base + 4 * (threadIdx.x + kThreads * r), d, kt, sk_prev, xrow);
-    list_registers<kFull, kMode == kPassEf, kList>(x, base, d, guess, sk, sh, ge, i, t, cand, cursor, tile_dir, overflow_flag);
 }
 
 // G: element type of g - float, or uint16_t (bfloat16 bits) for gradients handed over as bfloat16.
@@ -2505,9 +2506,9 @@ __global__ __launch_bounds__(kThreads) void tk_merge(TkGeom ge, const TkWorker *
     sk.on = kKey == kKeyScore ? 1u : 0u;
     const uint32_t guess = sv.ws[0].guess;
     if (base + kTile <= d)
-        list_registers<true, false, kListThreads>(w, base, d, guess, sk, sh, sv.ge, 0, t, sv.cand, sv.cursor, sv.tile_dir, &sv.ws[0].overflow);
+        list_registers<true, false>(w, base, d, guess, sk, sh, sv.ge, 0, t, sv.cand, sv.cursor, sv.tile_dir, &sv.ws[0].overflow);
     else
-        list_registers<false, false, kListThreads>(w, base, d, guess, sk, sh, sv.ge, 0, t, sv.cand, sv.cursor, sv.tile_dir, &sv.ws[0].overflow);
+        list_registers<false, false>(w, base, d, guess, sk, sh, sv.ge, 0, t, sv.cand, sv.cursor, sv.tile_dir, &sv.ws[0].overflow);
 }
 
 // CD-Adam (Algorithm 1), lines 10 and 12-16: gtilde += c, c = the kept coordinates of w, then the
