@@ -62,7 +62,8 @@ struct BsTable {
 // Short blocks.  With uniform blocks of a power of two below a tile a float4 lies inside one block, whose number is a shift
 // of the coordinate, and a block's float4 sit in consecutive lanes of one row r of the tile (or in consecutive rows):
 // the sum of |x| is a butterfly in registers, up to 256 coordinates inside one wavefront, and the block's scale is
-// complete in the workgroup of its tile.  No table, no staging in LDS, no bs_scale.  Step plus get_theta, n = 16,
+// complete in the workgroup of its tile.  No table, no staging in LDS, no bs_scale; on small vectors the whole step is one launch
+// with blocks of up to 256 (bs_step_short).  Step plus get_theta, n = 16,
 // d = 11.2 M, general way / this one, us: error feedback B = 16 660 / 507, B = 256 483 / 476, B = 2048 540 / 476; CD-Adam
 // B = 16 810 / 510, B = 1024 606 / 540; n = 20, d = 300, B = 16 under CD-Adam 43 / 24.
 constexpr int kSmallMinLog2 = 2, kSmallMaxLog2 = 11;      // 4 .. 2048 coordinates

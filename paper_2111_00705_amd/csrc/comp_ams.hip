@@ -808,7 +808,7 @@ int list_mode(const comp_ams *h)
 }
 
 // Dynamic LDS handed to tk_pass1: unused by the kernel, it only sets how many workgroups share a compute unit, counted
-// on top of the 24 KB of staging lists (which the variants that list from registers reserve here instead).  The passes
+// on top of the 24 KB of staging lists (which the error-feedback variants that list from registers reserve here instead on 32 bits).  The passes
 // that only read want as many as fit (staging: n = 16, d = 11.2 M, CD-Adam: 245 us with the six that the lists allow,
 // 257 with four; n = 8, d = 110 M: 1.134 against 1.173 ms).  The error-feedback pass, which also writes the row back,
 // is best with four or five on 32-bit gradients (n = 8, d = 110 M: step plus get_theta 2418 us, 2487 with seven) and

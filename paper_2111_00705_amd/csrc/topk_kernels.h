@@ -30,6 +30,7 @@
 //               after such a miss: the candidates are listed again from the stored x
 //   tk_resolve  one workgroup per worker: the remaining digits of Tc over those pieces, and the
 //               guess for the next step
+//               (in place of the last three: tk_small_select, one workgroup per worker, see one_launch_select)
 //   tk_final    per tile, all workers: candidates with comp >= Tc are the kept coordinates; their
 //               values are added into an LDS copy of the tile in ascending worker order; then
 //               gbar = acc / n and the AMSGrad update of the tile's theta, m, v, vhat
@@ -39,13 +40,14 @@
 //
 // The candidate regions are bounded (see region_base): a region that fills up is detected, and the step then
 // goes the way of a guess that was too high (whole-vector count, lists made anew) and, if the lists still do not
-// fit, selects without lists inside tk_resolve (exact_select).  In vectors of at most 16 tiles one kernel
+// fit, selects without lists inside tk_resolve (exact_select).  In vectors of at most 16 tiles, and in those whose lists one
+// workgroup holds (one_launch_select), one kernel
 // (tk_small_select) takes the place of tk_hist, tk_compact and tk_resolve, but for a first step beyond four tiles.
 //
 // Exact zeros under error feedback: when fewer than k coordinates are non-zero the k-th largest is a zero and
 // zeros are selected by lower index.  They are never listed as candidates (millions of equal keys would be);
-// tk_pass1 counts them per tile, and tk_resolve places the threshold among them from those counts
-// (zero_tail_threshold).  The other methods list zeros like any other value.
+// tk_pass1 counts them per tile, and tk_resolve (or tk_small_select, but on short vectors) places the threshold among them from
+// those counts (zero_tail_threshold).  The other methods list zeros like any other value.
 //
 // Rand-k (Appendix A, "Rand-k") runs through the same kernels: the 31 magnitude bits are replaced by a
 // 31-bit pseudo-random score of (seed, step, worker, index), see SelKey; everything after the key -
@@ -2088,9 +2090,10 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
 
 
 // ---------------------------------------------------------------------------------------------
-// Short vectors (at most kSmallTiles tiles): the selection in one launch.
+// The selection in one launch: short vectors (at most kSmallTiles tiles), and vectors of any length whose lists one workgroup
+// holds (one_launch_select).
 // On such a vector every kernel of the selection chain is a launch on an idle chip, and three of them cost more
-// than the work.  The listing pass is tk_pass1 itself with a single candidate region per vector (few tiles share
+// than the work.  The listing pass is tk_pass1 itself, on a short vector with a single candidate region per vector (few tiles share
 // its cursor); then one workgroup per vector finds the threshold from the list by itself - the digits of Tc over
 // the listed comp values, after listing the vector again when the list does not hold the k-th largest.  The tile directory and the list have the
 // usual form, so the kernels after it and the getters follow unchanged.  (Finding the threshold inside the listing
