@@ -102,6 +102,7 @@ struct comp_ams {
 
     uint2 *dense_dir = nullptr;                // [n][slices * parts * 4] {start, count} of each wavefront's piece
     bool has_guess = false;                    // a step has run since the selection records were reset
+    uint64_t guess_since = 0;                  // `steps` when it had not
     uint32_t *small_ctr = nullptr;             // [n + 1] short vectors: entries listed (the last one the server's)
     uint32_t *sel_count = nullptr, *sel_out_idx = nullptr;
     float *sel_out_val = nullptr;
@@ -741,6 +742,7 @@ int step_blocksign_cd(comp_ams *h, const G *g, hipStream_t st)
 // a miss: the whole vector's), leading digits and compaction of the threshold bin (after a miss: the lists anew),
 // last digits (or, rarest, the selection without lists).  kSrc / a / b say how the compressed vector is formed
 // again where that is needed.  cursor_b: the second set of region cursors, which the lists made anew count in.
+constexpr uint64_t kSettledSteps = 4;
 template <int kSrc, typename G>
 void launch_select(comp_ams *h, hipStream_t st, TkGeom ge, TkWorker *ws, uint2 *cand, uint32_t *cursor,
                    uint32_t *cursor_b, uint4 *tile_dir, uint32_t *hist1, uint32_t *histf, uint32_t *hist_full,
@@ -749,7 +751,10 @@ void launch_select(comp_ams *h, hipStream_t st, TkGeom ge, TkWorker *ws, uint2 *
 {
     // entries listed in steady state: 1.2 k for magnitudes; the slack of the guess above the k-th largest for scores
     const int64_t entries = ge.rand.on ? (int64_t)ge.k + (((int64_t)ge.rand.min_slack * ge.d) >> 17) : (int64_t)ge.k * 5 / 4;
-    if (h->has_guess && one_launch_select(entries, ge.n_tiles, ge.slices, h->method == COMP_AMS_METHOD_CD, ge.rand.on != 0)) {
+    // The first steps after the records were reset miss: the first one always, and under CD-Adam the third, when the Markov sequences
+    // hold what was kept (n = 8, d = 300 000 101 us with three launches, 278 with one).
+    if (h->has_guess && h->steps >= h->guess_since + kSettledSteps &&
+        one_launch_select(entries, ge.n_tiles, ge.slices, h->method == COMP_AMS_METHOD_CD, ge.rand.on != 0)) {
         // One workgroup lists a vector again after a miss, so the guess keeps a wider slack (misses of a worker or more in 150 steps,
         // 8 / 16 bins: error feedback n = 8, d = 300 000 1 / 0, n = 4, d = 500 000 bf16 4 / 1, n = 32, d = 400 000 2 / 0)
         ge.rand.min_slack = std::max(ge.rand.min_slack, kOneSelectSlack);
@@ -1027,6 +1032,7 @@ int reset_topk_workers(comp_ams *h)
     std::vector<TkWorker> init((size_t)h->n);
     fresh_tk_workers(init);
     h->has_guess = false;
+    h->guess_since = h->steps;
     HIP_TRY(h, hipMemcpy(h->ws, init.data(), init.size() * sizeof(TkWorker), hipMemcpyHostToDevice));
     HIP_TRY(h, hipMemset(h->cursor, 0, (size_t)h->n * h->ge.slices * kCursorStride * sizeof(uint32_t)));
     HIP_TRY(h, hipMemset(h->cursor_b, 0, (size_t)h->n * h->ge.slices * kCursorStride * sizeof(uint32_t)));
