@@ -1002,16 +1002,7 @@ void set_slices(TkGeom &ge, int slices)
     ge.slice_tiles = (ge.n_tiles + slices - 1) / slices;
     const int64_t want = (3 * (int64_t)ge.k / 2 + (int64_t)slices * 4096 - 1) / ((int64_t)slices * 4096);
     ge.parts = (int32_t)std::min<int64_t>({(int64_t)kMaxParts, (int64_t)kMaxPieces / (4 * slices), std::max<int64_t>(1, want)});
-    // Entries per region.  A vector's regions together hold twice max(4 k, d / 64) candidates: 1.2 k are listed in
-    // steady state (error feedback piles mass up just below the threshold), a first step or a step after a miss lists
-    // the coarse bin of the k-th largest and above (an eighth of an octave of magnitudes: about a hundredth of the
-    // coordinates of a gradient spread over several decades), and the factor two covers uneven regions.  What does
-    // not fit is found without lists (exact_select), which needs k entries in all: 8 k are there.  Never more than
-    // every coordinate of the region's tiles.
-    const int64_t full = (int64_t)ge.slice_tiles * kTile;
-    const int64_t cands = std::max<int64_t>(4 * (int64_t)ge.k, ge.d / 64);
-    const int64_t per_region = ((2 * cands + slices - 1) / slices + 1023) / 1024 * 1024;
-    ge.region_cap = (uint32_t)std::min<int64_t>(full, std::max<int64_t>(per_region, 2048));
+    ge.region_cap = (uint32_t)region_entries(ge.d, ge.k, (int64_t)ge.slice_tiles * kTile, slices);
 }
 
 // Initial selection records: no pending threshold, no guess.

@@ -6,6 +6,8 @@
 #include <stdint.h>
 #include <type_traits>
 
+#include "launch_rules.h"
+
 namespace cams {
 
 // Which tile a workgroup works on.  The hardware hands the workgroups of a launch to the chip's eight XCDs in
@@ -171,7 +173,7 @@ template <typename T>
 __device__ __forceinline__ T *at_offset(T *base, uint32_t at)
 {
     using Bytes = std::conditional_t<std::is_const<T>::value, const char, char>;
-    return reinterpret_cast<T *>(reinterpret_cast<Bytes *>(base) + (uint32_t)(at * (uint32_t)sizeof(T)));
+    return reinterpret_cast<T *>(reinterpret_cast<Bytes *>(base) + offset_bytes(at, (uint32_t)sizeof(T)));
 }
 
 __device__ __forceinline__ float4 ld4(const float *p) { return *reinterpret_cast<const float4 *>(p); }

@@ -73,6 +73,24 @@ inline bool one_launch_select(int64_t entries, int64_t n_tiles, int slices, bool
 // 502 / 510, n = 8, d = 40 M 861 / 889.
 inline bool merge_loads_early(int64_t n_tiles) { return n_tiles < 1024; }
 
+// Entries of one of a vector's candidate regions.  A vector's regions together hold twice max(4 k, d / 64) candidates: 1.2 k are
+// listed in steady state (error feedback piles mass up just below the threshold), a first step or a step after a miss lists the
+// coarse bin of the k-th largest and above (an eighth of an octave of magnitudes: about a hundredth of the coordinates of a gradient
+// spread over several decades), and the factor two covers uneven regions.  What does not fit is found without lists (exact_select),
+// which needs k entries in all: 8 k are there.  Never more than every coordinate of the region's tiles.
+inline int64_t region_entries(int64_t d, int64_t k, int64_t full, int slices)
+{
+    const int64_t cands = 4 * k > d / 64 ? 4 * k : d / 64;
+    const int64_t per_region = ((2 * cands + slices - 1) / slices + 1023) / 1024 * 1024;
+    const int64_t most = per_region > 2048 ? per_region : 2048;
+    return full < most ? full : most;
+}
+
+// Where the listing pass stores a candidate: the entry at which the tile's space begins (at: counted from the vector's first region,
+// up to 2^31, so in 64 bits), and bytes from there on for the place inside that space, of at most a tile's 4096 entries.
+constexpr int64_t tile_space(int64_t vector_base, uint32_t at) { return vector_base + (int64_t)at; }
+constexpr uint32_t offset_bytes(uint32_t at, uint32_t size) { return at * size; }
+
 // Grid of a kernel with one workgroup per tile (in x) under tile_of_block's mapping.
 inline unsigned grid_blocks(int64_t n_tiles, int chunk)
 {

@@ -612,10 +612,12 @@ __device__ __forceinline__ void list_registers(const float (&x)[4][4], uint32_t 
     const uint32_t mine = __popc(hits) | (kSkipZeros ? (uint32_t)__popc(zero) << 16 : 0u);
     const uint32_t incl = wave_scan(mine), both = scan_total(incl);
     take_tile_space(both & 0xffffu, both >> 16, sh, ge, i, t, cursor, tile_dir, overflow_flag);
-    uint32_t at = sh[4];
-    if (at == kNoSpace) return;
-    at += (wave > 0 ? sh[0] : 0u) + (wave > 1 ? sh[1] : 0u) + (wave > 2 ? sh[2] : 0u) + ((incl - mine) & 0xffffu);
-    uint2 *dst = cand + worker_base(ge, i);          // uniform
+    const uint32_t space = sh[4];
+    if (space == kNoSpace) return;
+    // the tile's space in 64 bits, uniform; the lanes' offsets inside it in 32
+    uint2 *dst = cand + tile_space(worker_base(ge, i), (uint32_t)__builtin_amdgcn_readfirstlane((int)space));
+    static_assert((uint64_t)kTile * sizeof(uint2) < (1ull << 32), "at_offset");
+    uint32_t at = (wave > 0 ? sh[0] : 0u) + (wave > 1 ? sh[1] : 0u) + (wave > 2 ? sh[2] : 0u) + ((incl - mine) & 0xffffu);
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll

@@ -90,6 +90,53 @@ def test_topk_at_the_largest_dimension():
     ora.close()
 
 
+def kept_mask(torch, x, k):
+    """Where the k largest magnitudes of x stand, the lower index first among equals."""
+    key = x.view(torch.int32) & 0x7fffffff
+    threshold = torch.sort(key).values[-k]
+    mask = key > threshold
+    ties = torch.nonzero(key == threshold).flatten()
+    mask[ties[:k - int(mask.sum())]] = True
+    return mask
+
+
+# lists of more than 2**29 entries of 8 bytes: from the second step on the listing pass (naive compression) and the merge (the server
+# of CD-Adam) append to them.  One worker and beta1 = 0, so that m is the compressed gradient itself.
+@pytest.mark.parametrize("method", [P.METHOD_NAIVE, P.METHOD_CD])
+def test_lists_beyond_four_gib(method):
+    import torch
+    d, k = 600_000_007, 75_000_000
+    announce(f"k = {k} of d = {d}, method {method}")
+    gpu = P.CompAms(d, 1, P.TOPK, k, 0.0, W.BETA2, W.EPS, W.LR)
+    gpu.set_method(method)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(75)
+    buf = torch.empty(d, dtype=torch.float32, device="cuda")
+    ghat, gtil = (torch.zeros(d, dtype=torch.float32, device="cuda") for _ in range(2))
+    for t in range(3):
+        print(f"[case] step {t}", flush=True)
+        g = torch.empty(d, dtype=torch.float32, device="cuda").normal_(generator=gen)
+        gpu.step(g)
+        gpu.sync()
+        if method == P.METHOD_CD:
+            u = g - ghat
+            ghat += torch.where(kept_mask(torch, u, k), u, 0.0)
+            gpu.get_ghat_worker(0, out=buf)
+            assert torch.equal(buf, ghat), f"step {t}: the worker's Markov sequence"
+            w = ghat - gtil                                    # one worker: the server's sequence is the worker's
+            gtil += torch.where(kept_mask(torch, w, k), w, 0.0)
+            gpu.get_gtilde(out=buf)
+            assert torch.equal(buf, gtil), f"step {t}: gtilde"
+            del u, w
+        else:
+            want = torch.where(kept_mask(torch, g, k), g, 0.0)
+            gpu.get_m(out=buf)
+            assert torch.equal(buf, want), f"step {t}: the compressed gradient"
+            del want
+        del g
+    gpu.destroy()
+
+
 def test_block_sign_at_the_largest_dimension():
     import torch
     announce("block sign at d = 2^31 - 1")
