@@ -749,8 +749,7 @@ void launch_select(comp_ams *h, hipStream_t st, TkGeom ge, TkWorker *ws, uint2 *
                    uint32_t *hist2, uint32_t *piece_bits, uint64_t *dense, uint2 *dense_dir, const void *a,
                    const float *b, const int (&slot)[3])
 {
-    // entries listed in steady state: 1.2 k for magnitudes; the slack of the guess above the k-th largest for scores
-    const int64_t entries = ge.rand.on ? (int64_t)ge.k + (((int64_t)ge.rand.min_slack * ge.d) >> 17) : (int64_t)ge.k * 5 / 4;
+    const int64_t entries = one_select_entries(ge.d, ge.k, ge.rand.min_slack, ge.rand.on != 0);
     // The first steps after the records were reset miss: the first one always, and under CD-Adam the third, when the Markov sequences
     // hold what was kept (n = 8, d = 300 000 101 us with three launches, 278 with one).
     if (h->has_guess && h->steps >= h->guess_since + kSettledSteps &&

@@ -52,19 +52,31 @@ inline bool one_launch_sign(int64_t n, int64_t d, int64_t n_tiles)
     return n_tiles <= kOneLaunchTiles && n * rows <= kOneLaunchPairs;
 }
 
+// Entries that a vector lists in steady state where one workgroup selects from them: 1.2 k for magnitudes; for scores those above the
+// guess, kOneSelectSlack fine bins (of 2^17) or min_slack below the k-th largest.
+constexpr uint32_t kOneSelectSlack = 16;
+inline int64_t one_select_entries(int64_t d, int64_t k, uint32_t min_slack, bool scores)
+{
+    const int64_t slack = min_slack > kOneSelectSlack ? min_slack : kOneSelectSlack;
+    return scores ? k + ((slack * d) >> 17) : k * 5 / 4;
+}
+
 // Whether one workgroup per vector selects from lists that lie in several regions (tk_small_select) instead of the three selection
 // launches; entries: what is expected to be listed.  It holds kHeldEntries, and a quarter is left for uneven regions.  After a miss
 // that workgroup lists the vector again by itself (d = 500 000: 340 us where many workgroups take tens), so magnitudes, whose
-// threshold may fall, stop at 64 tiles, and at 128 under CD-Adam, which selects twice and missed nothing; scores do not fall.  Fewer
-// than 16 entries were not measured and stay.  Step plus get_theta, us, three launches / one: error feedback n = 8, d = 100 000
-// 38.6 / 34.7, d = 300 000, k = 0.1 % 42.8 / 38.9, k = 1 % 44.2 / 39.9, Rand-k 44.8 / 41.9, n = 16, d = 1.2 M f16 79.0 / 74.7, n = 8, d = 11 M bf16,
-// k = 0.1 % 246.2 / 245.0; naive n = 8, d = 3 M bf16, k = 0.3 % (Rand-k) 69.5 / 66.3; CD-Adam n = 8, d = 300 000 67.5 / 56.0,
-// d = 500 000 bf16 69.8 / 59.5, n = 2, d = 200 000 62.6 / 50.2, Rand-k d = 400 000 71.3 / 63.7.
-constexpr int kHeldEntries = 24 * 1024, kOneSelectTiles = 64, kOneSelectMin = 16;
+// threshold may fall, stop at 64 tiles, and at 128 under CD-Adam, which selects twice and missed nothing.  Scores do not fall, and
+// stop where a fine bin, which holds d / 2^17 of them, gets near the few that are ranked as they are.  Fewer than 16 entries were not
+// measured with magnitudes and stay.  Step plus get_theta, us, three launches / one: error feedback n = 8, d = 100 000
+// 38.6 / 34.7, d = 300 000, k = 0.1 % 42.8 / 38.9, k = 1 % 44.2 / 39.9, Rand-k 44.8 / 41.9; naive n = 8, d = 3 M bf16, k = 0.3 %
+// (Rand-k) 69.5 / 66.3; CD-Adam n = 8, d = 300 000 67.5 / 56.0, d = 500 000 bf16 69.8 / 59.5, n = 2, d = 200 000 62.6 / 50.2, Rand-k
+// d = 400 000 71.3 / 63.7.  Rand-k by length: n = 16, d = 1.2 M f16 78.3 / 74.2, n = 8, d = 4 M 117.8 / 114.5, d = 11 M bf16
+// 245.3 / 243.0, naive bf16 11 M 155.8 / 154.0, 16 M 204.5 / 203.6, 24 M 284.2 / 283.8, 32 M 380.5 / 386.5, 60 M 668.9 / 676.7, n = 1,
+// 40 M fp32 298.2 / 310.3, CD-Adam 11 M 269.5 / 268.3, n = 4, 20 M 330.6 / 331.4.
+constexpr int kHeldEntries = 24 * 1024, kOneSelectTiles = 64, kOneSelectScoreTiles = 4096, kOneSelectMin = 16;
 inline bool one_launch_select(int64_t entries, int64_t n_tiles, int slices, bool cd, bool scores)
 {
     return (slices == 32 || slices == 64) && entries >= kOneSelectMin && entries <= kHeldEntries * 3 / 4 &&
-           (scores || n_tiles <= (cd ? 2 : 1) * kOneSelectTiles);
+           n_tiles <= (scores ? kOneSelectScoreTiles : (cd ? 2 : 1) * kOneSelectTiles);
 }
 
 // Whether tk_merge loads the server's vectors before the kept values: on few tiles nothing else hides that latency, on many the

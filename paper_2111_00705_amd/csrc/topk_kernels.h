@@ -92,7 +92,7 @@ constexpr int kResolveThreads = 1024;
 constexpr uint32_t kNoGuess = 1u << 17;      // fine-bin guess that lists nothing (before the first step)
 constexpr uint64_t kNoThreshold = ~0ull;     // Tc that keeps nothing (no pending selection)
 constexpr uint32_t kMinSlack = 8, kMaxSlack = 512, kFirstSlack = 8;   // in fine bins (0.2 % each)
-constexpr uint32_t kOneSelectSlack = 16;     // kMinSlack where one workgroup selects from several regions
+static_assert(kOneSelectSlack >= kMinSlack, "kMinSlack where one workgroup selects from several regions");
 constexpr uint32_t kZeroTail = 2;            // value of TkWorker::whole
 constexpr uint32_t kExact = 3;               // value of TkWorker::whole: exact_select has found Tc and listed the kept set
 
@@ -2092,7 +2092,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_resolve(TkGeom ge, TkWorke
 
 
 // ---------------------------------------------------------------------------------------------
-// The selection in one launch: short vectors (at most kSmallTiles tiles), and vectors of any length whose lists one workgroup
+// The selection in one launch: short vectors (at most kSmallTiles tiles), and longer ones whose lists one workgroup
 // holds (one_launch_select).
 // On such a vector every kernel of the selection chain is a launch on an idle chip, and three of them cost more
 // than the work.  The listing pass is tk_pass1 itself, on a short vector with a single candidate region per vector (few tiles share

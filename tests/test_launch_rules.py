@@ -50,10 +50,23 @@ def test_one_launch_sign_step_only_where_few_workers_share_a_quarter(tmp_path):
 
 def test_one_launch_selection_of_lists_that_one_workgroup_holds(tmp_path):
     cases = {(1000, 64, 32, 0, 0): 1, (1000, 65, 32, 0, 0): 0, (1000, 128, 32, 1, 0): 1, (1000, 129, 32, 1, 0): 0, (15, 20, 32, 0, 0): 0,
-             (16, 20, 32, 0, 0): 1, (18432, 60, 32, 0, 0): 1, (18433, 60, 32, 0, 0): 0, (18432, 20000, 64, 0, 1): 1,
-             (18432, 20000, 128, 1, 1): 0, (1000, 20, 16, 0, 0): 0}
+             (16, 20, 32, 0, 0): 1, (18432, 60, 32, 0, 0): 1, (18433, 60, 32, 0, 0): 0, (18432, 4096, 64, 0, 1): 1,
+             (18432, 4097, 64, 0, 1): 0, (18432, 4096, 128, 1, 1): 0, (1000, 20, 16, 0, 0): 0}
     calls = [f"one_launch_select({e}, {t}, {s}, {c}, {r})" for e, t, s, c, r in cases]
     assert evaluate(tmp_path, calls) == list(cases.values())
+
+
+def test_the_lists_of_scores_are_priced_with_the_slack_that_one_workgroup_uses(tmp_path):
+    """The k-th largest score and up, and 16 fine bins of 2**17 below it (or min_slack, where that is more): what is listed is what
+    the rule compares with the 24 576 entries that the workgroup holds."""
+    cases = [(1_199_882, 11_999, 6), (11_000_000, 11_000, 3), (16_700_000, 16_380, 4), (110_000_000, 11_000, 2), (110_000_000, 16_500, 2), (300_000_000, 10_000, 1),
+             (1_000_000_000, 1000, 1), (70_003, 30_000, 40)]
+    got = evaluate(tmp_path, [f"one_select_entries({d}, {k}, {slack}, true)" for d, k, slack in cases])
+    assert got == [k + max(16, slack) * d // 2**17 for d, k, slack in cases]
+    got = evaluate(tmp_path, [f"one_launch_select(one_select_entries({d}, {k}, {slack}, true), {(d + 4095) // 4096}, 64, false, true)"
+                              for d, k, slack in cases])
+    assert got == [1, 1, 1, 0, 0, 0, 0, 0]
+    assert evaluate(tmp_path, ["one_select_entries(500000, 5000, 0, false)"]) == [6250]
 
 
 def test_merge_loads_the_server_first_on_few_tiles(tmp_path):
