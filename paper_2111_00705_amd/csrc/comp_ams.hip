@@ -103,6 +103,9 @@ struct comp_ams {
     uint2 *dense_dir = nullptr;                // [n][slices * parts * 4] {start, count} of each wavefront's piece
     bool has_guess = false;                    // a step has run since the selection records were reset
     uint64_t guess_since = 0;                  // `steps` when it had not
+    uint32_t *miss_seen = nullptr;             // a flag in host memory, or none: raised by tk_small_select where it listed a vector again
+    uint64_t three_until = 0, three_steps = 0; // after that the selection takes three launches for three_steps steps, up to three_until
+    bool recording = false;                    // the running step is being recorded into a graph
     uint32_t *small_ctr = nullptr;             // [n + 1] short vectors: entries listed (the last one the server's)
     uint32_t *sel_count = nullptr, *sel_out_idx = nullptr;
     float *sel_out_val = nullptr;
@@ -371,6 +374,42 @@ template <typename T>
 int dev_alloc_t(comp_ams *h, std::vector<void *> &owner, T **out, size_t count, bool zero = true)
 {
     return dev_alloc(h, owner, reinterpret_cast<void **>(out), count * sizeof(T), zero);
+}
+
+// Flags that kernels raise for the host: words of one pinned block that the process keeps once a handle has wanted one (allocating it
+// takes 80 us), a cache line each, taken by a handle and given back by it.  Without one - the block is all taken, or was refused - a
+// handle does without what the flag is for.
+constexpr int kFlags = 512, kFlagWords = 16;
+std::mutex g_flag_mutex;
+uint32_t *g_flags = nullptr;
+bool g_flag_taken[kFlags] = {};
+
+uint32_t *take_flag()
+{
+    std::lock_guard<std::mutex> lock(g_flag_mutex);
+    if (!g_flags) {
+        void *p = nullptr;
+        if (hipHostMalloc(&p, kFlags * kFlagWords * sizeof(uint32_t),
+                          hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        g_flags = static_cast<uint32_t *>(p);
+    }
+    for (int q = 0; q < kFlags; ++q)
+        if (!g_flag_taken[q]) {
+            g_flag_taken[q] = true;
+            __atomic_store_n(g_flags + q * kFlagWords, 0u, __ATOMIC_RELAXED);
+            return g_flags + q * kFlagWords;
+        }
+    return nullptr;
+}
+
+void give_flag(uint32_t *flag)
+{
+    if (!flag) return;
+    std::lock_guard<std::mutex> lock(g_flag_mutex);
+    g_flag_taken[(flag - g_flags) / kFlagWords] = false;
 }
 
 void free_all(std::vector<void *> &owner)
@@ -738,29 +777,54 @@ int step_blocksign_cd(comp_ams *h, const G *g, hipStream_t st)
     return COMP_AMS_OK;
 }
 
+// Whether the guess is expected to hold, so that one workgroup may select from several regions (one_launch_select).  Scores do not
+// depend on the rows.  Magnitudes need settled records, and no miss of late: tk_small_select raises *miss_seen where
+// it lists a vector again, and the steps after the host has seen that take the three launches (three_launch_steps), whose many
+// workgroups list a vector again in a fraction of the time.  The flag is read as it stands, without a wait, so steps that were
+// handed over before are not called back; and a step recorded into a graph, which cannot change its mind, records three launches.
+// Step plus get_theta, us, three launches / always one / this: naive n = 8, d = 250 000, the gradients' scale alternating by two
+// 49 / 80 / 48, by 33 55 / 121 / 54, n = 4, a spike every tenth step 45 / 53 / 45; CD-Adam n = 4, d = 500 000, spikes 81 / 117 / 81,
+// constant gradients with noise, of which the guess misses every step from the 26th on, 84 / 152 / 81; d = 250 000, the scale halved
+// every tenth step 71 / 69 / 64; steady 71 / 56 / 56.
+constexpr uint64_t kSettledSteps = 4;      // CD-Adam misses in its third step
+bool guess_holds(comp_ams *h, bool scores)
+{
+    if (!h->has_guess || h->steps < h->guess_since + kSettledSteps) return false;
+    if (scores) return true;
+    if (!h->miss_seen || h->recording) return false;
+    if (__atomic_load_n(h->miss_seen, __ATOMIC_RELAXED)) {
+        __atomic_store_n(h->miss_seen, 0u, __ATOMIC_RELAXED);
+        if (h->steps >= h->three_until) {                              // else from a step handed over before the first was seen
+            h->three_steps = three_launch_steps(h->three_steps, h->steps - h->three_until);
+            h->three_until = h->steps + h->three_steps;
+        }
+    }
+    return h->steps >= h->three_until;
+}
+
 // The three selection launches between the listing pass and the kernel that uses Tc: candidate histograms (after
 // a miss: the whole vector's), leading digits and compaction of the threshold bin (after a miss: the lists anew),
 // last digits (or, rarest, the selection without lists).  kSrc / a / b say how the compressed vector is formed
 // again where that is needed.  cursor_b: the second set of region cursors, which the lists made anew count in.
-constexpr uint64_t kSettledSteps = 4;
 template <int kSrc, typename G>
 void launch_select(comp_ams *h, hipStream_t st, TkGeom ge, TkWorker *ws, uint2 *cand, uint32_t *cursor,
                    uint32_t *cursor_b, uint4 *tile_dir, uint32_t *hist1, uint32_t *histf, uint32_t *hist_full,
                    uint32_t *hist2, uint32_t *piece_bits, uint64_t *dense, uint2 *dense_dir, const void *a,
                    const float *b, const int (&slot)[3])
 {
-    const int64_t entries = one_select_entries(ge.d, ge.k, ge.rand.min_slack, ge.rand.on != 0);
-    // The first steps after the records were reset miss: the first one always, and under CD-Adam the third, when the Markov sequences
-    // hold what was kept (n = 8, d = 300 000 101 us with three launches, 278 with one).
-    if (h->has_guess && h->steps >= h->guess_since + kSettledSteps &&
-        one_launch_select(entries, ge.n_tiles, ge.slices, h->method == COMP_AMS_METHOD_CD, ge.rand.on != 0)) {
-        // One workgroup lists a vector again after a miss, so the guess keeps a wider slack (misses of a worker or more in 150 steps,
-        // 8 / 16 bins: error feedback n = 8, d = 300 000 1 / 0, n = 4, d = 500 000 bf16 4 / 1, n = 32, d = 400 000 2 / 0)
+    const bool scores = ge.rand.on != 0;
+    const int64_t entries = one_select_entries(ge.d, ge.k, ge.rand.min_slack, scores);
+    if (one_launch_select(entries, ge.n_tiles, ge.slices, h->method == COMP_AMS_METHOD_CD, scores)) {
+        // One workgroup lists a vector again after a miss, so the guess keeps a wider slack, whoever selects (misses of a worker or
+        // more in 150 steps, 8 / 16 bins: error feedback n = 8, d = 300 000 1 / 0, n = 4, d = 500 000 bf16 4 / 1, n = 32, d = 400 000 2 / 0)
         ge.rand.min_slack = std::max(ge.rand.min_slack, kOneSelectSlack);
-        launch_timed(h, slot[2], st, [&] {
-            KLAUNCH((tk_small_select<kSrc, G, true>), (unsigned)ge.n, kResolveThreads, st, ge, ws, cand, cursor, tile_dir, a, b);
-        });
-        return;
+        if (guess_holds(h, scores)) {
+            launch_timed(h, slot[2], st, [&] {
+                KLAUNCH((tk_small_select<kSrc, G, true>), (unsigned)ge.n, kResolveThreads, st, ge, ws, cand, cursor, tile_dir, a, b,
+                        h->miss_seen);
+            });
+            return;
+        }
     }
     const int per = ge.slices * ge.parts;
     // tk_compact: one workgroup per piece in the usual case; more (they leave at once then) where listing the vector
@@ -873,7 +937,7 @@ void launch_short_select(comp_ams *h, hipStream_t st, const TkGeom &sge, TkWorke
                          uint4 *tile_dir, const void *a, const float *b, int slot)
 {
     launch_timed(h, slot, st, [&] {
-        KLAUNCH((tk_small_select<kSrc, G, false>), (unsigned)sge.n, kResolveThreads, st, sge, ws, cand, count, tile_dir, a, b);
+        KLAUNCH((tk_small_select<kSrc, G, false>), (unsigned)sge.n, kResolveThreads, st, sge, ws, cand, count, tile_dir, a, b, nullptr);
     });
 }
 
@@ -1089,6 +1153,7 @@ int step_any(comp_ams *h, const G *grads_dev, void *hip_stream)
         else
             (void)hipGetLastError();
     }
+    h->recording = capturing;
     if (capturing && h->final_pending)
         return fail(h, COMP_AMS_ESTATE, "the update of the last step is still pending: call comp_ams_sync (or any getter) "
                                         "before recording a step into a graph");
@@ -1175,6 +1240,7 @@ int comp_ams_create(comp_ams_t **out, int64_t d, int32_t n, int32_t compressor, 
         g_create_error = h->err;
         free_all(h->allocs);
         free_all(h->tb_allocs);
+        give_flag(h->miss_seen);
         delete h;
         return rc;
     };
@@ -1240,6 +1306,8 @@ int comp_ams_create(comp_ams_t **out, int64_t d, int32_t n, int32_t compressor, 
             (rc = dev_alloc_t(h, h->allocs, &h->sel_out_idx, (size_t)ge.k)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->sel_out_val, (size_t)ge.k)))
             return bail(rc);
+        // for the lengths at which one workgroup may select from several regions of magnitudes
+        if (compressor == COMP_AMS_TOPK && ge.n_tiles > kSmallTiles && ge.n_tiles <= 2 * kOneSelectTiles) h->miss_seen = take_flag();
         if ((rc = reset_topk_workers(h))) return bail(rc);
     }
     apply_streaming(h);
@@ -1264,6 +1332,7 @@ void comp_ams_destroy(comp_ams_t *h)
             prof_clear(h);
             free_all(h->allocs);
             free_all(h->tb_allocs);
+            give_flag(h->miss_seen);
         }
     }
     delete h;

@@ -79,6 +79,16 @@ inline bool one_launch_select(int64_t entries, int64_t n_tiles, int slices, bool
            n_tiles <= (scores ? kOneSelectScoreTiles : (cd ? 2 : 1) * kOneSelectTiles);
 }
 
+// Steps that take three selection launches after one workgroup had to list a vector again; last: how many it was the time before,
+// since: steps from the end of those until the miss was seen.  One launch saves 4 to 17 us a step and a miss in it costs some 50 to 340,
+// so a miss in hundreds of steps is followed by a few, and where every guess misses there is one such step in 256.
+constexpr uint64_t kThreeFirst = 16, kThreeMost = 256;
+inline uint64_t three_launch_steps(uint64_t last, uint64_t since)
+{
+    if (since >= kThreeMost || last == 0) return kThreeFirst;
+    return 2 * last < kThreeMost ? 2 * last : kThreeMost;
+}
+
 // Whether tk_merge loads the server's vectors before the kept values: on few tiles nothing else hides that latency, on many the
 // registers (102 against 68) cost more wavefronts.  CD-Adam, step plus get_theta, us, late / early: Top-k n = 2, d = 600 000
 // 64.2 / 62.0, n = 8, d = 300 000 65.2 / 63.7, d = 2 M 107.7 / 104.3, Rand-k d = 5 M 188.3 / 188.1, Top-k d = 11.2 M bf16 334 / 337, n = 16

@@ -2333,12 +2333,13 @@ __device__ __forceinline__ uint64_t select_in_regions(const TkGeom &ge, int i, c
 
 // ge: the geometry the vectors were listed with, and so `count`: the regions' cursors, kCursorStride words apart (cleared here for
 // the next step).  kRegions: kHeldRegions regions or twice as many (lists of up to kHeldEntries entries, see one_launch_select);
-// else a single one per vector (short vectors).  a, b: how a vector is re-formed (Source4).
+// else a single one per vector (short vectors).  a, b: how a vector is re-formed (Source4).  miss_seen: host memory, or null; set
+// where a vector was listed again, which only the host's next choice of launches depends on (guess_holds).
 template <int kSrc, typename G, bool kRegions>
 __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom ge, TkWorker *__restrict__ ws,
                                                                    uint2 *__restrict__ cand, uint32_t *__restrict__ count,
                                                                    uint4 *__restrict__ tile_dir, const void *__restrict__ a,
-                                                                   const float *__restrict__ b)
+                                                                   const float *__restrict__ b, uint32_t *miss_seen)
 {
     __shared__ ResolveLds L;
     __shared__ union {
@@ -2442,6 +2443,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom ge, Tk
     if (tid == 0) {
         ws[i].relisted = missed ? 1u : 0u;
         ws[i].whole = missed && total == kNoSpace ? kExact : 0u;
+        if (kRegions && missed && miss_seen) __hip_atomic_store(miss_seen, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         if (kRegions) {                                                // for the records, as tk_compact leaves them
             ws[i].prefix = (uint32_t)top.prefix;
             ws[i].pshift = (uint32_t)(top.open - ge.idx_bits);

@@ -175,12 +175,23 @@ def sparse_pair(d, n, k, method, compressor=P.TOPK):
     return gpu, ora
 
 
-def sparse_steps(gpu, ora, fn, steps, method, tag, dtype="float32"):
+def selection_launches(gpu, step):
+    """(kernels of the workers' selection, of the CD-Adam server's) that step() launches."""
+    gpu.profile(True)
+    step()
+    counts = {name: launches for name, (_, launches) in gpu.profile_read().items()}
+    gpu.profile(False)
+    return sum(counts.get(name, 0) for name in ("tk_hist", "tk_compact", "tk_resolve")), counts.get("tk_select_server", 0)
+
+
+def sparse_steps(gpu, ora, fn, steps, method, tag, dtype="float32", after=None):
+    """after(t, launches): called behind each step's checks, with selection_launches of the step."""
     import torch
     step = {"float32": gpu.step, "bfloat16": gpu.step_bf16, "float16": gpu.step_f16}[dtype]
     for t in range(steps):
         g = fn(t)
-        step(torch.from_numpy(g).cuda().to(getattr(torch, dtype)))
+        gd = torch.from_numpy(g).cuda().to(getattr(torch, dtype))
+        launches = selection_launches(gpu, lambda: step(gd)) if after else step(gd)
         ora.step(g)
         for i in range(gpu.n):
             assert np.array_equal(gpu.get_selected(i)[0], ora.selected[i]), f"{tag} step {t} worker {i}: kept set"
@@ -193,6 +204,8 @@ def sparse_steps(gpu, ora, fn, steps, method, tag, dtype="float32"):
         for name, got, want in (("theta", gpu.get_theta(), ora.theta), ("m", gpu.get_m(), ora.m), ("v", gpu.get_v(), ora.v),
                                 ("vhat", gpu.get_vhat(), ora.vhat)):
             assert rel_close(got, want, STATE_RTOL).all(), f"{tag} step {t}: {name}"
+        if after:
+            after(t, launches)
 
 
 # vectors of up to 16 tiles: one selection kernel, its list in registers up to 4096 entries; 17 tiles: the chain
@@ -255,7 +268,7 @@ def test_short_vectors_of_equal_values_or_few_nonzeros(method, share):
     gpu.destroy()
 
 
-# one launch for the selection from several regions, and three on the other side of its lines: 32 and 64 regions (scores), the
+# one launch for the selection from several regions, and three on the other side of its lines and after a miss: 32 and 64 regions (scores), the
 # largest list, a scale that collapses or jumps (listed again), fewer non-zeros than k, one crowded region
 @pytest.mark.parametrize("method", ["ef", "naive", "cd"])
 @pytest.mark.parametrize("comp,d,n,k,kind", [
@@ -284,8 +297,80 @@ def test_selection_in_regions(method, comp, d, n, k, kind):
         elif kind == "ties":
             x = np.where(r.random((n, d)) < 0.2, f32(1.0), x * f32(0.01)).astype(f32)
         return np.ascontiguousarray(x, dtype=f32)
-    sparse_steps(gpu, ora, fn, 7, method, f"{kind} {method}")       # from the fifth step on in one launch
+
+    tiles, scores = (d + TILE - 1) // TILE, comp == P.RANDK
+    in_rule = scores or tiles <= (128 if method == "cd" else 64)
+    settled = 4
+    misses = []
+
+    def after(t, launches):
+        if in_rule and t >= settled and (scores or not any(misses)):
+            want = 1
+        else:
+            want = 3
+        if method == "cd" and kind != "plain" and t > 4:
+            want = launches[0]                                           # the server may have missed, which no record shows
+        assert want in (1, 3) and launches == (want, want if method == "cd" else 0), (t, launches)
+        infos = [gpu.get_selection_info(i) for i in range(n)]
+        if t >= settled and want == 1:
+            misses.append(any(i["relisted"] for i in infos))
+        if kind == "collapse" and t == 5 and method == "naive":
+            assert all(i["relisted"] for i in infos), infos
+        idx, val = gpu.get_selected(0)
+        if kind == "sparse" and method == "ef":
+            assert np.count_nonzero(val) < k, t                         # the threshold is a zero
+        if kind == "crowd":
+            assert np.count_nonzero(idx // TILE == 5) > 24 * 64 // 2, t   # more than a wavefront holds of two regions
+        if kind == "ties" and method == "naive":
+            assert (np.abs(val) == 1.0).all(), t                         # thousands under one value
+    sparse_steps(gpu, ora, fn, 7, method, f"{kind} {method}", after=after)
+    if kind in ("collapse", "jump") and method == "naive" and not scores:
+        assert any(misses)
+    if kind == "plain" and method != "cd":
+        assert not any(misses)
     gpu.destroy()
+
+
+# after a miss in one launch the selection takes three for 16 steps, for 32 where the next miss comes soon; then one again
+def test_three_launches_after_a_miss_of_one_workgroup():
+    d, n, k = 17 * TILE + 3, 1, 700
+    print(f"[case] a collapse of the scale under naive compression, d={d}", flush=True)
+    gpu, ora = sparse_pair(d, n, k, "naive")
+    base = grads_of(5, n, d)(0)
+    taken = []
+
+    def fn(t):
+        scale = f32(1.0 if t < 5 else 2.0 ** -3 if t < 25 else 2.0 ** -6)
+        return np.ascontiguousarray(np.roll(base, 97 * t, axis=1) * scale)
+
+    def after(t, launches):
+        taken.append(launches[0])
+        assert gpu.get_selection_info(0)["relisted"] == (1 if t in (0, 5, 25) else 0), t
+    sparse_steps(gpu, ora, fn, 61, "naive", "collapse", after=after)
+    assert taken == [3, 3, 3, 3, 1, 1] + [3] * 16 + [1] * 4 + [3] * 32 + [1] * 3
+    gpu.destroy()
+
+
+# the flags by which kernels report a miss: a handle without one takes three launches, and flags are given back
+def test_more_handles_than_flags_for_misses():
+    import torch
+    d, n, k = 17 * TILE, 1, 700
+    print(f"[case] 520 handles, d={d}", flush=True)
+    g = torch.from_numpy(grads_of(8, n, d)(0)).cuda()
+
+    def fifth_step(h):
+        for _ in range(4):
+            h.step(g)
+        return selection_launches(h, lambda: h.step(g))[0]
+    handles = [P.CompAms(d, n, P.TOPK, k) for _ in range(520)]
+    taken = [fifth_step(handles[0]), fifth_step(handles[-1])]
+    theta = [h.get_theta() for h in (handles[0], handles[-1])]
+    assert taken == [1, 3] and np.array_equal(bits(theta[0]), bits(theta[1]))
+    for h in handles:
+        h.destroy()
+    h = P.CompAms(d, n, P.TOPK, k)
+    assert fifth_step(h) == 1
+    h.destroy()
 
 
 # tk_merge lists the server's candidates: its vectors loaded before the kept values up to 1023 tiles, after them beyond; a first

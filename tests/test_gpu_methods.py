@@ -224,8 +224,20 @@ def test_a_step_can_be_captured_in_a_graph_and_replayed(comp, kb, method, d):
     Rand-k: a replayed step repeats the draw it was recorded with, so the oracle's draw is held at
     that number; under error feedback the deferred error memory of each replay must then be read with
     the draw of its predecessor - the same draw from the second replay on."""
+    record_and_replay(comp, kb, method, d, 2)
+
+
+# recorded after six eager steps, of which the last ones selected in one launch; an eager step between two replays
+@pytest.mark.parametrize("comp", [P.TOPK, P.RANDK])
+@pytest.mark.parametrize("method", [P.METHOD_EF, P.METHOD_CD, P.METHOD_NAIVE])
+def test_a_step_recorded_once_the_selection_takes_one_launch(comp, method):
+    record_and_replay(comp, 300, method, 70_003, 6, eager_between=True)
+
+
+def record_and_replay(comp, kb, method, d, eager, eager_between=False):
+    """`eager` ordinary steps, one recorded, five replays (and an ordinary step behind the second, if eager_between)."""
     import torch
-    announce(f"graph capture comp={comp} method={method} d={d}")
+    announce(f"graph capture comp={comp} method={method} d={d}, after {eager} steps")
     n = 4
     gpu = P.CompAms(d, n, comp, kb, W.BETA1, W.BETA2, W.EPS, W.LR)
     ora = O.Oracle(d, n, comp, kb, W.BETA1, W.BETA2, W.EPS, W.LR, method=method)
@@ -234,11 +246,11 @@ def test_a_step_can_be_captured_in_a_graph_and_replayed(comp, kb, method, d):
     if comp == P.RANDK:
         gpu.set_rand(seed, 0)
         ora.set_rand(seed, 0)
-    grads = [np.random.default_rng([13, t]).standard_normal((n, d)).astype(f32) for t in range(7)]
+    grads = [np.random.default_rng([13, t]).standard_normal((n, d)).astype(f32) for t in range(eager + 6)]
     side = torch.cuda.Stream()
     gbuf = torch.empty((n, d), dtype=torch.float32, device="cuda")
     with torch.cuda.stream(side):
-        for t in range(2):                                 # eager steps on the stream that will capture
+        for t in range(eager):                             # eager steps on the stream that will capture
             gbuf.copy_(torch.from_numpy(grads[t]))
             gpu.step(gbuf)
             ora.step(grads[t])
@@ -247,14 +259,14 @@ def test_a_step_can_be_captured_in_a_graph_and_replayed(comp, kb, method, d):
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph, stream=side):
         gpu.step(gbuf)                                     # recorded, not run
-    for t in range(2, 7):
+    for t in range(eager, eager + 5):
         with torch.cuda.stream(side):
             gbuf.copy_(torch.from_numpy(grads[t]))
         side.synchronize()
         graph.replay()
         torch.cuda.synchronize()
         if comp == P.RANDK:
-            ora.set_rand(seed, 2)                          # the recorded step was the third: draw number 2
+            ora.set_rand(seed, eager)                      # a replay repeats the recorded step's draw
         ora.step(grads[t])
         for name, got, want in (("theta", gpu.get_theta(), ora.theta), ("vhat", gpu.get_vhat(), ora.vhat)):
             ok = rel_close(got, want, STATE_RTOL)
@@ -265,6 +277,15 @@ def test_a_step_can_be_captured_in_a_graph_and_replayed(comp, kb, method, d):
             assert np.array_equal(bits(gpu.get_ghat_worker(1)), bits(ora.ghat_workers[1])), t
         if comp != P.BLOCKSIGN:
             assert np.array_equal(gpu.get_selected(2)[0], ora.selected[2]), t
+        if eager_between and t == eager + 1:
+            with torch.cuda.stream(side):
+                gbuf.copy_(torch.from_numpy(grads[-1]))
+                gpu.step(gbuf)
+            side.synchronize()
+            if comp == P.RANDK:
+                ora.set_rand(seed, eager + 1)              # the draw behind the recorded one
+            ora.step(grads[-1])
+            assert rel_close(gpu.get_theta(), ora.theta, STATE_RTOL).all(), t
     gpu.destroy()
 
 

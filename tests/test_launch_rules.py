@@ -69,6 +69,11 @@ def test_the_lists_of_scores_are_priced_with_the_slack_that_one_workgroup_uses(t
     assert evaluate(tmp_path, ["one_select_entries(500000, 5000, 0, false)"]) == [6250]
 
 
+def test_three_selection_launches_while_guesses_are_not_relied_on(tmp_path):
+    cases = {(0, 0): 16, (0, 10**6): 16, (16, 0): 32, (32, 255): 64, (64, 256): 16, (128, 1): 256, (256, 0): 256, (256, 300): 16}
+    assert evaluate(tmp_path, [f"three_launch_steps({last}, {since})" for last, since in cases]) == list(cases.values())
+
+
 def test_merge_loads_the_server_first_on_few_tiles(tmp_path):
     assert evaluate(tmp_path, [f"merge_loads_early({t})" for t in (1, 1023, 1024, 500_000)]) == [1, 1, 0, 0]
 
