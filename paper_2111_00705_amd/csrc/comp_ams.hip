@@ -102,7 +102,7 @@ struct comp_ams {
 
     uint2 *dense_dir = nullptr;                // [n][slices * parts * 4] {start, count} of each wavefront's piece
     bool has_guess = false;                    // a step has run since the selection records were reset
-    uint64_t guess_since = 0;                  // `steps` when it had not
+    uint64_t guess_since = 0;                  // `steps` when it had not, or when the rows under the guess were replaced
     uint32_t *miss_seen = nullptr;             // a flag in host memory, or none: raised by tk_small_select where it listed a vector again
     uint64_t three_until = 0, three_steps = 0; // after that the selection takes three launches for three_steps steps, up to three_until
     bool recording = false;                    // the running step is being recorded into a graph
@@ -778,7 +778,7 @@ int step_blocksign_cd(comp_ams *h, const G *g, hipStream_t st)
 }
 
 // Whether the guess is expected to hold, so that one workgroup may select from several regions (one_launch_select).  Scores do not
-// depend on the rows.  Magnitudes need settled records, and no miss of late: tk_small_select raises *miss_seen where
+// depend on the rows.  Magnitudes need settled records (settled_steps), and no miss of late: tk_small_select raises *miss_seen where
 // it lists a vector again, and the steps after the host has seen that take the three launches (three_launch_steps), whose many
 // workgroups list a vector again in a fraction of the time.  The flag is read as it stands, without a wait, so steps that were
 // handed over before are not called back; and a step recorded into a graph, which cannot change its mind, records three launches.
@@ -786,11 +786,9 @@ int step_blocksign_cd(comp_ams *h, const G *g, hipStream_t st)
 // 49 / 80 / 48, by 33 55 / 121 / 54, n = 4, a spike every tenth step 45 / 53 / 45; CD-Adam n = 4, d = 500 000, spikes 81 / 117 / 81,
 // constant gradients with noise, of which the guess misses every step from the 26th on, 84 / 152 / 81; d = 250 000, the scale halved
 // every tenth step 71 / 69 / 64; steady 71 / 56 / 56.
-constexpr uint64_t kSettledSteps = 4;      // CD-Adam misses in its third step
 bool guess_holds(comp_ams *h, bool scores)
 {
-    if (!h->has_guess || h->steps < h->guess_since + kSettledSteps) return false;
-    if (scores) return true;
+    if (!h->has_guess || scores) return h->has_guess;
     if (!h->miss_seen || h->recording) return false;
     if (__atomic_load_n(h->miss_seen, __ATOMIC_RELAXED)) {
         __atomic_store_n(h->miss_seen, 0u, __ATOMIC_RELAXED);
@@ -799,7 +797,7 @@ bool guess_holds(comp_ams *h, bool scores)
             h->three_until = h->steps + h->three_steps;
         }
     }
-    return h->steps >= h->three_until;
+    return h->steps >= h->three_until && h->steps - h->guess_since >= settled_steps(h->method == COMP_AMS_METHOD_CD);
 }
 
 // The three selection launches between the listing pass and the kernel that uses Tc: candidate histograms (after
@@ -1932,6 +1930,7 @@ int comp_ams_set_markov_state(comp_ams_t *h, const float *ghat_workers, const fl
         HIP_TRY(h, hipStreamSynchronize(h->stream));
         h->pending = false;   // the rows hold ghat_i itself
     }
+    h->guess_since = h->steps;
     return COMP_AMS_OK;   // the Top-k guesses are left as they are: a guess is only a hint
 }
 

@@ -79,6 +79,12 @@ inline bool one_launch_select(int64_t entries, int64_t n_tiles, int slices, bool
            n_tiles <= (scores ? kOneSelectScoreTiles : (cd ? 2 : 1) * kOneSelectTiles);
 }
 
+// Steps after the selection records were reset, or the rows under a guess replaced, whose guesses are not relied on (magnitudes).  The
+// first has none.  CD-Adam's second guess misses where gradients are correlated from step to step, its third where they are not, when
+// the Markov sequences hold what was kept (n = 8, d = 300 000 101 us with three launches, 278 with one), and here and there its
+// fourth.  Error feedback and naive compression missed in 2 of 150 second to fourth steps of a worker.
+inline uint64_t settled_steps(bool cd) { return cd ? 4 : 1; }
+
 // Steps that take three selection launches after one workgroup had to list a vector again; last: how many it was the time before,
 // since: steps from the end of those until the miss was seen.  One launch saves 4 to 17 us a step and a miss in it costs some 50 to 340,
 // so a miss in hundreds of steps is followed by a few, and where every guess misses there is one such step in 256.

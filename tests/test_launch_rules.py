@@ -70,6 +70,7 @@ def test_the_lists_of_scores_are_priced_with_the_slack_that_one_workgroup_uses(t
 
 
 def test_three_selection_launches_while_guesses_are_not_relied_on(tmp_path):
+    assert evaluate(tmp_path, ["settled_steps(false)", "settled_steps(true)"]) == [1, 4]
     cases = {(0, 0): 16, (0, 10**6): 16, (16, 0): 32, (32, 255): 64, (64, 256): 16, (128, 1): 256, (256, 0): 256, (256, 300): 16}
     assert evaluate(tmp_path, [f"three_launch_steps({last}, {since})" for last, since in cases]) == list(cases.values())
 
