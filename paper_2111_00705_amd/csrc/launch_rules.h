@@ -5,32 +5,21 @@
 namespace cams {
 
 // Whether the update of kept values takes a quarter of a tile per workgroup (tk_final_short) instead of a tile (tk_final).
-// The quarter form fills the chip and loads the state first.  Up to 320 tiles its 1280 workgroups run at once.  Step plus
-// get_theta, error feedback, a tile / a quarter, us, when each of the four wavefronts of a quarter still went through all lists
-// for itself (the quarter has gained since, 1 % of the step with 2 workers, 2-4 % with 16, up to 13 % with many kept values;
-// beyond the line it gained in places, n = 8, 342 tiles 77.0 / 72.5, and lost in others, 440 tiles 2-6 %, before its search got
-// shorter): Top-k, k = 2 %, n = 2, 288 tiles 56.7 / 52.6, 384 tiles 60.6 / 60.7; n = 8, 128 tiles 56.7 / 54.7, 320 tiles
-// 78.0 / 74.1, 352 tiles 80.9 / 81.7; n = 16, 319 tiles 106.7 / 104.6; k = 5 %, n = 24, 128 tiles 84.8 / 85.2, 200 tiles
-// 108.0 / 111.3; n = 32, 64 tiles 77.8 / 77.8, 128 tiles 101.1 / 102.2; n = 48, 64 tiles 98.2 / 98.4, 100 tiles 119.4 / 122.4;
-// Rand-k, k = 1 %, n = 16, 2 tiles 37.5 / 37.1; n = 48, 2 tiles 49.1 / 50.5, 16 tiles 57.0 / 56.2; n = 256, 5 tiles 133.4 / 150.2,
-// n = 1000, 5 tiles 446.6 / 514.0 (k = 0.1 % of the values 360.8 / 338.5, 2 % 395.1 / 416.5).
-constexpr int kShortFinalTiles = 320, kShortFinalWorkers = 48, kShortFinalLists = 3072;
-inline bool short_final(int64_t n, int64_t n_tiles)
-{
-    return n_tiles <= kShortFinalTiles && n <= kShortFinalWorkers && (n <= 16 || n * n_tiles <= kShortFinalLists);
-}
-
-// The same kernel pays beyond that line as well since its candidates are dealt out to all threads: up to 320 tiles whatever the
-// lists hold, and up to 448 with no more than eight workers.  Error feedback, step plus get_theta, us, a tile / a quarter: n = 2,
-// d = 1.5 M, k = 1 % 54.7 / 50.2, 1.8 M 56.8 / 52.5; n = 8, 1.5 M 73.6 / 69.8, k = 5 % 83.0 / 78.7, 1.8 M 78.8 / 74.8, naive bf16
-// 55.8 / 56.3, 2.1 M k = 0.1 % 82.4 / 83.5, naive bf16 60.2 / 62.3, 2.5 M 96.1 / 96.9; n = 12, 1.8 M 89.2 / 89.7, 2.1 M 97.8 / 100.2;
-// n = 16, 1.5 M 95.2 / 95.1, 2.5 M 130.8 / 134.7; n = 24, 800 000 85.2 / 83.0; n = 32, 400 000 73.4 / 69.5, k = 5 % bf16 81.5 / 76.7,
-// 800 000 99.8 / 96.5, 1.3 M 131.4 / 132.2, 1.5 M 144.2 / 144.5; n = 48, 400 000 93.0 / 88.0, 800 000 130.6 / 126.5, 1.3 M 177.8 / 177.8.
+// The quarter form fills the chip and loads the state first.  Up to 320 tiles its 1280 workgroups run at once; it pays up to 448 tiles
+// with no more than eight workers.  Step plus get_theta, the same handles in turn, us, a tile / a
+// quarter: error feedback, k = 1 %, n = 8, 367 tiles 73.5 / 69.3, 440 tiles 78.4 / 74.9 (k = 5 % 85.7 / 80.9, Rand-k f16
+// 75.5 / 71.4), n = 4, k = 0.1 % 62.5 / 59.0; naive bf16, 440 tiles, n = 1 47.9 / 47.1, n = 2 47.3 / 46.6, n = 4 50.3 / 49.9, but n = 6
+// 53.0 / 53.5, n = 8 55.0 / 55.6, 367 tiles 52.7 / 52.9, fp32 57.0 / 57.3; error feedback, 318 tiles, n = 12 80.7 / 75.9, n = 16
+// 91.6 / 87.9, n = 24 110.2 / 108.7, n = 32 131.6 / 130.6, n = 48 177.3 / 177.2, naive bf16 n = 32 73.0 / 71.9, n = 48 87.7 / 87.0;
+// 196 tiles, n = 24 85.6 / 82.3, n = 32 99.9 / 96.5, n = 48 130.9 / 127.0; 98 tiles, n = 32 73.0 / 69.4, n = 48 92.7 / 88.3.  Beyond, by
+// earlier figures: n = 8, 2.1 M, k = 0.1 % 82.4 / 83.5, 2.5 M 96.1 / 96.9; n = 12, 1.8 M 89.2 / 89.7; n = 16, 2.5 M 130.8 / 134.7; Rand-k
+// n = 256, 5 tiles 133.4 / 150.2, n = 1000, 5 tiles 446.6 / 514.0.
+constexpr int kShortFinalTiles = 320, kShortFinalWorkers = 48;
 constexpr int kQuarterTiles = 448, kQuarterWorkers = 8;
 inline bool quarter_final(int64_t n, int64_t n_tiles)
 {
-    return short_final(n, n_tiles) ||
-           n_tiles <= (n <= kQuarterWorkers ? kQuarterTiles : n <= kShortFinalWorkers ? kShortFinalTiles : 0);
+    if (n <= kQuarterWorkers) return n_tiles <= kQuarterTiles;
+    return n <= kShortFinalWorkers && n_tiles <= kShortFinalTiles;
 }
 
 // Workers whose kept values a workgroup of tk_final_short holds at a time.  Eight take 36 KB of LDS, which leaves four

@@ -875,7 +875,7 @@ __global__ __launch_bounds__(kThreads) void tk_final(TkGeom ge, const TkWorker *
     }
 }
 
-// The same with a quarter of a tile per workgroup, for vectors that leave the chip idle otherwise (see short_final): quarter
+// The same with a quarter of a tile per workgroup, for vectors that leave the chip idle otherwise (see quarter_final): quarter
 // w holds the coordinates of the listing pass's wavefront w, and wavefront r here updates row r of them (one float4 per lane,
 // the state loaded before anything else).
 // Bound by a chain of latencies: the records of all workers, then the candidates, are each loaded at once.  The candidates

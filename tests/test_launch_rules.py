@@ -20,16 +20,9 @@ def evaluate(tmp_path, expressions):
     return [int(x) for x in out.split()]
 
 
-def test_quarter_tile_update_only_where_the_lists_are_short(tmp_path):
-    cases = {(1, 320): 1, (1, 321): 0, (16, 320): 1, (17, 180): 1, (17, 181): 0, (24, 128): 1, (24, 192): 0, (32, 96): 1,
-             (32, 97): 0, (32, 288): 0, (48, 64): 1, (48, 65): 0, (49, 1): 0, (64, 128): 0, (1000, 1): 0, (65535, 1): 0,
-             (65535, 524288): 0}
-    got = evaluate(tmp_path, [f"short_final({n}, {tiles})" for n, tiles in cases])
-    assert got == list(cases.values())
-
-
 def test_quarter_tile_update_of_few_workers_or_few_tiles(tmp_path):
-    cases = {(1, 448): 1, (8, 448): 1, (8, 449): 0, (9, 320): 1, (9, 321): 0, (48, 320): 1, (48, 321): 0, (49, 1): 0, (65535, 1): 0,
+    cases = {(1, 320): 1, (1, 448): 1, (1, 449): 0, (8, 448): 1, (8, 449): 0, (9, 320): 1, (9, 321): 0, (16, 320): 1, (17, 180): 1, (24, 128): 1,
+             (32, 96): 1, (48, 64): 1, (48, 320): 1, (48, 321): 0, (49, 1): 0, (64, 128): 0, (1000, 1): 0, (65535, 1): 0, (65535, 524288): 0,
              (1, 524288): 0}
     got = evaluate(tmp_path, [f"quarter_final({n}, {tiles})" for n, tiles in cases])
     assert got == list(cases.values())
