@@ -851,7 +851,7 @@ void launch_final(comp_ams *h, hipStream_t st)
 {
     launch_timed(h, P_TK_FINAL, st, [&] {
         by_flag(h->params.stream_state, [&](auto ss) {
-            if (quarter_final(h->n, h->ge.n_tiles))
+            if (quarter_final(h->n, h->ge.n_tiles, h->method == COMP_AMS_METHOD_NAIVE))
                 by_flag(short_final_batch(h->ge.n_tiles) == 8, [&](auto eight) {
                     KLAUNCH((tk_final_short<decltype(ss)::value, decltype(eight)::value ? 8 : 5>), 4 * h->ge.n_tiles, kThreads, st, h->ge,
                             h->ws, h->cand, h->tile_dir, h->theta, h->m, h->v, h->vhat, h->params);

@@ -6,7 +6,7 @@ namespace cams {
 
 // Whether the update of kept values takes a quarter of a tile per workgroup (tk_final_short) instead of a tile (tk_final).
 // The quarter form fills the chip and loads the state first.  Up to 320 tiles its 1280 workgroups run at once; it pays up to 448 tiles
-// with no more than eight workers.  Step plus get_theta, the same handles in turn, us, a tile / a
+// with no more than eight workers, four under naive compression.  Step plus get_theta, the same handles in turn, us, a tile / a
 // quarter: error feedback, k = 1 %, n = 8, 367 tiles 73.5 / 69.3, 440 tiles 78.4 / 74.9 (k = 5 % 85.7 / 80.9, Rand-k f16
 // 75.5 / 71.4), n = 4, k = 0.1 % 62.5 / 59.0; naive bf16, 440 tiles, n = 1 47.9 / 47.1, n = 2 47.3 / 46.6, n = 4 50.3 / 49.9, but n = 6
 // 53.0 / 53.5, n = 8 55.0 / 55.6, 367 tiles 52.7 / 52.9, fp32 57.0 / 57.3; error feedback, 318 tiles, n = 12 80.7 / 75.9, n = 16
@@ -15,10 +15,10 @@ namespace cams {
 // earlier figures: n = 8, 2.1 M, k = 0.1 % 82.4 / 83.5, 2.5 M 96.1 / 96.9; n = 12, 1.8 M 89.2 / 89.7; n = 16, 2.5 M 130.8 / 134.7; Rand-k
 // n = 256, 5 tiles 133.4 / 150.2, n = 1000, 5 tiles 446.6 / 514.0.
 constexpr int kShortFinalTiles = 320, kShortFinalWorkers = 48;
-constexpr int kQuarterTiles = 448, kQuarterWorkers = 8;
-inline bool quarter_final(int64_t n, int64_t n_tiles)
+constexpr int kQuarterTiles = 448, kQuarterWorkers = 8, kQuarterWorkersNaive = 4;
+inline bool quarter_final(int64_t n, int64_t n_tiles, bool naive)
 {
-    if (n <= kQuarterWorkers) return n_tiles <= kQuarterTiles;
+    if (n <= (naive ? kQuarterWorkersNaive : kQuarterWorkers)) return n_tiles <= kQuarterTiles;
     return n <= kShortFinalWorkers && n_tiles <= kShortFinalTiles;
 }
 

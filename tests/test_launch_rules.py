@@ -24,8 +24,11 @@ def test_quarter_tile_update_of_few_workers_or_few_tiles(tmp_path):
     cases = {(1, 320): 1, (1, 448): 1, (1, 449): 0, (8, 448): 1, (8, 449): 0, (9, 320): 1, (9, 321): 0, (16, 320): 1, (17, 180): 1, (24, 128): 1,
              (32, 96): 1, (48, 64): 1, (48, 320): 1, (48, 321): 0, (49, 1): 0, (64, 128): 0, (1000, 1): 0, (65535, 1): 0, (65535, 524288): 0,
              (1, 524288): 0}
-    got = evaluate(tmp_path, [f"quarter_final({n}, {tiles})" for n, tiles in cases])
+    got = evaluate(tmp_path, [f"quarter_final({n}, {tiles}, false)" for n, tiles in cases])
     assert got == list(cases.values())
+    naive = {(1, 448): 1, (4, 448): 1, (4, 449): 0, (5, 320): 1, (5, 321): 0, (8, 321): 0, (48, 320): 1, (49, 1): 0}
+    got = evaluate(tmp_path, [f"quarter_final({n}, {tiles}, true)" for n, tiles in naive])
+    assert got == list(naive.values())
 
 
 def test_quarter_tile_update_holds_eight_workers_up_to_256_tiles(tmp_path):
