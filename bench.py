@@ -121,6 +121,8 @@ def kernel_algorithmic_bytes(name: str, n: int, d: int, method: str = "ef") -> i
         # CD-Adam with Top-k only reads g and ghat_i in the pass (ghat_i changes on the k kept coordinates)
         "tk_pass1": (4 if naive else 8 if method == "cd" else 12) * nd,
         "tk_final": 32 * d,
+        # a whole step in one launch; under CD-Adam the server's ghat and gtilde are read and written as well
+        "bs_step_short": (4 if naive else 12) * nd + (48 if method == "cd" else 32) * d,
         "bs_server": 12 * d,
         "bs_apply": 40 * d,
         "tk_merge": 12 * d,       # ghat read and written, gtilde read for the server's candidates

@@ -55,3 +55,10 @@ def test_which_summary_a_run_reads():
     assert bench.run_variant("ef", "f16", False) is None
     assert bench.run_variant("cd", "f32", True) is None
     assert set(bench.PROFILE_SUFFIX) == {"ef", "cd", "naive", "none", "bf16", "randk"}
+
+
+def test_the_one_launch_sign_step_carries_the_bytes_of_its_stages():
+    rows = {m: bench.kernel_algorithmic_bytes("bs_pass", 20, 300, m) for m in ("ef", "cd", "naive")}
+    for method, server in (("ef", 0), ("naive", 0), ("cd", 16 * 300)):        # ghat and gtilde read and written
+        assert bench.kernel_algorithmic_bytes("bs_step_short", 20, 300, method) == \
+            rows[method] + bench.kernel_algorithmic_bytes("bs_update", 20, 300, method) + server
