@@ -106,6 +106,7 @@ struct comp_ams {
     uint32_t *miss_seen = nullptr;             // a flag in host memory, or none: raised by tk_small_select where it listed a vector again
     uint64_t three_until = 0, three_steps = 0; // after that the selection takes three launches for three_steps steps, up to three_until
     bool recording = false;                    // the running step is being recorded into a graph
+    bool guess_good = false;                   // guess_holds of the running step, the same for the workers and the server
     uint32_t *small_ctr = nullptr;             // [n + 1] short vectors: entries listed (the last one the server's)
     uint32_t *sel_count = nullptr, *sel_out_idx = nullptr;
     float *sel_out_val = nullptr;
@@ -816,10 +817,9 @@ void launch_select(comp_ams *h, hipStream_t st, TkGeom ge, TkWorker *ws, uint2 *
         // One workgroup lists a vector again after a miss, so the guess keeps a wider slack, whoever selects (misses of a worker or
         // more in 150 steps, 8 / 16 bins: error feedback n = 8, d = 300 000 1 / 0, n = 4, d = 500 000 bf16 4 / 1, n = 32, d = 400 000 2 / 0)
         ge.rand.min_slack = std::max(ge.rand.min_slack, kOneSelectSlack);
-        if (guess_holds(h, scores)) {
+        if (h->guess_good) {
             launch_timed(h, slot[2], st, [&] {
-                KLAUNCH((tk_small_select<kSrc, G, true>), (unsigned)ge.n, kResolveThreads, st, ge, ws, cand, cursor, tile_dir, a, b,
-                        h->miss_seen);
+                KLAUNCH((tk_small_select<kSrc, G, true>), (unsigned)ge.n, kResolveThreads, st, ge, ws, cand, cursor, tile_dir, a, b);
             });
             return;
         }
@@ -935,7 +935,7 @@ void launch_short_select(comp_ams *h, hipStream_t st, const TkGeom &sge, TkWorke
                          uint4 *tile_dir, const void *a, const float *b, int slot)
 {
     launch_timed(h, slot, st, [&] {
-        KLAUNCH((tk_small_select<kSrc, G, false>), (unsigned)sge.n, kResolveThreads, st, sge, ws, cand, count, tile_dir, a, b, nullptr);
+        KLAUNCH((tk_small_select<kSrc, G, false>), (unsigned)sge.n, kResolveThreads, st, sge, ws, cand, count, tile_dir, a, b);
     });
 }
 
@@ -1078,6 +1078,15 @@ void fresh_tk_workers(std::vector<TkWorker> &init)
     }
 }
 
+// The record behind the last of a handle's workers, or of its server (zero as it was allocated where the handle has no flag).
+int set_flag_record(comp_ams *h, TkWorker *dst)
+{
+    if (!h->miss_seen) return COMP_AMS_OK;
+    const TkWorker record = flag_record(h->miss_seen);
+    HIP_TRY(h, hipMemcpy(dst, &record, sizeof record, hipMemcpyHostToDevice));
+    return COMP_AMS_OK;
+}
+
 // Resets the per-worker selection records: no pending threshold, no guess.
 int reset_topk_workers(comp_ams *h)
 {
@@ -1174,6 +1183,7 @@ int step_any(comp_ams *h, const G *grads_dev, void *hip_stream)
         const double sd_bins = std::sqrt((double)h->k * (1.0 - kd)) / (double)h->d * (double)(1u << 17);
         h->ge.rand.min_slack = h->srv.ge.rand.min_slack = (uint32_t)std::min(512.0, std::ceil(6.0 * 1.4143 * sd_bins));
     }
+    if (is_sparse(h)) h->guess_good = guess_holds(h, h->compressor == COMP_AMS_RANDK);
     if (h->method == COMP_AMS_METHOD_NONE)
         rc = step_plain(h, grads_dev, st);
     else if (is_sparse(h))
@@ -1287,7 +1297,7 @@ int comp_ams_create(comp_ams_t **out, int64_t d, int32_t n, int32_t compressor, 
         ge.relist_wgs = (int32_t)std::min<int64_t>(ge.n_tiles, std::max(1, 2048 / n));
         const size_t segs = (size_t)n * ge.n_tiles;
         const size_t region_entries = (size_t)n * ge.slices * (size_t)ge.region_cap;
-        if ((rc = dev_alloc_t(h, h->allocs, &h->ws, (size_t)n)) ||
+        if ((rc = dev_alloc_t(h, h->allocs, &h->ws, (size_t)n + 1)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->cand, region_entries, false)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->cursor, (size_t)n * ge.slices * kCursorStride)) ||
             (rc = dev_alloc_t(h, h->allocs, &h->cursor_b, (size_t)n * ge.slices * kCursorStride)) ||
@@ -1306,6 +1316,7 @@ int comp_ams_create(comp_ams_t **out, int64_t d, int32_t n, int32_t compressor, 
             return bail(rc);
         // for the lengths at which one workgroup may select from several regions of magnitudes
         if (compressor == COMP_AMS_TOPK && ge.n_tiles > kSmallTiles && ge.n_tiles <= 2 * kOneSelectTiles) h->miss_seen = take_flag();
+        if ((rc = set_flag_record(h, h->ws + n))) return bail(rc);
         if ((rc = reset_topk_workers(h))) return bail(rc);
     }
     apply_streaming(h);
@@ -1846,7 +1857,7 @@ int comp_ams_set_method(comp_ams_t *h, int32_t method)
             set_slices(sv.ge, slices);
             const size_t tiles = (size_t)sv.ge.n_tiles;
             const size_t region_entries = (size_t)sv.ge.slices * (size_t)sv.ge.region_cap;
-            if ((rc = dev_alloc_t(h, h->allocs, &sv.ws, 1)) ||
+            if ((rc = dev_alloc_t(h, h->allocs, &sv.ws, 2)) ||
                 (rc = dev_alloc_t(h, h->allocs, &sv.cand, region_entries, false)) ||
                 (rc = dev_alloc_t(h, h->allocs, &sv.cursor, (size_t)sv.ge.slices * kCursorStride)) ||
                 (rc = dev_alloc_t(h, h->allocs, &h->cursor_b_s, (size_t)sv.ge.slices * kCursorStride)) ||
@@ -1860,6 +1871,7 @@ int comp_ams_set_method(comp_ams_t *h, int32_t method)
                 (rc = dev_alloc_t(h, h->allocs, &h->piece_bits_s, (size_t)sv.ge.slices * sv.ge.parts * 4 * kPieceWords,
                                   false)))
                 return rc;
+            if ((rc = set_flag_record(h, sv.ws + 1))) return rc;
         }
     }
     if (is_sparse(h) && (rc = reset_topk_workers(h))) return rc;

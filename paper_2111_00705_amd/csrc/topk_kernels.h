@@ -120,6 +120,20 @@ struct TkWorker {
 };
 static_assert(sizeof(TkWorker) == 56, "TkWorker is copied between host and device as plain bytes");
 
+// The record behind a handle's last holds no selection: its tc is the address of a word in host memory that says so when a guess has
+// missed (0: no such word).  As an argument of tk_small_select the address cost it 0.2 to 0.4 of 8.5 us; with it here, and the miss
+// marked as rare there, steps take what they took without (CD-Adam n = 4, d = 84 814 50.5 / 50.8 us, n = 1, d = 369 518 53.8 / 53.4).
+inline TkWorker flag_record(const uint32_t *flag)
+{
+    TkWorker w{};
+    w.tc = reinterpret_cast<uint64_t>(flag);
+    return w;
+}
+__device__ __forceinline__ void raise_flag(const TkWorker &record)
+{
+    if (record.tc) __hip_atomic_store(reinterpret_cast<uint32_t *>(record.tc), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Rand-k: what the score of a coordinate depends on besides its index and the vector's number.
 struct TkRand {
     uint32_t on;          // 0: Top-k (keys are magnitudes)
@@ -2333,13 +2347,13 @@ __device__ __forceinline__ uint64_t select_in_regions(const TkGeom &ge, int i, c
 
 // ge: the geometry the vectors were listed with, and so `count`: the regions' cursors, kCursorStride words apart (cleared here for
 // the next step).  kRegions: kHeldRegions regions or twice as many (lists of up to kHeldEntries entries, see one_launch_select);
-// else a single one per vector (short vectors).  a, b: how a vector is re-formed (Source4).  miss_seen: host memory, or null; set
-// where a vector was listed again, which only the host's next choice of launches depends on (guess_holds).
+// else a single one per vector (short vectors).  a, b: how a vector is re-formed (Source4).  A vector that was listed again
+// raises the handle's flag (kRegions; see flag_record), which only the host's next choice of launches depends on.
 template <int kSrc, typename G, bool kRegions>
 __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom ge, TkWorker *__restrict__ ws,
                                                                    uint2 *__restrict__ cand, uint32_t *__restrict__ count,
                                                                    uint4 *__restrict__ tile_dir, const void *__restrict__ a,
-                                                                   const float *__restrict__ b, uint32_t *miss_seen)
+                                                                   const float *__restrict__ b)
 {
     __shared__ ResolveLds L;
     __shared__ union {
@@ -2370,7 +2384,10 @@ __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom ge, Tk
     // a list of every non-zero element (the guess was 0) needs no other, however short it is
     const bool missed = w.overflow || (total < sge.k && (zeros_listed || w.guess != 0u));
     ShortDigits top = {0ull, sge.k, 31 + sge.idx_bits};
-    if (missed) total = list_short_again<kSrc, G>(sge, i, a, b, sk, cand, tile_dir, L, U.again, top);
+    if (__builtin_expect(missed, 0)) {
+        if (kRegions && tid == 0) raise_flag(ws[ge.n]);
+        total = list_short_again<kSrc, G>(sge, i, a, b, sk, cand, tile_dir, L, U.again, top);
+    }
     uint64_t tc;
     if (missed && total == kNoSpace) {
         tc = exact_select(es, sge, i, cand, tile_dir, L, U.exact);
@@ -2443,7 +2460,6 @@ __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom ge, Tk
     if (tid == 0) {
         ws[i].relisted = missed ? 1u : 0u;
         ws[i].whole = missed && total == kNoSpace ? kExact : 0u;
-        if (kRegions && missed && miss_seen) __hip_atomic_store(miss_seen, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         if (kRegions) {                                                // for the records, as tk_compact leaves them
             ws[i].prefix = (uint32_t)top.prefix;
             ws[i].pshift = (uint32_t)(top.open - ge.idx_bits);
