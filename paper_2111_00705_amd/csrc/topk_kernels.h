@@ -2384,7 +2384,8 @@ __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom ge, Tk
     // a list of every non-zero element (the guess was 0) needs no other, however short it is
     const bool missed = w.overflow || (total < sge.k && (zeros_listed || w.guess != 0u));
     ShortDigits top = {0ull, sge.k, 31 + sge.idx_bits};
-    if (__builtin_expect(missed, 0)) {
+    // rare only where a flag is raised: short vectors gain nothing by the hint (CD-Adam n = 4, d = 16 908 39.2 us with it, 38.8 without)
+    if (kRegions ? __builtin_expect(missed, 0) : missed) {
         if (kRegions && tid == 0) raise_flag(ws[ge.n]);
         total = list_short_again<kSrc, G>(sge, i, a, b, sk, cand, tile_dir, L, U.again, top);
     }
