@@ -1078,20 +1078,13 @@ void fresh_tk_workers(std::vector<TkWorker> &init)
     }
 }
 
-// The record behind the last of a handle's workers, or of its server (zero as it was allocated where the handle has no flag).
-int set_flag_record(comp_ams *h, TkWorker *dst)
-{
-    if (!h->miss_seen) return COMP_AMS_OK;
-    const TkWorker record = flag_record(h->miss_seen);
-    HIP_TRY(h, hipMemcpy(dst, &record, sizeof record, hipMemcpyHostToDevice));
-    return COMP_AMS_OK;
-}
-
-// Resets the per-worker selection records: no pending threshold, no guess.
+// Resets the per-worker selection records: no pending threshold, no guess.  Behind the workers' and behind the server's one lies
+// flag_record.
 int reset_topk_workers(comp_ams *h)
 {
-    std::vector<TkWorker> init((size_t)h->n);
+    std::vector<TkWorker> init((size_t)h->n + 1);
     fresh_tk_workers(init);
+    init.back() = flag_record(h->miss_seen);
     h->has_guess = false;
     h->guess_since = h->steps;
     HIP_TRY(h, hipMemcpy(h->ws, init.data(), init.size() * sizeof(TkWorker), hipMemcpyHostToDevice));
@@ -1099,7 +1092,7 @@ int reset_topk_workers(comp_ams *h)
     HIP_TRY(h, hipMemset(h->cursor_b, 0, (size_t)h->n * h->ge.slices * kCursorStride * sizeof(uint32_t)));
     HIP_TRY(h, hipMemset(h->small_ctr, 0, ((size_t)h->n + 1) * kCursorStride * sizeof(uint32_t)));
     if (h->srv.ws) {
-        HIP_TRY(h, hipMemcpy(h->srv.ws, init.data(), sizeof(TkWorker), hipMemcpyHostToDevice));
+        HIP_TRY(h, hipMemcpy(h->srv.ws, init.data() + h->n - 1, 2 * sizeof(TkWorker), hipMemcpyHostToDevice));
         HIP_TRY(h, hipMemset(h->srv.cursor, 0, (size_t)h->srv.ge.slices * kCursorStride * sizeof(uint32_t)));
         HIP_TRY(h, hipMemset(h->cursor_b_s, 0, (size_t)h->srv.ge.slices * kCursorStride * sizeof(uint32_t)));
     }
@@ -1316,7 +1309,6 @@ int comp_ams_create(comp_ams_t **out, int64_t d, int32_t n, int32_t compressor, 
             return bail(rc);
         // for the lengths at which one workgroup may select from several regions of magnitudes
         if (compressor == COMP_AMS_TOPK && ge.n_tiles > kSmallTiles && ge.n_tiles <= 2 * kOneSelectTiles) h->miss_seen = take_flag();
-        if ((rc = set_flag_record(h, h->ws + n))) return bail(rc);
         if ((rc = reset_topk_workers(h))) return bail(rc);
     }
     apply_streaming(h);
@@ -1871,7 +1863,6 @@ int comp_ams_set_method(comp_ams_t *h, int32_t method)
                 (rc = dev_alloc_t(h, h->allocs, &h->piece_bits_s, (size_t)sv.ge.slices * sv.ge.parts * 4 * kPieceWords,
                                   false)))
                 return rc;
-            if ((rc = set_flag_record(h, sv.ws + 1))) return rc;
         }
     }
     if (is_sparse(h) && (rc = reset_topk_workers(h))) return rc;

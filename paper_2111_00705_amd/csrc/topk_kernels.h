@@ -121,8 +121,10 @@ struct TkWorker {
 static_assert(sizeof(TkWorker) == 56, "TkWorker is copied between host and device as plain bytes");
 
 // The record behind a handle's last holds no selection: its tc is the address of a word in host memory that says so when a guess has
-// missed (0: no such word).  As an argument of tk_small_select the address cost it 0.2 to 0.4 of 8.5 us; with it here, and the miss
-// marked as rare there, steps take what they took without (CD-Adam n = 4, d = 84 814 50.5 / 50.8 us, n = 1, d = 369 518 53.8 / 53.4).
+// missed (0: no such word).  As an argument of tk_small_select the address cost it 0.2 to 0.4 of 8.5 us; here, read by the kernel's last
+// instructions after a miss that is marked as rare, it costs steps that do not miss next to nothing (without / with it, us: CD-Adam
+// n = 8, d = 300 000 56.0 / 56.2, error feedback d = 200 000 37.8 / 38.0, n = 16, d = 378 180 53.7 / 53.6; raised ahead of the listing
+// 56.0 / 56.6, 37.8 / 37.9, 53.6 / 53.6).
 inline TkWorker flag_record(const uint32_t *flag)
 {
     TkWorker w{};
@@ -2385,10 +2387,8 @@ __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom ge, Tk
     const bool missed = w.overflow || (total < sge.k && (zeros_listed || w.guess != 0u));
     ShortDigits top = {0ull, sge.k, 31 + sge.idx_bits};
     // rare only where a flag is raised: short vectors gain nothing by the hint (CD-Adam n = 4, d = 16 908 39.2 us with it, 38.8 without)
-    if (kRegions ? __builtin_expect(missed, 0) : missed) {
-        if (kRegions && tid == 0) raise_flag(ws[ge.n]);
+    if (kRegions ? __builtin_expect(missed, 0) : missed)
         total = list_short_again<kSrc, G>(sge, i, a, b, sk, cand, tile_dir, L, U.again, top);
-    }
     uint64_t tc;
     if (missed && total == kNoSpace) {
         tc = exact_select(es, sge, i, cand, tile_dir, L, U.exact);
@@ -2459,6 +2459,7 @@ __global__ __launch_bounds__(kResolveThreads) void tk_small_select(TkGeom ge, Tk
     }
     if (kRegions && tid < ge.slices) count[(i * ge.slices + tid) * kCursorStride] = 0;
     if (tid == 0) {
+        if (kRegions && missed) raise_flag(ws[ge.n]);
         ws[i].relisted = missed ? 1u : 0u;
         ws[i].whole = missed && total == kNoSpace ? kExact : 0u;
         if (kRegions) {                                                // for the records, as tk_compact leaves them
