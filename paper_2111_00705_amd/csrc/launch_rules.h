@@ -54,8 +54,9 @@ inline int64_t one_select_entries(int64_t d, int64_t k, uint32_t min_slack, bool
 // launches; entries: what is expected to be listed.  It holds kHeldEntries, and a quarter is left for uneven regions.  After a miss
 // that workgroup lists the vector again by itself (d = 500 000: 340 us where many workgroups take tens), so magnitudes, whose
 // threshold may fall, stop at 64 tiles, and at 128 under CD-Adam, which selects twice and gains twice as much by it (see guess_holds
-// for runs that miss often).  Scores do not fall, and stop where a fine bin, which holds d / 2^17 of them, gets near the few that are ranked as they are.  Fewer than 16 entries were not
-// measured with magnitudes and stay.  Step plus get_theta, us, three launches / one: error feedback n = 8, d = 100 000
+// for runs that miss often).  Scores do not fall, and stop where a fine bin, which holds d / 2^17 of them, gets near the few that are
+// ranked as they are.  Fewer than 16 entries were not measured with magnitudes and stay.  Step plus get_theta, us, three launches /
+// one: error feedback n = 8, d = 100 000
 // 38.6 / 34.7, d = 300 000, k = 0.1 % 42.8 / 38.9, k = 1 % 44.2 / 39.9, Rand-k 44.8 / 41.9; naive n = 8, d = 3 M bf16, k = 0.3 %
 // (Rand-k) 69.5 / 66.3; CD-Adam n = 8, d = 300 000 67.5 / 56.0, d = 500 000 bf16 69.8 / 59.5, n = 2, d = 200 000 62.6 / 50.2, Rand-k
 // d = 400 000 71.3 / 63.7.  Rand-k by length: n = 16, d = 1.2 M f16 78.3 / 74.2, n = 8, d = 4 M 117.8 / 114.5, d = 11 M bf16
