@@ -103,7 +103,7 @@ struct comp_ams {
     uint2 *dense_dir = nullptr;                // [n][slices * parts * 4] {start, count} of each wavefront's piece
     bool has_guess = false;                    // a step has run since the selection records were reset
     uint64_t guess_since = 0;                  // `steps` when it had not, or when the rows under the guess were replaced
-    uint32_t *miss_seen = nullptr;             // a flag in host memory, or none: raised by tk_small_select where it listed a vector again
+    uint32_t *miss_seen = nullptr;             // a word in host memory, or none: raised by tk_small_select where it listed a vector again
     uint64_t three_until = 0, three_steps = 0; // after that the selection takes three launches for three_steps steps, up to three_until
     bool recording = false;                    // the running step is being recorded into a graph
     bool guess_good = false;                   // guess_holds of the running step, the same for the workers and the server
@@ -377,40 +377,22 @@ int dev_alloc_t(comp_ams *h, std::vector<void *> &owner, T **out, size_t count, 
     return dev_alloc(h, owner, reinterpret_cast<void **>(out), count * sizeof(T), zero);
 }
 
-// Flags that kernels raise for the host: words of one pinned block that the process keeps once a handle has wanted one (allocating it
-// takes 80 us), a cache line each, taken by a handle and given back by it.  Without one - the block is all taken, or was refused - a
-// handle does without what the flag is for.
-constexpr int kFlags = 512, kFlagWords = 16;
-std::mutex g_flag_mutex;
-uint32_t *g_flags = nullptr;
-bool g_flag_taken[kFlags] = {};
-
-uint32_t *take_flag()
+// The word that kernels raise for the host (miss_seen), in pinned memory; a handle that is refused it does without.  Allocating and
+// freeing it takes 7 us each of the 150 and 80 that a handle's memory takes (the process's first one 80).
+void take_flag(comp_ams *h)
 {
-    std::lock_guard<std::mutex> lock(g_flag_mutex);
-    if (!g_flags) {
-        void *p = nullptr;
-        if (hipHostMalloc(&p, kFlags * kFlagWords * sizeof(uint32_t),
-                          hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        g_flags = static_cast<uint32_t *>(p);
+    void *p = nullptr;
+    if (hipHostMalloc(&p, sizeof(uint32_t), hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
     }
-    for (int q = 0; q < kFlags; ++q)
-        if (!g_flag_taken[q]) {
-            g_flag_taken[q] = true;
-            __atomic_store_n(g_flags + q * kFlagWords, 0u, __ATOMIC_RELAXED);
-            return g_flags + q * kFlagWords;
-        }
-    return nullptr;
+    h->miss_seen = static_cast<uint32_t *>(p);
+    *h->miss_seen = 0u;
 }
 
-void give_flag(uint32_t *flag)
+void give_flag(comp_ams *h)
 {
-    if (!flag) return;
-    std::lock_guard<std::mutex> lock(g_flag_mutex);
-    g_flag_taken[(flag - g_flags) / kFlagWords] = false;
+    if (h->miss_seen) (void)hipHostFree(h->miss_seen);
 }
 
 void free_all(std::vector<void *> &owner)
@@ -1241,7 +1223,7 @@ int comp_ams_create(comp_ams_t **out, int64_t d, int32_t n, int32_t compressor, 
         g_create_error = h->err;
         free_all(h->allocs);
         free_all(h->tb_allocs);
-        give_flag(h->miss_seen);
+        give_flag(h);
         delete h;
         return rc;
     };
@@ -1308,7 +1290,7 @@ int comp_ams_create(comp_ams_t **out, int64_t d, int32_t n, int32_t compressor, 
             (rc = dev_alloc_t(h, h->allocs, &h->sel_out_val, (size_t)ge.k)))
             return bail(rc);
         // for the lengths at which one workgroup may select from several regions of magnitudes
-        if (compressor == COMP_AMS_TOPK && ge.n_tiles > kSmallTiles && ge.n_tiles <= 2 * kOneSelectTiles) h->miss_seen = take_flag();
+        if (compressor == COMP_AMS_TOPK && ge.n_tiles > kSmallTiles && ge.n_tiles <= 2 * kOneSelectTiles) take_flag(h);
         if ((rc = reset_topk_workers(h))) return bail(rc);
     }
     apply_streaming(h);
@@ -1333,7 +1315,7 @@ void comp_ams_destroy(comp_ams_t *h)
             prof_clear(h);
             free_all(h->allocs);
             free_all(h->tb_allocs);
-            give_flag(h->miss_seen);
+            give_flag(h);
         }
     }
     delete h;

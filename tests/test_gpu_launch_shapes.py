@@ -351,26 +351,26 @@ def test_three_launches_after_a_miss_of_one_workgroup():
     gpu.destroy()
 
 
-# the flags by which kernels report a miss: a handle without one takes three launches, and flags are given back
-def test_more_handles_than_flags_for_misses():
+# a miss sends the handle whose kernel it was to three launches, and no other; what a handle held is given back with it
+def test_a_miss_is_reported_to_its_own_handle():
     import torch
     d, n, k = 17 * TILE, 1, 700
-    print(f"[case] 520 handles, d={d}", flush=True)
+    print(f"[case] two handles, one miss, d={d}", flush=True)
     g = torch.from_numpy(grads_of(8, n, d)(0)).cuda()
-
-    def third_step(h):
-        h.step(g)
-        h.step(g)
-        return selection_launches(h, lambda: h.step(g))[0]
-    handles = [P.CompAms(d, n, P.TOPK, k) for _ in range(520)]
-    taken = [third_step(handles[0]), third_step(handles[-1])]
-    theta = [h.get_theta() for h in (handles[0], handles[-1])]
-    assert taken == [1, 3] and np.array_equal(bits(theta[0]), bits(theta[1]))
-    for h in handles:
-        h.destroy()
-    h = P.CompAms(d, n, P.TOPK, k)
-    assert third_step(h) == 1
-    h.destroy()
+    small = g * 0.125                                                    # the same order, another threshold
+    for _ in range(3):
+        steady, missing = (P.CompAms(d, n, P.TOPK, k) for _ in range(2))
+        for h in (steady, missing):
+            h.set_method(P.METHOD_NAIVE)
+            for _ in range(2):
+                h.step(g)
+        missing.step(small)
+        assert missing.get_selection_info(0)["relisted"] == 1
+        taken = [selection_launches(h, lambda: h.step(x))[0] for h, x in ((steady, g), (missing, small))]
+        assert taken == [1, 3]
+        assert np.array_equal(missing.get_selected(0)[0], steady.get_selected(0)[0])
+        steady.destroy()
+        missing.destroy()
 
 
 # CD-Adam: three launches in the steps whose guesses do not hold yet, also after the rows under the guess were replaced
