@@ -104,9 +104,9 @@ inline int64_t region_entries(int64_t d, int64_t k, int64_t full, int slices)
     return full < most ? full : most;
 }
 
-// Where the listing pass stores a candidate: the entry at which the tile's space begins (at: counted from the vector's first region,
-// up to 2^31, so in 64 bits), and bytes from there on for the place inside that space, of at most a tile's 4096 entries.
-constexpr int64_t tile_space(int64_t vector_base, uint32_t at) { return vector_base + (int64_t)at; }
+// Where the listing pass stores a candidate: the first entry of the tile's region, in 64 bits (a vector's regions hold up to 2^31
+// entries), and bytes from there on for the place inside the region, of at most a 32nd of 2^31 entries.
+constexpr int64_t region_first(int64_t vector, int slices, int slice, uint32_t region_cap) { return (vector * slices + slice) * region_cap; }
 constexpr uint32_t offset_bytes(uint32_t at, uint32_t size) { return at * size; }
 
 // Grid of a kernel with one workgroup per tile (in x) under tile_of_block's mapping.

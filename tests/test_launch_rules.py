@@ -77,7 +77,7 @@ def test_merge_loads_the_server_first_on_few_tiles(tmp_path):
 
 def test_candidates_of_the_largest_lists_are_stored_in_their_own_place(tmp_path):
     """From k of about 68 M on a vector's regions hold more than 2**29 entries of 8 bytes: a place counted from the first region does
-    not fit a 32-bit number of bytes, the one counted from the tile's space does."""
+    not fit a 32-bit number of bytes, the one counted from the tile's own region does."""
     checks = []
     for d, k, slices in ((2**31 - 1, 2**31 - 1, 64), (1_400_000_000, 70_000_000, 64), (600_000_007, 75_000_000, 64),
                          (600_000_007, 75_000_000, 512), (110_000_000, 110_000, 64)):
@@ -87,11 +87,11 @@ def test_candidates_of_the_largest_lists_are_stored_in_their_own_place(tmp_path)
         assert per_region <= full and per_region * slices < 2**32
         if k >= 70_000_000:
             assert per_region * slices > 2**29                    # the case this is about
-        for at in (0, per_region, (slices - 1) * per_region, slices * per_region - 4096):
-            for vector in (0, 3):
-                checks += [(vector * slices * per_region, at, in_tile) for in_tile in (0, 1, 4095)]
-    got = evaluate(tmp_path, [f"tile_space({base}, {at}u) * 8 + (int64_t)offset_bytes({q}, 8)" for base, at, q in checks])
-    assert got == [8 * (base + at + q) for base, at, q in checks]
+        assert per_region * 8 < 2**32
+        for region, at in ((0, 0), (1, 0), (1, per_region - 1), (slices - 1, 0), (slices - 1, per_region - 1)):
+            checks += [(vector, slices, region, per_region, at) for vector in (0, 3)]
+    got = evaluate(tmp_path, [f"region_first({v}, {s}, {r}, {cap}u) * 8 + (int64_t)offset_bytes({at}, 8)" for v, s, r, cap, at in checks])
+    assert got == [8 * ((v * s + r) * cap + at) for v, s, r, cap, at in checks]
 
 
 def test_uncompressed_update_pads_its_grid_to_no_more_than_eight_vectors(tmp_path):
