@@ -377,22 +377,48 @@ int dev_alloc_t(comp_ams *h, std::vector<void *> &owner, T **out, size_t count, 
     return dev_alloc(h, owner, reinterpret_cast<void **>(out), count * sizeof(T), zero);
 }
 
-// The word that kernels raise for the host (miss_seen), in pinned memory; a handle that is refused it does without.  Allocating and
-// freeing it takes 7 us each of the 150 and 80 that a handle's memory takes (the process's first one 80).
+// Words that kernels raise for the host (miss_seen): a pinned block of kFlags of them, a cache line each, which the process holds while a
+// handle has one and gives back with the last.  A word each from hipHostMalloc takes 20 to 90 us of the 140 to 750 that creating a
+// handle takes; one of the block nothing that shows, but for the 80 of the block with the first.  Without one - all are taken, or the block
+// was refused - a handle does without.
+constexpr int kFlags = 512, kFlagWords = 16;
+std::mutex g_flag_mutex;
+uint32_t *g_flags = nullptr;
+int g_flags_taken = 0;
+bool g_flag_taken[kFlags] = {};
+
 void take_flag(comp_ams *h)
 {
-    void *p = nullptr;
-    if (hipHostMalloc(&p, sizeof(uint32_t), hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
-        (void)hipGetLastError();
-        return;
+    std::lock_guard<std::mutex> lock(g_flag_mutex);
+    if (!g_flags) {
+        void *p = nullptr;
+        if (hipHostMalloc(&p, kFlags * kFlagWords * sizeof(uint32_t),
+                          hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        g_flags = static_cast<uint32_t *>(p);
     }
-    h->miss_seen = static_cast<uint32_t *>(p);
-    *h->miss_seen = 0u;
+    for (int q = 0; q < kFlags; ++q)
+        if (!g_flag_taken[q]) {
+            g_flag_taken[q] = true;
+            ++g_flags_taken;
+            h->miss_seen = g_flags + q * kFlagWords;
+            __atomic_store_n(h->miss_seen, 0u, __ATOMIC_RELAXED);
+            return;
+        }
 }
 
+// After the work of h has ended.
 void give_flag(comp_ams *h)
 {
-    if (h->miss_seen) (void)hipHostFree(h->miss_seen);
+    if (!h->miss_seen) return;
+    std::lock_guard<std::mutex> lock(g_flag_mutex);
+    g_flag_taken[(h->miss_seen - g_flags) / kFlagWords] = false;
+    if (--g_flags_taken == 0) {
+        (void)hipHostFree(g_flags);
+        g_flags = nullptr;
+    }
 }
 
 void free_all(std::vector<void *> &owner)

@@ -373,6 +373,28 @@ def test_a_miss_is_reported_to_its_own_handle():
         missing.destroy()
 
 
+# the flags by which kernels report a miss: a handle without one takes three launches, and flags are given back
+def test_more_handles_than_flags_for_misses():
+    import torch
+    d, n, k = 17 * TILE, 1, 700
+    print(f"[case] 520 handles, d={d}", flush=True)
+    g = torch.from_numpy(grads_of(8, n, d)(0)).cuda()
+
+    def third_step(h):
+        h.step(g)
+        h.step(g)
+        return selection_launches(h, lambda: h.step(g))[0]
+    handles = [P.CompAms(d, n, P.TOPK, k) for _ in range(520)]
+    taken = [third_step(handles[0]), third_step(handles[-1])]
+    theta = [h.get_theta() for h in (handles[0], handles[-1])]
+    assert taken == [1, 3] and np.array_equal(bits(theta[0]), bits(theta[1]))
+    for h in handles:
+        h.destroy()
+    h = P.CompAms(d, n, P.TOPK, k)
+    assert third_step(h) == 1
+    h.destroy()
+
+
 # CD-Adam: three launches in the steps whose guesses do not hold yet, also after the rows under the guess were replaced
 def test_three_launches_until_the_markov_sequences_are_settled():
     import torch
